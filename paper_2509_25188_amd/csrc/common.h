@@ -57,7 +57,8 @@ struct DynLdsAttr {
 
 // ---- small kernels (kernels_misc.hip) ----
 void launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
-void launch_rope_table(float* cos_t, float* sin_t, int max_pos, int head_dim, float base, hipStream_t s);
+// (cos, sin) of pos * base^(-2i / head_dim), [max_pos, head_dim / 2]
+void launch_rope_table(float2* table, int max_pos, int head_dim, float base, hipStream_t s);
 void launch_init_decode(int32_t* X, const int32_t* prompt, int B, int P, int G, int mask_id, int32_t* state,
                         int* ctl, hipStream_t s);
 void launch_prepare(const int32_t* state, int B, int n_blocks, int ragged, int* ctl, hipStream_t s,
@@ -68,11 +69,8 @@ void launch_embed(float* h, const void* emb, int dtype, const int32_t* tokens, R
 // through `src`.  part z is at parts + z * part_stride, laid out like h.  The sum is written back to h
 // when `write_back` is set; the final norm before the LM head leaves h alone (h is dead after it, and
 // two head rows may map to one row of h, so a write-back would race).
-// quad_tiled (bf16, d within the one-row-per-workgroup kernels' range): y is written in the
-// layout gemm_qkv_a_quad_tiled() describes instead of row-major; the arithmetic is the same.
 void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const void* gain,
-                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s,
-                    bool quad_tiled = false);
+                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s);
 constexpr int kFilterMaxLayers = 4;
 struct UpdateArgs {
   int32_t* X;            // [B, T]
@@ -144,8 +142,8 @@ void launch_gemm_f32(const float* A, const float* W, float* C, int M, int N, int
 // rotate q [rows, d] in place and copy/rotate k, v rows into the [B, Tmax, d] key/value stores at pos0 + t
 // (seq_gb / pos_per_gb: per-sequence position offsets as in QkvEpilogue)
 void launch_rope_store_f32(float* q, const float* k, const float* v, float* kstore, float* vstore, int B, int Tq,
-                           int pos0, int Tmax, int H, int Dh, const float* cos_t, const float* sin_t,
-                           const int* seq_gb, int pos_per_gb, Gate g, hipStream_t s);
+                           int pos0, int Tmax, int H, int Dh, const float2* rope, const int* seq_gb, int pos_per_gb, Gate g,
+                           hipStream_t s);
 void launch_attn_f32(const float* q, const float* kstore, const float* vstore, float* out, int B, int Tq, int Tk,
                      int Tmax, int H, int Dh, const int* tk_dev, Gate g, hipStream_t s);
 void launch_swiglu_f32(const float* gate, const float* up, float* act, size_t n, Gate g, hipStream_t s);
@@ -155,7 +153,7 @@ struct QkvEpilogue {
   bf16* q;               // [rows, d]
   bf16* kstore;          // [B, Tpad, d]
   bf16* vtstore;         // [B, H, Dh, Tpad]
-  const float *cos_t, *sin_t;  // [max_pos, Dh/2]
+  const float2* rope;    // [max_pos, Dh/2] (cos, sin)
   int Tq, pos0, Tpad, H, Dh, d;
   // per-sequence block pointers with a K/V cache: row t of sequence b sits at position
   // pos0 + seq_gb[b] * pos_per_gb + t (seq_gb = the control block's per-sequence active blocks); null: pos0 + t
@@ -165,25 +163,11 @@ struct QkvEpilogue {
 __device__ __forceinline__ int seq_pos_offset(const int* seq_gb, int per_gb, int b) {
   return seq_gb ? seq_gb[b] * per_gb : 0;
 }
-// Whether the fused Q/K/V (M rows, model width d, head size Dh) / gate/up (M rows, FFN width F) GEMM of
-// depth K reads its A operand straight into registers; it then expects it "quad-tiled": groups of four rows, and inside a group the
-// 16-byte chunks (8 bf16) of the four rows interleaved, element (r, k) at
-//   ((r / 4) * (K / 8) + k / 8) * 32 + (r % 4) * 8 + k % 8,
-// so that the 32 rows x 2 chunks a wavefront feeds to one MFMA K-step are eight whole 128-byte lines.
-// The buffer needs its row count rounded up to four.  A function of the launch shape only; the producer of
-// A (the RMSNorm before the GEMM) asks the same question.
-bool gemm_qkv_a_quad_tiled(int M, int d, int K, int Dh);
-bool gemm_swiglu_a_quad_tiled(int M, int F, int K);
-// the same question for the [N, K] projections that write split-K partials (output and down projection), whose
-// A operands are written by the attention kernel and by the gate/up GEMM's epilogue
-bool gemm_partial_a_quad_tiled(int M, int N, int K);
-// and for the LM head, whose A operand the final RMSNorm writes
-bool gemm_lmhead_a_quad_tiled(int M, int V, int K);
 void launch_gemm_qkv_bf16(const bf16* A, const bf16* wq, const bf16* wk, const bf16* wv, int M, int K,
                           const QkvEpilogue& e, Gate g, hipStream_t s);
-// partial[z][M,N] = A[:, z-th K slice] * W[:, slice]^T, z < splits (1 or 2)
+// partial[z][M,N] = A[:, z-th K slice] * W[:, slice]^T, z < wide_splits(M, N, K)
 void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t part_stride, int M, int N, int K,
-                              int splits, Gate g, hipStream_t s);
+                              Gate g, hipStream_t s);
 // Few-row GEMMs (block-only steps of the cached decode modes, at most kSkinnyRows rows) stream their
 // weights once; K is split until a launch has a few hundred workgroups, each K range staying a
 // multiple of the 64-wide stage.
@@ -198,10 +182,12 @@ void launch_skinny_qkv_finish(const float* parts, int n_parts, size_t part_strid
                               Gate g, hipStream_t s);
 void launch_skinny_swiglu_finish(const float* parts, int n_parts, size_t part_stride, int rows, int F, bf16* act,
                                  Gate g, hipStream_t s);
-// act[M, F] = silu(A Wg^T) * (A Wu^T); few rows take the fused few-row tiles when swiglu_few_rows_fused says so
+// act[M, F] = silu(A Wg^T) * (A Wu^T); few rows take the fused few-row kernel when swiglu_few_rows_fused says so
 bool swiglu_few_rows_fused(int M, int F);
 void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16* act, int M, int F, int K, Gate g,
-                             hipStream_t s, bool act_quad_tiled = false);
+                             hipStream_t s);
+void launch_gemm_few_rows_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16* act, int M, int F, int K, Gate g,
+                                      hipStream_t s);
 struct LmHeadEpilogue {
   float* logits;         // optional [M, V]
   float* part_max;       // optional [M, n_part]
@@ -214,10 +200,11 @@ struct LmHeadEpilogue {
 int lmhead_n_part(int V);
 void launch_gemm_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, const LmHeadEpilogue& e, Gate g,
                              hipStream_t s);
-// out_quad_tiled: write `out` in the layout gemm_partial_a_quad_tiled() asks for instead of row-major
+void launch_gemm_few_rows_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, const LmHeadEpilogue& e, Gate g,
+                                      hipStream_t s);
 void launch_attn_bf16(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16* out, int B, int Tq, int Tk,
                       int Tpad, int H, int Dh, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, Gate g,
-                      hipStream_t s, bool out_quad_tiled = false);
+                      hipStream_t s);
 // bytes of chunk workspace that lets launch_attn_bf16 spread few queries' keys over workgroups
 inline size_t attn_chunk_ws_bytes(int H, int Dh) { return (size_t)kSkinnyRowsAttn * H * 16 * (Dh + 2) * 4; }
 

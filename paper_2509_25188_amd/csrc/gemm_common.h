@@ -1,0 +1,77 @@
+// Device helpers shared by the bf16 GEMM kernels (many rows: gemm_bf16.hip, few rows: gemm_few_rows.hip).
+#pragma once
+#include "common.h"
+
+#include <type_traits>
+
+namespace l2pd {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+// fp32 -> bf16, round to nearest even, two values per v_cvt_pk_bf16_f32; lo lands in bits 15:0
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+  f32x2 v = {lo, hi};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2_t));
+}
+__device__ __forceinline__ unsigned short f2bf(float f) { return (unsigned short)(pack_bf16(f, 0.f) & 0xffffu); }
+
+// Lane exchange inside a row of 16 lanes by DPP (no LDS): quad_perm for xor 1 / xor 2, row_ror for rotations.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppRor = 0x120;
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float dppf(float x) {
+  return __builtin_bit_cast(float, dpp<CTRL>(__builtin_bit_cast(unsigned, x)));
+}
+
+// 4x4 transpose inside every aligned group of four lanes: on entry lane j of a group holds
+// element (j, k) in w[k]; on return it holds element (k, j).  In the MFMA C layout a lane owns one
+// column and four consecutive rows, so the transpose gives each lane four consecutive columns of
+// one row, which it can store as one piece instead of four.
+__device__ __forceinline__ void quad_transpose(unsigned (&w)[4], int lane) {
+  const bool o1 = lane & 1, o2 = lane & 2;
+  unsigned s0 = o1 ? w[0] : w[1], s1 = o1 ? w[2] : w[3];
+  s0 = dpp<kDppXor1>(s0);
+  s1 = dpp<kDppXor1>(s1);
+  if (o1) { w[0] = s0; w[2] = s1; } else { w[1] = s0; w[3] = s1; }
+  unsigned t0 = o2 ? w[0] : w[2], t1 = o2 ? w[1] : w[3];
+  t0 = dpp<kDppXor2>(t0);
+  t1 = dpp<kDppXor2>(t1);
+  if (o2) { w[0] = t0; w[1] = t1; } else { w[2] = t0; w[3] = t1; }
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {   // s_waitcnt vmcnt(N) only (expcnt / lgkmcnt untouched)
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+// Workgroup barrier without the memory-model fence of __syncthreads(), which would wait for every
+// outstanding global load (vmcnt(0)) and so drain the prefetch ring.  LDS visibility is ordered by
+// the explicit waits around it; the empty asm statements keep the compiler from moving LDS
+// accesses across the barrier.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// 16 bytes per lane, global -> LDS without passing through VGPRs.  The LDS destination of the whole
+// wavefront is M0 + 16 * lane.  Written as inline asm on purpose: the compiler's wait-count pass
+// falls back to lgkmcnt(0) before every LDS read while a direct-to-LDS load it knows of is in
+// flight, which would serialise the fragment prefetch; completion is tracked by hand with
+// wait_vmcnt<>().  (Untracked extra loads can only make the compiler's own vmcnt waits stricter,
+// because vmcnt retires in order.)
+__device__ __forceinline__ void dma16(const void* gptr, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(gptr), "s"(lds_addr)
+               : "memory", "m0");
+}
+
+}  // namespace l2pd

@@ -1,0 +1,410 @@
+// bf16 MFMA GEMM for few rows (a block-only step of the cached decode modes: up to 64 rows) on gfx950:
+// C[M, N] = A[M, K] * W[N, K]^T, fp32 accumulation.
+//
+// Such a GEMM is bound by streaming its weights once, which wants several workgroups per CU with deep rings in
+// flight: 32- or 64-row tiles whose operands go global -> LDS directly (global_load_lds_dwordx4: no VGPR staging, no
+// ds_write) through an NS-stage ring, so that loads run NS-1 K-steps ahead of the MFMAs; the wait for a stage is
+// a manual s_waitcnt vmcnt(n) that leaves the younger stages in flight.  LDS rows are swizzled as in
+// gemm_bf16.hip.  K is split into fp32 partials (Q/K/V, O and down projections; the rotary embedding and the
+// residual update run on their sums afterwards) or, where the output is wide enough, not at all (gate/up with SwiGLU
+// in the epilogue, LM head with its per-tile (max, sum exp, argmax) reduction).
+#include "gemm_common.h"
+
+namespace l2pd {
+namespace {
+
+enum { EPI_PARTIAL = 0, EPI_SWIGLU = 2, EPI_LMHEAD = 3 };
+
+struct FewArgs {
+  const bf16* A;
+  const bf16* B0;
+  const bf16* B1;
+  const bf16* B2;
+  int M, N, K;          // N counts tile-space columns (SwiGLU: gate and up columns)
+  int tiles_m, tiles_n, splits;
+  Gate gate;
+  // EPI_PARTIAL: K range z writes to parts + z * part_stride (fp32 [M, N])
+  float* parts;
+  size_t part_stride;
+  int n_sub;            // > 0: the N rows are the rows of B0, B1, B2 stacked, n_sub rows each
+  // EPI_SWIGLU (fragment 2p of a wavefront holds gate, fragment 2p+1 up columns of the same 32 features)
+  bf16* act;
+  int F;
+  // EPI_LMHEAD
+  LmHeadEpilogue lm;
+};
+
+template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
+__global__ void __launch_bounds__(WM* WN * 64) k_gemm_few_rows(FewArgs a) {
+  constexpr int NT = WM * WN * 64;
+  constexpr int NW = WM * WN;
+  constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
+  constexpr bool PAIR = EPI == EPI_SWIGLU;
+  static_assert(!PAIR || (FN % 2 == 0), "pair epilogues need an even number of column fragments");
+  static_assert(BK == 32 || BK == 64, "LDS tile rows hold 32 or 64 K elements");
+  constexpr int CPR = BK / 8;               // 16-byte chunks per LDS row
+  constexpr int RPD = 64 / CPR;             // rows filled by one direct-to-LDS wave load (1 KB)
+  constexpr int KEY_SHIFT = BK == 64 ? 1 : 2;   // rows per 256-byte bank sweep = 1 << KEY_SHIFT
+  constexpr int KS = BK / 16;               // MFMA K-steps per stage
+  constexpr int LROWS = BM + BN;    // tile rows staged in LDS
+  constexpr int LPS = LROWS / RPD / NW;     // direct-to-LDS loads per thread per stage
+  static_assert(LPS * NW * RPD == LROWS, "tile/threads mismatch");
+  static_assert(NS >= 3 && (NS - 2) * LPS < 64, "ring depth: at least 3 stages, vmcnt is 6 bits");
+
+  if (gate_skip(a.gate)) return;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  // [stage][A: BM rows | B: BN rows][BK bf16]
+  constexpr int STAGE_BYTES = LROWS * BK * 2;
+
+  // ---- tile assignment: consecutive ids on one XCD share a weight panel ----
+  const int total = a.tiles_m * a.tiles_n * a.splits;
+  const int per_xcd = (total + 7) / 8;
+  const int v = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (v >= total) return;
+  const int per_split = a.tiles_m * a.tiles_n;
+  const int z = v / per_split;
+  int rem = v % per_split;
+  constexpr int GM = 8;
+  const int chunk = rem / (GM * a.tiles_n);
+  rem -= chunk * GM * a.tiles_n;
+  const int gmc = min(GM, a.tiles_m - chunk * GM);
+  const int tile_n = rem / gmc;
+  const int tile_m = chunk * GM + rem % gmc;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / WN, wn = wave % WN;
+  const int hf = lane >> 5, lj = lane & 31;
+
+  const int k_len = a.K / a.splits;
+  const int k_begin = z * k_len;
+  const int nk = k_len / BK;
+
+  // ---- per-thread source pointers of the direct-to-LDS loads (fixed over the K loop) ----
+  // Load q of a stage (q = wave + i*NW) fills combined tile rows RPD*q .. RPD*q+RPD-1 (A rows first, then B).
+  const bf16* src[LPS];
+#pragma unroll
+  for (int i = 0; i < LPS; ++i) {
+    const int q = wave + i * NW;
+    const int rr = q * RPD + lane / CPR;         // row in the combined [A; B] tile
+    const int c = (lane % CPR) ^ ((rr >> KEY_SHIFT) & (CPR - 1));   // global chunk that belongs at this lane's slot
+    if (rr < BM) {
+      int gr = min(m0 + rr, a.M - 1);
+      src[i] = a.A + (size_t)gr * a.K + k_begin + c * 8;
+    } else {
+      const int r = rr - BM;
+      const bf16* base;
+      size_t grow;
+      if constexpr (!PAIR) {
+        int gn = min(n0 + r, a.N - 1);
+        base = a.B0;
+        if (a.n_sub > 0) {
+          const int mat = gn / a.n_sub;
+          gn -= mat * a.n_sub;
+          base = mat == 0 ? a.B0 : (mat == 1 ? a.B1 : a.B2);
+        }
+        grow = (size_t)gn;
+      } else {
+        const int rw = r / (32 * FN), f = (r >> 5) % FN, j = r & 31;
+        const int G = tile_n * (BN / 64) + rw * (FN / 2) + (f >> 1);
+        base = f & 1 ? a.B1 : a.B0;
+        grow = (size_t)min(G * 32 + j, a.F - 1);
+      }
+      src[i] = base + grow * a.K + k_begin + c * 8;
+    }
+  }
+  // LDS byte address of this wave's first slot in stage 0 (wave-uniform, goes to M0)
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane(
+      (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)(smem + wave * 1024));
+  // Loads of one stage are issued in KS parts (load i belongs to part i % KS), one part per K-step,
+  // so that they trickle into the texture-address queue behind MFMAs instead of arriving as a burst
+  // from every wave right after the barrier (a burst stalls instruction issue until the queue drains).
+  auto issue_part = [&](int kt, int part) {
+    const unsigned dst = lds0 + (kt % NS) * STAGE_BYTES;
+#pragma unroll
+    for (int i = 0; i < LPS; ++i)
+      if (i % KS == part) dma16(src[i] + kt * BK, dst + i * NW * 1024);
+  };
+
+  f32x16 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  // fragment row byte offsets inside a stage (row * 128) and the row's swizzle key
+  int offA[FM], offB[FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) offA[i] = (wm * (BM / WM) + i * 32 + lj) * (BK * 2);
+#pragma unroll
+  for (int j = 0; j < FN; ++j) offB[j] = BM * (BK * 2) + (wn * (BN / WN) + j * 32 + lj) * (BK * 2);
+  const int key = (lj >> KEY_SHIFT) & (CPR - 1);   // row's swizzle key (fragment bases are multiples of 32)
+
+  // Software pipeline.  Fragments are double-buffered in registers: the ds_reads of K-step kk+1 are
+  // issued before the MFMAs of step kk, and the first fragments of the next stage are read during
+  // the last step of the current one.  The ring advances (wait for stage kt+1, barrier, refill the
+  // buffer of stage kt-1 with stage kt+NS-1) right before that last step, so a wave that waits at
+  // the barrier leaves a full step of MFMAs queued behind it.
+  bf16x8_t fa[2][FM], fb[2][FN];
+  auto read_frags = [&](int buf, const unsigned char* base, int kk) {
+    const int sw = ((kk * 2 + hf) ^ key) << 4;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8_t*>(base + offA[i] + sw);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) fb[buf][j] = *reinterpret_cast<const bf16x8_t*>(base + offB[j] + sw);
+  };
+  // One K-step: the FM*FN MFMAs on fragment set `cur`, with the ds_reads that fetch set `cur ^ 1`
+  // (K-step kk_next of the stage at `nbase`) slotted in between them, one read after each of the
+  // first MFMAs, so that every read is issued while an MFMA occupies the matrix pipe.
+  constexpr int NR = FM + FN;
+  auto step = [&](int kk, const unsigned char* nbase, int kk_next, int dma_kt, int dma_part) {
+    const int cur = kk & 1;   // fragment set of K-step kk
+    const int sw = ((kk_next * 2 + hf) ^ key) << 4;
+    const int nxt = cur ^ 1;
+#pragma unroll
+    for (int idx = 0; idx < FM * FN; ++idx) {
+      const int i = idx / FN, j = idx % FN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        if ((r < FM * FN ? r : FM * FN - 1) != idx) continue;   // read r goes after MFMA min(r, last)
+        if (r < FM) fa[nxt][r] = *reinterpret_cast<const bf16x8_t*>(nbase + offA[r] + sw);
+        else fb[nxt][r - FM] = *reinterpret_cast<const bf16x8_t*>(nbase + offB[r - FM] + sw);
+      }
+      if (idx == 0 && dma_kt >= 0) issue_part(dma_kt, dma_part);   // stays in program order
+    }
+#pragma unroll
+    for (int idx = 0; idx < FM * FN; ++idx) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA, then the LDS reads of its slot
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+        if ((r < FM * FN ? r : FM * FN - 1) == idx) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // Prologue: stages 0 .. NS-2.  The wait counts loads, so nothing may move across it.
+#pragma unroll
+  for (int st = 0; st < NS - 1; ++st)
+    if (st < nk) {
+#pragma unroll
+      for (int part = 0; part < KS; ++part) issue_part(st, part);
+    }
+  __builtin_amdgcn_sched_barrier(0);
+  if (nk >= NS - 1) wait_vmcnt<(NS - 2) * LPS>();   // stage 0 has landed
+  else wait_vmcnt<0>();
+  __builtin_amdgcn_sched_barrier(0);
+  lds_barrier();
+  // Drain scalar loads here, so that only in-order LDS reads are pending when the loop is entered
+  // and the compiler can wait for "all but the newest reads" instead of lgkmcnt(0) at its head.
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+  read_frags(0, smem, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int kt = 0; kt < nk; ++kt) {
+    const unsigned char* base = smem + (kt % NS) * STAGE_BYTES;
+    // parts 1 .. KS-1 of stage kt+NS-2 (its part 0 went out with the last K-step of iteration kt-1; the prologue
+    // has issued all of stage NS-2)
+    const int dma_a = (kt >= 1 && kt + NS - 2 < nk) ? kt + NS - 2 : -1;
+#pragma unroll
+    for (int kk = 0; kk < KS - 1; ++kk) step(kk, base, kk + 1, dma_a, kk + 1);
+    if (kt + 1 < nk) {
+      // stage kt+1 has landed once at most the loads of the NS-3 younger stages are outstanding
+      if (kt + NS - 2 < nk) wait_vmcnt<(NS - 3) * LPS>();
+      else wait_vmcnt<0>();
+      lds_barrier();   // stage kt+1 visible to all; every wave is past its reads of stage kt-1
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // The reads of the next stage's first fragments are unconditional (after the last stage they
+    // fetch stale but valid LDS that nobody uses): a branch around them would make the compiler's
+    // LDS wait counts conservative at the join.  The buffer of stage kt-1 is free from here on:
+    // start refilling it with stage kt+NS-1.
+    step(KS - 1, smem + ((kt + 1) % NS) * STAGE_BYTES, 0, (kt + NS - 1 < nk) ? kt + NS - 1 : -1, 0);
+  }
+  lds_barrier();
+
+  // ------------------------------------------------------------------------------------------
+  // C layout of the 32x32 MFMA: register r of a lane is row (r/4)*8 + hf*4 + r%4, column lj.
+  const int row_base = m0 + wm * (BM / WM);
+  if constexpr (EPI == EPI_PARTIAL) {
+    float* out = a.parts + (size_t)z * a.part_stride;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        int col = n0 + wn * (BN / WN) + j * 32 + lj;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          int row = row_base + i * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
+          if (row < a.M && col < a.N) out[(size_t)row * a.N + col] = acc[i][j][r];
+        }
+      }
+  } else if constexpr (EPI == EPI_SWIGLU) {
+    const int lr = lj & 3, c4 = lj & ~3;   // after the transpose: row within the group, first of 4 columns
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int p = 0; p < FN / 2; ++p) {
+        const int G = tile_n * (BN / 64) + wn * (FN / 2) + p;
+        const int col = G * 32 + c4;
+#pragma unroll
+        for (int rq = 0; rq < 4; rq += 2) {   // two row groups share one transpose: low / high half words
+          unsigned w[4];
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) {
+            const float g0 = acc[i][2 * p][rq * 4 + rr], u0 = acc[i][2 * p + 1][rq * 4 + rr];
+            const float g1 = acc[i][2 * p][rq * 4 + 4 + rr], u1 = acc[i][2 * p + 1][rq * 4 + 4 + rr];
+            // SiLU(g) * u with the hardware reciprocal (1 ulp) instead of an exact division; the
+            // operations are spelled out so that every tile configuration rounds alike
+            const float s0 = __fmul_rn(__fmul_rn(g0, __builtin_amdgcn_rcpf(__fadd_rn(1.f, __expf(-g0)))), u0);
+            const float s1 = __fmul_rn(__fmul_rn(g1, __builtin_amdgcn_rcpf(__fadd_rn(1.f, __expf(-g1)))), u1);
+            w[rr] = pack_bf16(s0, s1);
+          }
+          quad_transpose(w, lane);
+#pragma unroll
+          for (int h2 = 0; h2 < 2; ++h2) {
+            const int row = row_base + i * 32 + (rq + h2) * 8 + hf * 4 + lr;
+            uint2 o;
+            o.x = h2 ? (w[0] >> 16) | (w[1] & 0xffff0000u) : (w[0] & 0xffffu) | (w[1] << 16);
+            o.y = h2 ? (w[2] >> 16) | (w[3] & 0xffff0000u) : (w[2] & 0xffffu) | (w[3] << 16);
+            if (row < a.M && col < a.F) {   // F is a multiple of 4, so a group of 4 columns is in or out as a whole
+              *reinterpret_cast<uint2*>(reinterpret_cast<unsigned short*>(a.act) + (size_t)row * a.F + col) = o;
+            }
+          }
+        }
+      }
+  } else {  // EPI_LMHEAD
+    const LmHeadEpilogue& e = a.lm;
+    float* s_m = reinterpret_cast<float*>(smem);            // [WN][BM]   (tile buffers are dead now)
+    float* s_s = s_m + WN * BM;
+    int* s_i = reinterpret_cast<int*>(s_s + WN * BM);
+    __syncthreads();
+    const bool biased = e.bias.value != 0.f && a.gate.ctl;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        int lrow = wm * (BM / WM) + i * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
+        int row = m0 + lrow;
+        float vals[FN];
+        float m = -INFINITY;
+        int mi = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          int col = n0 + wn * (BN / WN) + j * 32 + lj;
+          float v = acc[i][j][r];
+          if (biased && col == e.bias.token_id && row < a.M &&
+              a.gate.ctl[CTL_SEQ_GB + row / e.bias.block_len] * e.bias.block_len + (row % e.bias.block_len) >=
+                  e.bias.gen_pos_from)
+            v += e.bias.value;
+          if (e.logits && row < a.M && col < a.N) e.logits[(size_t)row * a.N + col] = v;
+          if (col == e.mask_id || col >= a.N) v = -INFINITY;
+          vals[j] = v;
+          if (v > m) { m = v; mi = col; }   // columns ascend with j: first maximum wins
+        }
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) {
+          float m2 = __shfl_xor(m, o, 64);
+          int i2 = __shfl_xor(mi, o, 64);
+          if (m2 > m || (m2 == m && i2 < mi)) { m = m2; mi = i2; }
+        }
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) sum += (m == -INFINITY) ? 0.f : __expf(vals[j] - m);
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (lj == 0) {
+          s_m[wn * BM + lrow] = m;
+          s_s[wn * BM + lrow] = sum;
+          s_i[wn * BM + lrow] = mi;
+        }
+      }
+    __syncthreads();
+    if (e.part_max) {
+      for (int lrow = tid; lrow < BM; lrow += NT) {
+        int row = m0 + lrow;
+        if (row >= a.M) continue;
+        float m = s_m[lrow], sum = s_s[lrow];
+        int mi = s_i[lrow];
+#pragma unroll
+        for (int w = 1; w < WN; ++w) {
+          float m2 = s_m[w * BM + lrow], s2 = s_s[w * BM + lrow];
+          int i2 = s_i[w * BM + lrow];
+          float M = fmaxf(m, m2);
+          float f1 = (m == -INFINITY) ? 0.f : __expf(m - M), f2 = (m2 == -INFINITY) ? 0.f : __expf(m2 - M);
+          sum = sum * f1 + s2 * f2;
+          if (m2 > m || (m2 == m && i2 < mi)) mi = i2;
+          m = M;
+        }
+        size_t o = (size_t)row * e.n_part + tile_n;
+        e.part_max[o] = m;
+        e.part_sum[o] = sum;
+        e.part_idx[o] = mi;
+      }
+    }
+  }
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
+void launch(FewArgs& a, hipStream_t s) {
+  auto kern = k_gemm_few_rows<BM, BN, BK, WM, WN, NS, EPI>;
+  constexpr int smem = NS * (BM + BN) * BK * 2;
+  static DynLdsAttr attr;
+  attr.ensure(reinterpret_cast<const void*>(kern), smem);
+  a.tiles_m = (a.M + BM - 1) / BM;
+  a.tiles_n = (a.N + BN - 1) / BN;
+  int total = a.tiles_m * a.tiles_n * a.splits;
+  int grid = ((total + 7) / 8) * 8;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), smem, s, a);
+}
+
+}  // namespace
+
+int skinny_splits(int N, int K) {
+  const int tiles = (N + 127) / 128;
+  int S = 1;
+  while (tiles * S < 256 && S < 16 && K % (S * 2 * 64) == 0 && K / (S * 2) >= 256) S *= 2;
+  return S;
+}
+
+// Few rows (a block-only step of the cached decode modes: 32 or 64 rows): every GEMM is bound by
+// streaming its weights once, which needs several workgroups per CU with deep rings in flight.
+// 32- or 64-row tiles, 128 columns, K split `splits` ways into fp32 partials; up to three weight
+// matrices of n_sub rows each are stacked along N (Q/K/V, gate/up) so that one launch covers them.
+// The nonlinear epilogues (RoPE, SwiGLU) run afterwards on the summed partials.
+void launch_gemm_skinny_bf16(const bf16* A, const bf16* w0, const bf16* w1, const bf16* w2, int n_sub, float* parts,
+                             size_t part_stride, int M, int N, int K, int splits, Gate g, hipStream_t s) {
+  FewArgs a = {};
+  a.A = A; a.B0 = w0; a.B1 = w1; a.B2 = w2; a.n_sub = w1 ? n_sub : 0;
+  a.M = M; a.N = N; a.K = K; a.splits = splits; a.gate = g;
+  a.parts = parts; a.part_stride = part_stride;
+  if (M <= 32) launch<32, 128, 64, 1, 4, 4, EPI_PARTIAL>(a, s);
+  else launch<64, 128, 64, 2, 2, 4, EPI_PARTIAL>(a, s);
+}
+
+// Few rows and a wide FFN: 64 (32 gate + 32 up) columns per workgroup already make a few hundred
+// workgroups, so the weights stream once without splitting K and SwiGLU stays in the epilogue
+// (measured against split-K partials plus a finishing kernel, weights coming from HBM: 40.6 us
+// against 44.1 + 4.6 us at 32 rows, 43.5 against 51.4 + 4.6 us at 64 rows, d_model 4096, d_ffn 12288).
+bool swiglu_few_rows_fused(int M, int F) { return M <= kSkinnyRows && F % 64 == 0 && 2 * F / 64 >= 256; }
+
+void launch_gemm_few_rows_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16* act, int M, int F, int K, Gate g,
+                                      hipStream_t s) {
+  FewArgs a = {};
+  a.A = A; a.B0 = wg; a.B1 = wu; a.M = M; a.N = 2 * F; a.K = K; a.splits = 1; a.gate = g;
+  a.act = act; a.F = F;
+  if (M <= 32) launch<32, 64, 64, 1, 1, 6, EPI_SWIGLU>(a, s);   // one wavefront per workgroup, 72 KB ring
+  else launch<64, 128, 64, 2, 2, 4, EPI_SWIGLU>(a, s);
+}
+
+// 128 columns per tile: the partial (max, sum, argmax) triples are per 128 logits
+void launch_gemm_few_rows_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, const LmHeadEpilogue& e, Gate g,
+                                      hipStream_t s) {
+  FewArgs a = {};
+  a.A = A; a.B0 = W; a.M = M; a.N = V; a.K = K; a.splits = 1; a.gate = g; a.lm = e;
+  if (M <= 32) launch<32, 128, 64, 1, 4, 4, EPI_LMHEAD>(a, s);
+  else launch<64, 128, 64, 2, 2, 4, EPI_LMHEAD>(a, s);
+}
+
+}  // namespace l2pd

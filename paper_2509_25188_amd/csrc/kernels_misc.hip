@@ -18,19 +18,17 @@ void launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s) {
 }
 
 // cos/sin of pos * base^(-2i/Dh), evaluated in double and stored as float.
-__global__ void k_rope_table(float* cos_t, float* sin_t, int max_pos, int half, int head_dim, float base) {
+__global__ void k_rope_table(float2* table, int max_pos, int half, int head_dim, float base) {
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= max_pos * half) return;
   int pos = idx / half, i = idx % half;
   double inv = pow((double)base, -2.0 * (double)i / (double)head_dim);
   double a = (double)pos * inv;
-  cos_t[idx] = (float)cos(a);
-  sin_t[idx] = (float)sin(a);
+  table[idx] = make_float2((float)cos(a), (float)sin(a));
 }
-void launch_rope_table(float* cos_t, float* sin_t, int max_pos, int head_dim, float base, hipStream_t s) {
+void launch_rope_table(float2* table, int max_pos, int head_dim, float base, hipStream_t s) {
   int half = head_dim / 2, n = max_pos * half;
-  hipLaunchKernelGGL(k_rope_table, dim3((n + 255) / 256), dim3(256), 0, s, cos_t, sin_t, max_pos, half, head_dim,
-                     base);
+  hipLaunchKernelGGL(k_rope_table, dim3((n + 255) / 256), dim3(256), 0, s, table, max_pos, half, head_dim, base);
 }
 
 // X <- prompt || [MASK]^G ; state <- 0   (Alg. 2, initialisation of X)
@@ -278,20 +276,11 @@ __global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* part
 template <typename T, int VPL, int NTH>
 __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* parts, int n_parts, size_t part_stride,
                                                     RowMap src, const T* gain, T* y, int rows, int d, float eps,
-                                                    int wb, int quad_tiled, Gate g) {
+                                                    int wb, Gate g) {
   if (gate_skip(g)) return;
   __shared__ float s_part[NTH / 64];
   const int tid = threadIdx.x;
-  int r = blockIdx.x;
-  if (quad_tiled) {
-    // Quad-tiled output interleaves four rows inside every 128-byte line.  Workgroups are dealt to the 8
-    // XCDs round-robin by their id; give the four rows of a group to workgroups of one XCD, so that the
-    // line is completed in that XCD's L2 before it is written back.  (A permutation of [0, gridDim.x), the
-    // grid being the row count rounded up to 32.)
-    const int xcd = r & 7, slot = r >> 3;
-    r = ((slot >> 2) * 8 + xcd) * 4 + (slot & 3);
-    if (r >= rows) return;
-  }
+  const int r = blockIdx.x;
   const size_t srow = (size_t)map_row(src, r, g.ctl);
   const int d4 = d >> 2;
   float4* x = reinterpret_cast<float4*>(h + srow * d);
@@ -354,8 +343,6 @@ __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* part
   ss = tree[0];
   const float inv = rsqrtf(ss / (float)d + eps);
   T* o = y + (size_t)r * d;
-  // quad-tiled: the row's 16-byte chunk c sits at ((r / 4) * (d / 8) + c) * 32 + (r % 4) * 8 elements
-  T* oq = y + (size_t)(r >> 2) * 4 * d + (r & 3) * 8;
 #pragma unroll
   for (int k = 0; k < VPL; ++k) {
     const int i = tid + NTH * k;
@@ -368,8 +355,7 @@ __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* part
       } else {
         T o4[4] = {from_f<T>(v[k].x * inv * to_f<T>(gp[0])), from_f<T>(v[k].y * inv * to_f<T>(gp[1])),
                    from_f<T>(v[k].z * inv * to_f<T>(gp[2])), from_f<T>(v[k].w * inv * to_f<T>(gp[3]))};
-        T* dst = quad_tiled ? oq + (i >> 1) * 32 + (i & 1) * 4 : o + 4 * i;
-        *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o4);
+        *reinterpret_cast<uint2*>(o + 4 * i) = *reinterpret_cast<const uint2*>(o4);
       }
     }
   }
@@ -378,28 +364,14 @@ __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* part
 constexpr int NORM_TX = 4;   // threads per row = 256 * NORM_TX
 template <typename T>
 static void launch_rmsnorm_t(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const T* gain,
-                             T* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s, bool quad_tiled) {
+                             T* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s) {
   const int wb = write_back ? 1 : 0;
-  if (quad_tiled) {
-    // only the one-row-per-workgroup kernels write it (gemm_qkv_a_quad_tiled() asks for it within their range only)
-    if (sizeof(T) != 2 || d % 8 != 0 || d < 2048 || d > 8192) {
-      // a caller's mistake, not an input's: the consumer would read another layout than the one written
-      fprintf(stderr, "l2pd: quad-tiled RMSNorm output asked for outside its range (d = %d)\n", d);
-      abort();
-    }
-    const int grid_q = (rows + 31) / 32 * 32;
-    if (d <= 4096)
-      hipLaunchKernelGGL((k_rmsnorm_row<T, 4 / NORM_TX, 256 * NORM_TX>), dim3(grid_q), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, 1, g);
-    else
-      hipLaunchKernelGGL((k_rmsnorm_row<T, 8 / NORM_TX, 256 * NORM_TX>), dim3(grid_q), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, 1, g);
-    return;
-  }
   dim3 grid((rows + 3) / 4), block(256);
   if (rows <= 4096) { grid = dim3(rows); block = dim3(64); }   // few rows: one wavefront per workgroup fills more CUs
   if (d % 4 == 0 && d >= 2048 && d <= 4096)
-    hipLaunchKernelGGL((k_rmsnorm_row<T, 4 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, 0, g);
+    hipLaunchKernelGGL((k_rmsnorm_row<T, 4 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
   else if (d % 4 == 0 && d > 4096 && d <= 8192)
-    hipLaunchKernelGGL((k_rmsnorm_row<T, 8 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, 0, g);
+    hipLaunchKernelGGL((k_rmsnorm_row<T, 8 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
   else if (d % 4 == 0 && d <= 1024)
     hipLaunchKernelGGL((k_rmsnorm_vec<T, 4>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
   else if (d % 4 == 0 && d <= 4096)
@@ -410,13 +382,12 @@ static void launch_rmsnorm_t(float* h, const float* parts, int n_parts, size_t p
     hipLaunchKernelGGL(k_rmsnorm<T>, grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
 }
 void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const void* gain,
-                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s,
-                    bool quad_tiled) {
+                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s) {
   if (!parts) n_parts = 0;
   if (dtype == L2PD_FP32)
-    launch_rmsnorm_t<float>(h, parts, n_parts, part_stride, src, (const float*)gain, (float*)y, rows, d, eps, write_back, g, s, quad_tiled);
+    launch_rmsnorm_t<float>(h, parts, n_parts, part_stride, src, (const float*)gain, (float*)y, rows, d, eps, write_back, g, s);
   else
-    launch_rmsnorm_t<bf16>(h, parts, n_parts, part_stride, src, (const bf16*)gain, (bf16*)y, rows, d, eps, write_back, g, s, quad_tiled);
+    launch_rmsnorm_t<bf16>(h, parts, n_parts, part_stride, src, (const bf16*)gain, (bf16*)y, rows, d, eps, write_back, g, s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -450,7 +421,8 @@ __global__ void __launch_bounds__(256) k_skinny_qkv_finish(const float* parts, i
     vt[o + (size_t)half * e.Tpad] = bf16_bits(x2);
     return;
   }
-  const float cs = e.cos_t[(size_t)pos * half + i], sn = e.sin_t[(size_t)pos * half + i];
+  const float2 rot = e.rope[(size_t)pos * half + i];
+  const float cs = rot.x, sn = rot.y;
   const float o1 = __fmaf_rn(x1, cs, -__fmul_rn(x2, sn)), o2 = __fmaf_rn(x2, cs, __fmul_rn(x1, sn));
   unsigned short* dst = reinterpret_cast<unsigned short*>(mat == 0 ? e.q : e.kstore);
   const size_t o = (mat == 0 ? (size_t)row * e.d : ((size_t)b * e.Tpad + pos) * e.d) + head * e.Dh + i;

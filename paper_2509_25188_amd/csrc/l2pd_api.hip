@@ -27,7 +27,7 @@ struct Carver {
 
 struct Layout {
   // offsets into the workspace
-  size_t cos_t, sin_t, ctl, state, state2, perm, perm2, teff, X, X2, h, xn, q, attn, act, parts, attn_ws, attn_ws_bytes, kstore, vstore, tmp_k, tmp_v, gate_up,
+  size_t rope, ctl, state, state2, perm, perm2, teff, X, X2, h, xn, q, attn, act, parts, attn_ws, attn_ws_bytes, kstore, vstore, tmp_k, tmp_v, gate_up,
       xn_head, logits, part_max, part_sum, part_idx, conf, pred, total;
   size_t kv_layer_stride_k, kv_layer_stride_v;
   int Tpad, n_part, lm_chunk;
@@ -100,8 +100,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
   L.lm_chunk = 1024;
   L.n_part = m.dtype == L2PD_FP32 ? (int)((V + L.lm_chunk - 1) / L.lm_chunk) : lmhead_n_part((int)V);
   const size_t head_rows = (size_t)max_batch * 256;   // block_len <= 256
-  L.cos_t = c.take((size_t)L.Tpad * (m.head_dim / 2) * 4);
-  L.sin_t = c.take((size_t)L.Tpad * (m.head_dim / 2) * 4);
+  L.rope = c.take((size_t)L.Tpad * (m.head_dim / 2) * 8);
   L.ctl = c.take((size_t)(CTL_WORDS + 2 * max_batch) * 4);   // control words, per-sequence blocks, per-sequence done flags
   L.state = c.take((size_t)max_batch * 3 * 4);
   L.state2 = c.take((size_t)max_batch * 3 * 4);   // second copies for batch compaction
@@ -111,10 +110,10 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
   L.X = c.take(rows * 4);
   L.X2 = c.take(rows * 4);
   L.h = c.take(rows * d * 4);
-  L.xn = c.take(align_up(rows, 4) * d * es);   // the quad-tiled layout holds whole groups of four rows
+  L.xn = c.take(rows * d * es);
   L.q = c.take(rows * d * es);
-  L.attn = c.take(align_up(rows, 4) * d * es);
-  L.act = c.take(align_up(rows, 4) * F * es);
+  L.attn = c.take(rows * d * es);
+  L.act = c.take(rows * F * es);
   const size_t kv_one = (size_t)max_batch * L.Tpad * d * es;
   const size_t n_kv = cache ? m.n_layers : 1;
   L.kv_layer_stride_k = kv_one;
@@ -149,7 +148,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
     L.attn_ws_bytes = attn_chunk_ws_bytes(m.n_heads, m.head_dim);
     L.attn_ws = c.take(L.attn_ws_bytes);
   }
-  L.xn_head = c.take(align_up(rows, 4) * d * es);   // l2pd_forward may ask for every row; quad-tiled layout: rows in fours
+  L.xn_head = c.take(rows * d * es);   // l2pd_forward may ask for every row
   L.part_max = c.take(head_rows * L.n_part * 4);
   L.part_sum = c.take(head_rows * L.n_part * 4);
   L.part_idx = c.take(head_rows * L.n_part * 4);
@@ -172,7 +171,7 @@ int ensure_device(l2pd_ctx* c, hipStream_t s) {
   if (c->device_ready) return L2PD_OK;
   // Zero the workspace once: padded key/value slots must hold finite numbers.
   launch_fill_u32(reinterpret_cast<uint32_t*>(c->ws), c->L.total / 4, 0u, s);
-  launch_rope_table(c->at<float>(c->L.cos_t), c->at<float>(c->L.sin_t), c->L.Tpad, c->m.head_dim, c->m.rope_base, s);
+  launch_rope_table(c->at<float2>(c->L.rope), c->L.Tpad, c->m.head_dim, c->m.rope_base, s);
   HIP_TRY(c, hipGetLastError());
   c->device_ready = true;
   return L2PD_OK;
@@ -224,8 +223,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
   launch_embed(h, c->tok_emb, m.dtype, p.tokens, RowMap{p.Tq, p.Tfull, p.pos0, p.pos_per_gb}, rows, d, g, s);
   const int* seq_gb = p.pos_per_gb ? c->at<int>(L.ctl) + CTL_SEQ_GB : nullptr;
   const size_t kv_seq_off = (size_t)p.kv_seq * L.Tpad * d * (m.dtype == L2PD_FP32 ? 4 : 2);
-  const float* cos_t = c->at<float>(L.cos_t);
-  const float* sin_t = c->at<float>(L.sin_t);
+  const float2* rope = c->at<float2>(L.rope);
   bool pending = false;   // bf16: split-K partials of the previous projection not yet folded into h
   int pend_splits = 0;
   size_t pend_stride = 0;
@@ -244,7 +242,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
         launch_gemm_f32(xn, (const float*)c->wk[l], c->at<float>(L.tmp_k), rows, d, d, 0, g, s);
         launch_gemm_f32(xn, (const float*)c->wv[l], c->at<float>(L.tmp_v), rows, d, d, 0, g, s);
         launch_rope_store_f32(q, c->at<float>(L.tmp_k), c->at<float>(L.tmp_v), ks, vs, p.B, p.Tq, p.pos0, L.Tpad, H,
-                              Dh, cos_t, sin_t, seq_gb, p.pos_per_gb, g, s); }
+                              Dh, rope, seq_gb, p.pos_per_gb, g, s); }
       if (p.kv_only_last && l + 1 == m.n_layers) break;
       { Timed t(c, L2PD_K_ATTN, s);
         launch_attn_f32(q, ks, vs, c->at<float>(L.attn), p.B, p.Tq, p.Tk, L.Tpad, H, Dh, p.tk_dev, g, s); }
@@ -267,16 +265,11 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       bf16* vts = reinterpret_cast<bf16*>(c->ws + L.vstore + kvo_v + kv_seq_off);
       float* parts = c->at<float>(L.parts);
       const bool skinny = rows <= kSkinnyRows;
-      // the activations go to the fused GEMMs in the layout these ask for (row-major or quad-tiled)
-      const bool tiled_qkv = !skinny && gemm_qkv_a_quad_tiled(rows, d, d, Dh);
-      const bool tiled_ffn = !skinny && gemm_swiglu_a_quad_tiled(rows, F, d);
-      const bool tiled_o = !skinny && gemm_partial_a_quad_tiled(rows, d, d);      // attention output -> output projection
-      const bool tiled_down = !skinny && gemm_partial_a_quad_tiled(rows, d, F);   // SwiGLU activations -> down projection
       { Timed t(c, L2PD_K_NORM, s);
         launch_rmsnorm(h, pending ? parts : nullptr, pend_splits, pend_stride, ident, c->attn_g[l], m.dtype, xn, rows,
-                       d, m.rms_eps, true, g, s, tiled_qkv); }
+                       d, m.rms_eps, true, g, s); }
       pending = false;
-      QkvEpilogue e = {q, ks, vts, cos_t, sin_t, p.Tq, p.pos0, L.Tpad, H, Dh, d, seq_gb, p.pos_per_gb};
+      QkvEpilogue e = {q, ks, vts, rope, p.Tq, p.pos0, L.Tpad, H, Dh, d, seq_gb, p.pos_per_gb};
       { Timed t(c, L2PD_K_GEMM_QKV, s);
         if (skinny) {
           const int S = skinny_splits(3 * d, d);
@@ -292,7 +285,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       bf16* ao = c->at<bf16>(L.attn);
       { Timed t(c, L2PD_K_ATTN, s);
         launch_attn_bf16(q, ks, vts, ao, p.B, p.Tq, p.Tk, L.Tpad, H, Dh, c->at<float>(L.attn_ws), L.attn_ws_bytes,
-                         p.tk_dev, g, s, tiled_o); }
+                         p.tk_dev, g, s); }
       // Few row tiles leave CUs idle on the [d, d] and [d, F] projections: split K as far as
       // wide_splits (wide path) or skinny_splits (few-row path) says.
       const int so = skinny ? skinny_splits(d, d) : wide_splits(rows, d, d);
@@ -303,10 +296,9 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
           launch_gemm_skinny_bf16(ao, (const bf16*)c->wo[l], nullptr, nullptr, 0, parts, stride_d, rows, d, d, so, g,
                                   s);
         else
-          launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], parts, stride_d, rows, d, d, so, g, s); }
+          launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], parts, stride_d, rows, d, d, g, s); }
       { Timed t(c, L2PD_K_NORM, s);
-        launch_rmsnorm(h, parts, so, stride_d, ident, c->ffn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s,
-                       tiled_ffn); }
+        launch_rmsnorm(h, parts, so, stride_d, ident, c->ffn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
       bf16* act = c->at<bf16>(L.act);
       { Timed t(c, L2PD_K_GEMM_GATEUP, s);
         if (skinny && !swiglu_few_rows_fused(rows, F)) {
@@ -315,15 +307,17 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
           launch_gemm_skinny_bf16(xn, (const bf16*)c->wg[l], (const bf16*)c->wu[l], nullptr, F, parts, stride, rows,
                                   2 * F, d, S, g, s);
           launch_skinny_swiglu_finish(parts, S, stride, rows, F, act, g, s);
+        } else if (skinny) {
+          launch_gemm_few_rows_swiglu_bf16(xn, (const bf16*)c->wg[l], (const bf16*)c->wu[l], act, rows, F, d, g, s);
         } else {
-          launch_gemm_swiglu_bf16(xn, (const bf16*)c->wg[l], (const bf16*)c->wu[l], act, rows, F, d, g, s, tiled_down);
+          launch_gemm_swiglu_bf16(xn, (const bf16*)c->wg[l], (const bf16*)c->wu[l], act, rows, F, d, g, s);
         } }
       { Timed t(c, L2PD_K_GEMM_DOWN, s);
         if (skinny)
           launch_gemm_skinny_bf16(act, (const bf16*)c->wd[l], nullptr, nullptr, 0, parts, stride_d, rows, d, F, sd, g,
                                   s);
         else
-          launch_gemm_partial_bf16(act, (const bf16*)c->wd[l], parts, stride_d, rows, d, F, sd, g, s); }
+          launch_gemm_partial_bf16(act, (const bf16*)c->wd[l], parts, stride_d, rows, d, F, g, s); }
       pending = true;
       pend_splits = sd;
       pend_stride = stride_d;
@@ -360,7 +354,7 @@ void run_head(l2pd_ctx* c, int B, int n_rows_per_seq, RowMap src, float* logits_
     const int sd = c->pend_splits;
     { Timed t(c, L2PD_K_NORM, s);
       launch_rmsnorm(h, sd > 0 ? c->at<float>(L.parts) : nullptr, sd, c->pend_stride, src, c->final_g, m.dtype, xh, hr,
-                     d, m.rms_eps, false, g, s, gemm_lmhead_a_quad_tiled(hr, V, d)); }
+                     d, m.rms_eps, false, g, s); }
     LmHeadEpilogue e = {};
     e.logits = logits_out;
     if (want_parts) {
@@ -372,7 +366,8 @@ void run_head(l2pd_ctx* c, int B, int n_rows_per_seq, RowMap src, float* logits_
     e.mask_id = m.mask_id;
     e.bias = bias;
     Timed t(c, L2PD_K_LMHEAD, s);
-    launch_gemm_lmhead_bf16(xh, (const bf16*)c->lm_head, hr, V, d, e, g, s);
+    if (hr <= kSkinnyRows) launch_gemm_few_rows_lmhead_bf16(xh, (const bf16*)c->lm_head, hr, V, d, e, g, s);
+    else launch_gemm_lmhead_bf16(xh, (const bf16*)c->lm_head, hr, V, d, e, g, s);
   }
 }
 

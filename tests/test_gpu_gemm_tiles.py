@@ -1,0 +1,54 @@
+"""Tile edges of the many-row bf16 GEMMs: forwards of one-layer models whose widths and row counts make the tile
+chooser take each of its tiles (128 x 64 up to 256 x 256), with the row counts just below, at and above a tile, K from
+one 64-deep stage (fewer than the ring holds) to odd numbers of them, output columns that no tile divides, and the LM
+head on 65, 128, 129 and 256 rows.  Same bound as the other bf16 forwards: 2e-2 of the largest logit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_25188_amd import binding as Bd
+from paper_2509_25188_amd import synth
+from tests import parity as Pz
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (d, H, Dh, F, V, B, T, head rows)
+    (64, 1, 64, 64, 300, 1, 65, 65),          # one stage of K, one tile, a row more than the few-row path
+    (64, 1, 64, 128, 257, 1, 128, 128),       # K of one and two stages
+    (192, 3, 64, 320, 385, 1, 129, 129),      # three and five stages; LM head 256 x 256 with one row in its second half
+    (256, 2, 128, 320, 500, 2, 128, 64),      # 256 rows in two sequences
+    (256, 4, 64, 448, 640, 1, 257, 256),      # one row in the second 256-row tile
+    (256, 2, 128, 12288, 300, 1, 700, 32),    # gate/up 256 x 192 tiles, down K = 12288 in four ranges
+    (256, 2, 128, 12288, 300, 3, 401, 32),    # gate/up 256 x 256 tiles, 1203 rows over three sequences
+    (512, 4, 128, 8192, 300, 2, 513, 200),    # 1026 rows; head rows of two sequences in slabs
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_tile_edges(case):
+    d, H, Dh, F, V, B, T, rows = CASES[case]
+    m = synth.ModelShape(1, d, H, Dh, F, V, V - 1, V - 2, dtype="bf16")
+    weights = synth.make_weights(m, 240 + case, "cpu")
+    ora = Pz.oracle_model(m, weights, gemm_input="bf16")
+    eng = Bd.Engine(m, Pz.to_dev(weights), B, T)
+    X = synth.make_prompt(260 + case, B, T, V - 2, "cpu")
+    got = eng.forward(X.cuda(), T - rows, rows)
+    again = eng.forward(X.cuda(), T - rows, rows)
+    assert torch.equal(got, again)
+    got = got.cpu().numpy()
+    for b in range(B):
+        ref = ora.forward(X[b].numpy())[T - rows:]
+        assert Pz.rel_err(got[b], ref) < 2e-2, b
+
+
+def test_rows_are_the_same_bits_in_every_tile():
+    # the same 300 rows alone (128- or 256-row tiles, a workgroup per K range) and as the first of nine sequences
+    # (larger tiles, K ranges walked by one workgroup): row by row the same sums in the same order
+    m = synth.ModelShape(1, 2048, 16, 128, 4096, 300, 299, 298, dtype="bf16")
+    eng = Bd.Engine(m, synth.make_weights(m, 3, "cuda"), 9, 300)
+    X = synth.make_prompt(5, 9, 300, 298, "cuda")
+    many = eng.forward(X, 0, 200)
+    for b in (0, 4, 8):
+        alone = eng.forward(X[b:b + 1].contiguous(), 0, 200)
+        assert torch.equal(alone[0], many[b]), b
