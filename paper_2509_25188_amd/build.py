@@ -8,7 +8,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libl2pd.so")
-SOURCES = ["kernels_misc.hip", "kernels_f32.hip", "gemm_bf16.hip", "gemm_few_rows.hip", "attn_bf16.hip", "l2pd_api.hip"]
+SOURCES = ["kernels_misc.hip", "kernels_train.hip", "kernels_f32.hip", "gemm_bf16.hip", "gemm_few_rows.hip", "attn_bf16.hip", "l2pd_api.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -740,169 +740,4 @@ void launch_seq_len(const int32_t* X, int B, int P, int G, int eos_id, int* teff
   hipLaunchKernelGGL(k_seq_len, dim3(1), dim3(256), 0, s, X, B, P, G, eos_id, teff, ctl);
 }
 
-// ------------------------------------------------------------------------------------------------
-// Filter training (Sec. 3.2, Eq. 6; Sec. 4.1: AdamW): full-batch epochs on the mean binary
-// cross-entropy of sigmoid(W2 relu(W1 c + b1) + b2) against the EGP labels.  One workgroup: the
-// model has a few thousand parameters and a data set of a few thousand rows, so the whole of it is
-// a latency-bound loop that wants no grid synchronisation.  Parameters and the chunk's
-// intermediates live in LDS; every thread owns a few parameters, accumulates their gradient over
-// the rows in ascending order (deterministic) and applies the AdamW update.
-constexpr int kTrainThreads = 1024;
-constexpr int kTrainMaxOwn = 20;                 // parameters per thread
-constexpr int kTrainLdsFloats = 36 * 1024;       // 144 KB
-int filter_param_count(int s, int hidden, int n_layers) {
-  int n = 0;
-  for (int k = 0; k < n_layers; ++k) {
-    const int in = k == 0 ? s : hidden, out = k == n_layers - 1 ? s : hidden;
-    n += out * in + out;
-  }
-  return n;
-}
-static int train_chunk_rows(int s, int hidden, int n_layers) {
-  const int left = kTrainLdsFloats - filter_param_count(s, hidden, n_layers) - 64;
-  int ch = left / (2 * (s + (n_layers - 1) * hidden));
-  return ch > 64 ? 64 : ch;
-}
-int filter_train_supported(int s, int hidden, int n_layers) {
-  return n_layers >= 1 && n_layers <= kFilterMaxLayers && s >= 1 && (n_layers == 1 || hidden >= 1) &&
-         filter_param_count(s, hidden, n_layers) <= kTrainThreads * kTrainMaxOwn &&
-         train_chunk_rows(s, hidden, n_layers) >= 8;
-}
-__global__ void __launch_bounds__(kTrainThreads) k_filter_train(TrainArgs a, int chunk) {
-  extern __shared__ float lds[];
-  const int s = a.s, h = a.hidden, L = a.n_layers, tid = threadIdx.x;
-  // layer k maps width in(k) to width out(k); its parameters sit at off(k) (weights, then biases).
-  // Closed forms rather than tables, so nothing here is indexed dynamically out of registers.
-  auto in = [&](int k) { return k == 0 ? s : h; };
-  auto out = [&](int k) { return k == L - 1 ? s : h; };
-  const int first = h * s + h, mid = h * h + h;            // parameters of layer 0 / of a hidden->hidden layer
-  auto off = [&](int k) { return k == 0 ? 0 : first + (k - 1) * mid; };
-  const int n_params = off(L - 1) + s * in(L - 1) + s;
-  auto layer_of = [&](int p) {
-    if (L == 1 || p < first) return 0;
-    const int k = 1 + (p - first) / mid;
-    return k < L - 1 ? k : L - 1;
-  };
-  // LDS: parameters, then per chunk the input of every layer (A(0) = the confidence rows) and the
-  // loss gradient at every layer's pre-activation (D), then reduction scratch
-  float* th = lds;
-  float* const baseA = th + n_params;
-  float* const baseD = baseA + chunk * (s + (L - 1) * h);
-  auto A = [&](int k) { return baseA + (k == 0 ? 0 : chunk * s + (k - 1) * chunk * h); };
-  auto D = [&](int k) { return baseD + k * chunk * h; };
-  float* red = baseD + chunk * ((L - 1) * h + s);          // 64 floats
-  for (int p = tid; p < n_params; p += kTrainThreads) {
-    const int k = layer_of(p), q = p - off(k), nw = out(k) * in(k);
-    th[p] = q < nw ? a.w[k][q] : a.b[k][q - nw];
-    a.opt_state[p] = 0.f;
-    a.opt_state[n_params + p] = 0.f;
-  }
-  __syncthreads();
-  const float inv_m = 1.f / ((float)a.n * (float)s);
-  float b1t = 1.f, b2t = 1.f;     // beta^t
-  for (int ep = 0; ep < a.epochs; ++ep) {
-    float g[kTrainMaxOwn];
-#pragma unroll
-    for (int o = 0; o < kTrainMaxOwn; ++o) g[o] = 0.f;
-    float loss = 0.f;
-    for (long long c0 = 0; c0 < a.n; c0 += chunk) {
-      const int rows = (int)min((long long)chunk, a.n - c0);
-      for (int i = tid; i < rows * s; i += kTrainThreads) A(0)[i] = a.conf[c0 * s + i];
-      __syncthreads();
-      for (int k = 0; k + 1 < L; ++k) {                            // hidden activations
-        const float* W = th + off(k);
-        const float* Bv = W + out(k) * in(k);
-        for (int i = tid; i < rows * out(k); i += kTrainThreads) {
-          const int r = i / out(k), t = i % out(k);
-          float acc = Bv[t];
-          for (int j = 0; j < in(k); ++j) acc += W[t * in(k) + j] * A(k)[r * in(k) + j];
-          A(k + 1)[i] = fmaxf(acc, 0.f);
-        }
-        __syncthreads();
-      }
-      {                                                            // logits, loss, dL/dz
-        const int k = L - 1;
-        const float* W = th + off(k);
-        const float* Bv = W + s * in(k);
-        for (int i = tid; i < rows * s; i += kTrainThreads) {
-          const int r = i / s, j = i % s;
-          float z = Bv[j];
-          for (int t = 0; t < in(k); ++t) z += W[j * in(k) + t] * A(k)[r * in(k) + t];
-          const float y = a.label[c0 * s + i];
-          loss += fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - y * z;   // softplus(z) - y z
-          D(k)[i] = (1.f / (1.f + expf(-z)) - y) * inv_m;
-        }
-        __syncthreads();
-      }
-      for (int k = L - 1; k > 0; --k) {                            // back through layer k and the ReLU before it
-        const float* W = th + off(k);
-        for (int i = tid; i < rows * in(k); i += kTrainThreads) {
-          const int r = i / in(k), t = i % in(k);
-          float acc = 0.f;
-          for (int j = 0; j < out(k); ++j) acc += D(k)[r * out(k) + j] * W[j * in(k) + t];
-          D(k - 1)[i] = A(k)[i] > 0.f ? acc : 0.f;
-        }
-        __syncthreads();
-      }
-#pragma unroll
-      for (int o = 0; o < kTrainMaxOwn; ++o) {                     // gradient of the owned parameters
-        const int p = tid + o * kTrainThreads;
-        if (p >= n_params) break;
-        const int k = layer_of(p), q = p - off(k), nw = out(k) * in(k);
-        float acc = 0.f;
-        if (q < nw) {
-          const int t = q / in(k), j = q % in(k);
-          for (int r = 0; r < rows; ++r) acc += D(k)[r * out(k) + t] * A(k)[r * in(k) + j];
-        } else {
-          const int t = q - nw;
-          for (int r = 0; r < rows; ++r) acc += D(k)[r * out(k) + t];
-        }
-        g[o] += acc;
-      }
-      __syncthreads();
-    }
-    // loss of the epoch (before its update)
-    if (a.loss_out) {
-#pragma unroll
-      for (int of = 32; of > 0; of >>= 1) loss += __shfl_xor(loss, of, 64);
-      if ((tid & 63) == 0) red[tid >> 6] = loss;
-      __syncthreads();
-      if (tid == 0) {
-        float tot = 0.f;
-        for (int w = 0; w < kTrainThreads / 64; ++w) tot += red[w];
-        a.loss_out[ep] = tot * inv_m;
-      }
-    }
-    // AdamW, decoupled weight decay
-    b1t *= a.beta1;
-    b2t *= a.beta2;
-#pragma unroll
-    for (int o = 0; o < kTrainMaxOwn; ++o) {
-      const int p = tid + o * kTrainThreads;
-      if (p >= n_params) break;
-      const float m = a.beta1 * a.opt_state[p] + (1.f - a.beta1) * g[o];
-      const float v = a.beta2 * a.opt_state[n_params + p] + (1.f - a.beta2) * g[o] * g[o];
-      a.opt_state[p] = m;
-      a.opt_state[n_params + p] = v;
-      const float mh = m / (1.f - b1t), vh = v / (1.f - b2t);
-      th[p] = th[p] - a.lr * (mh / (sqrtf(vh) + a.eps) + a.weight_decay * th[p]);
-    }
-    __syncthreads();
-  }
-  for (int p = tid; p < n_params; p += kTrainThreads) {
-    const int k = layer_of(p), q = p - off(k), nw = out(k) * in(k);
-    if (q < nw) a.w[k][q] = th[p];
-    else a.b[k][q - nw] = th[p];
-  }
-}
-void launch_filter_train(const TrainArgs& a, hipStream_t s) {
-  const int chunk = train_chunk_rows(a.s, a.hidden, a.n_layers);
-  const int n_params = filter_param_count(a.s, a.hidden, a.n_layers);
-  const size_t smem =
-      (size_t)(n_params + chunk * 2 * (a.s + (a.n_layers - 1) * a.hidden) + 64) * sizeof(float);
-  static DynLdsAttr attr;
-  attr.ensure(reinterpret_cast<const void*>(k_filter_train), kTrainLdsFloats * (int)sizeof(float));
-  hipLaunchKernelGGL(k_filter_train, dim3(1), dim3(kTrainThreads), smem, s, a, chunk);
-}
-
 }  // namespace l2pd

@@ -89,3 +89,30 @@ def test_filters_too_large_for_the_training_kernel_are_refused():
     C = torch.rand(10, 64, device="cuda")
     with pytest.raises(RuntimeError):
         Bd.train_filter(flt, C, (C > 0.5).float(), 2)
+
+
+@pytest.mark.parametrize("n_layers,s,h,n", [
+    (2, 16, 16, 16),      # one tile each way, one chunk without padding
+    (2, 17, 33, 100),     # widths one over a tile; rows that fill part of the last tile
+    (2, 32, 32, 256),     # the most rows that stay resident at this width
+    (2, 32, 32, 257),     # one more: two chunks
+    (3, 5, 7, 1),         # one row, everything padding
+    (4, 48, 48, 130),     # hidden gradients in place of the outputs, two chunks
+    (1, 128, 0, 70),      # single layer, five parameter tiles per wavefront
+    (1, 140, 0, 40),      # more tiles than wavefronts hold: the scalar kernel
+    (2, 16, 512, 30),     # likewise, two layers
+])
+def test_training_at_the_edges_of_the_kernels_tiles(n_layers, s, h, n):
+    # fp32 sums over at most 256 rows and 512 inputs in another order than NumPy's float64: 20 steps stay within
+    # 1e-5 of the loss and (where no ReLU switches) 1e-4 of a parameter, the bounds of the tests above
+    r = np.random.default_rng(91)
+    Cn = r.uniform(size=(n, s)).astype(np.float32)
+    Yn = (r.uniform(size=(n, s)) < 0.2 + 0.6 * Cn).astype(np.float32)
+    flt = synth.make_filter(92, s, h, "cpu", n_layers=n_layers)
+    fdev = {k: v.clone().cuda() for k, v in flt.items()}
+    losses = Bd.train_filter(fdev, torch.tensor(Cn).cuda(), torch.tensor(Yn).cuda(), 20, lr=1e-3).cpu().numpy()
+    ref, ref_losses = O.train_filter(Pz.np_filter(flt), Cn, Yn, 20, lr=1e-3)
+    np.testing.assert_allclose(losses, ref_losses, rtol=1e-5, atol=1e-7)
+    for k in ref:
+        d = np.abs(fdev[k].cpu().numpy() - ref[k])
+        assert np.mean(d < 1e-4) > 0.99 and d.max() < 2.5e-2, (k, d.max(), np.mean(d < 1e-4))
