@@ -4,30 +4,33 @@
 // kstore [B, Tpad, d] and transposed values vtstore [B, H, Dh, Tpad].  A workgroup owns 32*NQ
 // queries of one (sequence, head) and splits the keys into NSPL contiguous ranges; wavefront
 // (query group, key range) runs the online softmax of its 32 queries over its range, and the
-// ranges are merged at the end.  Key/value tiles of 64 keys are staged in LDS (XOR-swizzled rows,
-// NST buffers per range; the next tile waits in registers meanwhile), one tile per range and
-// iteration, shared by the query groups.
+// ranges are merged at the end.  Key/value tiles of 64 keys go global -> LDS directly into a ring of NST tiles
+// per range (rows XOR-swizzled on the global side), one tile per range and iteration, shared by the query groups:
+// one barrier per tile, after which the tiles NST - 1 ahead are sent off.
 //
 // The wave computes S^T = K Q^T (keys are MFMA rows, queries are columns), so that a lane holds
 // scores of ONE query: the row maximum is 31 register maxima plus one cross-lane exchange, and the
 // exponentiated scores are already laid out as the B operand of O^T = V^T P^T.  The key order
 // inside each 16-key MFMA step is the accumulator's (keys {4h..4h+3, 8+4h..8+4h+3} for lane half h);
 // V^T is read from LDS in that same order, which is legal because the contraction is a sum.
-#include "common.h"
+//
+// Exponents are taken relative to a reference that follows the running maximum only when that has grown by more
+// than 2^8 (for any query of the wavefront): P and its sums are floating point, so a common factor of up to 256 costs
+// no precision, and the 64 multiplications that rescale O^T are skipped for most tiles.
+//
+// Bound by vector instructions (32 exponentials a lane and tile) with two wavefronts per SIMD, by their latency
+// with one; with few queries by the stream of stored keys and values.
+#include "gemm_common.h"
 
 namespace l2pd {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-__device__ __forceinline__ unsigned int pack_bf16x2(float lo, float hi) {   // v_cvt_pk_bf16_f32, round to nearest even
-  f32x2 v = {lo, hi};
-  return __builtin_bit_cast(unsigned int, __builtin_convertvector(v, bf16x2_t));
+// the larger of x in the two halves of the wavefront, in every lane
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 template <int DH, int NQ, int NSPL, int NST>
@@ -37,23 +40,22 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
                                                               float* __restrict__ chunk_out,
                                                               const int* __restrict__ tk_dev, Gate g) {
   if (gate_skip(g)) return;
-  constexpr int NW = NQ * NSPL;
-  constexpr int NT = NW * 64;
   constexpr int KT = 64;                       // keys per LDS tile
   constexpr int K_ROW = DH * 2;                // bytes per key row
   constexpr int K_BYTES = KT * K_ROW;
   constexpr int V_BYTES = DH * KT * 2;         // [DH rows][64 keys]
   constexpr int STAGE = K_BYTES + V_BYTES;
-  constexpr int KCH = K_BYTES / 16 / NT, VCH = V_BYTES / 16 / NT;
-  static_assert(KCH * NT * 16 == K_BYTES && VCH * NT * 16 == V_BYTES, "tile/threads mismatch");
+  constexpr int KL = K_BYTES / 1024 / NQ, VL = V_BYTES / 1024 / NQ;   // 1 KB loads per wavefront and tile
+  static_assert(KL * NQ * 1024 == K_BYTES && VL * NQ * 1024 == V_BYTES, "tile/wavefronts mismatch");
+  static_assert(NST >= 2 && (NST - 2) * (KL + VL) < 64, "ring depth");
   constexpr int KK = DH / 16;                  // MFMA steps over the feature dim
   constexpr int FO = DH / 32;                  // output row fragments
   constexpr int XW = FO * 16 + 2;              // floats a wave hands over per lane: O^T fragments, m, l
-  static_assert(NST == 1 || NST == 2, "tile buffers are single or double");
   // the exchange area of the final merge reuses the tile buffers; the launch sizes LDS for the larger of the two
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [NST stages][NSPL key ranges][K tile | V^T tile]
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [NSPL key ranges][NST tiles][K tile | V^T tile]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5, lj = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, lj = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qg = wave % NQ, sp = wave / NQ;    // query group and key range of this wavefront
   // Workgroups are dealt to the 8 XCDs round-robin by their linear id.  All query tiles of one
   // (sequence, head) read the same K / V^T, so they are given ids that land on one XCD and share
@@ -87,56 +89,40 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
     for (int kk = 0; kk < KK; ++kk) fq[kk] = *reinterpret_cast<const bf16x8_t*>(qp + kk * 16);
   }
 
-  const bf16* kbase = kstore + (size_t)b * Tpad * d + h * DH;
-  const bf16* vbase = vtstore + (size_t)(b * H + h) * DH * Tpad;
-  // LDS swizzle: the 64 banks sweep 256 bytes.  A K row is 256 B (DH = 128: key = row & 15 over its
-  // 16 chunks) or 128 B (DH = 64: two rows per sweep, key = (row >> 1) & 7); a V^T row is 128 B.
+  // Direct-to-LDS loads of a tile: this wavefront's pieces are qg + i * NQ, 1 KB each, lane l at byte 16 * l.
+  // The 64 LDS banks sweep 256 bytes.  A K row is 256 B (DH = 128: key = row & 15 over its 16 chunks) or 128 B
+  // (DH = 64: two rows per sweep, key = (row >> 1) & 7); a V^T row is 128 B.
   auto kkey = [](int r) { return DH == 128 ? (r & 15) : ((r >> 1) & 7); };
-  const bf16* srcK[KCH];
-  int dstK[KCH];
+  constexpr int KC = DH / 8;                   // 16-byte chunks per key row
+  const bf16* srcK[KL];
+  const bf16* srcV[VL];
 #pragma unroll
-  for (int i = 0; i < KCH; ++i) {
-    int c = tid + i * NT;
-    int r = c / (DH / 8), cc = c % (DH / 8);
-    srcK[i] = kbase + (size_t)r * d + cc * 8;
-    dstK[i] = r * K_ROW + ((cc ^ kkey(r)) << 4);
+  for (int i = 0; i < KL; ++i) {
+    const int r = (qg + i * NQ) * (64 / KC) + lane / KC, c = (lane % KC) ^ kkey(r);
+    srcK[i] = kstore + ((size_t)b * Tpad + r) * d + h * DH + c * 8;
   }
-  const bf16* srcV[VCH];
-  int dstV[VCH];
 #pragma unroll
-  for (int i = 0; i < VCH; ++i) {
-    int c = tid + i * NT;
-    int r = c >> 3, cc = c & 7;
-    srcV[i] = vbase + (size_t)r * Tpad + cc * 8;
-    dstV[i] = K_BYTES + r * (KT * 2) + ((cc ^ ((r >> 1) & 7)) << 4);
+  for (int i = 0; i < VL; ++i) {
+    const int r = (qg + i * NQ) * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    srcV[i] = vtstore + ((size_t)(b * H + h) * DH + r) * Tpad + c * 8;
   }
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane(
+      (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)(smem + sp * NST * STAGE + qg * 1024));
   // The key tiles are dealt to the NSPL key ranges in contiguous runs of `per` tiles; every range
   // is walked by NQ wavefronts (one per query group), and all ranges advance together, one tile
-  // per iteration, so the dependent chain of a wavefront is `per` tiles long instead of n_tiles.
+  // per iteration.
   const int n_tiles = (Tk + KT - 1) / KT;
   const int per_chunk = (n_tiles + n_chunks - 1) / n_chunks;    // the host picks n_chunks so that no chunk is empty
   const int wg_first = ch * per_chunk, wg_count = min(per_chunk, n_tiles - wg_first);
   const int per = (wg_count + NSPL - 1) / NSPL;
-  u32x4 rk[NSPL][KCH], rv[NSPL][VCH];
-  auto gload = [&](int it) {
+  const int my_first = wg_first + sp * per, my_count = max(0, min(per, wg_first + wg_count - my_first));
+  auto load_tile = [&](int t) {
+    const size_t k0 = (size_t)(my_first + t) * KT;
+    const unsigned dst = lds0 + (t % NST) * STAGE;
 #pragma unroll
-    for (int x = 0; x < NSPL; ++x) {
-      const int k0 = min(wg_first + x * per + it, n_tiles - 1) * KT;   // ranges that have run out re-read a valid tile
+    for (int i = 0; i < KL; ++i) dma16(srcK[i] + k0 * d, dst + i * NQ * 1024);
 #pragma unroll
-      for (int i = 0; i < KCH; ++i) rk[x][i] = *reinterpret_cast<const u32x4*>(srcK[i] + (size_t)k0 * d);
-#pragma unroll
-      for (int i = 0; i < VCH; ++i) rv[x][i] = *reinterpret_cast<const u32x4*>(srcV[i] + k0);
-    }
-  };
-  auto sstore = [&](int stage) {
-#pragma unroll
-    for (int x = 0; x < NSPL; ++x) {
-      unsigned char* base = smem + ((NST == 2 ? stage : 0) * NSPL + x) * STAGE;
-#pragma unroll
-      for (int i = 0; i < KCH; ++i) *reinterpret_cast<u32x4*>(base + dstK[i]) = rk[x][i];
-#pragma unroll
-      for (int i = 0; i < VCH; ++i) *reinterpret_cast<u32x4*>(base + dstV[i]) = rv[x][i];
-    }
+    for (int i = 0; i < VL; ++i) dma16(srcV[i] + k0, dst + K_BYTES + i * NQ * 1024);
   };
 
   f32x16 o[FO];
@@ -144,90 +130,96 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
   for (int f = 0; f < FO; ++f)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[f][r] = 0.f;
-  float m = -INFINITY, lsum = 0.f;
+  float m = -INFINITY, lsum = 0.f;             // reference of the exponents (scaled scores, base 2), sum of P
   const float sc = rsqrtf((float)DH) * 1.4426950408889634f;   // softmax scale folded with log2(e)
   const int keyK = kkey(lj), keyV = (lj >> 1) & 7;   // fragment rows are lj modulo 32
-  const int my_first = wg_first + sp * per, my_count = max(0, min(per, wg_first + wg_count - my_first));
 
-  gload(0);
-  sstore(0);
-  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < NST - 1; ++t)
+    if (t < my_count) load_tile(t);
   for (int t = 0; t < per; ++t) {
-    const bool more = t + 1 < per;
-    if (more) gload(t + 1);
-    if (t < my_count) {
-      const unsigned char* base = smem + ((NST == 2 ? (t & 1) : 0) * NSPL + sp) * STAGE;
-      const int k0 = (my_first + t) * KT;
+    // tile t has landed (the younger ones, if all of them were sent off, may still be on their way) ...
+    if (t + NST - 2 < my_count) wait_vmcnt<(NST - 2) * (KL + VL)>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_s_waitcnt(0xc07f);        // ... and this wavefront's reads of tile t - 1 are complete
+    if constexpr (NQ * NSPL > 1) lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + NST - 1 < my_count) load_tile(t + NST - 1);   // into the place of tile t - 1
+    if (t >= my_count) continue;
+    const unsigned char* base = smem + (sp * NST + t % NST) * STAGE;
+    const int k0 = (my_first + t) * KT;
 
-      // S^T for the two 32-key halves of the tile
-      f32x16 s[2];
+    // S^T for the two 32-key halves of the tile
+    f32x16 s[2];
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
+    for (int sub = 0; sub < 2; ++sub) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
-        const unsigned char* krow = base + (sub * 32 + lj) * K_ROW;
+      for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
+      const unsigned char* krow = base + (sub * 32 + lj) * K_ROW;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          bf16x8_t fk = *reinterpret_cast<const bf16x8_t*>(krow + (((kk * 2 + hf) ^ keyK) << 4));
-          s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk, fq[kk], s[sub], 0, 0, 0);
-        }
+      for (int kk = 0; kk < KK; ++kk) {
+        bf16x8_t fk = *reinterpret_cast<const bf16x8_t*>(krow + (((kk * 2 + hf) ^ keyK) << 4));
+        s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk, fq[kk], s[sub], 0, 0, 0);
       }
-      float tmax = -INFINITY;
+    }
+    if (k0 + KT > Tk) {                        // the last tile: keys past the end
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          int kidx = k0 + sub * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
-          float v = kidx < Tk ? s[sub][r] * sc : -INFINITY;
-          s[sub][r] = v;
-          tmax = fmaxf(tmax, v);
-        }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+        for (int r = 0; r < 16; ++r)
+          if (k0 + sub * 32 + (r >> 2) * 8 + hf * 4 + (r & 3) >= Tk) s[sub][r] = -INFINITY;
+    }
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[sub][r]);
+    tmax = max_halves(tmax) * sc;
+    if (__any(tmax > m + 8.f)) {               // (m = -inf on the first tile)
       const float mn = fmaxf(m, tmax);
-      const float alpha = __builtin_amdgcn_exp2f(m - mn);       // m = -inf on the first tile gives 0
+      const float alpha = __builtin_amdgcn_exp2f(m - mn);
       m = mn;
-      float ps = 0.f;
-      unsigned int pk[2][8];                   // bf16 pairs: [sub][4 per 16-key step * 2 steps]
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          // v_exp_f32 directly: arguments are <= 0, and a result below the normal range may flush to zero
-          float p0 = __builtin_amdgcn_exp2f(s[sub][r] - mn), p1 = __builtin_amdgcn_exp2f(s[sub][r + 1] - mn);
-          ps += p0 + p1;
-          pk[sub][r >> 1] = pack_bf16x2(p0, p1);
-        }
-      lsum = lsum * alpha + ps;
+      lsum *= alpha;
 #pragma unroll
       for (int f = 0; f < FO; ++f)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[f][r] *= alpha;
+    }
+    float ps = 0.f;
+    unsigned int pk[2][8];                     // bf16 pairs: [sub][4 per 16-key step * 2 steps]
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        // v_exp_f32 directly: arguments are <= 8, and a result below the normal range may flush to zero
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[sub][r], sc, -m)), p1 = __builtin_amdgcn_exp2f(fmaf(s[sub][r + 1], sc, -m));
+        ps += p0 + p1;
+        pk[sub][r >> 1] = pack_bf16(p0, p1);
+      }
+    lsum += ps;
 
-      // O^T += V^T P^T, 16 keys per MFMA
+    // O^T += V^T P^T, 16 keys per MFMA
 #pragma unroll
-      for (int m16 = 0; m16 < 4; ++m16) {
-        const int sub = m16 >> 1, mm = m16 & 1;
-        u32x4 pw = {pk[sub][mm * 4 + 0], pk[sub][mm * 4 + 1], pk[sub][mm * 4 + 2], pk[sub][mm * 4 + 3]};
-        bf16x8_t fp = __builtin_bit_cast(bf16x8_t, pw);
+    for (int m16 = 0; m16 < 4; ++m16) {
+      const int sub = m16 >> 1, mm = m16 & 1;
+      u32x4 pw = {pk[sub][mm * 4 + 0], pk[sub][mm * 4 + 1], pk[sub][mm * 4 + 2], pk[sub][mm * 4 + 3]};
+      bf16x8_t fp = __builtin_bit_cast(bf16x8_t, pw);
 #pragma unroll
-        for (int f = 0; f < FO; ++f) {
-          const unsigned char* vrow = base + K_BYTES + (f * 32 + lj) * (KT * 2) + hf * 8;
-          u32x2 v0 = *reinterpret_cast<const u32x2*>(vrow + (((m16 * 2) ^ keyV) << 4));
-          u32x2 v1 = *reinterpret_cast<const u32x2*>(vrow + (((m16 * 2 + 1) ^ keyV) << 4));
-          u32x4 vw = {v0.x, v0.y, v1.x, v1.y};
-          bf16x8_t fv = __builtin_bit_cast(bf16x8_t, vw);
-          o[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv, fp, o[f], 0, 0, 0);
-        }
+      for (int f = 0; f < FO; ++f) {
+        const unsigned char* vrow = base + K_BYTES + (f * 32 + lj) * (KT * 2) + hf * 8;
+        u32x2 v0 = *reinterpret_cast<const u32x2*>(vrow + (((m16 * 2) ^ keyV) << 4));
+        u32x2 v1 = *reinterpret_cast<const u32x2*>(vrow + (((m16 * 2 + 1) ^ keyV) << 4));
+        u32x4 vw = {v0.x, v0.y, v1.x, v1.y};
+        bf16x8_t fv = __builtin_bit_cast(bf16x8_t, vw);
+        o[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv, fp, o[f], 0, 0, 0);
       }
     }
-    if constexpr (NST == 1) __syncthreads();   // single buffer: every wavefront is done with the tiles before the refill
-    if (more) sstore((t + 1) & 1);
-    __syncthreads();
   }
 
   // Merge the key ranges: range 0 of each query group folds in the others' (m, l, O^T), in range
   // order, through the tile buffers (dead now).  A range without keys hands over m = -inf, l = 0.
   if constexpr (NSPL > 1) {
+    __syncthreads();
     float* xch = reinterpret_cast<float*>(smem);
     if (sp > 0) {
       float* mine = xch + (size_t)((sp - 1) * NQ + qg) * XW * 64 + lane;
@@ -277,8 +269,8 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
         u32x2 w;
-        w.x = pack_bf16x2(o[f][rq * 4 + 0] * inv, o[f][rq * 4 + 1] * inv);
-        w.y = pack_bf16x2(o[f][rq * 4 + 2] * inv, o[f][rq * 4 + 3] * inv);
+        w.x = pack_bf16(o[f][rq * 4 + 0] * inv, o[f][rq * 4 + 1] * inv);
+        w.y = pack_bf16(o[f][rq * 4 + 2] * inv, o[f][rq * 4 + 3] * inv);
         *reinterpret_cast<u32x2*>(op + f * 32 + rq * 8 + hf * 4) = w;
       }
   }
@@ -306,8 +298,8 @@ __global__ void __launch_bounds__(256) k_attn_merge(const float* __restrict__ ch
   }
   const float inv = 1.f / L;
   u32x2 w2;
-  w2.x = pack_bf16x2(acc.x * inv, acc.y * inv);
-  w2.y = pack_bf16x2(acc.z * inv, acc.w * inv);
+  w2.x = pack_bf16(acc.x * inv, acc.y * inv);
+  w2.y = pack_bf16(acc.z * inv, acc.w * inv);
   unsigned short* op = reinterpret_cast<unsigned short*>(out) + ((size_t)b * Tq + qi) * (H * DH) + h * DH + f4 * 4;
   *reinterpret_cast<u32x2*>(op) = w2;
 }
@@ -324,7 +316,7 @@ static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16*
   const int q_tiles = (Tq + 32 * NQ - 1) / (32 * NQ), n_tiles = (Tk + 63) / 64;
   // few queries against many keys: deal the key tiles to several workgroups per query tile
   int n_chunks = 1;
-  if (chunk_ws && !tk_dev && q_tiles * H * B < 128 && n_tiles >= 2 * NSPL) {   // chunks must not be empty: launch-wide key count only
+  if (chunk_ws && !tk_dev && q_tiles * H * B < 128 && n_tiles >= (Tq <= 64 ? 2 * NSPL : 8)) {   // chunks must not be empty: launch-wide key count only
     int want = (256 + q_tiles * H * B - 1) / (q_tiles * H * B);
     if (want > 16) want = 16;
     if (want > n_tiles / NSPL) want = n_tiles / NSPL;   // a tile for every key range of a chunk
@@ -341,29 +333,38 @@ static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16*
   }
 }
 
-// 64 queries per workgroup, keys in four ranges, single-buffered tiles (128 KB of LDS at head size
-// 128): with one sequence of a few hundred tokens this gives a workgroup to every CU, two wavefronts
-// to every SIMD and a short chain of dependent key tiles per wavefront.  Measured at 32 heads of 128
-// (us, 512 / 1280 / 4096 tokens): two ranges double-buffered 15.9 / 93.5 / 756, four ranges
-// single-buffered 14.4 / 71.9 / 521; before the XCD-aware workgroup ids the first was 21.5.  The
-// configuration depends on the head size, the head count and the query rows per sequence, and the
-// chunking across workgroups on the shape of the launch, never on the data.
+// The number of key ranges depends on the head size, the query rows per sequence and the head count, never on the batch
+// size or the data (another number sums in another order, and a row's result must not depend on the batch it is
+// part of); a wavefront's 32 queries are the same in every configuration, so how many wavefronts share the tiles may
+// depend on the batch.  Measured with 32 heads of 128 (us; in brackets the kernel before: tiles through registers, four
+// ranges and two barriers a tile):
+//   512 rows          2 wavefronts x 2 ranges 14.1, 2 x 1 17.2, 8 x 1 22.2   (16.0)
+//   8 x 512 rows      2 x 2 106, 4 x 2 69, 8 x 1 56                          (123)
+//   1280 rows         4 x 2 54.7, 8 x 1 45.1                                 (70)
+//   8 x 32 rows over 1280 keys   1 x 2 34.6 (4.97 TB/s), 1 x 1 37.8          (43)
+//   32 x 64 rows over 768 keys   2 x 1 84.5 (5.16 TB/s), 2 x 2 94.3          (115)
+//   16 heads of 64, 221 rows 2 x 2 6.2, 2 x 4 6.3 (6.3); 8 x 384 rows 4 x 2 13.6, 2 x 4 20.6 (23.7)
+// Two ranges pay until one sequence by itself gives every CU a workgroup of 128 queries.
 void launch_attn_bf16(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16* out, int B, int Tq, int Tk,
                       int Tpad, int H, int Dh, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, Gate g,
                       hipStream_t s) {
-  // A sequence long enough to give every CU a workgroup of 128 queries by itself: the key tiles
-  // then serve four query groups instead of two (half the L2 -> LDS traffic per flop) and two
-  // workgroups of 64 KB fit a CU.  Measured at 32 heads of 128, one sequence (us): 1024 tokens
-  // 40.5 -> 27.8, 2048 tokens 141 -> 99, 4096 tokens 520 -> 375.  The batch size is left out of the
-  // criterion on purpose: the two configurations merge key ranges in different orders, and a row's
-  // result must not depend on the batch it is part of.
-  if ((long long)((Tq + 127) / 128) * H >= 256) {
-    if (Dh == 128) launch<128, 4, 2, 1>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, g, s);
-    else launch<64, 4, 2, 1>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, g, s);
-    return;
+#define L2PD_ATTN(DH, NQ, NSPL) \
+  launch<DH, NQ, NSPL, 2>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, g, s)
+#define L2PD_ATTN_DH(NQ, NSPL) (Dh == 128 ? L2PD_ATTN(128, NQ, NSPL) : L2PD_ATTN(64, NQ, NSPL))
+  auto wgs = [&](int queries) { return (long long)((Tq + queries - 1) / queries) * H; };   // per sequence
+  if (Tq <= 64) {      // block-only steps: bound by the stream of stored keys and values
+    if (Tq <= 32) L2PD_ATTN_DH(1, 2);
+    else if (wgs(64) * B >= 512) L2PD_ATTN_DH(2, 1);
+    else L2PD_ATTN_DH(2, 2);
+  } else if (wgs(128) <= 256) {
+    if (wgs(64) * B >= 512) L2PD_ATTN_DH(4, 2);
+    else L2PD_ATTN_DH(2, 2);
+  } else {
+    if (wgs(256) * B >= 128) L2PD_ATTN_DH(8, 1);
+    else L2PD_ATTN_DH(4, 1);
   }
-  if (Dh == 128) launch<128, 2, 4, 1>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, g, s);
-  else launch<64, 2, 4, 1>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, g, s);
+#undef L2PD_ATTN
+#undef L2PD_ATTN_DH
 }
 
 }  // namespace l2pd
