@@ -38,7 +38,7 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
                                                               const bf16* __restrict__ vtstore, bf16* __restrict__ out,
                                                               int B, int Tq, int Tk_all, int Tpad, int H, int n_chunks,
                                                               float* __restrict__ chunk_out,
-                                                              const int* __restrict__ tk_dev, Gate g) {
+                                                              const int* __restrict__ tk_dev, QueryRows sel, Gate g) {
   if (gate_skip(g)) return;
   constexpr int KT = 64;                       // keys per LDS tile
   constexpr int K_ROW = DH * 2;                // bytes per key row
@@ -79,6 +79,8 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
   // (O^T, m, l) to chunk_out and k_attn_merge combines them.
   const int qt = inner / n_chunks, ch = inner % n_chunks;
   const int q0 = qt * (32 * NQ) + qg * 32;
+  const int sel_lo = sel.n > 0 ? sel.base + (sel.seq_gb ? sel.seq_gb[b] * sel.per_gb : 0) : 0;
+  if (sel.n > 0 && (qt * (32 * NQ) >= sel_lo + sel.n || (qt + 1) * (32 * NQ) <= sel_lo)) return;   // no row asked for
   const int qrow = min(q0 + lj, Tq - 1);
 
   // Q as the B operand: lane (query lj, half hf) holds features kk*16 + hf*8 .. +7
@@ -262,8 +264,9 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
     return;
   }
   const float inv = 1.f / l;
-  if (q0 + lj < Tq) {
-    unsigned short* op = reinterpret_cast<unsigned short*>(out) + ((size_t)b * Tq + q0 + lj) * d + h * DH;
+  const int qi = q0 + lj, row = sel.n > 0 ? qi - sel_lo : qi, n_out = sel.n > 0 ? sel.n : Tq;   // row of the output
+  if (qi < Tq && row >= 0 && row < n_out) {
+    unsigned short* op = reinterpret_cast<unsigned short*>(out) + ((size_t)b * n_out + row) * d + h * DH;
 #pragma unroll
     for (int f = 0; f < FO; ++f)
 #pragma unroll
@@ -306,7 +309,7 @@ __global__ void __launch_bounds__(256) k_attn_merge(const float* __restrict__ ch
 
 template <int DH, int NQ, int NSPL, int NST>
 static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16* out, int B, int Tq, int Tk,
-                   int Tpad, int H, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, Gate g, hipStream_t s) {
+                   int Tpad, int H, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, QueryRows sel, Gate g, hipStream_t s) {
   auto kern = k_attn_bf16<DH, NQ, NSPL, NST>;
   constexpr int tiles = NST * NSPL * (64 * DH * 2 + DH * 64 * 2);
   constexpr int xchg = (NSPL - 1) * NQ * ((DH / 32) * 16 + 2) * 64 * 4;
@@ -316,7 +319,7 @@ static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16*
   const int q_tiles = (Tq + 32 * NQ - 1) / (32 * NQ), n_tiles = (Tk + 63) / 64;
   // few queries against many keys: deal the key tiles to several workgroups per query tile
   int n_chunks = 1;
-  if (chunk_ws && !tk_dev && q_tiles * H * B < 128 && n_tiles >= (Tq <= 64 ? 2 * NSPL : 8)) {   // chunks must not be empty: launch-wide key count only
+  if (chunk_ws && !tk_dev && sel.n == 0 && q_tiles * H * B < 128 && n_tiles >= (Tq <= 64 ? 2 * NSPL : 8)) {   // chunks must not be empty: launch-wide key count only
     int want = (256 + q_tiles * H * B - 1) / (q_tiles * H * B);
     if (want > 16) want = 16;
     if (want > n_tiles / NSPL) want = n_tiles / NSPL;   // a tile for every key range of a chunk
@@ -326,7 +329,7 @@ static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16*
   }
   dim3 grid(q_tiles * n_chunks * H * B);
   hipLaunchKernelGGL(kern, grid, dim3(NQ * NSPL * 64), smem, s, q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, n_chunks,
-                     chunk_ws, tk_dev, g);
+                     chunk_ws, tk_dev, sel, g);
   if (n_chunks > 1) {
     const int n = B * H * Tq * (DH / 4);
     hipLaunchKernelGGL(k_attn_merge<DH>, dim3((n + 255) / 256), dim3(256), 0, s, chunk_ws, out, B, Tq, H, n_chunks, g);
@@ -346,10 +349,10 @@ static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16*
 //   16 heads of 64, 221 rows 2 x 2 6.2, 2 x 4 6.3 (6.3); 8 x 384 rows 4 x 2 13.6, 2 x 4 20.6 (23.7)
 // Two ranges pay until one sequence by itself gives every CU a workgroup of 128 queries.
 void launch_attn_bf16(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16* out, int B, int Tq, int Tk,
-                      int Tpad, int H, int Dh, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, Gate g,
-                      hipStream_t s) {
+                      int Tpad, int H, int Dh, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, QueryRows sel,
+                      Gate g, hipStream_t s) {
 #define L2PD_ATTN(DH, NQ, NSPL) \
-  launch<DH, NQ, NSPL, 2>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, g, s)
+  launch<DH, NQ, NSPL, 2>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, sel, g, s)
 #define L2PD_ATTN_DH(NQ, NSPL) (Dh == 128 ? L2PD_ATTN(128, NQ, NSPL) : L2PD_ATTN(64, NQ, NSPL))
   auto wgs = [&](int queries) { return (long long)((Tq + queries - 1) / queries) * H; };   // per sequence
   if (Tq <= 64) {      // block-only steps: bound by the stream of stored keys and values

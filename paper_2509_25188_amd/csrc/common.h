@@ -69,8 +69,10 @@ void launch_embed(float* h, const void* emb, int dtype, const int32_t* tokens, R
 // through `src`.  part z is at parts + z * part_stride, laid out like h.  The sum is written back to h
 // when `write_back` is set; the final norm before the LM head leaves h alone (h is dead after it, and
 // two head rows may map to one row of h, so a write-back would race).
+// h_out: the parts are laid out like y and the sum goes to h_out, laid out like y too, instead of back to h.
 void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const void* gain,
-                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s);
+                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s,
+                    float* h_out = nullptr);
 constexpr int kFilterMaxLayers = 4;
 struct UpdateArgs {
   int32_t* X;            // [B, T]
@@ -165,16 +167,18 @@ __device__ __forceinline__ int seq_pos_offset(const int* seq_gb, int per_gb, int
 }
 void launch_gemm_qkv_bf16(const bf16* A, const bf16* wq, const bf16* wk, const bf16* wv, int M, int K,
                           const QkvEpilogue& e, Gate g, hipStream_t s);
-// partial[z][M,N] = A[:, z-th K slice] * W[:, slice]^T, z < wide_splits(M, N, K)
+// partial[z][M,N] = A[:, z-th K slice] * W[:, slice]^T, z < wide_splits(M, N, K, of_many).  of_many: the rows are some of
+// a pass of more than 256 and sum in the order of such a pass, however few they are.
 void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t part_stride, int M, int N, int K,
-                              Gate g, hipStream_t s);
+                              bool of_many, Gate g, hipStream_t s);
+int k_ranges(int K);                    // K ranges of a pass of more than 256 rows
 // Few-row GEMMs (block-only steps of the cached decode modes, at most kSkinnyRows rows) stream their
 // weights once; K is split until a launch has a few hundred workgroups, each K range staying a
 // multiple of the 64-wide stage.
 constexpr int kSkinnyRows = 64;
 constexpr int kSkinnyRowsAttn = 64;   // B * Tq up to which attention may chunk the keys across workgroups
 int skinny_splits(int N, int K);
-int wide_splits(int M, int N, int K);   // partial buffers the wide path's [d, d] / [d, F] projections write, at most 8
+int wide_splits(int M, int N, int K, bool of_many);   // partial buffers the wide path's [d, d] / [d, F] projections write, at most 8
 void launch_gemm_skinny_bf16(const bf16* A, const bf16* w0, const bf16* w1, const bf16* w2, int n_sub, float* parts,
                              size_t part_stride, int M, int N, int K, int splits, Gate g, hipStream_t s);
 // sums of the skinny GEMM's partials -> rotated q, K store, V^T store / SiLU(gate) * up
@@ -202,9 +206,15 @@ void launch_gemm_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, 
                              hipStream_t s);
 void launch_gemm_few_rows_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, const LmHeadEpilogue& e, Gate g,
                                       hipStream_t s);
+// `sel`: only n query rows of every sequence are wanted, from base + seq_gb[b] * per_gb on (seq_gb null: base); out is
+// then [B * n, d].  n == 0: all of them.
+struct QueryRows {
+  int n, base, per_gb;
+  const int* seq_gb;
+};
 void launch_attn_bf16(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16* out, int B, int Tq, int Tk,
-                      int Tpad, int H, int Dh, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, Gate g,
-                      hipStream_t s);
+                      int Tpad, int H, int Dh, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, QueryRows sel,
+                      Gate g, hipStream_t s);
 // bytes of chunk workspace that lets launch_attn_bf16 spread few queries' keys over workgroups
 inline size_t attn_chunk_ws_bytes(int H, int Dh) { return (size_t)kSkinnyRowsAttn * H * 16 * (Dh + 2) * 4; }
 

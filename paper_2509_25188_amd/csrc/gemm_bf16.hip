@@ -548,14 +548,14 @@ void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16
 // 28, against 141 and 60 estimated for 256x256 tiles and four partials).
 // Up to 256 rows (batched block-only steps of the cached modes) the split may go up to eight ways, as the estimate
 // says: 256 rows of the 8B shape split 4 ways, 128 rows 8 ways.
-static int k_ranges(int K) {
+int k_ranges(int K) {
   if (K % 256 == 0 && K / 4 >= 512) return 4;
   return K % 128 == 0 && K / 2 >= 512 ? 2 : 1;
 }
 constexpr double kFoldUs = 0.8;   // a partial of up to 256 rows costs the RMSNorm this much
 struct PartialPlan { int tile, splits, serial; };
-static PartialPlan plan_partial(int M, int N, int K) {
-  if (M <= 256) {
+static PartialPlan plan_partial(int M, int N, int K, bool of_many) {
+  if (M <= 256 && !of_many) {
     PartialPlan best = {5, 1, 0};
     for (int t : {5, 4})
       for (int S = 1; S <= 8 && K % (S * 64) == 0 && (S == 1 || K / S >= 512); S *= 2)
@@ -569,17 +569,18 @@ static PartialPlan plan_partial(int M, int N, int K) {
   PartialPlan best = {2, 1, R};
   double cost = tile_cost(2, M, N, K, 1) * 1.03 + fold_us;
   for (int t : {0, 1, 2, 4, 5}) {
+    if (M <= 128 && kTiles[t].bm > 128) continue;
     const double c = tile_cost(t, M, N, K, R) + R * fold_us;
     if (c < cost) { cost = c; best = {t, R, 0}; }
   }
   if (best.serial == 1) best.serial = 0;
   return best;
 }
-int wide_splits(int M, int N, int K) { return plan_partial(M, N, K).splits; }
+int wide_splits(int M, int N, int K, bool of_many) { return plan_partial(M, N, K, of_many).splits; }
 
 void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t part_stride, int M, int N, int K,
-                              Gate g, hipStream_t s) {
-  const PartialPlan p = plan_partial(M, N, K);
+                              bool of_many, Gate g, hipStream_t s) {
+  const PartialPlan p = plan_partial(M, N, K, of_many);
   GemmArgs a = {};
   a.A = A; a.B0 = W; a.M = M; a.N = N; a.K = K; a.splits = p.splits; a.gate = g;
   a.parts = parts; a.part_stride = part_stride; a.serial = p.serial;

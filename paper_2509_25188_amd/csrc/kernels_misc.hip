@@ -172,14 +172,15 @@ __device__ __forceinline__ float wave_sum(float v) {
 // parts + z * part_stride, laid out like h.
 template <typename T>
 __global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const T* gain,
-                          T* y, int rows, int d, float eps, int wb, Gate g) {
+                          T* y, int rows, int d, float eps, int wb, float* h_out, Gate g) {
   if (gate_skip(g)) return;
   int lane = threadIdx.x & 63;
   int r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (r >= rows) return;
   size_t srow = (size_t)map_row(src, r, g.ctl);
-  float* x = h + srow * d;
-  const float* a0 = parts + srow * d;
+  const float* x = h + srow * d;
+  float* xo = h_out ? h_out + (size_t)r * d : h + srow * d;
+  const float* a0 = parts + (h_out ? (size_t)r : srow) * d;
   float ss = 0.f;
   for (int i = lane; i < d; i += 64) {
     float v = x[i];
@@ -187,7 +188,7 @@ __global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part
       float ps = a0[i];
       for (int z = 1; z < n_parts; ++z) ps += a0[z * part_stride + i];
       v += ps;
-      if (wb) x[i] = v;
+      if (wb) xo[i] = v;
     }
     ss += v * v;
   }
@@ -195,7 +196,7 @@ __global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part
   float inv = rsqrtf(ss / (float)d + eps);
   T* o = y + (size_t)r * d;
   for (int i = lane; i < d; i += 64) {
-    float v = x[i];
+    float v = wb ? xo[i] : x[i];
     if (n_parts > 0 && !wb) {
       float ps = a0[i];
       for (int z = 1; z < n_parts; ++z) ps += a0[z * part_stride + i];
@@ -209,14 +210,16 @@ __global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part
 template <typename T, int VPL>
 __global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* parts, int n_parts, size_t part_stride,
                                                     RowMap src, const T* gain, T* y, int rows, int d, float eps,
-                                                    int wb, Gate g) {
+                                                    int wb, float* h_out, Gate g) {
   if (gate_skip(g)) return;
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (r >= rows) return;
   const size_t srow = (size_t)map_row(src, r, g.ctl);
   const int d4 = d >> 2;
-  float4* x = reinterpret_cast<float4*>(h + srow * d);
+  const float4* x = reinterpret_cast<const float4*>(h + srow * d);
+  float4* xo = reinterpret_cast<float4*>(h_out ? h_out + (size_t)r * d : h + srow * d);
+  const size_t prow = h_out ? (size_t)r : srow;
   float4 v[VPL];
 #pragma unroll
   for (int k = 0; k < VPL; ++k) {
@@ -226,7 +229,7 @@ __global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* part
   if (n_parts > 0) {
     float4 ps[VPL];
     for (int z = 0; z < n_parts; ++z) {
-      const float4* az = reinterpret_cast<const float4*>(parts + z * part_stride + srow * d);
+      const float4* az = reinterpret_cast<const float4*>(parts + z * part_stride + prow * d);
 #pragma unroll
       for (int k = 0; k < VPL; ++k) {
         const int i = lane + 64 * k;
@@ -239,7 +242,7 @@ __global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* part
     for (int k = 0; k < VPL; ++k) {
       const int i = lane + 64 * k;
       v[k].x += ps[k].x; v[k].y += ps[k].y; v[k].z += ps[k].z; v[k].w += ps[k].w;
-      if (wb && i < d4) x[i] = v[k];
+      if (wb && i < d4) xo[i] = v[k];
     }
   }
   float ss = 0.f;
@@ -276,14 +279,16 @@ __global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* part
 template <typename T, int VPL, int NTH>
 __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* parts, int n_parts, size_t part_stride,
                                                     RowMap src, const T* gain, T* y, int rows, int d, float eps,
-                                                    int wb, Gate g) {
+                                                    int wb, float* h_out, Gate g) {
   if (gate_skip(g)) return;
   __shared__ float s_part[NTH / 64];
   const int tid = threadIdx.x;
   const int r = blockIdx.x;
   const size_t srow = (size_t)map_row(src, r, g.ctl);
   const int d4 = d >> 2;
-  float4* x = reinterpret_cast<float4*>(h + srow * d);
+  const float4* x = reinterpret_cast<const float4*>(h + srow * d);
+  float4* xo = reinterpret_cast<float4*>(h_out ? h_out + (size_t)r * d : h + srow * d);
+  const size_t prow = h_out ? (size_t)r : srow;
   float4 v[VPL];
 #pragma unroll
   for (int k = 0; k < VPL; ++k) {
@@ -301,7 +306,7 @@ __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* part
 #pragma unroll
     for (int z = 0; z < GRP; ++z) {
       const bool have = z0 + z < n_parts;
-      const float4* a = reinterpret_cast<const float4*>(parts + (have ? z0 + z : z0) * part_stride + srow * d);
+      const float4* a = reinterpret_cast<const float4*>(parts + (have ? z0 + z : z0) * part_stride + prow * d);
 #pragma unroll
       for (int k = 0; k < VPL; ++k) {
         const int i = tid + NTH * k;
@@ -326,7 +331,7 @@ __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* part
 #pragma unroll
   for (int k = 0; k < VPL; ++k) {
     const int i = tid + NTH * k;
-    if (wb && n_parts > 0 && i < d4) x[i] = v[k];
+    if (wb && n_parts > 0 && i < d4) xo[i] = v[k];
     ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
   }
   ss = wave_sum(ss);
@@ -364,30 +369,31 @@ __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* part
 constexpr int NORM_TX = 4;   // threads per row = 256 * NORM_TX
 template <typename T>
 static void launch_rmsnorm_t(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const T* gain,
-                             T* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s) {
+                             T* y, int rows, int d, float eps, bool write_back, float* h_out, Gate g, hipStream_t s) {
   const int wb = write_back ? 1 : 0;
   dim3 grid((rows + 3) / 4), block(256);
   if (rows <= 4096) { grid = dim3(rows); block = dim3(64); }   // few rows: one wavefront per workgroup fills more CUs
   if (d % 4 == 0 && d >= 2048 && d <= 4096)
-    hipLaunchKernelGGL((k_rmsnorm_row<T, 4 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
+    hipLaunchKernelGGL((k_rmsnorm_row<T, 4 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else if (d % 4 == 0 && d > 4096 && d <= 8192)
-    hipLaunchKernelGGL((k_rmsnorm_row<T, 8 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
+    hipLaunchKernelGGL((k_rmsnorm_row<T, 8 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else if (d % 4 == 0 && d <= 1024)
-    hipLaunchKernelGGL((k_rmsnorm_vec<T, 4>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
+    hipLaunchKernelGGL((k_rmsnorm_vec<T, 4>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else if (d % 4 == 0 && d <= 4096)
-    hipLaunchKernelGGL((k_rmsnorm_vec<T, 16>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
+    hipLaunchKernelGGL((k_rmsnorm_vec<T, 16>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else if (d % 4 == 0 && d <= 8192)
-    hipLaunchKernelGGL((k_rmsnorm_vec<T, 32>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
+    hipLaunchKernelGGL((k_rmsnorm_vec<T, 32>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else
-    hipLaunchKernelGGL(k_rmsnorm<T>, grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, g);
+    hipLaunchKernelGGL(k_rmsnorm<T>, grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
 }
 void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const void* gain,
-                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s) {
+                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s,
+                    float* h_out) {
   if (!parts) n_parts = 0;
   if (dtype == L2PD_FP32)
-    launch_rmsnorm_t<float>(h, parts, n_parts, part_stride, src, (const float*)gain, (float*)y, rows, d, eps, write_back, g, s);
+    launch_rmsnorm_t<float>(h, parts, n_parts, part_stride, src, (const float*)gain, (float*)y, rows, d, eps, write_back, h_out, g, s);
   else
-    launch_rmsnorm_t<bf16>(h, parts, n_parts, part_stride, src, (const bf16*)gain, (bf16*)y, rows, d, eps, write_back, g, s);
+    launch_rmsnorm_t<bf16>(h, parts, n_parts, part_stride, src, (const bf16*)gain, (bf16*)y, rows, d, eps, write_back, h_out, g, s);
 }
 
 // ------------------------------------------------------------------------------------------------

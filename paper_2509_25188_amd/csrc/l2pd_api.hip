@@ -58,6 +58,7 @@ struct l2pd_ctx {
   int last_hip_error = 0;
   int pend_splits = 0;   // bf16: split-K partials of the last down projection still to be folded into h
   size_t pend_stride = 0;
+  bool tail = false;     // the last pass's rows behind the last attention are the wanted ones alone, in c->L.q (run_layers)
   // the last l2pd_generate: step launches enqueued, and the sum over them of the sequences each ran over
   int64_t stat_steps = 0, stat_seq_steps = 0;
 
@@ -140,7 +141,9 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
     size_t wide = 0;
     for (size_t top = 128;; top += 128) {
       const size_t M = top < rows ? top : rows;
-      const int S = std::max(wide_splits((int)M, m.d_model, m.d_model), wide_splits((int)M, m.d_model, m.d_ffn));
+      int S = 1;
+      for (int k : {m.d_model, m.d_ffn})
+        for (bool of_many : {false, true}) S = std::max(S, wide_splits((int)M, m.d_model, k, of_many));
       wide = std::max(wide, (size_t)S * M * d * 4);
       if (top >= rows) break;
     }
@@ -211,6 +214,10 @@ struct Pass {
   bool kv_only_last;    // refresh pass: the last layer only has to leave its K/V
   const int* tk_dev = nullptr;   // per-sequence number of keys (device), else null
   int kv_seq = 0;       // first sequence slot of the K/V stores this pass works on (single-sequence store rebuilds)
+  // Rows of every sequence that are wanted behind the last layer (`want`, taken through `want_map`); 0: all.  The last
+  // layer then works on all rows up to its keys and values, and on those rows only from its queries on.
+  int want = 0;
+  RowMap want_map = {0, 0, 0, 0};
   int pos_per_gb = 0;   // > 0: per-sequence block pointers with a cache: sequence b's rows sit at pos0 + own block * pos_per_gb
 };
 
@@ -227,6 +234,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
   bool pending = false;   // bf16: split-K partials of the previous projection not yet folded into h
   int pend_splits = 0;
   size_t pend_stride = 0;
+  c->tail = false;
   for (int l = 0; l < m.n_layers; ++l) {
     const size_t kvo_k = p.per_layer_kv ? L.kv_layer_stride_k * l : 0;
     const size_t kvo_v = p.per_layer_kv ? L.kv_layer_stride_v * l : 0;
@@ -283,20 +291,56 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
         } }
       if (p.kv_only_last && l + 1 == m.n_layers) break;
       bf16* ao = c->at<bf16>(L.attn);
+      // The wanted rows alone from here on: h of these rows goes to the place of the queries (dead after the
+      // attention; half as many rows at most, since h is 32 bits wide).  Same sums in the same order as on all rows.
+      const int few = p.B * p.want;
+      if (p.want > 0 && l + 1 == m.n_layers && !skinny && 2 * few <= rows) {
+        const RowMap& w = p.want_map;
+        const QueryRows sel = {p.want, w.off_base, w.off_per_gb, w.off_per_gb && g.ctl ? g.ctl + CTL_SEQ_GB : nullptr};
+        { Timed t(c, L2PD_K_ATTN, s);
+          launch_attn_bf16(q, ks, vts, ao, p.B, p.Tq, p.Tk, L.Tpad, H, Dh, nullptr, 0, p.tk_dev, sel, g, s); }
+        const size_t stride = (size_t)few * d;
+        auto project = [&](const bf16* A, const bf16* W, int K) {
+          if (few > kSkinnyRows) {
+            launch_gemm_partial_bf16(A, W, parts, stride, few, d, K, true, g, s);
+            return wide_splits(few, d, K, true);
+          }
+          launch_gemm_skinny_bf16(A, W, nullptr, nullptr, 0, parts, stride, few, d, K, k_ranges(K), g, s);
+          return k_ranges(K);
+        };
+        int S;
+        { Timed t(c, L2PD_K_GEMM_O, s);
+          S = project(ao, (const bf16*)c->wo[l], d); }
+        float* h_few = c->at<float>(L.q);
+        { Timed t(c, L2PD_K_NORM, s);
+          launch_rmsnorm(h, parts, S, stride, w, c->ffn_g[l], m.dtype, xn, few, d, m.rms_eps, true, g, s, h_few); }
+        bf16* act = c->at<bf16>(L.act);
+        { Timed t(c, L2PD_K_GEMM_GATEUP, s);
+          if (swiglu_few_rows_fused(few, F))
+            launch_gemm_few_rows_swiglu_bf16(xn, (const bf16*)c->wg[l], (const bf16*)c->wu[l], act, few, F, d, g, s);
+          else
+            launch_gemm_swiglu_bf16(xn, (const bf16*)c->wg[l], (const bf16*)c->wu[l], act, few, F, d, g, s); }
+        { Timed t(c, L2PD_K_GEMM_DOWN, s);
+          pend_splits = project(act, (const bf16*)c->wd[l], F); }
+        pending = true;
+        pend_stride = stride;
+        c->tail = true;
+        break;
+      }
       { Timed t(c, L2PD_K_ATTN, s);
         launch_attn_bf16(q, ks, vts, ao, p.B, p.Tq, p.Tk, L.Tpad, H, Dh, c->at<float>(L.attn_ws), L.attn_ws_bytes,
-                         p.tk_dev, g, s); }
+                         p.tk_dev, QueryRows{0, 0, 0, nullptr}, g, s); }
       // Few row tiles leave CUs idle on the [d, d] and [d, F] projections: split K as far as
       // wide_splits (wide path) or skinny_splits (few-row path) says.
-      const int so = skinny ? skinny_splits(d, d) : wide_splits(rows, d, d);
-      const int sd = skinny ? skinny_splits(d, F) : wide_splits(rows, d, F);
+      const int so = skinny ? skinny_splits(d, d) : wide_splits(rows, d, d, false);
+      const int sd = skinny ? skinny_splits(d, F) : wide_splits(rows, d, F, false);
       const size_t stride_d = (size_t)rows * d;
       { Timed t(c, L2PD_K_GEMM_O, s);
         if (skinny)
           launch_gemm_skinny_bf16(ao, (const bf16*)c->wo[l], nullptr, nullptr, 0, parts, stride_d, rows, d, d, so, g,
                                   s);
         else
-          launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], parts, stride_d, rows, d, d, g, s); }
+          launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], parts, stride_d, rows, d, d, false, g, s); }
       { Timed t(c, L2PD_K_NORM, s);
         launch_rmsnorm(h, parts, so, stride_d, ident, c->ffn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
       bf16* act = c->at<bf16>(L.act);
@@ -317,7 +361,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
           launch_gemm_skinny_bf16(act, (const bf16*)c->wd[l], nullptr, nullptr, 0, parts, stride_d, rows, d, F, sd, g,
                                   s);
         else
-          launch_gemm_partial_bf16(act, (const bf16*)c->wd[l], parts, stride_d, rows, d, F, g, s); }
+          launch_gemm_partial_bf16(act, (const bf16*)c->wd[l], parts, stride_d, rows, d, F, false, g, s); }
       pending = true;
       pend_splits = sd;
       pend_stride = stride_d;
@@ -335,7 +379,8 @@ void run_head(l2pd_ctx* c, int B, int n_rows_per_seq, RowMap src, float* logits_
   const l2pd_model_desc& m = c->m;
   const Layout& L = c->L;
   const int d = m.d_model, V = m.vocab, hr = B * n_rows_per_seq;
-  float* h = c->at<float>(L.h);
+  float* h = c->at<float>(c->tail ? L.q : L.h);
+  if (c->tail) src = RowMap{hr, 0, 0, 0};
   if (m.dtype == L2PD_FP32) {
     float* xh = c->at<float>(L.xn_head);
     { Timed t(c, L2PD_K_NORM, s);
@@ -474,8 +519,10 @@ void run_step(l2pd_ctx* c, int32_t* X, int B, int P, const l2pd_decode_cfg* cfg,
     run_head(c, B, sl, RowMap{sl, t_run, P, sl}, taps.logits, true, bias, g, s);
   } else {
     Pass p = {B, T, 0, T, T, X, false, false};
+    p.want = sl;
+    p.want_map = RowMap{sl, T, P, sl};
     run_layers(c, p, g, s);
-    run_head(c, B, sl, RowMap{sl, T, P, sl}, taps.logits, true, bias, g, s);
+    run_head(c, B, sl, p.want_map, taps.logits, true, bias, g, s);
   }
   UpdateArgs u = {};
   u.X = X; u.state = state; u.B = B; u.P = P; u.T = T; u.s = sl; u.n_blocks = nb;
@@ -631,6 +678,10 @@ int32_t l2pd_forward(l2pd_ctx* c, const int32_t* tokens_dev, int32_t B, int32_t 
   if (st) return st;
   Gate g = {nullptr, -1};
   Pass p = {B, T, 0, T, T, tokens_dev, false, false};
+  if (row_count <= 256) {   // one slab of the LM head below
+    p.want = row_count;
+    p.want_map = RowMap{row_count, T, row_begin, 0};
+  }
   run_layers(c, p, g, s);
   // the LM head runs in slabs of rows so that the fp32 path's scratch bound (256 rows per sequence) holds
   for (int r0 = 0; r0 < row_count; r0 += 256) {

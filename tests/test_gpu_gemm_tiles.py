@@ -52,3 +52,15 @@ def test_rows_are_the_same_bits_in_every_tile():
     for b in (0, 4, 8):
         alone = eng.forward(X[b:b + 1].contiguous(), 0, 200)
         assert torch.equal(alone[0], many[b]), b
+
+
+@pytest.mark.parametrize("B,row,rows", [(1, 100, 40), (1, 0, 130), (3, 31, 64), (3, 177, 110)])
+def test_wanted_rows_are_the_same_bits_as_all_rows(B, row, rows):
+    # logits of some rows (the last layer works on those alone behind its keys and values: few-row and tile kernels,
+    # query tiles without a wanted row skipped) against the same rows of a forward that returns them all
+    m = synth.ModelShape(2, 2048, 16, 128, 4096, 300, 299, 298, dtype="bf16")
+    eng = Bd.Engine(m, synth.make_weights(m, 3, "cuda"), B, 300)
+    X = synth.make_prompt(6, B, 300, 298, "cuda")
+    every = eng.forward(X, 0, 300)
+    some = eng.forward(X, row, rows)
+    assert torch.equal(some, every[:, row:row + rows])
