@@ -138,9 +138,13 @@ void launch_vocab_partials(float* logits, int rows, int V, int chunk, int mask_i
                            float* part_sum, int32_t* part_idx, int n_part, Gate g, hipStream_t s);
 
 // ---- fp32 path (kernels_f32.hip) ----
-// C[M,N] (+)= A[M,K] * W[N,K]^T
-void launch_gemm_f32(const float* A, const float* W, float* C, int M, int N, int K, int accumulate, Gate g,
-                     hipStream_t s);
+// C[i][M,N] (+)= A[M,K] * W[i][N,K]^T, i < n <= 3
+void launch_gemm_f32(const float* A, const float* const* W, float* const* C, int n, int M, int N, int K, int accumulate,
+                     Gate g, hipStream_t s);
+inline void launch_gemm_f32(const float* A, const float* W, float* C, int M, int N, int K, int accumulate, Gate g,
+                            hipStream_t s) {
+  launch_gemm_f32(A, &W, &C, 1, M, N, K, accumulate, g, s);
+}
 // rotate q [rows, d] in place and copy/rotate k, v rows into the [B, Tmax, d] key/value stores at pos0 + t
 // (seq_gb / pos_per_gb: per-sequence position offsets as in QkvEpilogue)
 void launch_rope_store_f32(float* q, const float* k, const float* v, float* kstore, float* vstore, int B, int Tq,

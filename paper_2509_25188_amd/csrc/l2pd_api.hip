@@ -246,9 +246,9 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       { Timed t(c, L2PD_K_NORM, s);
         launch_rmsnorm(h, nullptr, 0, 0, ident, c->attn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
       { Timed t(c, L2PD_K_GEMM_QKV, s);
-        launch_gemm_f32(xn, (const float*)c->wq[l], q, rows, d, d, 0, g, s);
-        launch_gemm_f32(xn, (const float*)c->wk[l], c->at<float>(L.tmp_k), rows, d, d, 0, g, s);
-        launch_gemm_f32(xn, (const float*)c->wv[l], c->at<float>(L.tmp_v), rows, d, d, 0, g, s);
+        const float* const w3[3] = {(const float*)c->wq[l], (const float*)c->wk[l], (const float*)c->wv[l]};
+        float* const o3[3] = {q, c->at<float>(L.tmp_k), c->at<float>(L.tmp_v)};
+        launch_gemm_f32(xn, w3, o3, 3, rows, d, d, 0, g, s);
         launch_rope_store_f32(q, c->at<float>(L.tmp_k), c->at<float>(L.tmp_v), ks, vs, p.B, p.Tq, p.pos0, L.Tpad, H,
                               Dh, rope, seq_gb, p.pos_per_gb, g, s); }
       if (p.kv_only_last && l + 1 == m.n_layers) break;
@@ -261,8 +261,9 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       float* gt = c->at<float>(L.gate_up);
       float* up = gt + (size_t)rows * F;
       { Timed t(c, L2PD_K_GEMM_GATEUP, s);
-        launch_gemm_f32(xn, (const float*)c->wg[l], gt, rows, F, d, 0, g, s);
-        launch_gemm_f32(xn, (const float*)c->wu[l], up, rows, F, d, 0, g, s);
+        const float* const w2[2] = {(const float*)c->wg[l], (const float*)c->wu[l]};
+        float* const o2[2] = {gt, up};
+        launch_gemm_f32(xn, w2, o2, 2, rows, F, d, 0, g, s);
         launch_swiglu_f32(gt, up, c->at<float>(L.act), (size_t)rows * F, g, s); }
       { Timed t(c, L2PD_K_GEMM_DOWN, s);
         launch_gemm_f32(c->at<float>(L.act), (const float*)c->wd[l], h, rows, d, F, 1, g, s); }
