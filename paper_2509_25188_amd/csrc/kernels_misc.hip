@@ -54,27 +54,34 @@ void launch_init_decode(int32_t* X, const int32_t* prompt, int B, int P, int G, 
 // Active block of the lock-step batch = smallest block index among sequences that are not done.
 // With `ragged` every sequence works on its own block (per-sequence block pointers): nobody idles
 // while another sequence finishes the common block.
-__global__ void k_prepare(const int32_t* state, int B, int n_blocks, int ragged, int* ctl, int done_at) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    int gb = n_blocks, all_done = 1, n_active = 0;
-    for (int b = 0; b < B; ++b) {
-      if (!state[b * 3 + 2]) {
-        all_done = 0;
-        ++n_active;
-        int bi = state[b * 3 + 0];
-        gb = bi < gb ? bi : gb;
-      }
+// One wavefront, a sequence per lane and round.
+__global__ void __launch_bounds__(64) k_prepare(const int32_t* state, int B, int n_blocks, int ragged, int* ctl,
+                                               int done_at) {
+  const int lane = threadIdx.x;
+  int gb = n_blocks, n_active = 0;
+  for (int b = lane; b < B; b += 64) {
+    const bool live = !state[b * 3 + 2];
+    if (live) {
+      gb = min(gb, state[b * 3 + 0]);
+      ++n_active;
     }
-    if (gb >= n_blocks) all_done = 1;
-    const int last = n_blocks > 0 ? n_blocks - 1 : 0;
-    ctl[CTL_GB] = all_done ? last : gb;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    gb = min(gb, __shfl_xor(gb, o, 64));
+    n_active += __shfl_xor(n_active, o, 64);
+  }
+  const int all_done = n_active == 0 || gb >= n_blocks;
+  const int last = n_blocks > 0 ? n_blocks - 1 : 0;
+  const int common = all_done ? last : gb;
+  if (lane == 0) {
+    ctl[CTL_GB] = common;
     ctl[CTL_ALL_DONE] = all_done;
     ctl[CTL_ACTIVE] = all_done ? 0 : n_active;
-    for (int b = 0; b < B; ++b) {
-      const int own = state[b * 3 + 0] < last ? state[b * 3 + 0] : last;
-      ctl[CTL_SEQ_GB + b] = ragged ? own : ctl[CTL_GB];
-      if (done_at > 0) ctl[done_at + b] = state[b * 3 + 2] ? 1 : 0;
-    }
+  }
+  for (int b = lane; b < B; b += 64) {
+    ctl[CTL_SEQ_GB + b] = ragged ? min(state[b * 3 + 0], last) : common;
+    if (done_at > 0) ctl[done_at + b] = state[b * 3 + 2] ? 1 : 0;
   }
 }
 void launch_prepare(const int32_t* state, int B, int n_blocks, int ragged, int* ctl, hipStream_t s, int done_at) {
@@ -150,10 +157,28 @@ __global__ void k_embed(float* h, const T* emb, const int32_t* tokens, RowMap to
   float* o = h + (size_t)r * d;
   for (int i = threadIdx.x; i < d; i += blockDim.x) o[i] = to_f<T>(e[i]);
 }
+// bf16 rows in 16-byte pieces (rows and table aligned to them): a piece per thread and round.  512 rows of 4096:
+// 11.5 us with 2-byte loads, 5.8 with these; bound by the round trip tokens -> row.
+__global__ void __launch_bounds__(256) k_embed_vec(float* h, const uint4* emb, const int32_t* tokens, RowMap tokmap,
+                                                  int d8, Gate g) {
+  if (gate_skip(g)) return;
+  const int r = blockIdx.x;
+  const uint4* e = emb + (size_t)tokens[map_row(tokmap, r, g.ctl)] * d8;
+  float4* o = reinterpret_cast<float4*>(h) + (size_t)r * d8 * 2;
+  for (int i = threadIdx.x; i < d8; i += 256) {
+    const uint4 v = e[i];
+    auto lo = [](unsigned w) { return __uint_as_float(w << 16); };
+    auto hi = [](unsigned w) { return __uint_as_float(w & 0xffff0000u); };
+    o[2 * i] = make_float4(lo(v.x), hi(v.x), lo(v.y), hi(v.y));
+    o[2 * i + 1] = make_float4(lo(v.z), hi(v.z), lo(v.w), hi(v.w));
+  }
+}
 void launch_embed(float* h, const void* emb, int dtype, const int32_t* tokens, RowMap tokmap, int rows, int d,
                   Gate g, hipStream_t s) {
   if (dtype == L2PD_FP32)
     hipLaunchKernelGGL(k_embed<float>, dim3(rows), dim3(256), 0, s, h, (const float*)emb, tokens, tokmap, rows, d, g);
+  else if (d % 8 == 0 && reinterpret_cast<uintptr_t>(emb) % 16 == 0)
+    hipLaunchKernelGGL(k_embed_vec, dim3(rows), dim3(256), 0, s, h, (const uint4*)emb, tokens, tokmap, d / 8, g);
   else
     hipLaunchKernelGGL(k_embed<bf16>, dim3(rows), dim3(256), 0, s, h, (const bf16*)emb, tokens, tokmap, rows, d, g);
 }
@@ -546,41 +571,43 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
     size_t base = (size_t)(b * s + j) * a.n_part;
     float m = -INFINITY, sum = 0.f;
     int idx = 0x7fffffff;
-    // partials are fetched eight per lane at a time, all loads in flight together, and folded in
-    // ascending order of p
-    for (int p0 = lane; p0 < a.n_part; p0 += 64 * 8) {
-      float pm8[8], ps8[8];
-      int pi8[8];
+    // Partials are fetched sixteen per lane at a time (a vocabulary of 131,072 at once), all loads in flight
+    // together.  A lane keeps the maximum of its partials, the lowest token that has it and the sum relative to it;
+    // the lanes are joined at the end.
+    constexpr int U = 16;
+    for (int p0 = lane; p0 < a.n_part; p0 += 64 * U) {
+      float pm[U], ps[U];
+      int pi[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < U; ++u) {
         const int p = p0 + 64 * u;
         const bool in = p < a.n_part;
-        pm8[u] = in ? a.part_max[base + p] : -INFINITY;
-        ps8[u] = in ? a.part_sum[base + p] : 0.f;
-        pi8[u] = in ? a.part_idx[base + p] : 0x7fffffff;
+        pm[u] = in ? a.part_max[base + p] : -INFINITY;
+        ps[u] = in ? a.part_sum[base + p] : 0.f;
+        pi[u] = in ? a.part_idx[base + p] : 0x7fffffff;
       }
+      float mn = m;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float pm = pm8[u], ps = ps8[u];
-        const int pi = pi8[u];
-        if (pm > m) {
-          sum = sum * (m == -INFINITY ? 0.f : expf(m - pm)) + ps;
-          m = pm; idx = pi;
-        } else if (pm > -INFINITY) {
-          sum += ps * expf(pm - m);
-          if (pm == m && pi < idx) idx = pi;
-        }
+      for (int u = 0; u < U; ++u) {
+        if (pm[u] > mn || (pm[u] == mn && pi[u] < idx)) idx = pi[u];
+        mn = fmaxf(mn, pm[u]);
+      }
+      if (mn > -INFINITY) {
+        sum *= exp_neg(mn - m);                // (m = -inf, sum = 0 at first)
+        m = mn;
+#pragma unroll
+        for (int u = 0; u < U; ++u) sum += ps[u] * exp_neg(m - pm[u]);
       }
     }
+    float M = m;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+    sum = m > -INFINITY ? sum * exp_neg(M - m) : 0.f;
+    if (m < M) idx = 0x7fffffff;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
-      float m2 = __shfl_xor(m, o, 64), s2 = __shfl_xor(sum, o, 64);
-      int i2 = __shfl_xor(idx, o, 64);
-      float M = fmaxf(m, m2);
-      float f1 = (m == -INFINITY) ? 0.f : expf(m - M), f2 = (m2 == -INFINITY) ? 0.f : expf(m2 - M);
-      sum = sum * f1 + s2 * f2;
-      if (m2 > m || (m2 == m && i2 < idx)) idx = i2;
-      m = M;
+      sum += __shfl_xor(sum, o, 64);
+      idx = min(idx, __shfl_xor(idx, o, 64));
     }
     if (lane == 0) { s_conf[j] = 1.f / sum; s_pred[j] = idx; }
   }
@@ -600,35 +627,45 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
   }
   __syncthreads();
   const int32_t* ref = a.reference ? a.reference + (size_t)b * a.gen_len + gb * s : nullptr;
-  // hidden layers of the filter (none for the single-layer variant), activations alternating
-  // between two LDS vectors
+  // Layers of the filter, activations alternating between two LDS vectors.  Sixteen lanes share a neuron: they read
+  // its weight row together and add up their parts through the lanes (a thread per neuron walks rows that lie
+  // `width` floats apart, 128 dependent rounds of it in the last layer of a 128-wide filter with 32 threads at work).
+  const int n16 = tid >> 4, l16 = tid & 15, groups = blockDim.x >> 4;
+  auto neuron = [&](const float* w, const float* x, int n) {
+    float acc = 0.f;
+#pragma unroll 4
+    for (int j = l16; j < n; j += 16) acc += w[j] * x[j];
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 16);
+    return acc;
+  };
   const float* act = s_cin;
   int width = s;
   for (int k = 0; !ref && k + 1 < a.n_layers; ++k) {
     float* nxt = s_hid[k & 1];
-    for (int t = tid; t < a.hidden; t += blockDim.x) {
-      float acc = a.fb[k][t];
-      const float* w = a.fw[k] + (size_t)t * width;
-      for (int j = 0; j < width; ++j) acc += w[j] * act[j];
-      nxt[t] = fmaxf(acc, 0.f);
+    for (int t = n16; t < a.hidden; t += groups) {
+      const float acc = a.fb[k][t] + neuron(a.fw[k] + (size_t)t * width, act, width);
+      if (l16 == 0) nxt[t] = fmaxf(acc, 0.f);
     }
     __syncthreads();
     act = nxt;
     width = a.hidden;
   }
-  if (tid < s) {
-    if (ref) {
+  if (ref) {
+    if (tid < s) {
       // EGP (Alg. 1): a masked position is unmasked exactly when its prediction is the reference token
       const bool hit = s_masked[tid] && s_pred[tid] == ref[tid];
       s_sel[tid] = hit;
       if (hit) atomicAdd(&s_flag[5], 1);
-    } else {
-      float z = a.fb[a.n_layers - 1][tid];
-      const float* w = a.fw[a.n_layers - 1] + (size_t)tid * width;
-      for (int t = 0; t < width; ++t) z += w[t] * act[t];
-      float p = 1.f / (1.f + expf(-z));
-      if (a.filt_out) a.filt_out[b * s + tid] = p;
-      s_sel[tid] = s_masked[tid] && (p > a.tau);
+    }
+  } else {
+    for (int t = n16; t < s; t += groups) {
+      const float z = a.fb[a.n_layers - 1][t] + neuron(a.fw[a.n_layers - 1] + (size_t)t * width, act, width);
+      const float p = 1.f / (1.f + expf(-z));
+      if (l16 == 0) {
+        if (a.filt_out) a.filt_out[b * s + t] = p;
+        s_sel[t] = s_masked[t] && (p > a.tau);
+      }
     }
   }
   __syncthreads();
@@ -643,12 +680,21 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
   __syncthreads();   // labels are read before the forced position is added to the selection
   // the most confident masked position always goes (in an EGP rollout only when nothing agreed,
   // and then with the reference token)
-  if (tid == 0 && n_masked > 0 && !(ref && s_flag[5] > 0)) {
-    float best = -INFINITY;
-    int bj = -1;
-    for (int j = 0; j < s; ++j)
-      if (s_masked[j] && (bj < 0 || s_conf[j] > best)) { best = s_conf[j]; bj = j; }
-    s_sel[bj] = 1;
+  if (wave == 0 && n_masked > 0 && !(ref && s_flag[5] > 0)) {
+    // the lowest of the masked positions with the highest confidence (one that is no number counts as the lowest)
+    float best = 0.f;
+    int bj = 0x7fffffff;
+    auto take = [&](float c, int j) {
+      if (j != 0x7fffffff && (bj == 0x7fffffff || c > best || (c == best && j < bj))) { best = c; bj = j; }
+    };
+    for (int j = lane; j < s; j += 64)
+      if (s_masked[j]) take(s_conf[j] == s_conf[j] ? s_conf[j] : -INFINITY, j);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const float c = __shfl_xor(best, o, 64);
+      take(c, __shfl_xor(bj, o, 64));
+    }
+    if (lane == 0) s_sel[bj] = 1;
   }
   __syncthreads();
   if (tid < s) {

@@ -75,16 +75,6 @@ static MfPlan mf_plan(int s, int h, int L, long long n) {
   return p;
 }
 
-// exp(-x) for x >= 0: the product with log2(e) in two parts, the small one applied to the result to first order
-// (about 1 ulp, a third of the instructions of expf).  Beyond 200 the result is 0 (and the two parts would be
-// infinities of opposite sign); NaN stays NaN.
-__device__ __forceinline__ float exp_neg(float x) {
-  x = x > 200.f ? 200.f : x;
-  const float l2e = 1.44269504089f, l2e_lo = 1.92596303e-8f;   // log2(e) = l2e + l2e_lo
-  const float hi = -x * l2e, lo = -fmaf(x, l2e, hi) - x * l2e_lo;
-  const float e = __builtin_amdgcn_exp2f(hi);
-  return fmaf(e, lo * 0.69314718056f, e);
-}
 // 1 / d for d in [1, 4): the hardware's reciprocal and one Newton step
 __device__ __forceinline__ float recip(float d) {
   const float r = __builtin_amdgcn_rcpf(d);
