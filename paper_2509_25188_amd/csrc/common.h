@@ -184,8 +184,9 @@ void launch_gemm_qkv_bf16(const bf16* A, const bf16* wq, const bf16* wk, const b
                           const QkvEpilogue& e, Gate g, hipStream_t s);
 // partial[z][M,N] = A[:, z-th K slice] * W[:, slice]^T, z < wide_splits(M, N, K, of_many).  of_many: the rows are some of
 // a pass of more than 256 and sum in the order of such a pass, however few they are.
+// add (wide_splits == 1): parts is the residual stream [M, N]; the sum is added to it in place instead of written.
 void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t part_stride, int M, int N, int K,
-                              bool of_many, Gate g, hipStream_t s);
+                              bool of_many, bool add, Gate g, hipStream_t s);
 int k_ranges(int K);                    // K ranges of a pass of more than 256 rows
 // Few-row GEMMs (block-only steps of the cached decode modes, at most kSkinnyRows rows) stream their
 // weights once; K is split until a launch has a few hundred workgroups, each K range staying a

@@ -47,6 +47,7 @@ struct GemmArgs {
   // EPI_PARTIAL: K range z writes to parts + z * part_stride (fp32 [M, N])
   float* parts;
   size_t part_stride;
+  int add;              // splits == 1: parts is the residual stream, and the sum is added to it in place
   int serial;           // EPI_PARTIAL_SER, splits == 1: the workgroup walks `serial` K ranges one after the other, each
                         // into a fresh accumulator, and writes their sum, formed in ascending order: the bits that
                         // `serial` workgroups' partials give when the RMSNorm sums them
@@ -99,8 +100,15 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
         for (int r = 0; r < 4; ++r) w[r] = __float_as_uint(acc[i][j][r]);   // (bit_cast of a vector element reads element 0)
         quad_transpose(w, lane);
         const int row = row_base + i * 16 + lr, col = col0 + j * 16;
-        if (row < a.M && col < a.N)                        // N is a multiple of 4
-          *reinterpret_cast<uint4*>(out + (size_t)row * a.N + col) = make_uint4(w[0], w[1], w[2], w[3]);
+        if (row < a.M && col < a.N) {                      // N is a multiple of 4
+          float4* o = reinterpret_cast<float4*>(out + (size_t)row * a.N + col);
+          float4 v = make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3]));
+          if (a.add) {
+            const float4 h = *o;
+            v = make_float4(h.x + v.x, h.y + v.y, h.z + v.z, h.w + v.w);
+          }
+          *o = v;
+        }
       }
   } else if constexpr (EPI == EPI_SWIGLU) {
     static_assert(FM % 2 == 0 && FN % 2 == 0, "fragments in pairs");
@@ -241,7 +249,6 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
         const int row = row_base + i * 16 + r;
         float vals[FN];
         float m = -INFINITY;
-        int mi = 0x7fffffff;
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
           const int col = col0 + j * 16 + cl;
@@ -253,16 +260,21 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
           if (e.logits && row < a.M && col < a.N) e.logits[(size_t)row * a.N + col] = v;
           if (col == e.mask_id || col >= a.N) v = -INFINITY;
           vals[j] = v;
-          if (v > m) { m = v; mi = col; }   // columns ascend with j: first maximum wins
+          m = fmaxf(m, v);
         }
-        auto fold = [&](float m2, int i2) {
-          if (m2 > m || (m2 == m && i2 < mi)) { m = m2; mi = i2; }
-        };
-        fold(dppf<kDppRor + 8>(m), (int)dpp<kDppRor + 8>((unsigned)mi));
-        fold(dppf<kDppRor + 4>(m), (int)dpp<kDppRor + 4>((unsigned)mi));
-        fold(dppf<kDppRor + 2>(m), (int)dpp<kDppRor + 2>((unsigned)mi));
-        fold(dppf<kDppRor + 1>(m), (int)dpp<kDppRor + 1>((unsigned)mi));
+        // the row's maximum over the 16 lanes, then the lowest column that has it and the sum relative to it
+        m = fmaxf(m, dppf<kDppRor + 8>(m));
+        m = fmaxf(m, dppf<kDppRor + 4>(m));
+        m = fmaxf(m, dppf<kDppRor + 2>(m));
+        m = fmaxf(m, dppf<kDppRor + 1>(m));
+        int mi = 0x7fffffff;
         float sum = 0.f;
+#pragma unroll
+        for (int j = FN - 1; j >= 0; --j) mi = vals[j] == m && m > -INFINITY ? col0 + j * 16 + cl : mi;
+        mi = min(mi, (int)dpp<kDppRor + 8>((unsigned)mi));
+        mi = min(mi, (int)dpp<kDppRor + 4>((unsigned)mi));
+        mi = min(mi, (int)dpp<kDppRor + 2>((unsigned)mi));
+        mi = min(mi, (int)dpp<kDppRor + 1>((unsigned)mi));
 #pragma unroll
         for (int j = 0; j < FN; ++j) sum += (m == -INFINITY) ? 0.f : __expf(vals[j] - m);
         sum += dppf<kDppRor + 8>(sum);
@@ -579,11 +591,11 @@ static PartialPlan plan_partial(int M, int N, int K, bool of_many) {
 int wide_splits(int M, int N, int K, bool of_many) { return plan_partial(M, N, K, of_many).splits; }
 
 void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t part_stride, int M, int N, int K,
-                              bool of_many, Gate g, hipStream_t s) {
+                              bool of_many, bool add, Gate g, hipStream_t s) {
   const PartialPlan p = plan_partial(M, N, K, of_many);
   GemmArgs a = {};
   a.A = A; a.B0 = W; a.M = M; a.N = N; a.K = K; a.splits = p.splits; a.gate = g;
-  a.parts = parts; a.part_stride = part_stride; a.serial = p.serial;
+  a.parts = parts; a.part_stride = part_stride; a.serial = p.serial; a.add = add;
   if (p.serial) launch<256, 128, 4, 2, 2, EPI_PARTIAL_SER>(a, s);
   else if (p.tile == 0) launch<256, 256, 2, 4, 2, EPI_PARTIAL>(a, s);
   else if (p.tile == 1) launch<256, 192, 4, 2, 2, EPI_PARTIAL>(a, s);

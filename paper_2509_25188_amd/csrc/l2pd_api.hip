@@ -303,7 +303,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
         const size_t stride = (size_t)few * d;
         auto project = [&](const bf16* A, const bf16* W, int K) {
           if (few > kSkinnyRows) {
-            launch_gemm_partial_bf16(A, W, parts, stride, few, d, K, true, g, s);
+            launch_gemm_partial_bf16(A, W, parts, stride, few, d, K, true, false, g, s);
             return wide_splits(few, d, K, true);
           }
           launch_gemm_skinny_bf16(A, W, nullptr, nullptr, 0, parts, stride, few, d, K, k_ranges(K), g, s);
@@ -335,15 +335,19 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       // wide_splits (wide path) or skinny_splits (few-row path) says.
       const int so = skinny ? skinny_splits(d, d) : wide_splits(rows, d, d, false);
       const int sd = skinny ? skinny_splits(d, F) : wide_splits(rows, d, F, false);
+      // A projection whose workgroups hold whole sums adds them to h itself (what the RMSNorm would do with a single
+      // partial, same bits): the sums are not written and read back
+      // (1.5 % of a step of 4096 rows).
+      const bool add_o = !skinny && so == 1, add_d = !skinny && sd == 1;
       const size_t stride_d = (size_t)rows * d;
       { Timed t(c, L2PD_K_GEMM_O, s);
         if (skinny)
           launch_gemm_skinny_bf16(ao, (const bf16*)c->wo[l], nullptr, nullptr, 0, parts, stride_d, rows, d, d, so, g,
                                   s);
         else
-          launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], parts, stride_d, rows, d, d, false, g, s); }
+          launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], add_o ? h : parts, stride_d, rows, d, d, false, add_o, g, s); }
       { Timed t(c, L2PD_K_NORM, s);
-        launch_rmsnorm(h, parts, so, stride_d, ident, c->ffn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
+        launch_rmsnorm(h, add_o ? nullptr : parts, so, stride_d, ident, c->ffn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
       bf16* act = c->at<bf16>(L.act);
       { Timed t(c, L2PD_K_GEMM_GATEUP, s);
         if (skinny && !swiglu_few_rows_fused(rows, F)) {
@@ -362,8 +366,8 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
           launch_gemm_skinny_bf16(act, (const bf16*)c->wd[l], nullptr, nullptr, 0, parts, stride_d, rows, d, F, sd, g,
                                   s);
         else
-          launch_gemm_partial_bf16(act, (const bf16*)c->wd[l], parts, stride_d, rows, d, F, false, g, s); }
-      pending = true;
+          launch_gemm_partial_bf16(act, (const bf16*)c->wd[l], add_d ? h : parts, stride_d, rows, d, F, false, add_d, g, s); }
+      pending = !add_d;
       pend_splits = sd;
       pend_stride = stride_d;
     }
