@@ -48,6 +48,15 @@ def step_flops(w):
     return lin, attn, head
 
 
+def wanted_rows(w):
+    """Rows of the last layer that a full-recompute step works on behind its keys and values: the active block's,
+    or all of them (fp32 models, step-granular EoTP, a block of more than half of the window)."""
+    T, rows = w.prompt_len + w.gen_len, w.batch * (w.prompt_len + w.gen_len)
+    if w.model.dtype != "bf16" or w.eotp_step or rows <= 64 or 2 * w.block_len > T:
+        return rows
+    return w.batch * w.block_len
+
+
 def note(msg):
     """Progress line on stderr (the one JSON line stays alone on stdout)."""
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
@@ -426,7 +435,12 @@ def main():
     lin, attn, head = step_flops(w)
     total_flops = lin + attn + head
     rows = w.batch * T
-    gu_flops = 2.0 * rows * m.d_model * 2 * m.d_ffn
+    # the last layer's launch covers the wanted rows alone: what is counted is the mean over a step's launches, and the
+    # step's rate leaves out what the last layer does not do on the other rows
+    last = wanted_rows(w)
+    gu_flops = 2.0 * (rows * (m.n_layers - 1) + last) / m.n_layers * m.d_model * 2 * m.d_ffn
+    done_flops = total_flops - 2.0 * (rows - last) * (m.d_model * m.d_model + 3 * m.d_model * m.d_ffn) - \
+        4.0 * (rows - last) * T * m.d_model
     avg_kern_ms = kern_ms / max(n_launch, 1)
     achieved = gu_flops / (avg_kern_ms * 1e-3) / 1e12 if n_launch else None
     result = {
@@ -445,10 +459,10 @@ def main():
                        "tokens_per_step": tokens_per_step, "generate_wall_s": gen_wall,
                        "generate_tokens_per_s": tokens_total / gen_wall},
         "step_tflop": total_flops / 1e12,
-        "step_mfma_frac": total_flops / (ms_per_step * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
+        "step_mfma_frac": done_flops / (ms_per_step * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
         "step_weight_stream_gbs": (sum(v.numel() * v.element_size() for k_, v in eng.weights.items()
                                        if k_ != "tok_emb") / 1e9) / (ms_per_step * 1e-3),
-        "roofline": {"bound": "mfma", "kernel": "k_gemm_bf16<SwiGLU gate/up>", "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": "k_gemm_turns<SwiGLU gate/up>", "achieved": achieved,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": (achieved / PEAK_BF16_TFLOPS) if achieved else None, "traffic": measured_traffic() if w.name == TRAFFIC_WORKLOAD else None,
                      "launches": n_launch, "avg_launch_ms": avg_kern_ms, "flop_per_launch": gu_flops},
