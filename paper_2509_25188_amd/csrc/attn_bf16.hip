@@ -2,11 +2,11 @@
 //
 // Inputs are what the QKV GEMM epilogue leaves: rotated queries q [B*Tq, d], rotated keys
 // kstore [B, Tpad, d] and transposed values vtstore [B, H, Dh, Tpad].  A workgroup owns 32*NQ
-// queries of one (sequence, head) and splits the keys into NSPL contiguous ranges; wavefront
-// (query group, key range) runs the online softmax of its 32 queries over its range, and the
-// ranges are merged at the end.  Key/value tiles of 64 keys go global -> LDS directly into a ring of NST tiles
-// per range (rows XOR-swizzled on the global side), one tile per range and iteration, shared by the query groups:
-// one barrier per tile, after which the tiles NST - 1 ahead are sent off.
+// queries of one (sequence, head) and splits the keys into contiguous ranges, NSPL of them walked side by side and NSER
+// one after the other; wavefront (query group, run of ranges) runs the online softmax of its 32 queries over each of its
+// ranges, and the ranges are joined at the end.  Key/value tiles of 64 keys go global -> LDS directly into a ring of
+// NST tiles per side (rows XOR-swizzled on the global side), one tile per side and iteration, shared by the query
+// groups: one barrier per tile, after which the tiles NST - 1 ahead are sent off.
 //
 // The wave computes S^T = K Q^T (keys are MFMA rows, queries are columns), so that a lane holds
 // scores of ONE query: the row maximum is 31 register maxima plus one cross-lane exchange, and the
@@ -20,7 +20,9 @@
 // instead of 0.4e-3 at a score spread of 4 and 512 keys.)  The rescaling is skipped where no query's maximum has grown.
 //
 // Bound by vector instructions (32 exponentials a lane and tile) with two wavefronts per SIMD, by their latency
-// with one; with few queries by the stream of stored keys and values.
+// with one; with few queries by the stream of stored keys and values.  The launch bounds ask for two wavefronts per SIMD
+// even where LDS allows one: with the whole register file to itself the compiler puts the accumulators into AGPRs, which
+// vector instructions reach by copies only (512 rows 17.3 us, 13.7 within 256 VGPRs).
 #include "gemm_common.h"
 
 namespace l2pd {
@@ -34,12 +36,14 @@ __device__ __forceinline__ float max_halves(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-template <int DH, int NQ, int NSPL, int NST>
-__global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __restrict__ q, const bf16* __restrict__ kstore,
-                                                              const bf16* __restrict__ vtstore, bf16* __restrict__ out,
-                                                              int B, int Tq, int Tk_all, int Tpad, int H, int n_chunks,
-                                                              float* __restrict__ chunk_out,
-                                                              const int* __restrict__ tk_dev, QueryRows sel, Gate g) {
+// Key ranges: NSPL side by side, one to a wavefront, times NSER that a wavefront walks one after the other, each with a
+// maximum, a sum and an output of its own.  They are joined in ascending order however they are dealt to wavefronts.
+template <int DH, int NQ, int NSPL, int NSER, int NST>
+__global__ void __launch_bounds__(NQ * NSPL * 64, 2) k_attn_bf16(const bf16* __restrict__ q, const bf16* __restrict__ kstore,
+                                                                 const bf16* __restrict__ vtstore, bf16* __restrict__ out,
+                                                                 int B, int Tq, int Tk_all, int Tpad, int H, int n_chunks,
+                                                                 float* __restrict__ chunk_out,
+                                                                 const int* __restrict__ tk_dev, QueryRows sel, Gate g) {
   if (gate_skip(g)) return;
   constexpr int KT = 64;                       // keys per LDS tile
   constexpr int K_ROW = DH * 2;                // bytes per key row
@@ -51,7 +55,9 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
   static_assert(NST >= 2 && (NST - 2) * (KL + VL) < 64, "ring depth");
   constexpr int KK = DH / 16;                  // MFMA steps over the feature dim
   constexpr int FO = DH / 32;                  // output row fragments
-  constexpr int XW = FO * 16 + 2;              // floats a wave hands over per lane: O^T fragments, m, l
+  constexpr int FH = FO / NSPL;                // of these, how many a wavefront joins and writes at the end
+  constexpr int XW = FH * 16 + 2;              // floats handed over per lane and range: O^T fragments, m, l
+  static_assert(NSPL == 1 || (NSPL == 2 && NSER <= 2), "side by side, a wavefront holds at most two ranges");
   // the exchange area of the final merge reuses the tile buffers; the launch sizes LDS for the larger of the two
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [NSPL key ranges][NST tiles][K tile | V^T tile]
 
@@ -97,35 +103,36 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
   // (DH = 64: two rows per sweep, key = (row >> 1) & 7); a V^T row is 128 B.
   auto kkey = [](int r) { return DH == 128 ? (r & 15) : ((r >> 1) & 7); };
   constexpr int KC = DH / 8;                   // 16-byte chunks per key row
-  const bf16* srcK[KL];
-  const bf16* srcV[VL];
+  // The swizzle key repeats every 16 rows: a wavefront's pieces KP (VP) apart differ by a constant stride.
+  constexpr int KP = NQ * (64 / KC) < 16 ? 16 / (NQ * (64 / KC)) : 1, VP = NQ * 8 < 16 ? 2 : 1;
+  const bf16* srcK[KP];
+  const bf16* srcV[VP];
 #pragma unroll
-  for (int i = 0; i < KL; ++i) {
+  for (int i = 0; i < KP; ++i) {
     const int r = (qg + i * NQ) * (64 / KC) + lane / KC, c = (lane % KC) ^ kkey(r);
     srcK[i] = kstore + ((size_t)b * Tpad + r) * d + h * DH + c * 8;
   }
 #pragma unroll
-  for (int i = 0; i < VL; ++i) {
+  for (int i = 0; i < VP; ++i) {
     const int r = (qg + i * NQ) * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
     srcV[i] = vtstore + ((size_t)(b * H + h) * DH + r) * Tpad + c * 8;
   }
   const unsigned lds0 = __builtin_amdgcn_readfirstlane(
       (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)(smem + sp * NST * STAGE + qg * 1024));
-  // The key tiles are dealt to the NSPL key ranges in contiguous runs of `per` tiles; every range
-  // is walked by NQ wavefronts (one per query group), and all ranges advance together, one tile
-  // per iteration.
+  // The key tiles are dealt to the NSPL * NSER key ranges in contiguous runs of `per` tiles; every range is walked by
+  // NQ wavefronts (one per query group), NSPL ranges at a time, which advance together, one tile per iteration.
   const int n_tiles = (Tk + KT - 1) / KT;
   const int per_chunk = (n_tiles + n_chunks - 1) / n_chunks;    // the host picks n_chunks so that no chunk is empty
   const int wg_first = ch * per_chunk, wg_count = min(per_chunk, n_tiles - wg_first);
-  const int per = (wg_count + NSPL - 1) / NSPL;
-  const int my_first = wg_first + sp * per, my_count = max(0, min(per, wg_first + wg_count - my_first));
+  const int per = (wg_count + NSPL * NSER - 1) / (NSPL * NSER);
+  const int my_first = wg_first + sp * NSER * per, my_count = max(0, min(NSER * per, wg_first + wg_count - my_first));
   auto load_tile = [&](int t) {
     const size_t k0 = (size_t)(my_first + t) * KT;
     const unsigned dst = lds0 + (t % NST) * STAGE;
 #pragma unroll
-    for (int i = 0; i < KL; ++i) dma16(srcK[i] + k0 * d, dst + i * NQ * 1024);
+    for (int i = 0; i < KL; ++i) dma16(srcK[i % KP] + (k0 + (i - i % KP) * NQ * (64 / KC)) * d, dst + i * NQ * 1024);
 #pragma unroll
-    for (int i = 0; i < VL; ++i) dma16(srcV[i] + k0, dst + K_BYTES + i * NQ * 1024);
+    for (int i = 0; i < VL; ++i) dma16(srcV[i % VP] + k0 + (size_t)((i - i % VP) * NQ * 8) * Tpad, dst + K_BYTES + i * NQ * 1024);
   };
 
   f32x16 o[FO];
@@ -137,10 +144,28 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
   const float sc = rsqrtf((float)DH) * 1.4426950408889634f;   // softmax scale folded with log2(e)
   const int keyK = kkey(lj), keyV = (lj >> 1) & 7;   // fragment rows are lj modulo 32
 
+  // Folds a later range (m2, l2, O2 by its accessor) into an earlier one, N output fragments of it.  A range without keys
+  // has m = -inf, l = 0; the first range always holds a tile, so the common maximum is finite.  The operations are
+  // spelled out: the same bits in every configuration.
+  auto fold = [&](auto& o1, float& m1, float& l1, float m2, float l2, auto o2) {
+    constexpr int N = sizeof(o1) / sizeof(f32x16);
+    const float M = fmaxf(m1, m2);
+    const float a1 = __builtin_amdgcn_exp2f(m1 - M), a2 = __builtin_amdgcn_exp2f(m2 - M);
+#pragma unroll
+    for (int f = 0; f < N; ++f)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o1[f][r] = __fmaf_rn(o1[f][r], a1, __fmul_rn(o2(f, r), a2));
+    l1 = __fmaf_rn(l1, a1, __fmul_rn(l2, a2));
+    m1 = M;
+  };
+  f32x16 ob[NSER > 1 ? FO : 1];                // the wavefront's finished ranges
+  float mb = -INFINITY, lb = 0.f;
+  int left = per;                              // tiles of the range at hand still to come
+
 #pragma unroll
   for (int t = 0; t < NST - 1; ++t)
     if (t < my_count) load_tile(t);
-  for (int t = 0; t < per; ++t) {
+  for (int t = 0; t < NSER * per; ++t) {
     // tile t has landed (the younger ones, if all of them were sent off, may still be on their way) ...
     if (t + NST - 2 < my_count) wait_vmcnt<(NST - 2) * (KL + VL)>();
     else wait_vmcnt<0>();
@@ -148,6 +173,24 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
     if constexpr (NQ * NSPL > 1) lds_barrier();
     __builtin_amdgcn_sched_barrier(0);
     if (t + NST - 1 < my_count) load_tile(t + NST - 1);   // into the place of tile t - 1
+    if constexpr (NSER > 1) {
+      if (left == 0) {                         // a range ends here: bank it and start the next from nothing
+        if (t == per) {
+          mb = m; lb = lsum;
+#pragma unroll
+          for (int f = 0; f < FO; ++f) ob[f] = o[f];
+        } else {
+          fold(ob, mb, lb, m, lsum, [&](int f, int r) { return o[f][r]; });
+        }
+        m = -INFINITY; lsum = 0.f;
+#pragma unroll
+        for (int f = 0; f < FO; ++f)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[f][r] = 0.f;
+        left = per;
+      }
+      --left;
+    }
     if (t >= my_count) continue;
     const unsigned char* base = smem + (sp * NST + t % NST) * STAGE;
     const int k0 = (my_first + t) * KT;
@@ -219,62 +262,90 @@ __global__ void __launch_bounds__(NQ * NSPL * 64) k_attn_bf16(const bf16* __rest
     }
   }
 
-  // Merge the key ranges: range 0 of each query group folds in the others' (m, l, O^T), in range
-  // order, through the tile buffers (dead now).  A range without keys hands over m = -inf, l = 0.
-  if constexpr (NSPL > 1) {
+  // Join the key ranges in ascending order.  Side by side, each of the two wavefronts of a query group takes half of the
+  // output features: it hands the other half of its ranges over through the tile buffers (dead now).
+  f32x16 res[FH];
+  float rm, rl;
+  if constexpr (NSPL == 1) {
+    if constexpr (NSER > 1) fold(ob, mb, lb, m, lsum, [&](int f, int r) { return o[f][r]; });
+#pragma unroll
+    for (int f = 0; f < FO; ++f) res[f] = NSER > 1 ? ob[NSER > 1 ? f : 0] : o[f];
+    rm = NSER > 1 ? mb : m;
+    rl = NSER > 1 ? lb : lsum;
+  } else {
     __syncthreads();
-    float* xch = reinterpret_cast<float*>(smem);
-    if (sp > 0) {
-      float* mine = xch + (size_t)((sp - 1) * NQ + qg) * XW * 64 + lane;
+    float* const xch = reinterpret_cast<float*>(smem) + lane;
+    auto area = [&](int to, int i) { return xch + (size_t)((to * NSER + i) * NQ + qg) * XW * 64; };
+    auto hand_over = [&](auto to, int i, const f32x16 (&v)[FO], float vm, float vl) {
+      float* x = area(to, i);
 #pragma unroll
-      for (int f = 0; f < FO; ++f)
+      for (int f = 0; f < FH; ++f)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[(f * 16 + r) * 64] = o[f][r];
-      mine[(FO * 16) * 64] = m;
-      mine[(FO * 16 + 1) * 64] = lsum;
-    }
+        for (int r = 0; r < 16; ++r) x[(f * 16 + r) * 64] = v[decltype(to)::value * FH + f][r];
+      x[(FH * 16) * 64] = vm;
+      x[(FH * 16 + 1) * 64] = vl;
+    };
+    auto hand_all = [&](auto to) {
+      if constexpr (NSER > 1) hand_over(to, 0, ob, mb, lb);
+      hand_over(to, NSER - 1, o, m, lsum);
+    };
+    if (sp == 0) hand_all(std::integral_constant<int, 1>{});
+    else hand_all(std::integral_constant<int, 0>{});
     __syncthreads();
-    if (sp > 0) return;
+    auto theirs = [&](int i) {                 // folds range i of the other wavefront
+      const float* x = area(sp, i);
+      fold(res, rm, rl, x[(FH * 16) * 64], x[(FH * 16 + 1) * 64], [&](int f, int r) { return x[(f * 16 + r) * 64]; });
+    };
+    if (sp == 0) {
 #pragma unroll
-    for (int x = 1; x < NSPL; ++x) {
-      const float* oth = xch + (size_t)((x - 1) * NQ + qg) * XW * 64 + lane;
-      const float m2 = oth[(FO * 16) * 64], l2 = oth[(FO * 16 + 1) * 64];
-      const float M = fmaxf(m, m2);   // m is finite: range 0 always holds the first tile
-      const float a1 = __builtin_amdgcn_exp2f(m - M), a2 = __builtin_amdgcn_exp2f(m2 - M);
+      for (int f = 0; f < FH; ++f) res[f] = NSER > 1 ? ob[NSER > 1 ? f : 0] : o[f];
+      rm = NSER > 1 ? mb : m;
+      rl = NSER > 1 ? lb : lsum;
+      if constexpr (NSER > 1) fold(res, rm, rl, m, lsum, [&](int f, int r) { return o[f][r]; });
 #pragma unroll
-      for (int f = 0; f < FO; ++f)
+      for (int i = 0; i < NSER; ++i) theirs(i);
+    } else {
+      const float* x = area(1, 0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[f][r] = o[f][r] * a1 + oth[(f * 16 + r) * 64] * a2;
-      lsum = lsum * a1 + l2 * a2;
-      m = M;
+      for (int f = 0; f < FH; ++f)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) res[f][r] = x[(f * 16 + r) * 64];
+      rm = x[(FH * 16) * 64];
+      rl = x[(FH * 16 + 1) * 64];
+      if constexpr (NSER > 1) {
+        theirs(1);
+        fold(res, rm, rl, mb, lb, [&](int f, int r) { return ob[FH + f][r]; });
+      }
+      fold(res, rm, rl, m, lsum, [&](int f, int r) { return o[FH + f][r]; });
     }
   }
 
-  const float l = lsum + __shfl_xor(lsum, 32, 64);
+  const float l = rl + __shfl_xor(rl, 32, 64);
+  const int f0 = NSPL > 1 ? sp * FH * 32 : 0;  // first feature of this wavefront's half
   if (n_chunks > 1) {
     if (q0 + lj < Tq) {
       float* po = chunk_out + ((((size_t)b * H + h) * Tq + q0 + lj) * n_chunks + ch) * (DH + 2);
 #pragma unroll
-      for (int f = 0; f < FO; ++f)
+      for (int f = 0; f < FH; ++f)
 #pragma unroll
         for (int rq = 0; rq < 4; ++rq)
-          *reinterpret_cast<float4*>(po + f * 32 + rq * 8 + hf * 4) =
-              make_float4(o[f][rq * 4 + 0], o[f][rq * 4 + 1], o[f][rq * 4 + 2], o[f][rq * 4 + 3]);
-      if (hf == 0) { po[DH] = m; po[DH + 1] = l; }
+          *reinterpret_cast<float4*>(po + f0 + f * 32 + rq * 8 + hf * 4) =
+              make_float4(res[f][rq * 4 + 0], res[f][rq * 4 + 1], res[f][rq * 4 + 2], res[f][rq * 4 + 3]);
+      if (hf == 0 && f0 == 0) { po[DH] = rm; po[DH + 1] = l; }
     }
     return;
   }
   const float inv = 1.f / l;
   const int qi = q0 + lj, row = sel.n > 0 ? qi - sel_lo : qi, n_out = sel.n > 0 ? sel.n : Tq;   // row of the output
   if (qi < Tq && row >= 0 && row < n_out) {
-    unsigned short* op = reinterpret_cast<unsigned short*>(out) + ((size_t)b * n_out + row) * d + h * DH;
+    unsigned short* op = reinterpret_cast<unsigned short*>(out) + ((size_t)b * n_out + row) * d + h * DH + f0;
 #pragma unroll
-    for (int f = 0; f < FO; ++f)
+    for (int f = 0; f < FH; ++f)
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
         u32x2 w;
-        w.x = pack_bf16(o[f][rq * 4 + 0] * inv, o[f][rq * 4 + 1] * inv);
-        w.y = pack_bf16(o[f][rq * 4 + 2] * inv, o[f][rq * 4 + 3] * inv);
+        w.x = pack_bf16(res[f][rq * 4 + 0] * inv, res[f][rq * 4 + 1] * inv);
+        w.y = pack_bf16(res[f][rq * 4 + 2] * inv, res[f][rq * 4 + 3] * inv);
         *reinterpret_cast<u32x2*>(op + f * 32 + rq * 8 + hf * 4) = w;
       }
   }
@@ -308,22 +379,23 @@ __global__ void __launch_bounds__(256) k_attn_merge(const float* __restrict__ ch
   *reinterpret_cast<u32x2*>(op) = w2;
 }
 
-template <int DH, int NQ, int NSPL, int NST>
+template <int DH, int NQ, int NSPL, int NSER, int NST>
 static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16* out, int B, int Tq, int Tk,
                    int Tpad, int H, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, QueryRows sel, Gate g, hipStream_t s) {
-  auto kern = k_attn_bf16<DH, NQ, NSPL, NST>;
+  auto kern = k_attn_bf16<DH, NQ, NSPL, NSER, NST>;
   constexpr int tiles = NST * NSPL * (64 * DH * 2 + DH * 64 * 2);
-  constexpr int xchg = (NSPL - 1) * NQ * ((DH / 32) * 16 + 2) * 64 * 4;
+  constexpr int xchg = NSPL == 1 ? 0 : NSPL * NSER * NQ * ((DH / 32 / NSPL) * 16 + 2) * 64 * 4;
   constexpr int smem = tiles > xchg ? tiles : xchg;
   static DynLdsAttr attr;
   attr.ensure(reinterpret_cast<const void*>(kern), smem);
   const int q_tiles = (Tq + 32 * NQ - 1) / (32 * NQ), n_tiles = (Tk + 63) / 64;
-  // few queries against many keys: deal the key tiles to several workgroups per query tile
+  // few queries against many keys: deal the key tiles to several workgroups per query tile, a tile to every key range
+  constexpr int R = NSPL * NSER;
   int n_chunks = 1;
-  if (chunk_ws && !tk_dev && sel.n == 0 && q_tiles * H * B < 128 && n_tiles >= (Tq <= 64 ? 2 * NSPL : 8)) {   // chunks must not be empty: launch-wide key count only
+  if (chunk_ws && !tk_dev && sel.n == 0 && q_tiles * H * B < 128 && n_tiles >= 8) {   // chunks must not be empty: launch-wide key count only
     int want = (256 + q_tiles * H * B - 1) / (q_tiles * H * B);
     if (want > 16) want = 16;
-    if (want > n_tiles / NSPL) want = n_tiles / NSPL;   // a tile for every key range of a chunk
+    if (want > (n_tiles + R - 1) / R) want = (n_tiles + R - 1) / R;
     const int per_chunk = (n_tiles + want - 1) / want;
     n_chunks = (n_tiles + per_chunk - 1) / per_chunk;       // every chunk gets at least one tile
     if ((size_t)B * H * Tq * n_chunks * (DH + 2) * 4 > chunk_ws_bytes) n_chunks = 1;
@@ -337,35 +409,46 @@ static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16*
   }
 }
 
-// The number of key ranges depends on the head size, the query rows per sequence and the head count, never on the batch
-// size or the data (another number sums in another order, and a row's result must not depend on the batch it is
-// part of); a wavefront's 32 queries are the same in every configuration, so how many wavefronts share the tiles may
-// depend on the batch.  Measured with 32 heads of 128 (us; in brackets the kernel before: tiles through registers, four
-// ranges and two barriers a tile):
-//   512 rows          2 wavefronts x 2 ranges 14.1, 2 x 1 17.2, 8 x 1 22.2   (16.0)
-//   8 x 512 rows      2 x 2 106, 4 x 2 69, 8 x 1 56                          (123)
-//   1280 rows         4 x 2 54.7, 8 x 1 45.1                                 (70)
-//   8 x 32 rows over 1280 keys   1 x 2 34.6 (4.97 TB/s), 1 x 1 37.8          (43)
-//   32 x 64 rows over 768 keys   2 x 1 84.5 (5.16 TB/s), 2 x 2 94.3          (115)
-//   16 heads of 64, 221 rows 2 x 2 6.2, 2 x 4 6.3 (6.3); 8 x 384 rows 4 x 2 13.6, 2 x 4 20.6 (23.7)
-// Two ranges pay until one sequence by itself gives every CU a workgroup of 128 queries.
+// The number of key ranges, and with it the order of the sums, depends on the query rows of a sequence and the head count,
+// never on the batch size or the data (a row's result must not depend on the batch it is part of): four, or two where one
+// sequence by itself gives every CU a workgroup of 128 queries.  More ranges are also more exact, since each has its own
+// heaviest key with P = 1.  How the ranges are dealt to wavefronts and how many wavefronts share the tiles changes no bit
+// and follows the batch: side by side while the launch is one round of workgroups, one after the other (half the LDS, a
+// second workgroup per CU) beyond that.  Only a launch of fewer than 128 workgroups over 512 keys or more is cut up by the
+// shape of the launch (n_chunks above).
+// Measured (us; in brackets with tiles through registers, four wavefronts' ranges and two barriers a tile):
+//   32 heads of 128        2 wavefronts x 2 ranges side by side, x 2 in turn / 4 x 1, x 4 in turn
+//     512 rows             13.7 / 19.1   (16.0)          2 x 512 rows   26.1 / 21.1  (30.2)
+//     8 x 512 rows         105 / 61      (128)           2 x 300 rows   21.8 / 15.0  (25.9)
+//   16 heads of 64
+//     221 rows             6.2 / 8.4     (6.3)           8 x 221 rows   8.9 / 9.4    (12.1)
+//     8 x 384 rows         17.5 / 15.9   (24.2)          8 x 600 rows   32.5 / 28.2  (50.5)
+//   two ranges in all      4 x 2 side by side / 4 x 1, x 2 in turn
+//     1024 rows, 32 of 128 27.2 / 31.8   (32.0)          1280 rows      56.9 / 48.3  (68.0)
+//     4 x 1280 rows        156 / 139     (199)           2 x 2200 rows, 16 of 64  74.7 / 71.6  (108)
+//   block rows over a store, 32 heads of 128
+//     32 over 1280 keys    15.7 (16.7; chunks and merge)  8 x 32        35.3 (44.2; 4.9 TB/s)
+//     64 over 768 keys     14.2 (15.6)                    8 x 64        2 x 2 x 2 24.7, 2 x 1 x 4 25.9 (30.9)
+//     32 x 64              2 x 2 x 2 93.9, 2 x 1 x 4 86.9 (114; 5.0 TB/s)
 void launch_attn_bf16(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16* out, int B, int Tq, int Tk,
                       int Tpad, int H, int Dh, float* chunk_ws, size_t chunk_ws_bytes, const int* tk_dev, QueryRows sel,
                       Gate g, hipStream_t s) {
-#define L2PD_ATTN(DH, NQ, NSPL) \
-  launch<DH, NQ, NSPL, 2>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, sel, g, s)
-#define L2PD_ATTN_DH(NQ, NSPL) (Dh == 128 ? L2PD_ATTN(128, NQ, NSPL) : L2PD_ATTN(64, NQ, NSPL))
+#define L2PD_ATTN(DH, NQ, NSPL, NSER) \
+  launch<DH, NQ, NSPL, NSER, 2>(q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, chunk_ws, chunk_ws_bytes, tk_dev, sel, g, s)
+#define L2PD_ATTN_DH(NQ, NSPL, NSER) (Dh == 128 ? L2PD_ATTN(128, NQ, NSPL, NSER) : L2PD_ATTN(64, NQ, NSPL, NSER))
   auto wgs = [&](int queries) { return (long long)((Tq + queries - 1) / queries) * H; };   // per sequence
-  if (Tq <= 64) {      // block-only steps: bound by the stream of stored keys and values
-    if (Tq <= 32) L2PD_ATTN_DH(1, 2);
-    else if (wgs(64) * B >= 512) L2PD_ATTN_DH(2, 1);
-    else L2PD_ATTN_DH(2, 2);
-  } else if (wgs(128) <= 256) {
-    if (wgs(64) * B >= 512) L2PD_ATTN_DH(4, 2);
-    else L2PD_ATTN_DH(2, 2);
+  const int room = 256 * (128 / Dh);       // workgroups with two ranges' tiles that the chip holds at once (160 KB of LDS a CU)
+  if (Tq <= 32) {
+    L2PD_ATTN_DH(1, 2, 2);
+  } else if (Tq <= 64) {
+    if (wgs(64) * B <= room) L2PD_ATTN_DH(2, 2, 2);
+    else L2PD_ATTN_DH(2, 1, 4);
+  } else if (wgs(128) < 256) {
+    if (wgs(64) * B <= room) L2PD_ATTN_DH(2, 2, 2);
+    else L2PD_ATTN_DH(4, 1, 4);
   } else {
-    if (wgs(256) * B >= 128) L2PD_ATTN_DH(8, 1);
-    else L2PD_ATTN_DH(4, 1);
+    if (wgs(128) * B <= room) L2PD_ATTN_DH(4, 2, 1);
+    else L2PD_ATTN_DH(4, 1, 2);
   }
 #undef L2PD_ATTN
 #undef L2PD_ATTN_DH

@@ -4,6 +4,7 @@ sizes; scores that grow along the keys, so that the reference of the exponents h
 the first tile.  Bound of the other bf16 forwards: 2e-2 of the largest logit."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2509_25188_amd import binding as Bd
 from paper_2509_25188_amd import synth
@@ -34,3 +35,24 @@ def test_attention_edges(case, sharp):
     for b in {0, B - 1}:
         ref = ora.forward(X[b].numpy())[T - rows:]
         assert Pz.rel_err(got[b], ref) < 2e-2, b
+
+
+@pytest.mark.parametrize("H,Dh,block", [(32, 64, 64), (32, 64, 40), (16, 128, 64), (16, 128, 32), (16, 128, 17)])
+def test_block_rows_are_the_same_bits_in_every_batch(H, Dh, block):
+    # block-only steps over a dual cache, more than 256 rows in every batch (up to there the projections' K ranges follow
+    # the row count) and at least 128 workgroups (below, the keys are dealt to several): a sequence's logits may not
+    # depend on how many others are in the launch, whatever that does to the choice of kernel
+    B, n, P = max(48, -(-600 // H) + 8), 3, 3 * block + 5
+    m = synth.ModelShape(1, H * Dh, H, Dh, 128, 300, 299, 298, dtype="bf16")
+    eng = Bd.Engine(m, synth.make_weights(m, 31, "cuda"), B, P + n * block, prefix_cache=True)
+    flt = synth.make_filter(3, block, 32, "cuda")
+    X = synth.make_prompt(32, B, P + n * block, 298, "cuda")
+    cfg = Bd.Engine.cfg_struct(n * block, block, 0.5, dual_cache=True)
+    def logits(first, count):
+        state = torch.tensor([[1, 0, 0]] * count, dtype=torch.int32, device="cuda")
+        return eng.denoise_step(X[first:first + count].clone(), P, state, flt, cfg, want_logits=True)["logits"]
+    every = logits(0, B)
+    few = max(-(-257 // block), -(-128 // H))
+    for first, count in ((0, few), (B - few, few), (1, 512 // H - 1), (2, 512 // H), (3, B - 5)):
+        if count >= few:
+            assert torch.equal(logits(first, count), every[first:first + count]), (first, count)
