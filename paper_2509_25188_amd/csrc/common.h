@@ -182,19 +182,19 @@ __device__ __forceinline__ int seq_pos_offset(const int* seq_gb, int per_gb, int
 }
 void launch_gemm_qkv_bf16(const bf16* A, const bf16* wq, const bf16* wk, const bf16* wv, int M, int K,
                           const QkvEpilogue& e, Gate g, hipStream_t s);
-// partial[z][M,N] = A[:, z-th K slice] * W[:, slice]^T, z < wide_splits(M, N, K, of_many).  of_many: the rows are some of
-// a pass of more than 256 and sum in the order of such a pass, however few they are.
+// partial[z][M,N] = A[:, z-th K slice] * W[:, slice]^T, z < wide_splits(M, N, K, pass_rows).  The rows may be some of a
+// pass over pass_rows >= M: they sum in the order of that pass, however few they are.
 // add (wide_splits == 1): parts is the residual stream [M, N]; the sum is added to it in place instead of written.
 void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t part_stride, int M, int N, int K,
-                              bool of_many, bool add, Gate g, hipStream_t s);
-int k_ranges(int K);                    // K ranges of a pass of more than 256 rows
+                              int pass_rows, bool add, Gate g, hipStream_t s);
+int k_ranges(int pass_rows, int N, int K);   // K ranges that a [pass_rows, N] projection sums in (more than 64 rows)
 // Few-row GEMMs (block-only steps of the cached decode modes, at most kSkinnyRows rows) stream their
 // weights once; K is split until a launch has a few hundred workgroups, each K range staying a
 // multiple of the 64-wide stage.
 constexpr int kSkinnyRows = 64;
 constexpr int kSkinnyRowsAttn = 64;   // B * Tq up to which attention may chunk the keys across workgroups
 int skinny_splits(int N, int K);
-int wide_splits(int M, int N, int K, bool of_many);   // partial buffers the wide path's [d, d] / [d, F] projections write, at most 8
+int wide_splits(int M, int N, int K, int pass_rows);   // partial buffers the wide path's [d, d] / [d, F] projections write, at most 8
 void launch_gemm_skinny_bf16(const bf16* A, const bf16* w0, const bf16* w1, const bf16* w2, int n_sub, float* parts,
                              size_t part_stride, int M, int N, int K, int splits, Gate g, hipStream_t s);
 // sums of the skinny GEMM's partials -> rotated q, K store, V^T store / SiLU(gate) * up

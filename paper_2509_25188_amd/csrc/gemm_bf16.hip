@@ -560,22 +560,26 @@ void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16
 // 28, against 141 and 60 estimated for 256x256 tiles and four partials).
 // Up to 256 rows (batched block-only steps of the cached modes) the split may go up to eight ways, as the estimate
 // says: 256 rows of the 8B shape split 4 ways, 128 rows 8 ways.
-int k_ranges(int K) {
+// Rows that are some of a pass's (the wanted ones behind the last layer's attention) take the number of ranges of
+// the pass and choose the tile for themselves.
+constexpr double kFoldUs = 0.8;   // a partial of up to 256 rows costs the RMSNorm this much
+struct PartialPlan { int tile, splits, serial; };
+static PartialPlan plan_small_pass(int M, int N, int K) {
+  PartialPlan best = {5, 1, 0};
+  for (int t : {5, 4})
+    for (int S = 1; S <= 8 && K % (S * 64) == 0 && (S == 1 || K / S >= 512); S *= 2)
+      if (tile_cost(t, M, N, K, S) + S * kFoldUs < tile_cost(best.tile, M, N, K, best.splits) + best.splits * kFoldUs)
+        best = {t, S, 0};
+  return best;
+}
+int k_ranges(int pass_rows, int N, int K) {
+  if (pass_rows <= 256) return plan_small_pass(pass_rows, N, K).splits;
   if (K % 256 == 0 && K / 4 >= 512) return 4;
   return K % 128 == 0 && K / 2 >= 512 ? 2 : 1;
 }
-constexpr double kFoldUs = 0.8;   // a partial of up to 256 rows costs the RMSNorm this much
-struct PartialPlan { int tile, splits, serial; };
-static PartialPlan plan_partial(int M, int N, int K, bool of_many) {
-  if (M <= 256 && !of_many) {
-    PartialPlan best = {5, 1, 0};
-    for (int t : {5, 4})
-      for (int S = 1; S <= 8 && K % (S * 64) == 0 && (S == 1 || K / S >= 512); S *= 2)
-        if (tile_cost(t, M, N, K, S) + S * kFoldUs < tile_cost(best.tile, M, N, K, best.splits) + best.splits * kFoldUs)
-          best = {t, S, 0};
-    return best;
-  }
-  const int R = k_ranges(K);
+static PartialPlan plan_partial(int M, int N, int K, int pass_rows) {
+  const int R = k_ranges(pass_rows, N, K);
+  if (pass_rows <= 256) return {tile_cost(4, M, N, K, R) < tile_cost(5, M, N, K, R) ? 4 : 5, R, 0};
   M = (M + 127) / 128 * 128;   // a function of the count of 128-row tiles: the workspace is sized from it
   const double fold_us = (double)M * N * 8 / 5e6;    // a partial is written and read once, at about 5 TB/s
   PartialPlan best = {2, 1, R};
@@ -588,11 +592,11 @@ static PartialPlan plan_partial(int M, int N, int K, bool of_many) {
   if (best.serial == 1) best.serial = 0;
   return best;
 }
-int wide_splits(int M, int N, int K, bool of_many) { return plan_partial(M, N, K, of_many).splits; }
+int wide_splits(int M, int N, int K, int pass_rows) { return plan_partial(M, N, K, pass_rows).splits; }
 
 void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t part_stride, int M, int N, int K,
-                              bool of_many, bool add, Gate g, hipStream_t s) {
-  const PartialPlan p = plan_partial(M, N, K, of_many);
+                              int pass_rows, bool add, Gate g, hipStream_t s) {
+  const PartialPlan p = plan_partial(M, N, K, pass_rows);
   GemmArgs a = {};
   a.A = A; a.B0 = W; a.M = M; a.N = N; a.K = K; a.splits = p.splits; a.gate = g;
   a.parts = parts; a.part_stride = part_stride; a.serial = p.serial; a.add = add;

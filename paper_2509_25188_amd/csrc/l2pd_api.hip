@@ -143,7 +143,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
       const size_t M = top < rows ? top : rows;
       int S = 1;
       for (int k : {m.d_model, m.d_ffn})
-        for (bool of_many : {false, true}) S = std::max(S, wide_splits((int)M, m.d_model, k, of_many));
+        for (int pass : {(int)M, std::max((int)M, 257)}) S = std::max(S, wide_splits((int)M, m.d_model, k, pass));
       wide = std::max(wide, (size_t)S * M * d * 4);
       if (top >= rows) break;
     }
@@ -293,7 +293,9 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       if (p.kv_only_last && l + 1 == m.n_layers) break;
       bf16* ao = c->at<bf16>(L.attn);
       // The wanted rows alone from here on: h of these rows goes to the place of the queries (dead after the
-      // attention; half as many rows at most, since h is 32 bits wide).  Same sums in the same order as on all rows.
+      // attention; half as many rows at most, since h is 32 bits wide).  Same sums in the same order as on all rows: the
+      // projections' K ranges are those of the whole pass.  (Partials of at most 64 rows fit where the pass's do: a
+      // pass of up to 256 rows has as many ranges and more rows, a larger one has four ranges at most.)
       const int few = p.B * p.want;
       if (p.want > 0 && l + 1 == m.n_layers && !skinny && 2 * few <= rows) {
         const RowMap& w = p.want_map;
@@ -303,11 +305,12 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
         const size_t stride = (size_t)few * d;
         auto project = [&](const bf16* A, const bf16* W, int K) {
           if (few > kSkinnyRows) {
-            launch_gemm_partial_bf16(A, W, parts, stride, few, d, K, true, false, g, s);
-            return wide_splits(few, d, K, true);
+            launch_gemm_partial_bf16(A, W, parts, stride, few, d, K, rows, false, g, s);
+            return wide_splits(few, d, K, rows);
           }
-          launch_gemm_skinny_bf16(A, W, nullptr, nullptr, 0, parts, stride, few, d, K, k_ranges(K), g, s);
-          return k_ranges(K);
+          const int R = k_ranges(rows, d, K);
+          launch_gemm_skinny_bf16(A, W, nullptr, nullptr, 0, parts, stride, few, d, K, R, g, s);
+          return R;
         };
         int S;
         { Timed t(c, L2PD_K_GEMM_O, s);
@@ -333,8 +336,8 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
                          p.tk_dev, QueryRows{0, 0, 0, nullptr}, g, s); }
       // Few row tiles leave CUs idle on the [d, d] and [d, F] projections: split K as far as
       // wide_splits (wide path) or skinny_splits (few-row path) says.
-      const int so = skinny ? skinny_splits(d, d) : wide_splits(rows, d, d, false);
-      const int sd = skinny ? skinny_splits(d, F) : wide_splits(rows, d, F, false);
+      const int so = skinny ? skinny_splits(d, d) : wide_splits(rows, d, d, rows);
+      const int sd = skinny ? skinny_splits(d, F) : wide_splits(rows, d, F, rows);
       // A projection whose workgroups hold whole sums adds them to h itself (what the RMSNorm would do with a single
       // partial, same bits): the sums are not written and read back
       // (1.5 % of a step of 4096 rows).
@@ -345,7 +348,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
           launch_gemm_skinny_bf16(ao, (const bf16*)c->wo[l], nullptr, nullptr, 0, parts, stride_d, rows, d, d, so, g,
                                   s);
         else
-          launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], add_o ? h : parts, stride_d, rows, d, d, false, add_o, g, s); }
+          launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], add_o ? h : parts, stride_d, rows, d, d, rows, add_o, g, s); }
       { Timed t(c, L2PD_K_NORM, s);
         launch_rmsnorm(h, add_o ? nullptr : parts, so, stride_d, ident, c->ffn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
       bf16* act = c->at<bf16>(L.act);
@@ -366,7 +369,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
           launch_gemm_skinny_bf16(act, (const bf16*)c->wd[l], nullptr, nullptr, 0, parts, stride_d, rows, d, F, sd, g,
                                   s);
         else
-          launch_gemm_partial_bf16(act, (const bf16*)c->wd[l], add_d ? h : parts, stride_d, rows, d, F, false, add_d, g, s); }
+          launch_gemm_partial_bf16(act, (const bf16*)c->wd[l], add_d ? h : parts, stride_d, rows, d, F, rows, add_d, g, s); }
       pending = !add_d;
       pend_splits = sd;
       pend_stride = stride_d;

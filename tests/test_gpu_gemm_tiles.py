@@ -64,3 +64,18 @@ def test_wanted_rows_are_the_same_bits_as_all_rows(B, row, rows):
     every = eng.forward(X, 0, 300)
     some = eng.forward(X, row, rows)
     assert torch.equal(some, every[:, row:row + rows])
+
+
+@pytest.mark.parametrize("d,F,B,T,row,rows", [
+    (2048, 4096, 1, 100, 31, 40), (2048, 4096, 1, 256, 0, 128), (2048, 4096, 2, 120, 7, 50), (1024, 2816, 3, 77, 40, 36),
+    (4096, 12288, 1, 100, 60, 32), (4096, 12288, 2, 128, 3, 64),
+])
+def test_wanted_rows_of_a_short_pass_are_the_same_bits_as_all_rows(d, F, B, T, row, rows):
+    # the same for passes of 65 to 256 rows, whose projections choose their K ranges by the row count: the last layer's wanted
+    # rows sum in the ranges of the pass that they belong to
+    m = synth.ModelShape(2, d, d // 128, 128, F, 300, 299, 298, dtype="bf16")
+    eng = Bd.Engine(m, synth.make_weights(m, 3, "cuda"), B, T)
+    X = synth.make_prompt(6, B, T, 298, "cuda")
+    every = eng.forward(X, 0, T)
+    some = eng.forward(X, row, rows)
+    assert torch.equal(some, every[:, row:row + rows])
