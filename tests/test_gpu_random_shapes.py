@@ -47,17 +47,16 @@ def test_random_bf16_shape_forward(seed):
         assert Pz.rel_err(alone, got[B - 1]) < 2e-2
 
 
-# Widths from 2048 up take the tiles that read their A operand into registers from quad-tiled activations
-# (256 x 96 for Q/K/V, 256 x 192 for gate/up, 256 x 128 with K split four ways for the output and down
-# projections where K is a multiple of 1024); the 8B-width tests cover one shape of them.  Others by hand:
-# both head sizes, gate/up columns that no tile divides, depths that do and do not allow the four-way split,
-# row counts that no tile divides, a batch whose row groups straddle sequences.
+# Widths from 2048 up, where the tile chooser has the larger tiles and K is summed in ranges; the 8B-width tests cover one
+# shape of them.  Others by hand, every row of the batch returned (so that the last layer, too, works on all of them):
+# both head sizes, gate/up columns that no tile divides, row counts that no tile divides, groups of four rows that straddle
+# sequences.
 WIDE = [
     # (d, H, Dh, F, V, B, T)
-    (2048, 32, 64, 4096, 1500, 1, 300),     # head size 64; O and down both split four ways
-    (2048, 16, 128, 5632, 1100, 2, 261),    # F = 5.5 x 1024: down takes 128 x 128 tiles and a row-major act; 522 rows
+    (2048, 32, 64, 4096, 1500, 1, 300),     # head size 64; O and down both in four ranges
+    (2048, 16, 128, 5632, 1100, 2, 261),    # F = 22 x 256: down in four ranges of 1408; 522 rows
     (2560, 20, 128, 6400, 900, 1, 515),     # K = 2560 for Q/K/V and gate/up; 12800 gate/up columns (66.7 tiles of 192)
-    (3072, 24, 128, 3072, 700, 3, 171),     # three sequences of 171 rows: 513 rows, quads straddle sequences
+    (3072, 24, 128, 3072, 700, 3, 171),     # three sequences of 171 rows: 513 rows, a row group straddles two sequences
 ]
 
 

@@ -78,9 +78,9 @@ def test_8b_width_forward_is_bitwise_reproducible():
 
 
 def test_8b_width_row_count_that_no_tile_divides():
-    # 509 rows (a prime): the last 256-row GEMM tile, the last group of 32 rows of the quad-tiled activations and
-    # the last group of four are all ragged; one layer, first and last block
-    w = synth.with_layers(synth.WORKLOADS["8b_g256"], 1)
+    # 509 rows (a prime): the last row tile of every GEMM is ragged in the first of two layers (the last layer works on
+    # the block's rows alone behind its keys and values); first and last block
+    w = synth.with_layers(synth.WORKLOADS["8b_g256"], 2)
     w = dataclasses.replace(w, prompt_len=221, gen_len=288)
     eng, ora, flt = setup(w)
     rep = Pz.StepReport()
@@ -91,7 +91,7 @@ def test_8b_width_row_count_that_no_tile_divides():
 
 def test_8b_width_eotp_workload_bias_and_long_window():
     # T = 1280 (ragged against 256-row tiles), EOS logit bias from generation position 300
-    w = synth.with_layers(synth.WORKLOADS["8b_g1024_eotp"], 1)
+    w = synth.with_layers(synth.WORKLOADS["8b_g1024_eotp"], 2)
     eng, ora, flt = setup(w)
     rep = Pz.StepReport()
     forced_steps(w, eng, ora, flt, [(9, 5, 4), (2, 0, 5)], rep)   # block 9 holds position 300
