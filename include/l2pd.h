@@ -217,7 +217,7 @@ int32_t l2pd_egp_rollout(l2pd_ctx* ctx, const int32_t* prompt_dev, const int32_t
  * of sigmoid(f(conf_row)) against label_row over all n_rows * in_dim entries.  The filter's parameters are
  * UPDATED IN PLACE through the pointers of `filter` (device memory, fp32).  opt_state_dev: 2 * n_params
  * floats of device scratch (n_params = sum over the layers of out_k * in_k + out_k; layer after layer,
- * weights before biases), zeroed by the call;
+ * weights before biases), never read before it is written;
  * loss_out_dev [epochs] (optional) receives the loss of every epoch before its update.  Runs as one
  * workgroup; returns L2PD_ENOTIMPL for filters too large for it (more than 20480 parameters). */
 typedef struct {
@@ -237,7 +237,7 @@ int32_t l2pd_filter_train(const l2pd_filter* filter, const float* conf_rows_dev,
  *     every result is as for l2pd_filter_train (same kernel, bit-identical parameters and losses).
  *   - The first call on a device looks the array's address up once (HIP loads the library's code object then
  *     if nothing has yet): make one call outside a capture before capturing.
- *   - All calls on one GPU share that GPU's array.  The kernel zeroes the moments before its first epoch, so
+ *   - All calls on one GPU share that GPU's array.  Training starts from moments of zero whatever the array holds, so
  *     nothing survives from call to call; calls that overlap on one GPU (different streams) race. */
 int32_t l2pd_filter_train_static(const l2pd_filter* filter, const float* conf_rows_dev,
                                  const float* label_rows_dev, int64_t n_rows, const l2pd_train_cfg* train_cfg,

@@ -128,7 +128,7 @@ struct TrainArgs {
   long long n;
   int epochs;
   float lr, beta1, beta2, eps, weight_decay;
-  float* opt_state;           // [2 * n_params], zeroed by the kernel
+  float* opt_state;           // [2 * n_params], never read before it is written; holds the moments at the end
   float* loss_out;            // [epochs] or null
 };
 int filter_param_count(int s, int hidden, int n_layers);

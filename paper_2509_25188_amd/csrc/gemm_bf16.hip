@@ -612,7 +612,10 @@ void launch_gemm_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, 
                              hipStream_t s) {
   GemmArgs a = {};
   a.A = A; a.B0 = W; a.M = M; a.N = V; a.K = K; a.splits = 1; a.gate = g; a.lm = e;
-  // the partial (max, sum, argmax) triples are per 128 logits in every configuration
+  // The partial (max, sum, argmax) triples are per 128 logits in every configuration.  The weights are read once per row
+  // tile, so from 129 rows on a 256-row tile halves the stream; up to 128 rows it would multiply empty rows (us, 128x128 /
+  // 256x256 tiles; 4096 x 126464: 128 rows 225 / 228, 129 rows 334 / 227, 512 rows 649 / 412, 2048 rows 2400 / 1530;
+  // 1024 x 32000: 128 rows 20 / 36, 256 rows 34 / 37, 288 rows 47 / 40, 1024 rows 116 / 75).
   if (M <= 128) launch<128, 128, 4, 2, 3, EPI_LMHEAD>(a, s);
   else launch<256, 256, 2, 4, 2, EPI_LMHEAD>(a, s);
 }

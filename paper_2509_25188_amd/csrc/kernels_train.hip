@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(kMfThreads) k_filter_train_mfma(TrainArgs a, M
     return Slot{packed >> 16, (packed >> 8) & 255, packed & 255};
   };
 
-  // rows of a chunk on their way from memory: element i = tid + 512 u of the chunk's rows * s
+  // rows of a chunk on their way from memory: element i = tid + kMfThreads * u of the chunk's rows * s
   float conf[kRowRegs], label[kRowRegs];
   int at[kRowRegs];                           // its place in a [R][sp + 4] array
 #pragma unroll

@@ -990,7 +990,7 @@ int32_t l2pd_filter_train_static(const l2pd_filter* f, const float* conf_rows_de
   int32_t st = L2PD_OK;
   float* moments = static_scratch(&st);
   if (!moments) return st;
-  // the kernel zeroes the moments before its first epoch, so what an earlier call left is never read
+  // training starts from moments of zero and writes them before it reads them: what an earlier call left is never read
   return l2pd_filter_train(f, conf_rows_dev, label_rows_dev, n_rows, tc, moments, loss_out_dev, stream);
 }
 

@@ -30,6 +30,19 @@ def test_step_flops_of_the_benched_workload():
     assert abs((lin + attn + head) / 1e12 - 7.317) < 1e-3        # the figure the bench line reports as step_tflop
 
 
+def test_rows_of_the_last_layer_follow_the_library():
+    # bench.wanted_rows restates the condition under which run_layers works on the wanted rows alone; if that
+    # condition changes there, the rate that the bench line reports has to change with it
+    with open(os.path.join(ROOT, "paper_2509_25188_amd", "csrc", "l2pd_api.hip")) as fh:
+        source = fh.read()
+    assert source.count("if (p.want > 0 && l + 1 == m.n_layers && !skinny && 2 * few <= rows) {") == 1
+    assert "const bool skinny = rows <= kSkinnyRows;" in source and source.count("p.want = sl;") == 1
+    with open(os.path.join(ROOT, "paper_2509_25188_amd", "csrc", "common.h")) as fh:
+        assert "constexpr int kSkinnyRows = 64;" in fh.read()
+    rows = {name: bench.wanted_rows(w) for name, w in synth.WORKLOADS.items() if not (w.prefix_cache or w.dual_cache)}
+    assert rows == {"tiny": 96, "mid": 256, "8b_g256": 32, "8b_b8_g256": 256, "8b_g1024_eotp": 32, "8b_g1024_eotp_step": 1280}
+
+
 def test_hbm_counter_figure_follows_the_kernel_source(tmp_path, monkeypatch):
     with open(bench.GEMM_SOURCE, "rb") as fh:
         sha = hashlib.sha256(fh.read()).hexdigest()
