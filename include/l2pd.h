@@ -219,7 +219,8 @@ int32_t l2pd_egp_rollout(l2pd_ctx* ctx, const int32_t* prompt_dev, const int32_t
  * floats of device scratch (n_params = sum over the layers of out_k * in_k + out_k; layer after layer,
  * weights before biases), never read before it is written;
  * loss_out_dev [epochs] (optional) receives the loss of every epoch before its update.  Runs as one
- * workgroup; returns L2PD_ENOTIMPL for filters too large for it (more than 20480 parameters). */
+ * workgroup (it has no memory for several: see l2pd_filter_train_split); returns L2PD_ENOTIMPL for filters too
+ * large for it (more than 20480 parameters). */
 typedef struct {
   float lr, beta1, beta2, eps, weight_decay;
   int32_t epochs;
@@ -228,13 +229,23 @@ int32_t l2pd_filter_train(const l2pd_filter* filter, const float* conf_rows_dev,
                           int64_t n_rows, const l2pd_train_cfg* train_cfg, float* opt_state_dev,
                           float* loss_out_dev, void* stream);
 
-/* l2pd_filter_train for callers that cannot allocate device memory (code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc): the same training, with the optimiser moments kept in a
- * device array that is part of the library image instead of opt_state_dev.  The call allocates and frees
+/* The same training with a workspace for partial gradients: the rows are dealt to workgroups, one or two launches an epoch.
+ * l2pd_filter_train_workspace_bytes says how much a training on n_rows rows takes (0: one workgroup is the better
+ * choice, or the filter is not supported).  workspace_dev: 256-byte aligned device scratch of at least that size
+ * (L2PD_ENOMEM if smaller), never read before it is written, or null for l2pd_filter_train.  Results are those of
+ * l2pd_filter_train up to the order of the sums over rows. */
+size_t l2pd_filter_train_workspace_bytes(const l2pd_filter* filter, int64_t n_rows);
+int32_t l2pd_filter_train_split(const l2pd_filter* filter, const float* conf_rows_dev, const float* label_rows_dev,
+                                int64_t n_rows, const l2pd_train_cfg* train_cfg, float* opt_state_dev,
+                                float* loss_out_dev, void* workspace_dev, size_t workspace_bytes, void* stream);
+
+/* l2pd_filter_train_split for callers that cannot allocate device memory (code under HIP graph capture, tight
+ * serving loops, harnesses that forbid hipMalloc): the same training, with the optimiser moments and the workspace
+ * kept in a device array that is part of the library image instead of caller buffers.  The call allocates and frees
  * nothing, on the device or through any library.
- *   - Limit: filters of at most 20480 parameters (160 KB of moments per GPU, resident until the process
+ *   - Limit: filters of at most 20480 parameters (10.4 MB per GPU, resident until the process
  *     ends); a larger filter returns L2PD_ENOMEM before anything is launched.  Every other argument and
- *     every result is as for l2pd_filter_train (same kernel, bit-identical parameters and losses).
+ *     every result is as for l2pd_filter_train_split (same kernels, bit-identical parameters and losses).
  *   - The first call on a device looks the array's address up once (HIP loads the library's code object then
  *     if nothing has yet): make one call outside a capture before capturing.
  *   - All calls on one GPU share that GPU's array.  Training starts from moments of zero whatever the array holds, so

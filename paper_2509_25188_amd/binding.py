@@ -86,7 +86,8 @@ class TrainCfg(C.Structure):
 
 
 EXPORTS = ("l2pd_workspace_bytes", "l2pd_create", "l2pd_destroy", "l2pd_forward", "l2pd_denoise_step",
-           "l2pd_generate", "l2pd_egp_rollout", "l2pd_filter_train", "l2pd_filter_train_static", "l2pd_profile_select", "l2pd_profile_read", "l2pd_generate_stats", "l2pd_strerror")
+           "l2pd_generate", "l2pd_egp_rollout", "l2pd_filter_train", "l2pd_filter_train_split", "l2pd_filter_train_static",
+           "l2pd_filter_train_workspace_bytes", "l2pd_profile_select", "l2pd_profile_read", "l2pd_generate_stats", "l2pd_strerror")
 
 
 def load_library() -> C.CDLL:
@@ -112,6 +113,10 @@ def load_library() -> C.CDLL:
     lib.l2pd_egp_rollout.argtypes = [vp, vp, vp, i32, i32, C.POINTER(DecodeCfg), vp, vp, vp, vp]
     lib.l2pd_filter_train.restype = i32
     lib.l2pd_filter_train.argtypes = [C.POINTER(Filter), vp, vp, C.c_int64, C.POINTER(TrainCfg), vp, vp, vp]
+    lib.l2pd_filter_train_workspace_bytes.restype = sz
+    lib.l2pd_filter_train_workspace_bytes.argtypes = [C.POINTER(Filter), C.c_int64]
+    lib.l2pd_filter_train_split.restype = i32
+    lib.l2pd_filter_train_split.argtypes = [C.POINTER(Filter), vp, vp, C.c_int64, C.POINTER(TrainCfg), vp, vp, vp, sz, vp]
     lib.l2pd_filter_train_static.restype = i32
     lib.l2pd_filter_train_static.argtypes = [C.POINTER(Filter), vp, vp, C.c_int64, C.POINTER(TrainCfg), vp, vp]
     lib.l2pd_profile_select.restype = i32
@@ -303,8 +308,11 @@ def train_filter(flt: Dict[str, torch.Tensor], conf_rows: torch.Tensor, label_ro
         return losses
     n_params = sum(t.numel() for t in flt.values())
     state = torch.empty(2 * n_params, dtype=torch.float32, device=conf_rows.device)
-    _check(lib().l2pd_filter_train(C.byref(f), conf_rows.data_ptr(), label_rows.data_ptr(), n, C.byref(tc),
-                                   state.data_ptr(), losses.data_ptr(), _stream()), "l2pd_filter_train")
+    nbytes = lib().l2pd_filter_train_workspace_bytes(C.byref(f), n)
+    work = torch.empty(nbytes, dtype=torch.uint8, device=conf_rows.device) if nbytes else None
+    _check(lib().l2pd_filter_train_split(C.byref(f), conf_rows.data_ptr(), label_rows.data_ptr(), n, C.byref(tc),
+                                         state.data_ptr(), losses.data_ptr(), _ptr(work), nbytes, _stream()),
+           "l2pd_filter_train_split")
     return losses
 
 

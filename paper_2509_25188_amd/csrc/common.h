@@ -133,7 +133,10 @@ struct TrainArgs {
 };
 int filter_param_count(int s, int hidden, int n_layers);
 int filter_train_supported(int s, int hidden, int n_layers);
-void launch_filter_train(const TrainArgs& a, hipStream_t s);
+// `ws` (16-byte aligned, filter_train_split_bytes of it; null: one workgroup does it all): rows over workgroups
+void launch_filter_train(const TrainArgs& a, float* ws, hipStream_t s);
+constexpr size_t kTrainSplitFloats = 2560000;   // filter_train_split_bytes never asks for more: 10.2 MB
+size_t filter_train_split_bytes(int s, int hidden, int n_layers, long long n);   // 0: one workgroup is the better choice
 void launch_seq_len(const int32_t* X, int B, int P, int G, int eos_id, int* teff, int* ctl, hipStream_t s);
 // keys[b] = base + ctl[CTL_SEQ_GB + b] * per_gb: keys a sequence's block rows may see under the prefix cache
 void launch_block_keys(const int* ctl, int B, int base, int per_gb, int* keys, hipStream_t s);

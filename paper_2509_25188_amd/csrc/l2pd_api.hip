@@ -580,12 +580,13 @@ int sync_seq_len(l2pd_ctx* c, const int32_t* X, const int32_t* state, int B, int
   return c->pinned[CTL_TMAX];
 }
 // ---- filter training for callers that cannot allocate ----
-// The optimiser moments (first and second, one float each per parameter) live in a file-scope device
-// array instead of a caller buffer.  Every GPU holds its own copy at its own address: the address is
+// The optimiser moments (first and second, one float each per parameter) and, behind them, the workspace of
+// the split training live in a file-scope device
+// array instead of caller buffers.  Every GPU holds its own copy at its own address: the address is
 // resolved once per device, with that device current, and only that pointer is ever handed to kernels
 // (the array's name in host code is a host-side stand-in, not a device address).
 constexpr int kStaticTrainParams = 20480;                 // the training kernel's own limit
-static __device__ __align__(256) float scratch[2 * kStaticTrainParams];   // 160 KB per GPU, held until the process ends
+static __device__ __align__(256) float scratch[2 * kStaticTrainParams + kTrainSplitFloats];   // 10.4 MB per GPU, held until the process ends
 constexpr int kMaxDevices = 64;
 float* g_scratch_ptr[kMaxDevices] = {};
 std::mutex g_scratch_mu;
@@ -954,9 +955,16 @@ int32_t l2pd_egp_rollout(l2pd_ctx* c, const int32_t* prompt_dev, const int32_t* 
   return L2PD_OK;
 }
 
-int32_t l2pd_filter_train(const l2pd_filter* f, const float* conf_rows_dev, const float* label_rows_dev,
-                          int64_t n_rows, const l2pd_train_cfg* tc, float* opt_state_dev, float* loss_out_dev,
-                          void* stream) {
+size_t l2pd_filter_train_workspace_bytes(const l2pd_filter* f, int64_t n_rows) {
+  if (!f || f->n_layers < 1 || f->n_layers > L2PD_FILTER_MAX_LAYERS || f->in_dim < 1 || f->in_dim > 20480) return 0;
+  if (f->n_layers > 1 && (f->hidden < 1 || f->hidden > 1024)) return 0;
+  if (n_rows < 1 || n_rows > (1ll << 24) || !filter_train_supported(f->in_dim, f->hidden, f->n_layers)) return 0;
+  return filter_train_split_bytes(f->in_dim, f->hidden, f->n_layers, n_rows);
+}
+
+int32_t l2pd_filter_train_split(const l2pd_filter* f, const float* conf_rows_dev, const float* label_rows_dev,
+                                int64_t n_rows, const l2pd_train_cfg* tc, float* opt_state_dev, float* loss_out_dev,
+                                void* workspace_dev, size_t workspace_bytes, void* stream) {
   if (!f || !tc || !conf_rows_dev || !label_rows_dev || !opt_state_dev) return L2PD_EINVAL;
   if (!filter_ok(f)) return L2PD_EINVAL;
   if (n_rows < 1 || n_rows > (1ll << 24) || tc->epochs < 1 || tc->epochs > 1000000) return L2PD_EINVAL;
@@ -964,6 +972,10 @@ int32_t l2pd_filter_train(const l2pd_filter* f, const float* conf_rows_dev, cons
       !(tc->eps > 0.f) || !(tc->weight_decay >= 0.f))
     return L2PD_EINVAL;
   if (!filter_train_supported(f->in_dim, f->hidden, f->n_layers)) return L2PD_ENOTIMPL;
+  if (workspace_dev) {
+    if ((uintptr_t)workspace_dev % 256) return L2PD_EINVAL;
+    if (workspace_bytes < filter_train_split_bytes(f->in_dim, f->hidden, f->n_layers, n_rows)) return L2PD_ENOMEM;
+  }
   TrainArgs a = {};
   for (int k = 0; k < f->n_layers; ++k) {
     a.w[k] = const_cast<float*>(f->w_dev[k]);
@@ -973,8 +985,15 @@ int32_t l2pd_filter_train(const l2pd_filter* f, const float* conf_rows_dev, cons
   a.conf = conf_rows_dev; a.label = label_rows_dev; a.n = n_rows; a.epochs = tc->epochs;
   a.lr = tc->lr; a.beta1 = tc->beta1; a.beta2 = tc->beta2; a.eps = tc->eps; a.weight_decay = tc->weight_decay;
   a.opt_state = opt_state_dev; a.loss_out = loss_out_dev;
-  launch_filter_train(a, static_cast<hipStream_t>(stream));
+  launch_filter_train(a, static_cast<float*>(workspace_dev), static_cast<hipStream_t>(stream));
   return hipGetLastError() == hipSuccess ? L2PD_OK : L2PD_EHIP;
+}
+
+int32_t l2pd_filter_train(const l2pd_filter* f, const float* conf_rows_dev, const float* label_rows_dev,
+                          int64_t n_rows, const l2pd_train_cfg* tc, float* opt_state_dev, float* loss_out_dev,
+                          void* stream) {
+  return l2pd_filter_train_split(f, conf_rows_dev, label_rows_dev, n_rows, tc, opt_state_dev, loss_out_dev, nullptr, 0,
+                                 stream);
 }
 
 int32_t l2pd_filter_train_static(const l2pd_filter* f, const float* conf_rows_dev, const float* label_rows_dev,
@@ -990,8 +1009,9 @@ int32_t l2pd_filter_train_static(const l2pd_filter* f, const float* conf_rows_de
   int32_t st = L2PD_OK;
   float* moments = static_scratch(&st);
   if (!moments) return st;
-  // training starts from moments of zero and writes them before it reads them: what an earlier call left is never read
-  return l2pd_filter_train(f, conf_rows_dev, label_rows_dev, n_rows, tc, moments, loss_out_dev, stream);
+  // training starts from moments of zero and writes everything before it reads it: what an earlier call left is never read
+  return l2pd_filter_train_split(f, conf_rows_dev, label_rows_dev, n_rows, tc, moments, loss_out_dev,
+                                 moments + 2 * kStaticTrainParams, kTrainSplitFloats * sizeof(float), stream);
 }
 
 int32_t l2pd_profile_select(l2pd_ctx* c, int32_t cls) {

@@ -1,0 +1,87 @@
+"""Filter training with its rows dealt to workgroups (l2pd_filter_train_split) against the oracle and against the
+one-workgroup entry point: ragged last workgroups, several chunks of rows in one workgroup, one launch an epoch and two,
+widths that are no multiple of 16, one to four layers."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import l2pd_oracle as O
+from paper_2509_25188_amd import binding as Bd
+from paper_2509_25188_amd import synth
+from tests import parity as Pz
+
+pytestmark = pytest.mark.gpu
+
+
+def train(flt, conf, label, epochs, split):
+    lib = Bd.lib()
+    f = Bd._filter_struct(flt)
+    n = conf.shape[0]
+    need = lib.l2pd_filter_train_workspace_bytes(C.byref(f), n)
+    n_params = sum(t.numel() for t in flt.values())
+    opt = torch.full((2 * n_params,), float("nan"), device="cuda")
+    loss = torch.full((epochs,), float("nan"), device="cuda")
+    work = torch.full((max(need, 4) // 4,), float("nan"), device="cuda")     # never read before it is written
+    tc = Bd.TrainCfg(1e-3, 0.9, 0.999, 1e-8, 0.01, epochs)
+    rc = lib.l2pd_filter_train_split(C.byref(f), conf.data_ptr(), label.data_ptr(), n, C.byref(tc), opt.data_ptr(),
+                                     loss.data_ptr(), work.data_ptr() if split else None, need if split else 0,
+                                     torch.cuda.current_stream().cuda_stream)
+    assert rc == Bd.L2PD_OK
+    return need, opt, loss
+
+
+# width, hidden, layers, rows
+SHAPES = [(32, 32, 2, 241), (32, 32, 2, 129), (64, 128, 2, 4096), (64, 128, 2, 17), (24, 40, 3, 333), (20, 1, 1, 1001),
+          (48, 48, 4, 2049), (1, 1, 2, 5000), (32, 32, 2, 20011), (128, 64, 2, 3001), (64, 128, 2, 16387)]
+
+
+@pytest.mark.parametrize("s,h,L,n", SHAPES)
+def test_rows_over_workgroups_match_oracle_and_one_workgroup(s, h, L, n):
+    r = np.random.default_rng(91)
+    Cn = r.uniform(size=(n, s)).astype(np.float32)
+    Yn = (r.uniform(size=(n, s)) < 0.2 + 0.6 * Cn).astype(np.float32)
+    flt = synth.make_filter(92, s, h, "cpu", n_layers=L)
+    Cd, Yd = torch.tensor(Cn).cuda(), torch.tensor(Yn).cuda()
+    epochs = 4
+    one = {k: v.clone().cuda() for k, v in flt.items()}
+    many = {k: v.clone().cuda() for k, v in flt.items()}
+    _, opt1, loss1 = train(one, Cd, Yd, epochs, False)
+    need, opt, loss = train(many, Cd, Yd, epochs, True)
+    again = {k: v.clone().cuda() for k, v in flt.items()}
+    train(again, Cd, Yd, epochs, True)
+    assert need > 0 or n * s * h < 1 << 20
+    ref, ref_losses = O.train_filter(Pz.np_filter(flt), Cn, Yn, epochs, lr=1e-3)
+    np.testing.assert_allclose(loss.cpu().numpy(), ref_losses, rtol=1e-5, atol=1e-7)
+    np.testing.assert_allclose(loss1.cpu().numpy(), ref_losses, rtol=1e-5, atol=1e-7)
+    for k in ref:
+        assert torch.equal(again[k], many[k]), k
+        # four updates of at most 1e-3 each; where a gradient entry is rounding noise its sign is free
+        d = np.abs(many[k].cpu().numpy() - ref[k])
+        assert d.max() < 8.5e-3 and np.mean(d < 1e-4) > 0.995, (k, d.max())
+    # moments: gradients to the rounding of their sums, relative to the largest entry
+    N = opt.numel() // 2
+    for a, b in ((opt[:N], opt1[:N]), (opt[N:], opt1[N:])):
+        assert torch.isfinite(a).all()
+        assert float((a - b).abs().max()) <= 2e-4 * float(b.abs().max())
+
+
+def test_workspace_is_checked_before_any_launch():
+    lib = Bd.lib()
+    flt = {k: v.cuda() for k, v in synth.make_filter(93, 32, 32, "cpu").items()}
+    f = Bd._filter_struct(flt)
+    rows = torch.zeros((500, 32), device="cuda")
+    need = lib.l2pd_filter_train_workspace_bytes(C.byref(f), 500)
+    assert need > 0
+    opt, work = torch.zeros(2 * 2112, device="cuda"), torch.zeros(need // 4 + 64, device="cuda")
+    tc = Bd.TrainCfg(1e-3, 0.9, 0.999, 1e-8, 0.01, 1)
+    w1 = flt["w1"].clone()
+
+    def call(ptr, nbytes):
+        return lib.l2pd_filter_train_split(C.byref(f), rows.data_ptr(), rows.data_ptr(), 500, C.byref(tc),
+                                           opt.data_ptr(), None, ptr, nbytes, torch.cuda.current_stream().cuda_stream)
+    assert call(work.data_ptr(), need - 4) == Bd.L2PD_ENOMEM
+    assert call(work.data_ptr() + 4, need) == Bd.L2PD_EINVAL
+    torch.cuda.synchronize()
+    assert torch.equal(flt["w1"], w1)
