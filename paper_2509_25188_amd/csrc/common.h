@@ -74,15 +74,15 @@ void launch_init_decode(int32_t* X, const int32_t* prompt, int B, int P, int G, 
                         int* ctl, hipStream_t s);
 void launch_prepare(const int32_t* state, int B, int n_blocks, int ragged, int* ctl, hipStream_t s,
                     int done_at = 0);   // done_at > 0: also ctl[done_at + b] = sequence b's done flag
-void launch_embed(float* h, const void* emb, int dtype, const int32_t* tokens, RowMap tokmap, int rows, int d,
+void launch_embed(float* h, const bf16* emb, const int32_t* tokens, RowMap tokmap, int rows, int d,
                   Gate g, hipStream_t s);
 // h (+= the sum part[0] + ... + part[n_parts-1], formed first, in that order, when given) -> y = rmsnorm(h) * gain, rows taken
 // through `src`.  part z is at parts + z * part_stride, laid out like h.  The sum is written back to h
 // when `write_back` is set; the final norm before the LM head leaves h alone (h is dead after it, and
 // two head rows may map to one row of h, so a write-back would race).
 // h_out: the parts are laid out like y and the sum goes to h_out, laid out like y too, instead of back to h.
-void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const void* gain,
-                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s,
+void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const bf16* gain,
+                    bf16* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s,
                     float* h_out = nullptr);
 constexpr int kFilterMaxLayers = 4;
 struct UpdateArgs {
@@ -141,32 +141,52 @@ void launch_seq_len(const int32_t* X, int B, int P, int G, int eos_id, int* teff
 // keys[b] = base + ctl[CTL_SEQ_GB + b] * per_gb: keys a sequence's block rows may see under the prefix cache
 void launch_block_keys(const int* ctl, int B, int base, int per_gb, int* keys, hipStream_t s);
 
-// ---- vocabulary reduction over materialised logits (fp32 path and the logits tap) ----
 struct BiasArgs {
   int token_id, gen_pos_from, block_len;
   float value;           // 0: off
 };
-// partials over column chunks of `chunk` logits: max, sum exp(x - max), argmax (lowest id on ties),
-// mask_id excluded.  logits [rows, V] are modified in place by the bias first.
-void launch_vocab_partials(float* logits, int rows, int V, int chunk, int mask_id, BiasArgs bias, float* part_max,
-                           float* part_sum, int32_t* part_idx, int n_part, Gate g, hipStream_t s);
+struct LmHeadEpilogue {
+  float* logits;         // optional [M, V]
+  float* part_max;       // optional [M, n_part]: per part of the columns max, sum exp(x - max), argmax (lowest id on ties),
+  float* part_sum;       // mask_id excluded
+  int32_t* part_idx;
+  int n_part;
+  int mask_id;
+  BiasArgs bias;         // applied when value != 0 (needs ctl for the active block)
+};
 
 // ---- fp32 path (kernels_f32.hip) ----
-// C[i][M,N] (+)= A[M,K] * W[i][N,K]^T, i < n <= 3
-void launch_gemm_f32(const float* A, const float* const* W, float* const* C, int n, int M, int N, int K, int accumulate,
-                     Gate g, hipStream_t s);
-inline void launch_gemm_f32(const float* A, const float* W, float* C, int M, int N, int K, int accumulate, Gate g,
-                            hipStream_t s) {
-  launch_gemm_f32(A, &W, &C, 1, M, N, K, accumulate, g, s);
-}
-// rotate q [rows, d] in place and copy/rotate k, v rows into the [B, Tmax, d] key/value stores at pos0 + t
-// (seq_gb / pos_per_gb: per-sequence position offsets as in QkvEpilogue)
-void launch_rope_store_f32(float* q, const float* k, const float* v, float* kstore, float* vstore, int B, int Tq,
-                           int pos0, int Tmax, int H, int Dh, const float2* rope, const int* seq_gb, int pos_per_gb, Gate g,
-                           hipStream_t s);
+// One product of a layer with what comes before and behind it:
+//   F32_QKV     rows of A, RMS-normalised with `gain`, times W[0..2]: rotated q into C [rows, H * Dh], rotated k and v into the
+//               [B, Tmax, H * Dh] stores at pos0 + t (seq_gb / pos_per_gb: per-sequence offsets as in QkvEpilogue).
+//               N = 3 * H * Dh / 2 pairs
+//   F32_SWIGLU  normalised rows times W[0], W[1]: silu(.) * . into C [rows, N]
+//   F32_LMHEAD  normalised rows times W[0]: logits and partials; a part is f32_lmhead_cols columns
+//   F32_PLAIN   C [rows, N] (+)= A W[0]^T
+enum { F32_PLAIN = 0, F32_QKV = 1, F32_SWIGLU = 2, F32_LMHEAD = 3 };
+struct F32Product {
+  const float* A;          // row r of the product is row map_row(rows, r) of A [., K], or of the table A at that token
+  RowMap rows;
+  const int32_t* tokens;   // null: rows of A as they are
+  float* h_out;            // optional (with tokens): the rows as they are, [M, K]
+  const float* gain;
+  float eps;
+  const float* W[3];
+  int M, N, K;
+  float* C;
+  int accumulate;
+  float *kstore, *vstore;
+  const float2* rope;
+  int Tq, pos0, Tmax, H, Dh;
+  const int* seq_gb;
+  int pos_per_gb;
+  LmHeadEpilogue lm;
+  Gate gate;
+};
+void launch_product_f32(const F32Product& a, int kind, hipStream_t s);
+int f32_lmhead_cols(int rows, int V);   // 32 or 64
 void launch_attn_f32(const float* q, const float* kstore, const float* vstore, float* out, int B, int Tq, int Tk,
                      int Tmax, int H, int Dh, const int* tk_dev, Gate g, hipStream_t s);
-void launch_swiglu_f32(const float* gate, const float* up, float* act, size_t n, Gate g, hipStream_t s);
 
 // ---- bf16 path ----
 struct QkvEpilogue {
@@ -211,15 +231,6 @@ void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16
                              hipStream_t s);
 void launch_gemm_few_rows_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16* act, int M, int F, int K, Gate g,
                                       hipStream_t s);
-struct LmHeadEpilogue {
-  float* logits;         // optional [M, V]
-  float* part_max;       // optional [M, n_part]
-  float* part_sum;
-  int32_t* part_idx;
-  int n_part;            // = V / 128 rounded up
-  int mask_id;
-  BiasArgs bias;         // applied when value != 0 (needs ctl for the active block)
-};
 int lmhead_n_part(int V);
 void launch_gemm_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, const LmHeadEpilogue& e, Gate g,
                              hipStream_t s);

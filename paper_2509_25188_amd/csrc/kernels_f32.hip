@@ -1,261 +1,473 @@
-// fp32 path (small models, tight tolerance): plain tiled kernels, fp32 everywhere.
-#include "common.h"
+// fp32 path (small models, tight tolerance): products and attention on the fp32 matrix cores, fp32 everywhere.
+//
+// A decode of a small model is a chain of launches of a few microseconds each, so a layer is five of them: the RMSNorm
+// (and, in the first layer, the embedding) is part of the product that reads it, rotation and K / V store, SiLU * up, the
+// residual sum and the vocabulary reduction are epilogues.  Two layers, 96 rows, 128 wide, vocabulary of 1024: a forward is
+// 56 us (135 with nine launches a layer, vector arithmetic and tiles through LDS); bound by launch, two memory round trips
+// and the chain of products in every kernel (products 4.6-5.6 us, attention 5.0).
+#include "gemm_common.h"
 
 namespace l2pd {
+namespace {
 
-// C[M,N] (+)= A[M,K] * W[N,K]^T.  64x64 tile, 16x16 threads, 4x4 outputs per thread, K tile 16.
-__global__ void __launch_bounds__(256) k_gemm_f32(const float* __restrict__ A, const float* __restrict__ W,
-                                                  float* __restrict__ C, int M, int N, int K, int accumulate,
-                                                  Gate g) {
-  if (gate_skip(g)) return;
-  __shared__ float sA[16][64 + 1];
-  __shared__ float sW[16][64 + 1];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = tid; i < 64 * 16; i += 256) {
-      int r = i >> 4, k = i & 15;
-      int gm = m0 + r, gn = n0 + r, gk = k0 + k;
-      sA[k][r] = (gm < M && gk < K) ? A[(size_t)gm * K + gk] : 0.f;
-      sW[k][r] = (gn < N && gk < K) ? W[(size_t)gn * K + gk] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], w[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = sA[k][ty * 4 + i]; w[i] = sW[k][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * w[j];
-    }
-    __syncthreads();
-  }
-  for (int i = 0; i < 4; ++i) {
-    int gm = m0 + ty * 4 + i;
-    if (gm >= M) continue;
-    for (int j = 0; j < 4; ++j) {
-      int gn = n0 + tx * 4 + j;
-      if (gn >= N) continue;
-      size_t o = (size_t)gm * N + gn;
-      C[o] = accumulate ? C[o] + acc[i][j] : acc[i][j];
-    }
+// C[M, N] = A[M, K] W[N, K]^T in 16 x 16 fragments of v_mfma_f32_16x16x4_f32.  Operands go from memory straight to
+// registers: both are K-contiguous and the order inside K is free, so that lane group g takes elements 4g .. 4g+3 of 16
+// as one 16-byte load and feeds them to four successive MFMAs.
+//   K is summed in four ranges, which are added in ascending order.  A small product (KS = 4) gives every range a wavefront
+// of one workgroup, 16 x 32 outputs: a chain of a quarter of the length, all loads of up to 64 K elements in flight, no
+// barrier but the one before the ranges meet in LDS.  A large one (KS = 1) has 64 x 64 outputs in every wavefront, which walks
+// the ranges itself: the same bits, so that a sequence's logits do not depend on the batch it is in.
+//   us a forward of two layers (32 x 32 and 64 x 64 tiles of vector arithmetic before / these): 4 x 256 rows, 512 wide, FFN 2048:
+// 1,324 / 425; 8 x 512 rows, 2048 wide, FFN 4096: 19,707 / 9,417 (73 TFLOP/s).
+//   NORM: rows are RMS-normalised on the way: gain is multiplied in as the row is read, the row's sum of squares is formed
+// beside the products, and the sums are scaled at the end.
+enum { EPI_PLAIN = 0, EPI_ROPE = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3 };
+constexpr bool pair_epi(int epi) { return epi == EPI_ROPE || epi == EPI_SWIGLU; }
+
+// Weight row behind feature f (pair epilogues: side 0 or 1 of it).
+template <int EPI>
+__device__ __forceinline__ const float* weight_row(const F32Product& a, int f, int side) {
+  f = min(f, a.N - 1);
+  if constexpr (EPI == EPI_ROPE) {
+    const int half = a.Dh / 2, per = a.H * half, mat = f / per, i = f % per;
+    const float* W = mat == 0 ? a.W[0] : (mat == 1 ? a.W[1] : a.W[2]);
+    return W + (size_t)(i / half * a.Dh + i % half + side * half) * a.K;
+  } else if constexpr (EPI == EPI_SWIGLU) {
+    return a.W[side] + (size_t)f * a.K;
+  } else {
+    return a.W[0] + (size_t)f * a.K;
   }
 }
-// Small products (the 64 x 64 tiles above would be fewer than the CUs): 32 x 32 tiles, 16 x 16 threads with 2 x 2 outputs
-// each, 32 deep; the next K step waits in registers while one is worked on, so a step costs its arithmetic and not
-// a round trip to memory.  VEC: rows in 16-byte pieces (K a multiple of 4, operands aligned).  Up to three products of
-// one A and weights of one shape share a launch.  Every output sums over K in ascending order, as above: same bits.
-// 96 x 128 x 128: 21.6 us with the 64 x 64 tiles (four of them), 7.0 with these.
-struct GemmF32Set {
-  const float* W[3];
-  float* C[3];
-};
-template <bool VEC>
-__global__ void __launch_bounds__(256) k_gemm_f32_small(const float* __restrict__ A, GemmF32Set set, int M, int N, int K,
-                                                        int accumulate, Gate g) {
-  if (gate_skip(g)) return;
-  constexpr int LD = 34;
-  __shared__ __attribute__((aligned(8))) float sA[32][LD], sW[32][LD];
-  const float* __restrict__ W = blockIdx.z == 0 ? set.W[0] : (blockIdx.z == 1 ? set.W[1] : set.W[2]);
-  float* C = blockIdx.z == 0 ? set.C[0] : (blockIdx.z == 1 ? set.C[1] : set.C[2]);
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-  const int r = tid >> 3, kq = (tid & 7) * 4;      // this thread's row and first of four K elements of a tile
-  const float* pa = A + (size_t)min(m0 + r, M - 1) * K + kq;
-  const float* pw = W + (size_t)min(n0 + r, N - 1) * K + kq;
-  float va[4], vw[4];
-  auto fetch = [&](int k0) {
+// Output of one row: columns f and, for pair epilogues, both sides of feature f.
+__device__ __forceinline__ void put_plain(const F32Product& a, int row, int f, float x) {
+  if (row >= a.M || f >= a.N) return;
+  float* o = a.C + (size_t)row * a.N + f;
+  *o = a.accumulate ? *o + x : x;
+}
+__device__ __forceinline__ void put_swiglu(const F32Product& a, int row, int f, float g, float u) {
+  if (row < a.M && f < a.N) a.C[(size_t)row * a.N + f] = g / (1.f + expf(-g)) * u;
+}
+// rotate-half pairs (i, i + Dh/2): q rotated in place of the product, k rotated and v as it is into the stores
+__device__ __forceinline__ void put_rope(const F32Product& a, int row, int f, float x1, float x2) {
+  if (row >= a.M || f >= a.N) return;
+  const int half = a.Dh / 2, per = a.H * half, mat = f / per, i = f % per, e = i % half;
+  const int b = row / a.Tq, pos = a.pos0 + seq_pos_offset(a.seq_gb, a.pos_per_gb, b) + row % a.Tq;
+  const int d = a.H * a.Dh, col = i / half * a.Dh + e;
+  float* o = mat == 0 ? a.C + (size_t)row * d + col : (mat == 1 ? a.kstore : a.vstore) + ((size_t)b * a.Tmax + pos) * d + col;
+  if (mat < 2) {
+    const float2 rot = a.rope[(size_t)pos * half + e];
+    const float y1 = x1 * rot.x - x2 * rot.y;
+    x2 = x2 * rot.x + x1 * rot.y;
+    x1 = y1;
+  }
+  o[0] = x1;
+  o[half] = x2;
+}
+// The row's logits in this tile, NF fragments of 16 columns from f0 (lane cl holds column f0 + 16 j + cl): logits, and the
+// tile's (max, sum exp(x - max), lowest column that has the maximum), the mask id being no candidate.
+template <int NF>
+__device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0, int cl, float (&x)[NF]) {
+  const LmHeadEpilogue& e = a.lm;
+  const bool biased = e.bias.value != 0.f && a.gate.ctl && row < a.M &&
+                      a.gate.ctl[CTL_SEQ_GB + row / e.bias.block_len] * e.bias.block_len + row % e.bias.block_len >= e.bias.gen_pos_from;
+  float m = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < NF; ++j) {
+    const int col = f0 + 16 * j + cl;
+    if (biased && col == e.bias.token_id) x[j] += e.bias.value;
+    if (e.logits && row < a.M && col < a.N) e.logits[(size_t)row * a.N + col] = x[j];
+    if (col == e.mask_id || col >= a.N) x[j] = -INFINITY;
+    m = fmaxf(m, x[j]);
+  }
+  if (!e.part_max) return;
+  m = fmaxf(m, dppf<kDppRor + 8>(m));
+  m = fmaxf(m, dppf<kDppRor + 4>(m));
+  m = fmaxf(m, dppf<kDppRor + 2>(m));
+  m = fmaxf(m, dppf<kDppRor + 1>(m));
+  int mi = 0x7fffffff;
+  float sum = 0.f;
+#pragma unroll
+  for (int j = NF - 1; j >= 0; --j) mi = x[j] == m && m > -INFINITY ? f0 + 16 * j + cl : mi;
+#pragma unroll
+  for (int j = 0; j < NF; ++j) sum += m == -INFINITY ? 0.f : exp_neg(m - x[j]);
+  mi = min(mi, (int)dpp<kDppRor + 8>((unsigned)mi));
+  mi = min(mi, (int)dpp<kDppRor + 4>((unsigned)mi));
+  mi = min(mi, (int)dpp<kDppRor + 2>((unsigned)mi));
+  mi = min(mi, (int)dpp<kDppRor + 1>((unsigned)mi));
+  sum += dppf<kDppRor + 8>(sum);
+  sum += dppf<kDppRor + 4>(sum);
+  sum += dppf<kDppRor + 2>(sum);
+  sum += dppf<kDppRor + 1>(sum);
+  if (cl == 0 && row < a.M) {
+    const size_t o = (size_t)row * e.n_part + f0 / (16 * NF);
+    e.part_max[o] = m;
+    e.part_sum[o] = sum;
+    e.part_idx[o] = mi;
+  }
+}
+// Finished values of one row: v[j] is fragment j, column lane cl.
+template <int EPI, int FN>
+__device__ __forceinline__ void put_row(const F32Product& a, int row, int f0, int cl, float (&v)[FN]) {
+  if constexpr (EPI == EPI_LMHEAD) {
+    put_lmhead<FN>(a, row, f0, cl, v);
+  } else if constexpr (pair_epi(EPI)) {
+#pragma unroll
+    for (int p = 0; p < FN / 2; ++p) {
+      if constexpr (EPI == EPI_ROPE) put_rope(a, row, f0 + 16 * p + cl, v[2 * p], v[2 * p + 1]);
+      else put_swiglu(a, row, f0 + 16 * p + cl, v[2 * p], v[2 * p + 1]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < FN; ++j) put_plain(a, row, f0 + 16 * j + cl, v[j]);
+  }
+}
+
+template <int FM, int FN, int KS, int EPI, bool NORM, bool VEC>
+__global__ void __launch_bounds__(256) k_product_f32(F32Product a) {
+  if (gate_skip(a.gate)) return;
+  static_assert(KS == 1 || (KS == 4 && FM == 1), "four wavefronts share one row of fragments, or none");
+  constexpr int U = KS == 4 ? 4 : 1;           // 16-deep K steps per round of loads
+  constexpr int TN = (pair_epi(EPI) ? FN / 2 : FN) * 16;   // features of a tile
+  __shared__ float s_part[KS == 4 ? 4 : 1][KS == 4 ? 4 * FN : 1][64];
+  __shared__ float s_ss[KS == 4 ? 4 : 1][64];
+  const int lane = threadIdx.x & 63, g = lane >> 4, cl = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // KS == 1: the four wavefronts of a workgroup are 2 x 2 neighbours
+  const int tile_m = KS == 4 ? blockIdx.y : blockIdx.y * 2 + (wave >> 1);
+  const int tile_n = KS == 4 ? blockIdx.x : blockIdx.x * 2 + (wave & 1);
+  const int m0 = tile_m * 16 * FM, f0 = tile_n * TN;
+  if (KS == 1 && (m0 >= a.M || f0 >= a.N)) return;
+  const int steps = (a.K + 15) / 16, per = (steps + 3) / 4;
+
+  const float* pa[FM];
+  const float* pw[FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    int r = map_row(a.rows, min(m0 + i * 16 + cl, a.M - 1), a.gate.ctl);
+    if (a.tokens) r = a.tokens[r];
+    pa[i] = a.A + (size_t)r * a.K + g * 4;
+  }
+#pragma unroll
+  for (int j = 0; j < FN; ++j)
+    pw[j] = (pair_epi(EPI) ? weight_row<EPI>(a, f0 + j / 2 * 16 + cl, j & 1) : weight_row<EPI>(a, f0 + j * 16 + cl, 0)) + g * 4;
+  // a lane's four K elements of step c, zero beyond K or the range
+  auto fetch = [&](const float* p, int c, int c1) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
     if constexpr (VEC) {
-      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-      const float4 x = k0 + kq < K ? *reinterpret_cast<const float4*>(pa + k0) : z;
-      const float4 y = k0 + kq < K ? *reinterpret_cast<const float4*>(pw + k0) : z;
-      va[0] = x.x; va[1] = x.y; va[2] = x.z; va[3] = x.w;
-      vw[0] = y.x; vw[1] = y.y; vw[2] = y.z; vw[3] = y.w;
+      if (c < c1 && c * 16 + g * 4 < a.K) v = *reinterpret_cast<const f32x4*>(p + c * 16);
     } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool in = k0 + kq + i < K;
-        va[i] = in ? pa[k0 + i] : 0.f;
-        vw[i] = in ? pw[k0 + i] : 0.f;
-      }
+      for (int j = 0; j < 4; ++j)
+        if (c < c1 && c * 16 + g * 4 + j < a.K) v[j] = p[c * 16 + j];
+    }
+    return v;
+  };
+  struct Round { f32x4 x[U][FM], w[U][FN], gain[NORM ? U : 1]; };
+  auto load = [&](Round& r, int c, int c1) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) r.x[u][i] = fetch(pa[i], c + u, c1);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) r.w[u][j] = fetch(pw[j], c + u, c1);
+      if constexpr (NORM) r.gain[u] = fetch(a.gain + g * 4, c + u, c1);
     }
   };
-  float acc[2][2] = {};
-  fetch(0);
-  for (int k0 = 0; k0 < K; k0 += 32) {
+  f32x4 acc[FM][FN];
+  float ss[FM];
+  auto clear = [&]() {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { sA[kq + i][r] = va[i]; sW[kq + i][r] = vw[i]; }
-    __syncthreads();
-    if (k0 + 32 < K) fetch(k0 + 32);
+    for (int i = 0; i < FM; ++i) {
+      ss[i] = 0.f;
 #pragma unroll
-    for (int k = 0; k < 32; ++k) {
-      const float2 x = *reinterpret_cast<const float2*>(&sA[k][ty * 2]), y = *reinterpret_cast<const float2*>(&sW[k][tx * 2]);
-      acc[0][0] += x.x * y.x; acc[0][1] += x.x * y.y;
-      acc[1][0] += x.y * y.x; acc[1][1] += x.y * y.y;
+      for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    __syncthreads();
-  }
+  };
+  auto work = [&](Round& r, int c, int c1) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int gm = m0 + ty * 2 + i;
-    if (gm >= M) continue;
+    for (int u = 0; u < U; ++u) {
+      if (c + u >= c1) break;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int gn = n0 + tx * 2 + j;
-      if (gn >= N) continue;
-      const size_t o = (size_t)gm * N + gn;
-      C[o] = accumulate ? C[o] + acc[i][j] : acc[i][j];
-    }
-  }
-}
-void launch_gemm_f32(const float* A, const float* const* W, float* const* C, int n, int M, int N, int K, int accumulate,
-                     Gate g, hipStream_t s) {
-  const long long tiles = (long long)((N + 63) / 64) * ((M + 63) / 64) * n;
-  if (tiles < 256) {
-    GemmF32Set set = {};
-    uintptr_t bits = reinterpret_cast<uintptr_t>(A);
-    for (int i = 0; i < n; ++i) {
-      set.W[i] = W[i];
-      set.C[i] = C[i];
-      bits |= reinterpret_cast<uintptr_t>(W[i]);
-    }
-    const dim3 grid((N + 31) / 32, (M + 31) / 32, n);
-    if (K % 4 == 0 && bits % 16 == 0)
-      hipLaunchKernelGGL(k_gemm_f32_small<true>, grid, dim3(256), 0, s, A, set, M, N, K, accumulate, g);
-    else
-      hipLaunchKernelGGL(k_gemm_f32_small<false>, grid, dim3(256), 0, s, A, set, M, N, K, accumulate, g);
-    return;
-  }
-  const dim3 grid((N + 63) / 64, (M + 63) / 64);
-  for (int i = 0; i < n; ++i)
-    hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, s, A, W[i], C[i], M, N, K, accumulate, g);
-}
-
-// Rotary embedding (pairs (i, i + Dh/2)) on q in place; k rotated and v copied into the key/value
-// stores at absolute position pos0 + t.
-__global__ void k_rope_store_f32(float* q, const float* k, const float* v, float* kstore, float* vstore, int B,
-                                 int Tq, int pos0, int Tmax, int H, int Dh, const float2* rope, const int* seq_gb, int pos_per_gb, Gate g) {
-  if (gate_skip(g)) return;
-  const int half = Dh / 2, d = H * Dh;
-  size_t n = (size_t)B * Tq * H * half;
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int e = i % half;
-  int hh = (i / half) % H;
-  int r = i / ((size_t)half * H);
-  int b = r / Tq, t = r % Tq, pos = pos0 + seq_pos_offset(seq_gb, pos_per_gb, b) + t;
-  const float2 rot = rope[pos * half + e];
-  const float c = rot.x, sn = rot.y;
-  size_t src = (size_t)r * d + hh * Dh + e;
-  size_t dst = ((size_t)b * Tmax + pos) * d + hh * Dh + e;
-  float q1 = q[src], q2 = q[src + half];
-  q[src] = q1 * c - q2 * sn;
-  q[src + half] = q2 * c + q1 * sn;
-  float k1 = k[src], k2 = k[src + half];
-  kstore[dst] = k1 * c - k2 * sn;
-  kstore[dst + half] = k2 * c + k1 * sn;
-  vstore[dst] = v[src];
-  vstore[dst + half] = v[src + half];
-}
-void launch_rope_store_f32(float* q, const float* k, const float* v, float* kstore, float* vstore, int B, int Tq,
-                           int pos0, int Tmax, int H, int Dh, const float2* rope, const int* seq_gb, int pos_per_gb, Gate g,
-                           hipStream_t s) {
-  size_t n = (size_t)B * Tq * H * (Dh / 2);
-  hipLaunchKernelGGL(k_rope_store_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, q, k, v, kstore, vstore,
-                     B, Tq, pos0, Tmax, H, Dh, rope, seq_gb, pos_per_gb, g);
-}
-
-// Bidirectional softmax attention, one wavefront per (sequence, head, query): lanes own keys for the
-// scores and feature dims for the output.  Scores are staged in LDS in chunks of 1024 keys with an
-// online rescale between chunks.
-__global__ void __launch_bounds__(64) k_attn_f32(const float* q, const float* kstore, const float* vstore,
-                                                 float* out, int B, int Tq, int Tk_all, int Tmax, int H, int Dh,
-                                                 const int* tk_dev, Gate g) {
-  if (gate_skip(g)) return;
-  const int Tk = tk_dev ? min(Tk_all, tk_dev[blockIdx.z]) : Tk_all;   // per-sequence key count when given
-  __shared__ float s_q[256];
-  __shared__ float s_p[1024];
-  const int lane = threadIdx.x;
-  const int t = blockIdx.x, hh = blockIdx.y, b = blockIdx.z;
-  const int d = H * Dh;
-  const float scale = rsqrtf((float)Dh);
-  const float* qv = q + ((size_t)b * Tq + t) * d + hh * Dh;
-  for (int e = lane; e < Dh; e += 64) s_q[e] = qv[e];
-  __syncthreads();
-  float m = -INFINITY, l = 0.f;
-  float o[4] = {0.f, 0.f, 0.f, 0.f};   // Dh <= 256
-  for (int k0 = 0; k0 < Tk; k0 += 1024) {
-    int kn = min(1024, Tk - k0);
-    float cm = -INFINITY;
-    for (int j = lane; j < kn; j += 64) {
-      const float* kv = kstore + ((size_t)b * Tmax + k0 + j) * d + hh * Dh;
-      float sc = 0.f;
-      if (Dh % 4 == 0) {       // rows of the store start at multiples of Dh floats of an aligned buffer
-#pragma unroll 4
-        for (int e = 0; e < Dh; e += 4) {
-          const float4 k4 = *reinterpret_cast<const float4*>(kv + e);
-          sc += s_q[e] * k4.x; sc += s_q[e + 1] * k4.y; sc += s_q[e + 2] * k4.z; sc += s_q[e + 3] * k4.w;
+      for (int i = 0; i < FM; ++i) {
+        if (a.h_out && tile_n == 0 && m0 + i * 16 + cl < a.M) {   // embedding: the rows are the residual stream's
+          float* h = a.h_out + (size_t)(m0 + i * 16 + cl) * a.K + (c + u) * 16 + g * 4;
+          if constexpr (VEC) {
+            if ((c + u) * 16 + g * 4 < a.K) *reinterpret_cast<f32x4*>(h) = r.x[u][i];
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if ((c + u) * 16 + g * 4 + j < a.K) h[j] = r.x[u][i][j];
+          }
         }
-      } else {
-        for (int e = 0; e < Dh; ++e) sc += s_q[e] * kv[e];
+        if constexpr (NORM) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) ss[i] += r.x[u][i][j] * r.x[u][i][j];
+          r.x[u][i] *= r.gain[u];
+        }
       }
-      sc *= scale;
-      s_p[j] = sc;
-      cm = fmaxf(cm, sc);
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.x[u][i][t], r.w[u][j][t], acc[i][j], 0, 0, 0);
     }
-#pragma unroll
-    for (int of = 32; of > 0; of >>= 1) cm = fmaxf(cm, __shfl_xor(cm, of, 64));
-    float mn = fmaxf(m, cm);
-    float alpha = (m == -INFINITY) ? 0.f : expf(m - mn);
-    float ls = 0.f;
-    __syncthreads();
-    for (int j = lane; j < kn; j += 64) {
-      float p = expf(s_p[j] - mn);
-      s_p[j] = p;
-      ls += p;
+  };
+  // one K range, the next round's loads in flight behind the one at work
+  auto range = [&](int z) {
+    const int c1 = min(steps, (z + 1) * per);
+    Round r0, r1;
+    load(r0, z * per, c1);
+    for (int c = z * per; c < c1; c += 2 * U) {
+      load(r1, c + U, c1);
+      work(r0, c, c1);
+      load(r0, c + 2 * U, c1);
+      work(r1, c + U, c1);
     }
+  };
+  clear();
+  if constexpr (KS == 4) {
+    range(wave);
 #pragma unroll
-    for (int of = 32; of > 0; of >>= 1) ls += __shfl_xor(ls, of, 64);
-    l = l * alpha + ls;
-    m = mn;
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_part[wave][j * 4 + r][lane] = acc[0][j][r];
+    if constexpr (NORM) s_ss[wave][lane] = ss[0];
     __syncthreads();
+    // C layout: register r of a lane is row 4 g + r, column cl; wavefront w finishes the rows with r = w
+    float v[FN];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      int e = lane + c * 64;
-      if (e < Dh) {
-        float acc = o[c] * alpha;
-#pragma unroll 16
-        for (int j = 0; j < kn; ++j) acc += s_p[j] * vstore[((size_t)b * Tmax + k0 + j) * d + hh * Dh + e];
-        o[c] = acc;
+    for (int j = 0; j < FN; ++j)
+      v[j] = s_part[0][j * 4 + wave][lane] + s_part[1][j * 4 + wave][lane] + s_part[2][j * 4 + wave][lane] +
+             s_part[3][j * 4 + wave][lane];
+    if constexpr (NORM) {
+      float q = s_ss[0][lane] + s_ss[1][lane] + s_ss[2][lane] + s_ss[3][lane];   // row cl, K elements of group g
+      q += __shfl_xor(q, 16, 64);
+      q += __shfl_xor(q, 32, 64);
+      const float inv = __shfl(rsqrtf(q / (float)a.K + a.eps), g * 4 + wave, 64);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) v[j] *= inv;
+    }
+    put_row<EPI, FN>(a, m0 + g * 4 + wave, f0, cl, v);
+  } else {
+    f32x4 tot[FM][FN];
+    float tss[FM];
+    for (int z = 0; z < 4; ++z) {
+      if (z > 0) clear();
+      range(z);
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        tss[i] = z == 0 ? ss[i] : tss[i] + ss[i];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) tot[i][j] = z == 0 ? acc[i][j] : tot[i][j] + acc[i][j];
       }
     }
-    __syncthreads();
-  }
-  float* ov = out + ((size_t)b * Tq + t) * d + hh * Dh;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    int e = lane + c * 64;
-    if (e < Dh) ov[e] = o[c] / l;
+    for (int i = 0; i < FM; ++i) {
+      float inv = 1.f;
+      if constexpr (NORM) {
+        float q = tss[i];
+        q += __shfl_xor(q, 16, 64);
+        q += __shfl_xor(q, 32, 64);
+        inv = rsqrtf(q / (float)a.K + a.eps);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float v[FN];
+        const float s = NORM ? __shfl(inv, g * 4 + r, 64) : 1.f;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) v[j] = NORM ? tot[i][j][r] * s : tot[i][j][r];
+        put_row<EPI, FN>(a, m0 + i * 16 + g * 4 + r, f0, cl, v);
+      }
+    }
   }
 }
+
+// Tile choice: 64 x 64 outputs a wavefront once there are enough of them for every SIMD.
+constexpr int kBigTiles = 1024;
+bool big_product(int M, int cols) { return (long long)((M + 63) / 64) * ((cols + 63) / 64) >= kBigTiles; }
+
+template <int EPI, bool NORM>
+void launch_product(const F32Product& a, hipStream_t s) {
+  constexpr int sides = pair_epi(EPI) ? 2 : 1;
+  uintptr_t bits = reinterpret_cast<uintptr_t>(a.A) | reinterpret_cast<uintptr_t>(a.gain) | reinterpret_cast<uintptr_t>(a.h_out);
+  for (const float* w : a.W) bits |= reinterpret_cast<uintptr_t>(w);
+  const bool vec = a.K % 4 == 0 && bits % 16 == 0;
+  if (big_product(a.M, a.N * sides)) {
+    const int tn = 64 / sides;
+    const dim3 grid((a.N + 2 * tn - 1) / (2 * tn), (a.M + 127) / 128);
+    if (vec) hipLaunchKernelGGL((k_product_f32<4, 4, 1, EPI, NORM, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_product_f32<4, 4, 1, EPI, NORM, false>), grid, dim3(256), 0, s, a);
+  } else {
+    const int tn = 32 / sides;
+    const dim3 grid((a.N + tn - 1) / tn, (a.M + 15) / 16);
+    if (vec) hipLaunchKernelGGL((k_product_f32<1, 2, 4, EPI, NORM, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_product_f32<1, 2, 4, EPI, NORM, false>), grid, dim3(256), 0, s, a);
+  }
+}
+
+// Bidirectional softmax attention, 16 queries of one (sequence, head) per workgroup; its four wavefronts deal the keys
+// among them in contiguous runs and join at the end (the same runs whatever the batch).  S^T = K Q^T, so that a lane holds
+// scores of one query (column cl; rows 4 g + r are keys) and its exponentials are the B operand of O^T = V^T P^T as they
+// are: MFMA r of a 16-key tile takes keys 4 g + r.  Operands from memory straight to registers, 32 keys a round, the values
+// sent off before the scores.  96 rows, 4 heads of 32: 5.0 us (7.2 with the values behind the scores, 8.9 with a wavefront per
+// query).
+// ND: 16-wide pieces of the head, padded with zeros.
+template <int ND, bool VEC>
+__global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, const float* __restrict__ kstore,
+                                                  const float* __restrict__ vstore, float* __restrict__ out, int Tq, int Tk_all,
+                                                  int Tmax, int H, int Dh, const int* __restrict__ tk_dev, Gate gate) {
+  if (gate_skip(gate)) return;
+  constexpr int LD = 16 * ND + 4;
+  extern __shared__ __attribute__((aligned(16))) float s_o[];   // [wavefront][query][feature], then maxima and sums
+  float* const s_m = s_o + 4 * 16 * LD;
+  float* const s_l = s_m + 64;
+  const int lane = threadIdx.x & 63, g = lane >> 4, cl = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hh = blockIdx.y, b = blockIdx.z, d = H * Dh, q0 = blockIdx.x * 16;
+  const int Tk = tk_dev ? min(Tk_all, tk_dev[b]) : Tk_all;
+  const float scale = rsqrtf((float)Dh);
+  auto piece = [&](const float* p, int c) {      // features 16 c + 4 g .. + 3 of a row
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    const int e = c * 16 + g * 4;
+    if constexpr (VEC) {
+      if (e < Dh) v = *reinterpret_cast<const f32x4*>(p + e);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (e + j < Dh) v[j] = p[e + j];
+    }
+    return v;
+  };
+  f32x4 fq[ND];
+  const float* qp = q + ((size_t)b * Tq + min(q0 + cl, Tq - 1)) * d + hh * Dh;
+#pragma unroll
+  for (int c = 0; c < ND; ++c) fq[c] = piece(qp, c);
+  const float* kb = kstore + (size_t)b * Tmax * d + hh * Dh;
+  const float* vb = vstore + (size_t)b * Tmax * d + hh * Dh;
+
+  f32x4 o[ND];
+#pragma unroll
+  for (int f = 0; f < ND; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  const int tiles = (Tk + 15) / 16, per = (tiles + 3) / 4;
+  const int t1 = min(tiles, (wave + 1) * per);
+  for (int t = wave * per; t < t1; t += 2) {
+    f32x4 s[2];
+    float p[2][4];
+    // values of the round: sent off before the scores that they wait for (heads of up to 128)
+    float v[ND <= 8 ? ND : 1][2][4];
+    auto value = [&](int f, int u, int r) {
+      return f * 16 + cl < Dh ? vb[(size_t)min((t + u) * 16 + g * 4 + r, Tk - 1) * d + f * 16 + cl] : 0.f;
+    };
+    if constexpr (ND <= 8) {
+#pragma unroll
+      for (int f = 0; f < ND; ++f)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[f][u][r] = value(f, u, r);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const float* kr = kb + (size_t)min((t + u) * 16 + cl, Tk - 1) * d;
+#pragma unroll
+      for (int c = 0; c < ND; ++c) {
+        const f32x4 x = piece(kr, c);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], fq[c][j], s[u], 0, 0, 0);
+      }
+    }
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool in = t + u < t1 && (t + u) * 16 + g * 4 + r < Tk;
+        p[u][r] = in ? s[u][r] * scale : -INFINITY;
+        tmax = fmaxf(tmax, p[u][r]);
+      }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    const float mn = fmaxf(m, tmax), alpha = exp_neg(mn - m);   // (m = -inf at first: 0)
+    m = mn;
+    l *= alpha;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        p[u][r] = exp_neg(mn - p[u][r]);
+        l += p[u][r];
+      }
+#pragma unroll
+    for (int f = 0; f < ND; ++f) {
+      o[f] *= alpha;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          o[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(ND <= 8 ? v[ND <= 8 ? f : 0][u][r] : value(f, u, r), p[u][r], o[f], 0, 0, 0);
+    }
+  }
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  // O^T fragment f: features 16 f + 4 g + r of query cl
+#pragma unroll
+  for (int f = 0; f < ND; ++f) *reinterpret_cast<f32x4*>(s_o + (wave * 16 + cl) * LD + f * 16 + g * 4) = o[f];
+  if (g == 0) { s_m[wave * 16 + cl] = m; s_l[wave * 16 + cl] = l; }
+  __syncthreads();
+  const int qi = threadIdx.x >> 4;              // a query per 16 lanes
+  float M = s_m[qi];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) M = fmaxf(M, s_m[w * 16 + qi]);
+  float f[4], L = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    f[w] = exp_neg(M - s_m[w * 16 + qi]);
+    L += s_l[w * 16 + qi] * f[w];
+  }
+  if (q0 + qi >= Tq) return;
+  float* ov = out + ((size_t)b * Tq + q0 + qi) * d + hh * Dh;
+  for (int e = threadIdx.x & 15; e < Dh; e += 16) {
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v += s_o[(w * 16 + qi) * LD + e] * f[w];
+    ov[e] = v / L;
+  }
+}
+template <int ND, bool VEC>
+void launch_attn(const float* q, const float* kstore, const float* vstore, float* out, int B, int Tq, int Tk, int Tmax, int H,
+                 int Dh, const int* tk_dev, Gate g, hipStream_t s) {
+  auto kern = k_attn_f32<ND, VEC>;
+  constexpr int smem = (4 * 16 * (16 * ND + 4) + 128) * 4;
+  static DynLdsAttr attr;
+  attr.ensure(reinterpret_cast<const void*>(kern), smem);
+  hipLaunchKernelGGL(kern, dim3((Tq + 15) / 16, H, B), dim3(256), smem, s, q, kstore, vstore, out, Tq, Tk, Tmax, H, Dh, tk_dev, g);
+}
+
+}  // namespace
+
+int f32_lmhead_cols(int rows, int V) { return big_product(rows, V) ? 64 : 32; }
+
+void launch_product_f32(const F32Product& a, int kind, hipStream_t s) {
+  if (kind == F32_QKV) launch_product<EPI_ROPE, true>(a, s);
+  else if (kind == F32_SWIGLU) launch_product<EPI_SWIGLU, true>(a, s);
+  else if (kind == F32_LMHEAD) launch_product<EPI_LMHEAD, true>(a, s);
+  else launch_product<EPI_PLAIN, false>(a, s);
+}
+
 void launch_attn_f32(const float* q, const float* kstore, const float* vstore, float* out, int B, int Tq, int Tk,
                      int Tmax, int H, int Dh, const int* tk_dev, Gate g, hipStream_t s) {
-  hipLaunchKernelGGL(k_attn_f32, dim3(Tq, H, B), dim3(64), 0, s, q, kstore, vstore, out, B, Tq, Tk, Tmax, H, Dh, tk_dev,
-                     g);
-}
-
-__global__ void k_swiglu_f32(const float* gate, const float* up, float* act, size_t n, Gate g) {
-  if (gate_skip(g)) return;
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float x = gate[i];
-  act[i] = x / (1.f + expf(-x)) * up[i];
-}
-void launch_swiglu_f32(const float* gate, const float* up, float* act, size_t n, Gate g, hipStream_t s) {
-  hipLaunchKernelGGL(k_swiglu_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, gate, up, act, n, g);
+#define L2PD_ATTN(ND)                                                                                         \
+  (Dh % 4 == 0 ? launch_attn<ND, true>(q, kstore, vstore, out, B, Tq, Tk, Tmax, H, Dh, tk_dev, g, s)           \
+               : launch_attn<ND, false>(q, kstore, vstore, out, B, Tq, Tk, Tmax, H, Dh, tk_dev, g, s))
+  if (Dh <= 32) L2PD_ATTN(2);
+  else if (Dh <= 64) L2PD_ATTN(4);
+  else if (Dh <= 128) L2PD_ATTN(8);
+  else L2PD_ATTN(16);
+#undef L2PD_ATTN
 }
 
 }  // namespace l2pd

@@ -1,5 +1,4 @@
-// Small kernels of the decoding loop: embedding gather, RMSNorm (wavefront reduction), the
-// vocabulary reduction over materialised logits, the filter + unmask + EoTP update, loop control.
+// Small kernels of the decoding loop: embedding gather, RMSNorm (wavefront reduction), the filter + unmask + EoTP update, loop control.
 #include "common.h"
 
 namespace l2pd {
@@ -135,27 +134,16 @@ void launch_compact(const int32_t* X_src, int32_t* X_dst, const int32_t* state_s
 }
 
 // ------------------------------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ float to_f(T v);
-template <>
-__device__ __forceinline__ float to_f<float>(float v) { return v; }
-template <>
-__device__ __forceinline__ float to_f<bf16>(bf16 v) { return __bfloat162float(v); }
-template <typename T>
-__device__ __forceinline__ T from_f(float v);
-template <>
-__device__ __forceinline__ float from_f<float>(float v) { return v; }
-template <>
-__device__ __forceinline__ bf16 from_f<bf16>(float v) { return __float2bfloat16(v); }
+__device__ __forceinline__ float to_f(bf16 v) { return __bfloat162float(v); }
+__device__ __forceinline__ bf16 from_f(float v) { return __float2bfloat16(v); }
 
-template <typename T>
-__global__ void k_embed(float* h, const T* emb, const int32_t* tokens, RowMap tokmap, int rows, int d, Gate g) {
+__global__ void k_embed(float* h, const bf16* emb, const int32_t* tokens, RowMap tokmap, int rows, int d, Gate g) {
   if (gate_skip(g)) return;
   int r = blockIdx.x;
   int tok = tokens[map_row(tokmap, r, g.ctl)];
-  const T* e = emb + (size_t)tok * d;
+  const bf16* e = emb + (size_t)tok * d;
   float* o = h + (size_t)r * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) o[i] = to_f<T>(e[i]);
+  for (int i = threadIdx.x; i < d; i += blockDim.x) o[i] = to_f(e[i]);
 }
 // bf16 rows in 16-byte pieces (rows and table aligned to them): a piece per thread and round.  512 rows of 4096:
 // 11.5 us with 2-byte loads, 5.8 with these; bound by the round trip tokens -> row.
@@ -173,14 +161,12 @@ __global__ void __launch_bounds__(256) k_embed_vec(float* h, const uint4* emb, c
     o[2 * i + 1] = make_float4(lo(v.z), hi(v.z), lo(v.w), hi(v.w));
   }
 }
-void launch_embed(float* h, const void* emb, int dtype, const int32_t* tokens, RowMap tokmap, int rows, int d,
+void launch_embed(float* h, const bf16* emb, const int32_t* tokens, RowMap tokmap, int rows, int d,
                   Gate g, hipStream_t s) {
-  if (dtype == L2PD_FP32)
-    hipLaunchKernelGGL(k_embed<float>, dim3(rows), dim3(256), 0, s, h, (const float*)emb, tokens, tokmap, rows, d, g);
-  else if (d % 8 == 0 && reinterpret_cast<uintptr_t>(emb) % 16 == 0)
+  if (d % 8 == 0 && reinterpret_cast<uintptr_t>(emb) % 16 == 0)
     hipLaunchKernelGGL(k_embed_vec, dim3(rows), dim3(256), 0, s, h, (const uint4*)emb, tokens, tokmap, d / 8, g);
   else
-    hipLaunchKernelGGL(k_embed<bf16>, dim3(rows), dim3(256), 0, s, h, (const bf16*)emb, tokens, tokmap, rows, d, g);
+    hipLaunchKernelGGL(k_embed, dim3(rows), dim3(256), 0, s, h, emb, tokens, tokmap, rows, d, g);
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -195,9 +181,8 @@ __device__ __forceinline__ float wave_sum(float v) {
 // workgroups walk the K ranges one after the other forms the same sum in registers and writes it as its only
 // partial: summing the partials before h is what makes the two bit-identical.)  Part z is at
 // parts + z * part_stride, laid out like h.
-template <typename T>
-__global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const T* gain,
-                          T* y, int rows, int d, float eps, int wb, float* h_out, Gate g) {
+__global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const bf16* gain,
+                          bf16* y, int rows, int d, float eps, int wb, float* h_out, Gate g) {
   if (gate_skip(g)) return;
   int lane = threadIdx.x & 63;
   int r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -219,7 +204,7 @@ __global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part
   }
   ss = wave_sum(ss);
   float inv = rsqrtf(ss / (float)d + eps);
-  T* o = y + (size_t)r * d;
+  bf16* o = y + (size_t)r * d;
   for (int i = lane; i < d; i += 64) {
     float v = wb ? xo[i] : x[i];
     if (n_parts > 0 && !wb) {
@@ -227,14 +212,14 @@ __global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part
       for (int z = 1; z < n_parts; ++z) ps += a0[z * part_stride + i];
       v += ps;
     }
-    o[i] = from_f<T>(v * inv * to_f<T>(gain[i]));
+    o[i] = from_f(v * inv * to_f(gain[i]));
   }
 }
 // Same, with the row held in registers: VPL float4 per lane, all loads of a row in flight at once,
 // one pass over memory.  Used when d is a multiple of 4 and d <= 1024 * VPL.
-template <typename T, int VPL>
+template <int VPL>
 __global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* parts, int n_parts, size_t part_stride,
-                                                    RowMap src, const T* gain, T* y, int rows, int d, float eps,
+                                                    RowMap src, const bf16* gain, bf16* y, int rows, int d, float eps,
                                                     int wb, float* h_out, Gate g) {
   if (gate_skip(g)) return;
   const int lane = threadIdx.x & 63;
@@ -275,21 +260,15 @@ __global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* part
   for (int k = 0; k < VPL; ++k) ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
   ss = wave_sum(ss);
   const float inv = rsqrtf(ss / (float)d + eps);
-  T* o = y + (size_t)r * d;
+  bf16* o = y + (size_t)r * d;
 #pragma unroll
   for (int k = 0; k < VPL; ++k) {
     const int i = lane + 64 * k;
     if (i < d4) {
-      const T* gp = gain + 4 * i;
-      if constexpr (sizeof(T) == 4) {
-        float4 gg = *reinterpret_cast<const float4*>(gp);
-        *reinterpret_cast<float4*>(o + 4 * i) =
-            make_float4(v[k].x * inv * gg.x, v[k].y * inv * gg.y, v[k].z * inv * gg.z, v[k].w * inv * gg.w);
-      } else {
-        T o4[4] = {from_f<T>(v[k].x * inv * to_f<T>(gp[0])), from_f<T>(v[k].y * inv * to_f<T>(gp[1])),
-                   from_f<T>(v[k].z * inv * to_f<T>(gp[2])), from_f<T>(v[k].w * inv * to_f<T>(gp[3]))};
-        *reinterpret_cast<uint2*>(o + 4 * i) = *reinterpret_cast<const uint2*>(o4);
-      }
+      const bf16* gp = gain + 4 * i;
+      bf16 o4[4] = {from_f(v[k].x * inv * to_f(gp[0])), from_f(v[k].y * inv * to_f(gp[1])),
+                    from_f(v[k].z * inv * to_f(gp[2])), from_f(v[k].w * inv * to_f(gp[3]))};
+      *reinterpret_cast<uint2*>(o + 4 * i) = *reinterpret_cast<const uint2*>(o4);
     }
   }
 }
@@ -301,9 +280,9 @@ __global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* part
 // (256 threads per row before).  The choice between this kernel and the one-wavefront-per-row kernels
 // depends on d only, never on the number of rows, so that a row's result does not depend on the batch it
 // is part of.
-template <typename T, int VPL, int NTH>
+template <int VPL, int NTH>
 __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* parts, int n_parts, size_t part_stride,
-                                                    RowMap src, const T* gain, T* y, int rows, int d, float eps,
+                                                    RowMap src, const bf16* gain, bf16* y, int rows, int d, float eps,
                                                     int wb, float* h_out, Gate g) {
   if (gate_skip(g)) return;
   __shared__ float s_part[NTH / 64];
@@ -372,55 +351,39 @@ __global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* part
     for (int w = 0; w < n / 2; ++w) tree[w] = tree[2 * w] + tree[2 * w + 1];
   ss = tree[0];
   const float inv = rsqrtf(ss / (float)d + eps);
-  T* o = y + (size_t)r * d;
+  bf16* o = y + (size_t)r * d;
 #pragma unroll
   for (int k = 0; k < VPL; ++k) {
     const int i = tid + NTH * k;
     if (i < d4) {
-      const T* gp = gain + 4 * i;
-      if constexpr (sizeof(T) == 4) {
-        float4 gg = *reinterpret_cast<const float4*>(gp);
-        *reinterpret_cast<float4*>(o + 4 * i) =
-            make_float4(v[k].x * inv * gg.x, v[k].y * inv * gg.y, v[k].z * inv * gg.z, v[k].w * inv * gg.w);
-      } else {
-        T o4[4] = {from_f<T>(v[k].x * inv * to_f<T>(gp[0])), from_f<T>(v[k].y * inv * to_f<T>(gp[1])),
-                   from_f<T>(v[k].z * inv * to_f<T>(gp[2])), from_f<T>(v[k].w * inv * to_f<T>(gp[3]))};
-        *reinterpret_cast<uint2*>(o + 4 * i) = *reinterpret_cast<const uint2*>(o4);
-      }
+      const bf16* gp = gain + 4 * i;
+      bf16 o4[4] = {from_f(v[k].x * inv * to_f(gp[0])), from_f(v[k].y * inv * to_f(gp[1])),
+                    from_f(v[k].z * inv * to_f(gp[2])), from_f(v[k].w * inv * to_f(gp[3]))};
+      *reinterpret_cast<uint2*>(o + 4 * i) = *reinterpret_cast<const uint2*>(o4);
     }
   }
 }
 
 constexpr int NORM_TX = 4;   // threads per row = 256 * NORM_TX
-template <typename T>
-static void launch_rmsnorm_t(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const T* gain,
-                             T* y, int rows, int d, float eps, bool write_back, float* h_out, Gate g, hipStream_t s) {
+void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const bf16* gain, bf16* y,
+                    int rows, int d, float eps, bool write_back, Gate g, hipStream_t s, float* h_out) {
+  if (!parts) n_parts = 0;
   const int wb = write_back ? 1 : 0;
   dim3 grid((rows + 3) / 4), block(256);
   if (rows <= 4096) { grid = dim3(rows); block = dim3(64); }   // few rows: one wavefront per workgroup fills more CUs
   if (d % 4 == 0 && d >= 2048 && d <= 4096)
-    hipLaunchKernelGGL((k_rmsnorm_row<T, 4 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
+    hipLaunchKernelGGL((k_rmsnorm_row<4 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else if (d % 4 == 0 && d > 4096 && d <= 8192)
-    hipLaunchKernelGGL((k_rmsnorm_row<T, 8 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
+    hipLaunchKernelGGL((k_rmsnorm_row<8 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else if (d % 4 == 0 && d <= 1024)
-    hipLaunchKernelGGL((k_rmsnorm_vec<T, 4>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
+    hipLaunchKernelGGL((k_rmsnorm_vec<4>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else if (d % 4 == 0 && d <= 4096)
-    hipLaunchKernelGGL((k_rmsnorm_vec<T, 16>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
+    hipLaunchKernelGGL((k_rmsnorm_vec<16>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else if (d % 4 == 0 && d <= 8192)
-    hipLaunchKernelGGL((k_rmsnorm_vec<T, 32>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
+    hipLaunchKernelGGL((k_rmsnorm_vec<32>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
   else
-    hipLaunchKernelGGL(k_rmsnorm<T>, grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
+    hipLaunchKernelGGL(k_rmsnorm, grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
 }
-void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const void* gain,
-                    int dtype, void* y, int rows, int d, float eps, bool write_back, Gate g, hipStream_t s,
-                    float* h_out) {
-  if (!parts) n_parts = 0;
-  if (dtype == L2PD_FP32)
-    launch_rmsnorm_t<float>(h, parts, n_parts, part_stride, src, (const float*)gain, (float*)y, rows, d, eps, write_back, h_out, g, s);
-  else
-    launch_rmsnorm_t<bf16>(h, parts, n_parts, part_stride, src, (const bf16*)gain, (bf16*)y, rows, d, eps, write_back, h_out, g, s);
-}
-
 // ------------------------------------------------------------------------------------------------
 // Finishing kernels of the few-row ("skinny") GEMM path: the GEMM leaves fp32 partial products per
 // K range; these sum them in ascending range order and apply what the wide path fuses into its
@@ -488,62 +451,6 @@ void launch_skinny_swiglu_finish(const float* parts, int n_parts, size_t part_st
   const int n = rows * F;
   hipLaunchKernelGGL(k_skinny_swiglu_finish, dim3((n + 255) / 256), dim3(256), 0, s, parts, n_parts, part_stride, rows,
                      F, act, g);
-}
-
-// ------------------------------------------------------------------------------------------------
-// Vocabulary reduction over materialised fp32 logits: per (row, column chunk) the running
-// (max, sum exp(x - max), argmax) triple of Eq. 3 / Eq. 4; the mask id is not a data token.
-__global__ void k_vocab_partials(float* logits, int rows, int V, int chunk, int mask_id, BiasArgs bias,
-                                 float* part_max, float* part_sum, int32_t* part_idx, int n_part, Gate g) {
-  if (gate_skip(g)) return;
-  __shared__ float s_m[256];
-  __shared__ int s_i[256];
-  __shared__ float s_s[256];
-  int p = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
-  float* row = logits + (size_t)r * V;
-  int c0 = p * chunk, c1 = min(V, c0 + chunk);
-  if (bias.value != 0.f && bias.token_id >= c0 && bias.token_id < c1 && tid == 0) {
-    int gb = g.ctl ? g.ctl[CTL_SEQ_GB + r / bias.block_len] : 0;
-    int genpos = gb * bias.block_len + (r % bias.block_len);
-    if (genpos >= bias.gen_pos_from) row[bias.token_id] += bias.value;
-  }
-  __syncthreads();
-  float m = -INFINITY;
-  int mi = 0x7fffffff;
-  for (int c = c0 + tid; c < c1; c += 256) {
-    float v = c == mask_id ? -INFINITY : row[c];
-    if (v > m || (v == m && c < mi)) { m = v; mi = c; }
-  }
-  s_m[tid] = m; s_i[tid] = mi;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) {
-      float m2 = s_m[tid + o]; int i2 = s_i[tid + o];
-      if (m2 > s_m[tid] || (m2 == s_m[tid] && i2 < s_i[tid])) { s_m[tid] = m2; s_i[tid] = i2; }
-    }
-    __syncthreads();
-  }
-  float M = s_m[0];
-  float sum = 0.f;
-  for (int c = c0 + tid; c < c1; c += 256) {
-    float v = c == mask_id ? -INFINITY : row[c];
-    sum += (M == -INFINITY) ? 0.f : expf(v - M);
-  }
-  s_s[tid] = sum;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) s_s[tid] += s_s[tid + o];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    size_t o = (size_t)r * n_part + p;
-    part_max[o] = M; part_sum[o] = s_s[0]; part_idx[o] = s_i[0];
-  }
-}
-void launch_vocab_partials(float* logits, int rows, int V, int chunk, int mask_id, BiasArgs bias, float* part_max,
-                           float* part_sum, int32_t* part_idx, int n_part, Gate g, hipStream_t s) {
-  hipLaunchKernelGGL(k_vocab_partials, dim3(n_part, rows), dim3(256), 0, s, logits, rows, V, chunk, mask_id, bias,
-                     part_max, part_sum, part_idx, n_part, g);
 }
 
 // ------------------------------------------------------------------------------------------------

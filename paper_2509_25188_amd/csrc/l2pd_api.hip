@@ -27,10 +27,10 @@ struct Carver {
 
 struct Layout {
   // offsets into the workspace
-  size_t rope, ctl, state, state2, perm, perm2, teff, X, X2, h, xn, q, attn, act, parts, attn_ws, attn_ws_bytes, kstore, vstore, tmp_k, tmp_v, gate_up,
-      xn_head, logits, part_max, part_sum, part_idx, conf, pred, total;
+  size_t rope, ctl, state, state2, perm, perm2, teff, X, X2, h, xn, q, attn, act, parts, attn_ws, attn_ws_bytes, kstore, vstore,
+      xn_head, part_max, part_sum, part_idx, conf, pred, total;
   size_t kv_layer_stride_k, kv_layer_stride_v;
-  int Tpad, n_part, lm_chunk;
+  int Tpad;
 };
 
 struct ProfileEv {
@@ -98,8 +98,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
   const size_t rows = (size_t)max_batch * max_seq;
   const size_t d = m.d_model, F = m.d_ffn, V = m.vocab;
   L.Tpad = (int)align_up(max_seq, 64);
-  L.lm_chunk = 1024;
-  L.n_part = m.dtype == L2PD_FP32 ? (int)((V + L.lm_chunk - 1) / L.lm_chunk) : lmhead_n_part((int)V);
+  const size_t n_part = m.dtype == L2PD_FP32 ? (V + 31) / 32 : lmhead_n_part((int)V);   // the most that a head pass may have
   const size_t head_rows = (size_t)max_batch * 256;   // block_len <= 256
   L.rope = c.take((size_t)L.Tpad * (m.head_dim / 2) * 8);
   L.ctl = c.take((size_t)(CTL_WORDS + 2 * max_batch) * 4);   // control words, per-sequence blocks, per-sequence done flags
@@ -111,7 +110,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
   L.X = c.take(rows * 4);
   L.X2 = c.take(rows * 4);
   L.h = c.take(rows * d * 4);
-  L.xn = c.take(rows * d * es);
+  if (m.dtype == L2PD_BF16) L.xn = c.take(rows * d * es);
   L.q = c.take(rows * d * es);
   L.attn = c.take(rows * d * es);
   L.act = c.take(rows * F * es);
@@ -121,12 +120,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
   L.kv_layer_stride_v = kv_one;
   L.kstore = c.take(kv_one * n_kv);
   L.vstore = c.take(kv_one * n_kv);
-  if (m.dtype == L2PD_FP32) {
-    L.tmp_k = c.take(rows * d * 4);
-    L.tmp_v = c.take(rows * d * 4);
-    L.gate_up = c.take(rows * F * 4 * 2);
-    L.logits = c.take(head_rows * V * 4);
-  } else {
+  if (m.dtype == L2PD_BF16) {
     // fp32 split-K partials: two [rows, d] buffers on the wide path; on the few-row path up to
     // kSkinnyRows rows of every K range of the widest stacked projection
     size_t skinny = 0;
@@ -151,10 +145,10 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
     L.attn_ws_bytes = attn_chunk_ws_bytes(m.n_heads, m.head_dim);
     L.attn_ws = c.take(L.attn_ws_bytes);
   }
-  L.xn_head = c.take(rows * d * es);   // l2pd_forward may ask for every row
-  L.part_max = c.take(head_rows * L.n_part * 4);
-  L.part_sum = c.take(head_rows * L.n_part * 4);
-  L.part_idx = c.take(head_rows * L.n_part * 4);
+  if (m.dtype == L2PD_BF16) L.xn_head = c.take(rows * d * es);   // l2pd_forward may ask for every row
+  L.part_max = c.take(head_rows * n_part * 4);
+  L.part_sum = c.take(head_rows * n_part * 4);
+  L.part_idx = c.take(head_rows * n_part * 4);
   L.conf = c.take(head_rows * 4);
   L.pred = c.take(head_rows * 4);
   L.total = c.off;
@@ -227,7 +221,8 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
   const int rows = p.B * p.Tq, d = m.d_model, F = m.d_ffn, H = m.n_heads, Dh = m.head_dim;
   const RowMap ident = {rows, 0, 0, 0};
   float* h = c->at<float>(L.h);
-  launch_embed(h, c->tok_emb, m.dtype, p.tokens, RowMap{p.Tq, p.Tfull, p.pos0, p.pos_per_gb}, rows, d, g, s);
+  const RowMap token_map = {p.Tq, p.Tfull, p.pos0, p.pos_per_gb};
+  if (m.dtype == L2PD_BF16) launch_embed(h, (const bf16*)c->tok_emb, p.tokens, token_map, rows, d, g, s);
   const int* seq_gb = p.pos_per_gb ? c->at<int>(L.ctl) + CTL_SEQ_GB : nullptr;
   const size_t kv_seq_off = (size_t)p.kv_seq * L.Tpad * d * (m.dtype == L2PD_FP32 ? 4 : 2);
   const float2* rope = c->at<float2>(L.rope);
@@ -239,34 +234,37 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
     const size_t kvo_k = p.per_layer_kv ? L.kv_layer_stride_k * l : 0;
     const size_t kvo_v = p.per_layer_kv ? L.kv_layer_stride_v * l : 0;
     if (m.dtype == L2PD_FP32) {
-      float* xn = c->at<float>(L.xn);
       float* q = c->at<float>(L.q);
       float* ks = reinterpret_cast<float*>(c->ws + L.kstore + kvo_k + kv_seq_off);
       float* vs = reinterpret_cast<float*>(c->ws + L.vstore + kvo_v + kv_seq_off);
-      { Timed t(c, L2PD_K_NORM, s);
-        launch_rmsnorm(h, nullptr, 0, 0, ident, c->attn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
+      F32Product base = {};
+      base.A = h; base.rows = ident; base.M = rows; base.K = d; base.eps = m.rms_eps; base.gate = g;
       { Timed t(c, L2PD_K_GEMM_QKV, s);
-        const float* const w3[3] = {(const float*)c->wq[l], (const float*)c->wk[l], (const float*)c->wv[l]};
-        float* const o3[3] = {q, c->at<float>(L.tmp_k), c->at<float>(L.tmp_v)};
-        launch_gemm_f32(xn, w3, o3, 3, rows, d, d, 0, g, s);
-        launch_rope_store_f32(q, c->at<float>(L.tmp_k), c->at<float>(L.tmp_v), ks, vs, p.B, p.Tq, p.pos0, L.Tpad, H,
-                              Dh, rope, seq_gb, p.pos_per_gb, g, s); }
+        F32Product a = base;
+        if (l == 0) {           // the embedding is read here, and left in h for the residual sums
+          a.A = (const float*)c->tok_emb; a.rows = token_map; a.tokens = p.tokens; a.h_out = h;
+        }
+        a.gain = (const float*)c->attn_g[l];
+        a.W[0] = (const float*)c->wq[l]; a.W[1] = (const float*)c->wk[l]; a.W[2] = (const float*)c->wv[l];
+        a.N = 3 * H * (Dh / 2); a.C = q; a.kstore = ks; a.vstore = vs; a.rope = rope;
+        a.Tq = p.Tq; a.pos0 = p.pos0; a.Tmax = L.Tpad; a.H = H; a.Dh = Dh; a.seq_gb = seq_gb; a.pos_per_gb = p.pos_per_gb;
+        launch_product_f32(a, F32_QKV, s); }
       if (p.kv_only_last && l + 1 == m.n_layers) break;
       { Timed t(c, L2PD_K_ATTN, s);
         launch_attn_f32(q, ks, vs, c->at<float>(L.attn), p.B, p.Tq, p.Tk, L.Tpad, H, Dh, p.tk_dev, g, s); }
       { Timed t(c, L2PD_K_GEMM_O, s);
-        launch_gemm_f32(c->at<float>(L.attn), (const float*)c->wo[l], h, rows, d, d, 1, g, s); }
-      { Timed t(c, L2PD_K_NORM, s);
-        launch_rmsnorm(h, nullptr, 0, 0, ident, c->ffn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
-      float* gt = c->at<float>(L.gate_up);
-      float* up = gt + (size_t)rows * F;
+        F32Product a = base;
+        a.A = c->at<float>(L.attn); a.W[0] = (const float*)c->wo[l]; a.N = d; a.C = h; a.accumulate = 1;
+        launch_product_f32(a, F32_PLAIN, s); }
       { Timed t(c, L2PD_K_GEMM_GATEUP, s);
-        const float* const w2[2] = {(const float*)c->wg[l], (const float*)c->wu[l]};
-        float* const o2[2] = {gt, up};
-        launch_gemm_f32(xn, w2, o2, 2, rows, F, d, 0, g, s);
-        launch_swiglu_f32(gt, up, c->at<float>(L.act), (size_t)rows * F, g, s); }
+        F32Product a = base;
+        a.gain = (const float*)c->ffn_g[l]; a.W[0] = (const float*)c->wg[l]; a.W[1] = (const float*)c->wu[l];
+        a.N = F; a.C = c->at<float>(L.act);
+        launch_product_f32(a, F32_SWIGLU, s); }
       { Timed t(c, L2PD_K_GEMM_DOWN, s);
-        launch_gemm_f32(c->at<float>(L.act), (const float*)c->wd[l], h, rows, d, F, 1, g, s); }
+        F32Product a = base;
+        a.A = c->at<float>(L.act); a.W[0] = (const float*)c->wd[l]; a.N = d; a.K = F; a.C = h; a.accumulate = 1;
+        launch_product_f32(a, F32_PLAIN, s); }
     } else {
       bf16* xn = c->at<bf16>(L.xn);
       bf16* q = c->at<bf16>(L.q);
@@ -275,7 +273,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       float* parts = c->at<float>(L.parts);
       const bool skinny = rows <= kSkinnyRows;
       { Timed t(c, L2PD_K_NORM, s);
-        launch_rmsnorm(h, pending ? parts : nullptr, pend_splits, pend_stride, ident, c->attn_g[l], m.dtype, xn, rows,
+        launch_rmsnorm(h, pending ? parts : nullptr, pend_splits, pend_stride, ident, (const bf16*)c->attn_g[l], xn, rows,
                        d, m.rms_eps, true, g, s); }
       pending = false;
       QkvEpilogue e = {q, ks, vts, rope, p.Tq, p.pos0, L.Tpad, H, Dh, d, seq_gb, p.pos_per_gb};
@@ -317,7 +315,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
           S = project(ao, (const bf16*)c->wo[l], d); }
         float* h_few = c->at<float>(L.q);
         { Timed t(c, L2PD_K_NORM, s);
-          launch_rmsnorm(h, parts, S, stride, w, c->ffn_g[l], m.dtype, xn, few, d, m.rms_eps, true, g, s, h_few); }
+          launch_rmsnorm(h, parts, S, stride, w, (const bf16*)c->ffn_g[l], xn, few, d, m.rms_eps, true, g, s, h_few); }
         bf16* act = c->at<bf16>(L.act);
         { Timed t(c, L2PD_K_GEMM_GATEUP, s);
           if (swiglu_few_rows_fused(few, F))
@@ -350,7 +348,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
         else
           launch_gemm_partial_bf16(ao, (const bf16*)c->wo[l], add_o ? h : parts, stride_d, rows, d, d, rows, add_o, g, s); }
       { Timed t(c, L2PD_K_NORM, s);
-        launch_rmsnorm(h, add_o ? nullptr : parts, so, stride_d, ident, c->ffn_g[l], m.dtype, xn, rows, d, m.rms_eps, true, g, s); }
+        launch_rmsnorm(h, add_o ? nullptr : parts, so, stride_d, ident, (const bf16*)c->ffn_g[l], xn, rows, d, m.rms_eps, true, g, s); }
       bf16* act = c->at<bf16>(L.act);
       { Timed t(c, L2PD_K_GEMM_GATEUP, s);
         if (skinny && !swiglu_few_rows_fused(rows, F)) {
@@ -380,6 +378,14 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
   c->pend_stride = pend_stride;
 }
 
+// Parts of the vocabulary reduction over `rows` head rows.
+int head_parts(const l2pd_ctx* c, int rows) {
+  const int V = c->m.vocab;
+  if (c->m.dtype == L2PD_BF16) return lmhead_n_part(V);
+  const int cols = f32_lmhead_cols(rows, V);
+  return (V + cols - 1) / cols;
+}
+
 // Final RMSNorm of the selected rows + LM head.  Produces the vocabulary partials (and optionally
 // the fp32 logits) of `n_rows_per_seq` rows per sequence, taken from h through `src`.
 void run_head(l2pd_ctx* c, int B, int n_rows_per_seq, RowMap src, float* logits_out, bool want_parts,
@@ -389,16 +395,22 @@ void run_head(l2pd_ctx* c, int B, int n_rows_per_seq, RowMap src, float* logits_
   const int d = m.d_model, V = m.vocab, hr = B * n_rows_per_seq;
   float* h = c->at<float>(c->tail ? L.q : L.h);
   if (c->tail) src = RowMap{hr, 0, 0, 0};
+  LmHeadEpilogue e = {};
+  e.logits = logits_out;
+  if (want_parts) {
+    e.part_max = c->at<float>(L.part_max);
+    e.part_sum = c->at<float>(L.part_sum);
+    e.part_idx = c->at<int32_t>(L.part_idx);
+  }
+  e.n_part = head_parts(c, hr);
+  e.mask_id = m.mask_id;
+  e.bias = bias;
   if (m.dtype == L2PD_FP32) {
-    float* xh = c->at<float>(L.xn_head);
-    { Timed t(c, L2PD_K_NORM, s);
-      launch_rmsnorm(h, nullptr, 0, 0, src, c->final_g, m.dtype, xh, hr, d, m.rms_eps, false, g, s); }
-    float* lg = logits_out ? logits_out : c->at<float>(L.logits);
     Timed t(c, L2PD_K_LMHEAD, s);
-    launch_gemm_f32(xh, (const float*)c->lm_head, lg, hr, V, d, 0, g, s);
-    if (want_parts)
-      launch_vocab_partials(lg, hr, V, L.lm_chunk, m.mask_id, bias, c->at<float>(L.part_max),
-                            c->at<float>(L.part_sum), c->at<int32_t>(L.part_idx), L.n_part, g, s);
+    F32Product a = {};
+    a.A = h; a.rows = src; a.gain = (const float*)c->final_g; a.eps = m.rms_eps; a.gate = g;
+    a.W[0] = (const float*)c->lm_head; a.M = hr; a.N = V; a.K = d; a.lm = e;
+    launch_product_f32(a, F32_LMHEAD, s);
   } else {
     // the last down projection's split-K partials are summed onto the selected rows in fixed order;
     // h itself is left as it is (nothing reads it afterwards, and with shortened sequences two head
@@ -406,18 +418,8 @@ void run_head(l2pd_ctx* c, int B, int n_rows_per_seq, RowMap src, float* logits_
     bf16* xh = c->at<bf16>(L.xn_head);
     const int sd = c->pend_splits;
     { Timed t(c, L2PD_K_NORM, s);
-      launch_rmsnorm(h, sd > 0 ? c->at<float>(L.parts) : nullptr, sd, c->pend_stride, src, c->final_g, m.dtype, xh, hr,
+      launch_rmsnorm(h, sd > 0 ? c->at<float>(L.parts) : nullptr, sd, c->pend_stride, src, (const bf16*)c->final_g, xh, hr,
                      d, m.rms_eps, false, g, s); }
-    LmHeadEpilogue e = {};
-    e.logits = logits_out;
-    if (want_parts) {
-      e.part_max = c->at<float>(L.part_max);
-      e.part_sum = c->at<float>(L.part_sum);
-      e.part_idx = c->at<int32_t>(L.part_idx);
-    }
-    e.n_part = L.n_part;
-    e.mask_id = m.mask_id;
-    e.bias = bias;
     Timed t(c, L2PD_K_LMHEAD, s);
     if (hr <= kSkinnyRows) launch_gemm_few_rows_lmhead_bf16(xh, (const bf16*)c->lm_head, hr, V, d, e, g, s);
     else launch_gemm_lmhead_bf16(xh, (const bf16*)c->lm_head, hr, V, d, e, g, s);
@@ -536,7 +538,7 @@ void run_step(l2pd_ctx* c, int32_t* X, int B, int P, const l2pd_decode_cfg* cfg,
   u.X = X; u.state = state; u.B = B; u.P = P; u.T = T; u.s = sl; u.n_blocks = nb;
   u.mask_id = c->m.mask_id; u.eos_id = c->m.eos_id; u.eotp = cfg->eotp;
   u.part_max = c->at<float>(L.part_max); u.part_sum = c->at<float>(L.part_sum);
-  u.part_idx = c->at<int32_t>(L.part_idx); u.n_part = L.n_part;
+  u.part_idx = c->at<int32_t>(L.part_idx); u.n_part = head_parts(c, B * sl);
   if (f) {
     for (int k = 0; k < f->n_layers; ++k) { u.fw[k] = f->w_dev[k]; u.fb[k] = f->b_dev[k]; }
     u.n_layers = f->n_layers;
