@@ -44,7 +44,6 @@ __global__ void __launch_bounds__(NQ * NSPL * 64, 2) k_attn_bf16(const bf16* __r
                                                                  int B, int Tq, int Tk_all, int Tpad, int H, int n_chunks,
                                                                  float* __restrict__ chunk_out,
                                                                  const int* __restrict__ tk_dev, QueryRows sel, Gate g) {
-  if (gate_skip(g)) return;
   constexpr int KT = 64;                       // keys per LDS tile
   constexpr int K_ROW = DH * 2;                // bytes per key row
   constexpr int K_BYTES = KT * K_ROW;
@@ -162,9 +161,14 @@ __global__ void __launch_bounds__(NQ * NSPL * 64, 2) k_attn_bf16(const bf16* __r
   float mb = -INFINITY, lb = 0.f;
   int left = per;                              // tiles of the range at hand still to come
 
+  const int2 gate = gate_words(g);             // looked at when the first loads are on their way
 #pragma unroll
   for (int t = 0; t < NST - 1; ++t)
     if (t < my_count) load_tile(t);
+  if (gate_closed(g, gate)) {
+    wait_vmcnt<0>();                           // LDS stays this workgroup's until its loads have landed
+    return;
+  }
   for (int t = 0; t < NSER * per; ++t) {
     // tile t has landed (the younger ones, if all of them were sent off, may still be on their way) ...
     if (t + NST - 2 < my_count) wait_vmcnt<(NST - 2) * (KL + VL)>();

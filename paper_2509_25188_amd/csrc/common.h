@@ -21,15 +21,19 @@ enum { CTL_GB = 0, CTL_ALL_DONE = 1, CTL_ACTIVE = 2, CTL_TMAX = 3, CTL_WORDS = 8
 // Every kernel of a step is gated: once decoding has stopped (or, with the prefix cache, once the
 // block the host enqueued it for is finished) it returns at once, so steps that the host enqueued
 // ahead of the device's progress cost a launch and nothing else.
+// A kernel asks for the two words first, sends off its first loads, and only then looks at them: the round trip to the
+// control block (0.2 us, in each of the 60 to 230 kernels of a step) is not waited for.
 struct Gate {
-  const int* ctl;   // nullptr: never skip
-  int expect_gb;    // >= 0: skip unless ctl[CTL_GB] == expect_gb
+  const int* ctl;     // the control block, for kernels that read more of it; nullptr: there is none
+  int expect_gb;      // >= 0: skip unless the active block is this one
+  const int2* words;  // never null: (active block, all done) of the control block, or zeros
 };
-__device__ __forceinline__ bool gate_skip(const Gate& g) {
-  if (!g.ctl) return false;
-  if (g.ctl[CTL_ALL_DONE]) return true;
-  return g.expect_gb >= 0 && g.ctl[CTL_GB] != g.expect_gb;
+static_assert(CTL_GB == 0 && CTL_ALL_DONE == 1, "the gate's two words");
+__device__ __forceinline__ int2 gate_words(const Gate& g) { return *g.words; }
+__device__ __forceinline__ bool gate_closed(const Gate& g, int2 w) {
+  return (w.y != 0) | ((g.expect_gb >= 0) & (w.x != g.expect_gb));
 }
+__device__ __forceinline__ bool gate_skip(const Gate& g) { return gate_closed(g, gate_words(g)); }
 
 // Maps a compact row index r (b * rows_per_seq + j) to a row of a [B, seq_stride] array:
 //   b * seq_stride + off_base + gb_b * off_per_gb + j,  gb_b = sequence b's active block from the control block.
@@ -93,6 +97,9 @@ struct UpdateArgs {
   const float* part_sum;
   const int32_t* part_idx;
   int n_part;
+  // the filter as it goes to LDS, filled in by launch_update: layer k's weights (nw) at `at`, its biases (nb) behind them;
+  // layers that there are not stand for one number of the first.  total 0: it does not fit, or there is none
+  struct Staged { const float *w[kFilterMaxLayers], *b[kFilterMaxLayers]; int nw[kFilterMaxLayers], nb[kFilterMaxLayers], at[kFilterMaxLayers], total; } staged;
   // filter: n_layers layers of widths s -> hidden -> ... -> hidden -> s (layer k: fw[k] [out, in], fb[k] [out])
   const float* fw[kFilterMaxLayers];
   const float* fb[kFilterMaxLayers];
@@ -109,8 +116,9 @@ struct UpdateArgs {
   float* egp_conf;            // [B, gen_len, s]: row = step index of the sequence
   float* egp_label;
   int gen_len;
+  int next_ctl, ragged;       // B == 1: also leave the control block as launch_prepare would for the state afterwards
 };
-void launch_update(const UpdateArgs& a, Gate g, hipStream_t s);
+void launch_update(UpdateArgs a, Gate g, hipStream_t s);
 void launch_finalize(const int32_t* X, const int32_t* state, const int* teff, const int32_t* perm, int B, int P,
                      int G, int s_len, int mask_id, int32_t* tokens_out, int32_t* steps_out, int32_t* dlen_out,
                      hipStream_t s);

@@ -328,7 +328,6 @@ __global__ void __launch_bounds__(512) k_gemm_turns(GemmArgs a) {
   static_assert(DEPTH >= 2 && (DEPTH - 1) * (LA + LB) < 64, "ring depth");
   static_assert(RA * A_BYTES + RB * B_BYTES <= 163840, "LDS");
   static_assert(EPI != EPI_LMHEAD || 3 * WN * BM * 4 <= RA * A_BYTES, "reduction scratch");
-  if (gate_skip(a.gate)) return;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [RA][A tile] [RB][B tile]
   unsigned char* const smemB = smem + RA * A_BYTES;
 
@@ -428,10 +427,15 @@ __global__ void __launch_bounds__(512) k_gemm_turns(GemmArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   };
 
+  const int2 gate = gate_words(a.gate);    // looked at when the first loads are on their way
   const int lead = min(DEPTH, nk);
   for (int k = 0; k < lead; ++k) {
     load_a(k, k);
     load_b(k, k);
+  }
+  if (gate_closed(a.gate, gate)) {
+    wait_vmcnt<0>();                       // LDS stays this workgroup's until its loads have landed
+    return;
   }
   if (nk >= DEPTH) wait_vmcnt<(DEPTH - 1) * (LA + LB)>();   // stage 0 has landed
   else wait_vmcnt<0>();

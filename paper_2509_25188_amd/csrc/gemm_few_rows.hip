@@ -51,7 +51,6 @@ __global__ void __launch_bounds__(WM* WN * 64) k_gemm_few_rows(FewArgs a) {
   static_assert(LPS * NW * RPD == LROWS, "tile/threads mismatch");
   static_assert(NS >= 3 && (NS - 2) * LPS < 64, "ring depth: at least 3 stages, vmcnt is 6 bits");
 
-  if (gate_skip(a.gate)) return;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // [stage][A: BM rows | B: BN rows][BK bf16]
   constexpr int STAGE_BYTES = LROWS * BK * 2;
@@ -185,6 +184,7 @@ __global__ void __launch_bounds__(WM* WN * 64) k_gemm_few_rows(FewArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   };
 
+  const int2 gate = gate_words(a.gate);    // looked at when the first loads are on their way
   // Prologue: stages 0 .. NS-2.  The wait counts loads, so nothing may move across it.
 #pragma unroll
   for (int st = 0; st < NS - 1; ++st)
@@ -193,6 +193,10 @@ __global__ void __launch_bounds__(WM* WN * 64) k_gemm_few_rows(FewArgs a) {
       for (int part = 0; part < KS; ++part) issue_part(st, part);
     }
   __builtin_amdgcn_sched_barrier(0);
+  if (gate_closed(a.gate, gate)) {
+    wait_vmcnt<0>();                       // LDS stays this workgroup's until its loads have landed
+    return;
+  }
   if (nk >= NS - 1) wait_vmcnt<(NS - 2) * LPS>();   // stage 0 has landed
   else wait_vmcnt<0>();
   __builtin_amdgcn_sched_barrier(0);

@@ -1,5 +1,5 @@
 // Small kernels of the decoding loop: embedding gather, RMSNorm (wavefront reduction), the filter + unmask + EoTP update, loop control.
-#include "common.h"
+#include "gemm_common.h"
 
 namespace l2pd {
 
@@ -215,175 +215,149 @@ __global__ void k_rmsnorm(float* h, const float* parts, int n_parts, size_t part
     o[i] = from_f(v * inv * to_f(gain[i]));
   }
 }
-// Same, with the row held in registers: VPL float4 per lane, all loads of a row in flight at once,
-// one pass over memory.  Used when d is a multiple of 4 and d <= 1024 * VPL.
-template <int VPL>
-__global__ void __launch_bounds__(256) k_rmsnorm_vec(float* h, const float* parts, int n_parts, size_t part_stride,
-                                                    RowMap src, const bf16* gain, bf16* y, int rows, int d, float eps,
-                                                    int wb, float* h_out, Gate g) {
-  if (gate_skip(g)) return;
-  const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  const size_t srow = (size_t)map_row(src, r, g.ctl);
-  const int d4 = d >> 2;
-  const float4* x = reinterpret_cast<const float4*>(h + srow * d);
-  float4* xo = reinterpret_cast<float4*>(h_out ? h_out + (size_t)r * d : h + srow * d);
-  const size_t prow = h_out ? (size_t)r : srow;
-  float4 v[VPL];
-#pragma unroll
-  for (int k = 0; k < VPL; ++k) {
-    const int i = lane + 64 * k;
-    v[k] = i < d4 ? x[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  if (n_parts > 0) {
-    float4 ps[VPL];
-    for (int z = 0; z < n_parts; ++z) {
-      const float4* az = reinterpret_cast<const float4*>(parts + z * part_stride + prow * d);
-#pragma unroll
-      for (int k = 0; k < VPL; ++k) {
-        const int i = lane + 64 * k;
-        float4 t = i < d4 ? az[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-        if (z == 0) ps[k] = t;
-        else { ps[k].x += t.x; ps[k].y += t.y; ps[k].z += t.z; ps[k].w += t.w; }
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < VPL; ++k) {
-      const int i = lane + 64 * k;
-      v[k].x += ps[k].x; v[k].y += ps[k].y; v[k].z += ps[k].z; v[k].w += ps[k].w;
-      if (wb && i < d4) xo[i] = v[k];
-    }
-  }
-  float ss = 0.f;
-#pragma unroll
-  for (int k = 0; k < VPL; ++k) ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
-  ss = wave_sum(ss);
-  const float inv = rsqrtf(ss / (float)d + eps);
-  bf16* o = y + (size_t)r * d;
-#pragma unroll
-  for (int k = 0; k < VPL; ++k) {
-    const int i = lane + 64 * k;
-    if (i < d4) {
-      const bf16* gp = gain + 4 * i;
-      bf16 o4[4] = {from_f(v[k].x * inv * to_f(gp[0])), from_f(v[k].y * inv * to_f(gp[1])),
-                    from_f(v[k].z * inv * to_f(gp[2])), from_f(v[k].w * inv * to_f(gp[3]))};
-      *reinterpret_cast<uint2*>(o + 4 * i) = *reinterpret_cast<const uint2*>(o4);
-    }
-  }
+// Reductions over the 64 lanes: inside rows of 16 by DPP, then the four rows through scalar registers.  Every lane gets the result.
+template <typename T, typename F>
+__device__ __forceinline__ T wave_reduce(T x, F f) {
+  static_assert(sizeof(T) == 4, "one register");
+  auto ror = [&](auto c) { return __builtin_bit_cast(T, dpp<kDppRor + decltype(c)::value>(__builtin_bit_cast(unsigned, x))); };
+  x = f(x, ror(std::integral_constant<int, 8>{}));
+  x = f(x, ror(std::integral_constant<int, 4>{}));
+  x = f(x, ror(std::integral_constant<int, 2>{}));
+  x = f(x, ror(std::integral_constant<int, 1>{}));
+  auto row = [&](int lane) { return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane)); };
+  return f(f(row(0), row(16)), f(row(32), row(48)));
 }
-
-// Wide rows (d >= 2048): one row per workgroup of NTH threads (1024: a float4 per thread and stream at the 8B
-// width), the row's sum of squares combined across the wavefronts through LDS in a fixed pairwise tree.
-// Many wavefronts with few loads each hide the latency of the partials, which the preceding projection has
-// just written: 7.2 -> 5.6 us at 32 rows folding eight partials, 11.7 -> 11.2 us at 512 rows folding four
-// (256 threads per row before).  The choice between this kernel and the one-wavefront-per-row kernels
-// depends on d only, never on the number of rows, so that a row's result does not depend on the batch it
-// is part of.
-template <int VPL, int NTH>
-__global__ void __launch_bounds__(NTH) k_rmsnorm_row(float* h, const float* parts, int n_parts, size_t part_stride,
-                                                    RowMap src, const bf16* gain, bf16* y, int rows, int d, float eps,
-                                                    int wb, float* h_out, Gate g) {
-  if (gate_skip(g)) return;
-  __shared__ float s_part[NTH / 64];
-  const int tid = threadIdx.x;
-  const int r = blockIdx.x;
-  const size_t srow = (size_t)map_row(src, r, g.ctl);
-  const int d4 = d >> 2;
-  const float4* x = reinterpret_cast<const float4*>(h + srow * d);
-  float4* xo = reinterpret_cast<float4*>(h_out ? h_out + (size_t)r * d : h + srow * d);
-  const size_t prow = h_out ? (size_t)r : srow;
-  float4 v[VPL];
+// Same, with the row held in registers: VPL float4 per thread and stream, one pass over memory, the wavefronts' sums of
+// squares combined through LDS in a fixed pairwise tree.  NP partials, summed in ascending order before they are added to h.
+//   Bound by the chain arguments - loads - sums - stores at a few hundred rows, by memory at thousands: so the arguments
+// come in one piece, nothing is computed to find an address that is known, all loads (up to 16 partials) are sent off together
+// and unconditionally (threads past the row read its end), and the gate is looked at behind them.
+//   us, this / with a branch around every load and partials in guarded groups: 32 rows of 4096 folding eight partials
+// 4.8 / 5.2; 512 rows folding four 10.0 / 10.6; 221 rows of 1024 folding two or four 4.2 / 4.9.
+//   Threads per row: a wavefront up to 1024 wide, 1024 threads beyond.  That depends on d only, never on the number of rows,
+// so that a row's result does not depend on the batch it is part of.
+struct NormArgs {
+  float* h;
+  const float* parts;
+  size_t part_stride;
+  const bf16* gain;
+  bf16* y;
+  float* h_out;
+  RowMap src;
+  int d, mapped, write_back;
+  float eps;
+  Gate gate;
+};
+template <int VPL, int NTH, int NP>
+__global__ void __launch_bounds__(NTH) k_rmsnorm_row(NormArgs a) {
+  constexpr int NW = NTH / 64, GRP = NP < 16 / VPL ? NP : 16 / VPL;   // partials in flight together
+  const int tid = threadIdx.x, r = blockIdx.x, d4 = a.d >> 2;
+  const int2 gate = gate_words(a.gate);
+  const int srow = a.mapped ? map_row(a.src, r, a.gate.ctl) : r;
+  const size_t at = (size_t)srow * d4, at_out = a.h_out ? (size_t)r * d4 : at;
+  const float4* x = reinterpret_cast<const float4*>(a.h) + at;
+  int i[VPL];
+  bool in[VPL];
 #pragma unroll
   for (int k = 0; k < VPL; ++k) {
-    const int i = tid + NTH * k;
-    v[k] = i < d4 ? x[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    in[k] = tid + NTH * k < d4;
+    i[k] = min(tid + NTH * k, d4 - 1);
   }
-  // partials four at a time (the few-row path folds eight or more): the loads of a group are in
-  // flight together, the adds stay in ascending order
-  constexpr int GRP = 4;
-  float4 ps[VPL];
+  float4 v[VPL], ps[VPL];
+  uint2 gain[VPL];
 #pragma unroll
-  for (int k = 0; k < VPL; ++k) ps[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int z0 = 0; z0 < n_parts; z0 += GRP) {
-    float4 t[GRP][VPL];
+  for (int k = 0; k < VPL; ++k) v[k] = x[i[k]];
+#pragma unroll
+  for (int z0 = 0; z0 < NP; z0 += GRP) {
+    float4 p[GRP > 0 ? GRP : 1][VPL];
 #pragma unroll
     for (int z = 0; z < GRP; ++z) {
-      const bool have = z0 + z < n_parts;
-      const float4* a = reinterpret_cast<const float4*>(parts + (have ? z0 + z : z0) * part_stride + prow * d);
+      const float4* pz = reinterpret_cast<const float4*>(a.parts + (z0 + z) * a.part_stride) + at_out;
 #pragma unroll
-      for (int k = 0; k < VPL; ++k) {
-        const int i = tid + NTH * k;
-        t[z][k] = (have && i < d4) ? a[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+      for (int k = 0; k < VPL; ++k) p[z][k] = pz[i[k]];
+    }
+    if (z0 == 0) {
+#pragma unroll
+      for (int k = 0; k < VPL; ++k) gain[k] = reinterpret_cast<const uint2*>(a.gain)[i[k]];
+      if (gate_closed(a.gate, gate)) return;
     }
 #pragma unroll
     for (int z = 0; z < GRP; ++z)
-      if (z0 + z < n_parts) {
 #pragma unroll
-        for (int k = 0; k < VPL; ++k) {
-          if (z0 + z == 0) ps[k] = t[z][k];
-          else { ps[k].x += t[z][k].x; ps[k].y += t[z][k].y; ps[k].z += t[z][k].z; ps[k].w += t[z][k].w; }
-        }
+      for (int k = 0; k < VPL; ++k) {
+        if (z0 + z == 0) ps[k] = p[z][k];
+        else { ps[k].x += p[z][k].x; ps[k].y += p[z][k].y; ps[k].z += p[z][k].z; ps[k].w += p[z][k].w; }
       }
   }
-  if (n_parts > 0) {   // the partials' sum, then the residual: h + (p0 + p1 + ...)
+  if constexpr (NP == 0) {
 #pragma unroll
-    for (int k = 0; k < VPL; ++k) { v[k].x += ps[k].x; v[k].y += ps[k].y; v[k].z += ps[k].z; v[k].w += ps[k].w; }
+    for (int k = 0; k < VPL; ++k) gain[k] = reinterpret_cast<const uint2*>(a.gain)[i[k]];
+    if (gate_closed(a.gate, gate)) return;
+  } else {             // the partials' sum, then the residual: h + (p0 + p1 + ...)
+    float4* xo = reinterpret_cast<float4*>(a.h_out ? a.h_out : a.h) + at_out;
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) {
+      v[k].x += ps[k].x; v[k].y += ps[k].y; v[k].z += ps[k].z; v[k].w += ps[k].w;
+      if (a.write_back && in[k]) xo[i[k]] = v[k];
+    }
   }
   float ss = 0.f;
 #pragma unroll
-  for (int k = 0; k < VPL; ++k) {
-    const int i = tid + NTH * k;
-    if (wb && n_parts > 0 && i < d4) xo[i] = v[k];
-    ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
+  for (int k = 0; k < VPL; ++k)
+    ss += in[k] ? v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w : 0.f;
+  ss = wave_reduce(ss, [](float x, float y) { return x + y; });
+  if constexpr (NW > 1) {
+    __shared__ __attribute__((aligned(16))) float s_part[NW];
+    if ((tid & 63) == 0) s_part[tid >> 6] = ss;
+    __syncthreads();
+    float tree[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) tree[w] = s_part[w];
+#pragma unroll
+    for (int n = NW; n > 1; n >>= 1)
+#pragma unroll
+      for (int w = 0; w < n / 2; ++w) tree[w] = tree[2 * w] + tree[2 * w + 1];
+    ss = tree[0];
   }
-  ss = wave_sum(ss);
-  if ((tid & 63) == 0) s_part[tid >> 6] = ss;
-  __syncthreads();
-  // the wavefronts' sums in a fixed pairwise tree
-  float tree[NTH / 64];
+  const float inv = rsqrtf(ss / (float)a.d + a.eps);
+  uint2* o = reinterpret_cast<uint2*>(a.y) + (size_t)r * d4;
+  auto lo = [](unsigned w) { return __uint_as_float(w << 16); };
+  auto hi = [](unsigned w) { return __uint_as_float(w & 0xffff0000u); };
 #pragma unroll
-  for (int w = 0; w < NTH / 64; ++w) tree[w] = s_part[w];
-#pragma unroll
-  for (int n = NTH / 64; n > 1; n >>= 1)
-#pragma unroll
-    for (int w = 0; w < n / 2; ++w) tree[w] = tree[2 * w] + tree[2 * w + 1];
-  ss = tree[0];
-  const float inv = rsqrtf(ss / (float)d + eps);
-  bf16* o = y + (size_t)r * d;
-#pragma unroll
-  for (int k = 0; k < VPL; ++k) {
-    const int i = tid + NTH * k;
-    if (i < d4) {
-      const bf16* gp = gain + 4 * i;
-      bf16 o4[4] = {from_f(v[k].x * inv * to_f(gp[0])), from_f(v[k].y * inv * to_f(gp[1])),
-                    from_f(v[k].z * inv * to_f(gp[2])), from_f(v[k].w * inv * to_f(gp[3]))};
-      *reinterpret_cast<uint2*>(o + 4 * i) = *reinterpret_cast<const uint2*>(o4);
-    }
-  }
+  for (int k = 0; k < VPL; ++k)
+    if (in[k])
+      o[i[k]] = make_uint2(pack_bf16(v[k].x * inv * lo(gain[k].x), v[k].y * inv * hi(gain[k].x)),
+                           pack_bf16(v[k].z * inv * lo(gain[k].y), v[k].w * inv * hi(gain[k].y)));
 }
-
-constexpr int NORM_TX = 4;   // threads per row = 256 * NORM_TX
+template <int VPL, int NTH>
+static bool launch_rmsnorm_row(const NormArgs& a, int n_parts, int rows, hipStream_t s) {
+  switch (n_parts) {       // (ranges of K: powers of two up to 16)
+    case 0: hipLaunchKernelGGL((k_rmsnorm_row<VPL, NTH, 0>), dim3(rows), dim3(NTH), 0, s, a); return true;
+    case 1: hipLaunchKernelGGL((k_rmsnorm_row<VPL, NTH, 1>), dim3(rows), dim3(NTH), 0, s, a); return true;
+    case 2: hipLaunchKernelGGL((k_rmsnorm_row<VPL, NTH, 2>), dim3(rows), dim3(NTH), 0, s, a); return true;
+    case 4: hipLaunchKernelGGL((k_rmsnorm_row<VPL, NTH, 4>), dim3(rows), dim3(NTH), 0, s, a); return true;
+    case 8: hipLaunchKernelGGL((k_rmsnorm_row<VPL, NTH, 8>), dim3(rows), dim3(NTH), 0, s, a); return true;
+    case 16: hipLaunchKernelGGL((k_rmsnorm_row<VPL, NTH, 16>), dim3(rows), dim3(NTH), 0, s, a); return true;
+  }
+  return false;
+}
 void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const bf16* gain, bf16* y,
                     int rows, int d, float eps, bool write_back, Gate g, hipStream_t s, float* h_out) {
   if (!parts) n_parts = 0;
-  const int wb = write_back ? 1 : 0;
+  const bool mapped = src.off_base || src.off_per_gb || (rows > src.rows_per_seq && src.seq_stride != src.rows_per_seq);
+  if (d % 4 == 0 && reinterpret_cast<uintptr_t>(gain) % 8 == 0) {
+    const NormArgs a = {h, parts, part_stride, gain, y, h_out, src, d, mapped, write_back, eps, g};
+    if (d <= 1024 ? launch_rmsnorm_row<4, 64>(a, n_parts, rows, s)
+                  : (d <= 4096 ? launch_rmsnorm_row<1, 1024>(a, n_parts, rows, s)
+                               : d <= 8192 && launch_rmsnorm_row<2, 1024>(a, n_parts, rows, s)))
+      return;
+  }
   dim3 grid((rows + 3) / 4), block(256);
   if (rows <= 4096) { grid = dim3(rows); block = dim3(64); }   // few rows: one wavefront per workgroup fills more CUs
-  if (d % 4 == 0 && d >= 2048 && d <= 4096)
-    hipLaunchKernelGGL((k_rmsnorm_row<4 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
-  else if (d % 4 == 0 && d > 4096 && d <= 8192)
-    hipLaunchKernelGGL((k_rmsnorm_row<8 / NORM_TX, 256 * NORM_TX>), dim3(rows), dim3(256 * NORM_TX), 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
-  else if (d % 4 == 0 && d <= 1024)
-    hipLaunchKernelGGL((k_rmsnorm_vec<4>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
-  else if (d % 4 == 0 && d <= 4096)
-    hipLaunchKernelGGL((k_rmsnorm_vec<16>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
-  else if (d % 4 == 0 && d <= 8192)
-    hipLaunchKernelGGL((k_rmsnorm_vec<32>), grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
-  else
-    hipLaunchKernelGGL(k_rmsnorm, grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, wb, h_out, g);
+  hipLaunchKernelGGL(k_rmsnorm, grid, block, 0, s, h, parts, n_parts, part_stride, src, gain, y, rows, d, eps, write_back ? 1 : 0,
+                     h_out, g);
 }
+
 // ------------------------------------------------------------------------------------------------
 // Finishing kernels of the few-row ("skinny") GEMM path: the GEMM leaves fp32 partial products per
 // K range; these sum them in ascending range order and apply what the wide path fuses into its
@@ -454,11 +428,40 @@ void launch_skinny_swiglu_finish(const float* parts, int n_parts, size_t part_st
 }
 
 // ------------------------------------------------------------------------------------------------
+// A single sequence's control block for the step after this one, as k_prepare would write it.
+__device__ __forceinline__ void next_control(const UpdateArgs& a, int block, int done) {
+  const int all_done = done || block >= a.n_blocks, last = a.n_blocks > 0 ? a.n_blocks - 1 : 0;
+  const int gb = all_done ? last : block;
+  a.ctl[CTL_GB] = gb;
+  a.ctl[CTL_ALL_DONE] = all_done;
+  a.ctl[CTL_ACTIVE] = all_done ? 0 : 1;
+  a.ctl[CTL_SEQ_GB] = a.ragged ? min(block, last) : gb;
+}
 // Per sequence: combine the vocabulary partials into conf / pre (Eq. 3, Eq. 4), evaluate the filter
 // p = sigmoid(W2 relu(W1 c + b1) + b2) on the block's confidences (committed positions enter as 1.0),
 // unmask where p > tau plus the most confident masked position, advance the block, apply EoTP.
+// One workgroup per sequence, bound by a chain of memory round trips and barriers.  What does not depend on the partials is
+// sent off before them: the filter (into LDS behind them, up to kStaged parameters: 80 KB) and the block's tokens.
+// 32 rows with 32 / 250 / 988 partials each: 8.5 / 9.8 / 15.8 us (13.1 / 16.2 / 19.5 with the filter read from memory where it
+// is used, all sixteen partials of a lane worked on whether there or not, and reductions by LDS permutes); the partials are
+// half of the last figure: 16 instructions each on one CU.
+constexpr int kStaged = 20480;
 __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
-  if (gate_skip(g)) return;
+  extern __shared__ float s_filter[];          // layer after layer, weights before biases
+  const int tid = threadIdx.x;
+  constexpr int kAhead = 4;                    // weights of a layer per thread on their way: all of 32 -> 128 -> 32
+  float ahead[kFilterMaxLayers][kAhead], ahead_b[kFilterMaxLayers];
+  const int2 gw = gate_words(g);
+  const bool staged = a.staged.total > 0;
+  if (staged) {
+#pragma unroll
+    for (int k = 0; k < kFilterMaxLayers; ++k) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) ahead[k][u] = a.staged.w[k][min(tid + 1024 * u, a.staged.nw[k] - 1)];
+      ahead_b[k] = a.staged.b[k][min(tid, a.staged.nb[k] - 1)];
+    }
+  }
+  if (gate_closed(g, gw)) return;
   __shared__ float s_conf[256];
   __shared__ int s_pred[256];
   __shared__ float s_cin[256];
@@ -466,12 +469,14 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
   __shared__ unsigned char s_masked[256];
   __shared__ unsigned char s_sel[256];
   __shared__ int s_flag[6];   // masked, committed, end-of-text seen, still masked afterwards, first end-of-text, EGP hits
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.x, lane = tid & 63, wave = tid >> 6;
   const int s = a.s;
   const int gb = a.ctl[CTL_SEQ_GB + b];   // the batch's common block, or this sequence's own
   const int lo = a.P + gb * s;
   int32_t* X = a.X + (size_t)b * a.T;
   int32_t* st = a.state + b * 3;
+  const int32_t token = tid < s ? X[lo + tid] : 0;
+  const int st_block = st[0], st_steps = st[1], st_done = st[2];
 
   const int n_waves = blockDim.x >> 6;
   for (int j = wave; j < s; j += n_waves) {
@@ -482,12 +487,12 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
     // together.  A lane keeps the maximum of its partials, the lowest token that has it and the sum relative to it;
     // the lanes are joined at the end.
     constexpr int U = 16;
-    for (int p0 = lane; p0 < a.n_part; p0 += 64 * U) {
+    for (int p0 = 0; p0 < a.n_part; p0 += 64 * U) {
       float pm[U], ps[U];
       int pi[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int p = p0 + 64 * u;
+        const int p = p0 + 64 * u + lane;
         const bool in = p < a.n_part;
         pm[u] = in ? a.part_max[base + p] : -INFINITY;
         ps[u] = in ? a.part_sum[base + p] : 0.f;
@@ -495,28 +500,36 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
       }
       float mn = m;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (pm[u] > mn || (pm[u] == mn && pi[u] < idx)) idx = pi[u];
-        mn = fmaxf(mn, pm[u]);
-      }
-      if (mn > -INFINITY) {
-        sum *= exp_neg(mn - m);                // (m = -inf, sum = 0 at first)
-        m = mn;
+      for (int u = 0; u < U; ++u) mn = fmaxf(mn, pm[u]);
+      if (mn > m) idx = 0x7fffffff;
+      // (a lane without any partial so far: everything relative to the lowest number, sums of zero)
+      const float ref = fmaxf(mn, -3.402823466e38f);
+      sum *= exp_neg(ref - m);                 // (m = -inf, sum = 0 at first)
+      m = mn;
 #pragma unroll
-        for (int u = 0; u < U; ++u) sum += ps[u] * exp_neg(m - pm[u]);
+      for (int u = 0; u < U; ++u) {
+        if (p0 + 64 * u >= a.n_part) break;    // none of the lanes has one
+        idx = pm[u] == mn ? min(idx, pi[u]) : idx;
+        sum += ps[u] * exp_neg(ref - pm[u]);
       }
     }
-    float M = m;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+    const float M = wave_reduce(m, [](float x, float y) { return fmaxf(x, y); });
     sum = m > -INFINITY ? sum * exp_neg(M - m) : 0.f;
     if (m < M) idx = 0x7fffffff;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      sum += __shfl_xor(sum, o, 64);
-      idx = min(idx, __shfl_xor(idx, o, 64));
-    }
+    sum = wave_reduce(sum, [](float x, float y) { return x + y; });
+    idx = wave_reduce(idx, [](int x, int y) { return min(x, y); });
     if (lane == 0) { s_conf[j] = 1.f / sum; s_pred[j] = idx; }
+  }
+#pragma unroll
+  for (int k = 0; k < kFilterMaxLayers; ++k) {
+    if (!staged || k >= a.n_layers) break;
+    const int nw = a.staged.nw[k];
+    float* w = s_filter + a.staged.at[k];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (tid + 1024 * u < nw) w[tid + 1024 * u] = ahead[k][u];
+    for (int i = tid + 1024 * kAhead; i < nw; i += 1024) w[i] = a.staged.w[k][i];
+    if (tid < a.staged.nb[k]) w[nw + tid] = ahead_b[k];    // (at most 1024 of them)
   }
   if (tid < 4 || tid == 5) s_flag[tid] = 0;
   if (tid == 4) s_flag[4] = 0x7fffffff;
@@ -525,7 +538,7 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
   const int teff = a.teff ? a.teff[b] : a.T;
   __syncthreads();
   if (tid < s) {
-    bool mk = X[lo + tid] == a.mask_id && lo + tid < teff;
+    bool mk = token == a.mask_id && lo + tid < teff;
     s_masked[tid] = mk;
     s_cin[tid] = mk ? s_conf[tid] : 1.0f;
     if (a.conf_out) a.conf_out[b * s + tid] = s_conf[tid];
@@ -542,16 +555,20 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
     float acc = 0.f;
 #pragma unroll 4
     for (int j = l16; j < n; j += 16) acc += w[j] * x[j];
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 16);
+    acc += dppf<kDppRor + 8>(acc);
+    acc += dppf<kDppRor + 4>(acc);
+    acc += dppf<kDppRor + 2>(acc);
+    acc += dppf<kDppRor + 1>(acc);
     return acc;
   };
   const float* act = s_cin;
   int width = s;
   for (int k = 0; !ref && k + 1 < a.n_layers; ++k) {
     float* nxt = s_hid[k & 1];
+    const float* w = staged ? s_filter + a.staged.at[k] : a.fw[k];
+    const float* bias = staged ? w + a.hidden * width : a.fb[k];
     for (int t = n16; t < a.hidden; t += groups) {
-      const float acc = a.fb[k][t] + neuron(a.fw[k] + (size_t)t * width, act, width);
+      const float acc = bias[t] + neuron(w + (size_t)t * width, act, width);
       if (l16 == 0) nxt[t] = fmaxf(acc, 0.f);
     }
     __syncthreads();
@@ -566,8 +583,10 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
       if (hit) atomicAdd(&s_flag[5], 1);
     }
   } else {
+    const float* w = staged ? s_filter + a.staged.at[a.n_layers - 1] : a.fw[a.n_layers - 1];
+    const float* bias = staged ? w + s * width : a.fb[a.n_layers - 1];
     for (int t = n16; t < s; t += groups) {
-      const float z = a.fb[a.n_layers - 1][t] + neuron(a.fw[a.n_layers - 1] + (size_t)t * width, act, width);
+      const float z = bias[t] + neuron(w + (size_t)t * width, act, width);
       const float p = 1.f / (1.f + expf(-z));
       if (l16 == 0) {
         if (a.filt_out) a.filt_out[b * s + t] = p;
@@ -577,10 +596,10 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
   }
   __syncthreads();
   const int n_masked = s_flag[0];
-  const bool mine = !st[2] && st[0] == gb;
+  const bool mine = !st_done && st_block == gb;
   if (ref && mine && n_masked > 0 && tid < s) {
     // the step's training row: confidences as the filter would see them, labels 1 = may be unmasked
-    const size_t row = ((size_t)b * a.gen_len + st[1]) * s + tid;
+    const size_t row = ((size_t)b * a.gen_len + st_steps) * s + tid;
     a.egp_conf[row] = s_cin[tid];
     a.egp_label[row] = (!s_masked[tid] || s_sel[tid]) ? 1.f : 0.f;
   }
@@ -589,18 +608,21 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
   // and then with the reference token)
   if (wave == 0 && n_masked > 0 && !(ref && s_flag[5] > 0)) {
     // the lowest of the masked positions with the highest confidence (one that is no number counts as the lowest)
-    float best = 0.f;
-    int bj = 0x7fffffff;
-    auto take = [&](float c, int j) {
-      if (j != 0x7fffffff && (bj == 0x7fffffff || c > best || (c == best && j < bj))) { best = c; bj = j; }
-    };
-    for (int j = lane; j < s; j += 64)
-      if (s_masked[j]) take(s_conf[j] == s_conf[j] ? s_conf[j] : -INFINITY, j);
+    float c[4], best = -INFINITY;              // (s <= 256)
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float c = __shfl_xor(best, o, 64);
-      take(c, __shfl_xor(bj, o, 64));
+    for (int q = 0; q < 4; ++q) {
+      const int j = lane + 64 * q;
+      c[q] = j < s && s_masked[j] && s_conf[j] == s_conf[j] ? s_conf[j] : -INFINITY;
+      best = fmaxf(best, c[q]);
     }
+    best = wave_reduce(best, [](float x, float y) { return fmaxf(x, y); });
+    int bj = 0x7fffffff;
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+      const int j = lane + 64 * q;
+      if (j < s && s_masked[j] && c[q] == best) bj = j;
+    }
+    bj = wave_reduce(bj, [](int x, int y) { return min(x, y); });
     if (lane == 0) s_sel[bj] = 1;
   }
   __syncthreads();
@@ -613,7 +635,10 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
     }
   }
   __syncthreads();
-  if (!mine) return;
+  if (!mine) {
+    if (a.next_ctl && tid == 0) next_control(a, st_block, st_done);
+    return;
+  }
   bool complete = s_flag[1] == n_masked;   // also true when nothing was masked
   if (a.eotp == 2) {
     // after this step's commits: the first end-of-text of the response shortens the sequence, and
@@ -633,15 +658,28 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
   }
   __syncthreads();
   if (tid == 0) {
-    if (n_masked > 0) st[1] += 1;
-    if (complete) {
-      st[0] = gb + 1;
-      if (s_flag[2] || gb + 1 >= a.n_blocks) st[2] = 1;
-    }
+    const int stop = complete && (s_flag[2] || gb + 1 >= a.n_blocks);
+    if (n_masked > 0) st[1] = st_steps + 1;
+    if (complete) st[0] = gb + 1;
+    if (stop) st[2] = 1;
+    if (a.next_ctl) next_control(a, complete ? gb + 1 : gb, stop);
   }
 }
-void launch_update(const UpdateArgs& a, Gate g, hipStream_t s) {
-  hipLaunchKernelGGL(k_update, dim3(a.B), dim3(1024), 0, s, a, g);   // 16 wavefronts share the block's rows
+void launch_update(UpdateArgs a, Gate g, hipStream_t s) {
+  UpdateArgs::Staged& st = a.staged;
+  st = {};
+  for (int k = 0, in = a.s; k < a.n_layers; ++k) {
+    const int out = k + 1 < a.n_layers ? a.hidden : a.s;
+    st.w[k] = a.fw[k]; st.b[k] = a.fb[k];
+    st.nw[k] = out * in; st.nb[k] = out; st.at[k] = st.total;
+    st.total += out * in + out;
+    in = out;
+  }
+  if (st.total > kStaged) st.total = 0;
+  for (int k = a.n_layers; k < kFilterMaxLayers; ++k) { st.w[k] = st.b[k] = a.fw[0]; st.nw[k] = st.nb[k] = 1; }
+  static DynLdsAttr attr;
+  attr.ensure(reinterpret_cast<const void*>(k_update), kStaged * (int)sizeof(float));
+  hipLaunchKernelGGL(k_update, dim3(a.B), dim3(1024), st.total * sizeof(float), s, a, g);   // 16 wavefronts share the block's rows
 }
 
 // response_i = X[P : P+G], steps, decoded length

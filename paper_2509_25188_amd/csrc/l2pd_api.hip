@@ -27,7 +27,7 @@ struct Carver {
 
 struct Layout {
   // offsets into the workspace
-  size_t rope, ctl, state, state2, perm, perm2, teff, X, X2, h, xn, q, attn, act, parts, attn_ws, attn_ws_bytes, kstore, vstore,
+  size_t rope, ctl, open, state, state2, perm, perm2, teff, X, X2, h, xn, q, attn, act, parts, attn_ws, attn_ws_bytes, kstore, vstore,
       xn_head, part_max, part_sum, part_idx, conf, pred, total;
   size_t kv_layer_stride_k, kv_layer_stride_v;
   int Tpad;
@@ -102,6 +102,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
   const size_t head_rows = (size_t)max_batch * 256;   // block_len <= 256
   L.rope = c.take((size_t)L.Tpad * (m.head_dim / 2) * 8);
   L.ctl = c.take((size_t)(CTL_WORDS + 2 * max_batch) * 4);   // control words, per-sequence blocks, per-sequence done flags
+  L.open = c.take(8);   // zeros: the gate of launches that are not gated
   L.state = c.take((size_t)max_batch * 3 * 4);
   L.state2 = c.take((size_t)max_batch * 3 * 4);   // second copies for batch compaction
   L.perm = c.take((size_t)max_batch * 4);
@@ -173,6 +174,13 @@ int ensure_device(l2pd_ctx* c, hipStream_t s) {
   c->device_ready = true;
   return L2PD_OK;
 }
+
+// Launches that stop with the decode (or, expect_gb >= 0, outside that block); launches that always run.
+Gate gated(l2pd_ctx* c, int expect_gb = -1) {
+  const int* ctl = c->at<int>(c->L.ctl);
+  return Gate{ctl, expect_gb, reinterpret_cast<const int2*>(ctl)};
+}
+Gate ungated(l2pd_ctx* c) { return Gate{nullptr, -1, c->at<int2>(c->L.open)}; }
 
 // ---- timing aid ----
 struct Timed {
@@ -492,15 +500,20 @@ void run_refresh_seq(l2pd_ctx* c, const int32_t* X, int b, int P, const l2pd_dec
 // sequence follows its own block pointer (then the store rebuilds are the caller's, per sequence).
 // t_run > 0 (step-granular EoTP): the forward runs over the first t_run positions of every sequence,
 // each sequence attending to its own teff[b] <= t_run keys.
+// Ctl: the update of a single sequence can leave the control block for the next step (`leave`), which then starts without
+// the kernel that writes it (`ready`).
+struct Ctl {
+  bool leave = false, ready = false;
+};
 void run_step(l2pd_ctx* c, int32_t* X, int B, int P, const l2pd_decode_cfg* cfg, const l2pd_filter* f,
               int32_t* state, int host_gb, const StepTaps& taps, hipStream_t s, int t_run = 0,
-              const EgpArgs* egp = nullptr) {
+              const EgpArgs* egp = nullptr, Ctl* own = nullptr) {
   const Layout& L = c->L;
   const int sl = cfg->block_len, T = P + cfg->gen_len, nb = cfg->gen_len / sl;
   int* ctl = c->at<int>(L.ctl);
-  launch_prepare(state, B, nb, cfg->ragged, ctl, s);
+  if (!own || !own->ready) launch_prepare(state, B, nb, cfg->ragged, ctl, s);
   const bool own_blocks_cached = cfg->kv_cache && cfg->ragged;
-  Gate g = {ctl, (cfg->kv_cache && !own_blocks_cached) ? host_gb : -1};
+  const Gate g = gated(c, (cfg->kv_cache && !own_blocks_cached) ? host_gb : -1);
   BiasArgs bias = {cfg->bias.token_id, cfg->bias.gen_pos_from, sl, cfg->bias.value};
   if (own_blocks_cached) {
     // per-sequence block pointers: every sequence's block rows sit at its own positions (read from the
@@ -550,6 +563,8 @@ void run_step(l2pd_ctx* c, int32_t* X, int B, int P, const l2pd_decode_cfg* cfg,
   u.conf_out = taps.conf; u.pred_out = taps.pred; u.filt_out = taps.filt; u.unmask_out = taps.unmask;
   u.ctl = ctl;
   u.teff = t_run > 0 ? c->at<int>(L.teff) : nullptr;
+  u.next_ctl = own && own->leave; u.ragged = cfg->ragged;
+  if (own) own->ready = own->leave;
   Timed t(c, L2PD_K_UPDATE, s);
   launch_update(u, g, s);
 }
@@ -687,7 +702,7 @@ int32_t l2pd_forward(l2pd_ctx* c, const int32_t* tokens_dev, int32_t B, int32_t 
   hipStream_t s = static_cast<hipStream_t>(stream);
   int st = ensure_device(c, s);
   if (st) return st;
-  Gate g = {nullptr, -1};
+  const Gate g = ungated(c);
   Pass p = {B, T, 0, T, T, tokens_dev, false, false};
   if (row_count <= 256) {   // one slab of the LM head below
     p.want = row_count;
@@ -735,9 +750,9 @@ int32_t l2pd_denoise_step(l2pd_ctx* c, int32_t* tokens_dev, int32_t B, int32_t p
       // every live sequence's slice of the stores is rebuilt for its own block
       for (int b = 0; b < B && !cfg->keep_kv; ++b)
         if (!hs[b * 3 + 2] && hs[b * 3] < nb)
-          run_refresh_seq(c, tokens_dev, b, prompt_len, cfg, hs[b * 3], Gate{nullptr, -1}, s);
+          run_refresh_seq(c, tokens_dev, b, prompt_len, cfg, hs[b * 3], ungated(c), s);
     } else if (!cfg->keep_kv) {
-      run_refresh(c, tokens_dev, B, prompt_len, cfg, host_gb, Gate{nullptr, -1}, s);
+      run_refresh(c, tokens_dev, B, prompt_len, cfg, host_gb, ungated(c), s);
     }
   }
   StepTaps taps = {logits_dev, conf_dev, pred_dev, filt_dev, unmask_dev};
@@ -791,16 +806,18 @@ int32_t l2pd_generate(l2pd_ctx* c, const int32_t* prompt_dev, int32_t B, int32_t
   int32_t *X_alt = c->at<int32_t>(L.X2), *state_alt = c->at<int32_t>(L.state2);
   int32_t *perm = nullptr, *perm_alt = c->at<int32_t>(L.perm);
   const bool compacting = cfg->ragged == L2PD_RAGGED_COMPACT && B > 1;
+  Ctl own;
+  own.leave = B == 1;
   auto run_until = [&](int host_gb, int max_steps) -> int {   // returns 1 when everything is done
     int issued = 0, slot = 0;
     bool have_prev = false;
     while (issued < max_steps) {
       for (int i = 0; i < CHUNK && issued < max_steps; ++i, ++issued) {
-        run_step(c, X, Bc, P, cfg, f, state, host_gb, no_taps, s);
+        run_step(c, X, Bc, P, cfg, f, state, host_gb, no_taps, s, 0, nullptr, &own);
         ++c->stat_steps;
         c->stat_seq_steps += Bc;
       }
-      launch_prepare(state, Bc, nb, cfg->ragged, ctl, s);
+      if (!own.ready) launch_prepare(state, Bc, nb, cfg->ragged, ctl, s);
       if (hipMemcpyAsync(c->pinned + slot * CTL_WORDS, ctl, CTL_WORDS * sizeof(int), hipMemcpyDeviceToHost, s) !=
               hipSuccess ||
           hipEventRecord(c->poll_ev[slot], s) != hipSuccess)
@@ -893,7 +910,7 @@ int32_t l2pd_generate(l2pd_ctx* c, const int32_t* prompt_dev, int32_t B, int32_t
       for (int b = 0; b < Bc; ++b) {
         const int gb = c->pinned[CTL_SEQ_GB + b];
         if (c->pinned[done_at + b] || gb == host_gb[b]) continue;
-        run_refresh_seq(c, X, b, P, cfg, gb, Gate{nullptr, -1}, s);
+        run_refresh_seq(c, X, b, P, cfg, gb, ungated(c), s);
         host_gb[b] = gb;
       }
       run_step(c, X, Bc, P, cfg, f, state, -1, no_taps, s);
@@ -902,8 +919,9 @@ int32_t l2pd_generate(l2pd_ctx* c, const int32_t* prompt_dev, int32_t B, int32_t
     }
   } else if (cfg->kv_cache) {
     for (int gb = 0; gb < nb; ++gb) {
-      launch_prepare(state, B, nb, cfg->ragged, ctl, s);
-      run_refresh(c, X, B, P, cfg, gb, Gate{ctl, -1}, s);
+      if (!own.ready) launch_prepare(state, B, nb, cfg->ragged, ctl, s);
+      own.ready = own.leave;
+      run_refresh(c, X, B, P, cfg, gb, gated(c), s);
       int r = run_until(gb, sl);   // a block needs at most block_len steps
       if (r < 0) { c->last_hip_error = (int)hipGetLastError(); return L2PD_EHIP; }
       if (r == 1) break;
@@ -943,11 +961,13 @@ int32_t l2pd_egp_rollout(l2pd_ctx* c, const int32_t* prompt_dev, const int32_t* 
   c->stat_steps = c->stat_seq_steps = 0;
   const StepTaps no_taps = {nullptr, nullptr, nullptr, nullptr, nullptr};
   const EgpArgs egp = {reference_dev, conf_rows_dev, label_rows_dev};
+  Ctl own;
+  own.leave = B == 1;
   // every step commits at least one position per unfinished sequence: at most gen_len steps;
   // the control block is looked at every few steps, as in l2pd_generate
   for (int k = 0; k < G;) {
-    for (int i = 0; i < 4 && k < G; ++i, ++k) run_step(c, X, B, P, cfg, nullptr, state, -1, no_taps, s, 0, &egp);
-    launch_prepare(state, B, nb, cfg->ragged, ctl, s);
+    for (int i = 0; i < 4 && k < G; ++i, ++k) run_step(c, X, B, P, cfg, nullptr, state, -1, no_taps, s, 0, &egp, &own);
+    if (!own.ready) launch_prepare(state, B, nb, cfg->ragged, ctl, s);
     HIP_TRY(c, hipMemcpyAsync(c->pinned, ctl, CTL_WORDS * sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     if (c->pinned[CTL_ALL_DONE]) break;
