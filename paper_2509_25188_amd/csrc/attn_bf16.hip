@@ -36,6 +36,11 @@ __device__ __forceinline__ float max_halves(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+struct AttnDivs {
+  Div per_head, heads, chunks;   // by query tiles x key chunks, by H, by the chunks
+  int per_head_n;
+};
+
 // Key ranges: NSPL side by side, one to a wavefront, times NSER that a wavefront walks one after the other, each with a
 // maximum, a sum and an output of its own.  They are joined in ascending order however they are dealt to wavefronts.
 template <int DH, int NQ, int NSPL, int NSER, int NST>
@@ -43,7 +48,7 @@ __global__ void __launch_bounds__(NQ * NSPL * 64, 2) k_attn_bf16(const bf16* __r
                                                                  const bf16* __restrict__ vtstore, bf16* __restrict__ out,
                                                                  int B, int Tq, int Tk_all, int Tpad, int H, int n_chunks,
                                                                  float* __restrict__ chunk_out,
-                                                                 const int* __restrict__ tk_dev, QueryRows sel, Gate g) {
+                                                                 const int* __restrict__ tk_dev, QueryRows sel, AttnDivs div, Gate g) {
   constexpr int KT = 64;                       // keys per LDS tile
   constexpr int K_ROW = DH * 2;                // bytes per key row
   constexpr int K_BYTES = KT * K_ROW;
@@ -66,24 +71,18 @@ __global__ void __launch_bounds__(NQ * NSPL * 64, 2) k_attn_bf16(const bf16* __r
   // Workgroups are dealt to the 8 XCDs round-robin by their linear id.  All query tiles of one
   // (sequence, head) read the same K / V^T, so they are given ids that land on one XCD and share
   // its L2 (T = 512: 1 MB of K/V per XCD instead of all 8 MB through every L2).
-  const int per_head = gridDim.x / (H * B);     // query tiles x key chunks
-  int hb, inner;
-  if ((H * B) % 8 == 0) {
-    const int slot = blockIdx.x >> 3;
-    hb = (slot / per_head) * 8 + (blockIdx.x & 7);
-    inner = slot % per_head;
-  } else {
-    hb = blockIdx.x / per_head;
-    inner = blockIdx.x % per_head;
-  }
-  const int b = hb / H, h = hb % H;
+  const bool spread = (H * B) % 8 == 0;
+  const int slot = spread ? blockIdx.x >> 3 : blockIdx.x, quot = div.per_head(slot);
+  const int inner = slot - quot * div.per_head_n;
+  const int hb = spread ? quot * 8 + (blockIdx.x & 7) : quot;
+  const int b = div.heads(hb), h = hb - b * H;
   // per-sequence key count (sequences shortened by step-granular EoTP), else the launch's
   const int Tk = tk_dev ? min(Tk_all, tk_dev[b]) : Tk_all;
   const int d = H * DH;
   // With n_chunks > 1 the keys are also dealt to n_chunks workgroups per query tile (few queries,
   // many keys: one workgroup per head would leave most CUs idle); each writes its unnormalised
   // (O^T, m, l) to chunk_out and k_attn_merge combines them.
-  const int qt = inner / n_chunks, ch = inner % n_chunks;
+  const int qt = div.chunks(inner), ch = inner - qt * n_chunks;
   const int q0 = qt * (32 * NQ) + qg * 32;
   const int sel_lo = sel.n > 0 ? sel.base + (sel.seq_gb ? sel.seq_gb[b] * sel.per_gb : 0) : 0;
   if (sel.n > 0 && (qt * (32 * NQ) >= sel_lo + sel.n || (qt + 1) * (32 * NQ) <= sel_lo)) return;   // no row asked for
@@ -121,7 +120,7 @@ __global__ void __launch_bounds__(NQ * NSPL * 64, 2) k_attn_bf16(const bf16* __r
   // The key tiles are dealt to the NSPL * NSER key ranges in contiguous runs of `per` tiles; every range is walked by
   // NQ wavefronts (one per query group), NSPL ranges at a time, which advance together, one tile per iteration.
   const int n_tiles = (Tk + KT - 1) / KT;
-  const int per_chunk = (n_tiles + n_chunks - 1) / n_chunks;    // the host picks n_chunks so that no chunk is empty
+  const int per_chunk = div.chunks(n_tiles + n_chunks - 1);     // the host picks n_chunks so that no chunk is empty
   const int wg_first = ch * per_chunk, wg_count = min(per_chunk, n_tiles - wg_first);
   const int per = (wg_count + NSPL * NSER - 1) / (NSPL * NSER);
   const int my_first = wg_first + sp * NSER * per, my_count = max(0, min(NSER * per, wg_first + wg_count - my_first));
@@ -355,30 +354,47 @@ __global__ void __launch_bounds__(NQ * NSPL * 64, 2) k_attn_bf16(const bf16* __r
   }
 }
 
-// One thread per (sequence, head, query, 4 features): combines the key chunks in ascending order.
-template <int DH>
-__global__ void __launch_bounds__(256) k_attn_merge(const float* __restrict__ chunk_out, bf16* __restrict__ out, int B,
-                                                   int Tq, int H, int n_chunks, Gate g) {
-  if (gate_skip(g)) return;
+// One thread per (sequence, head, query, 4 features): combines the key chunks in ascending order.  NC: the chunks rounded up,
+// so that all loads are in flight together (those past the last chunk read it again and count nothing).  32 queries of
+// 32 heads, 5 chunks: 4.8 us (5.2 with two loops over the chunks).
+template <int DH, int NC>
+__global__ void __launch_bounds__(256) k_attn_merge(const float* __restrict__ chunk_out, bf16* __restrict__ out, int n, int Tq,
+                                                   int H, int n_chunks, Div queries, Div heads, Gate g) {
+  const int2 gate = gate_words(g);
   const int t = blockIdx.x * 256 + threadIdx.x;
-  const int per_q = DH / 4;
-  if (t >= B * H * Tq * per_q) return;
-  const int f4 = t % per_q, qi = (t / per_q) % Tq, h = (t / per_q / Tq) % H, b = t / per_q / Tq / H;
-  const float* p = chunk_out + ((((size_t)b * H + h) * Tq + qi) * n_chunks) * (DH + 2);
-  float M = -INFINITY;
-  for (int c = 0; c < n_chunks; ++c) M = fmaxf(M, p[c * (DH + 2) + DH]);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  constexpr int per_q = DH / 4;
+  const int f4 = t % per_q, row = min(t / per_q, n - 1);      // row: query by query, head by head, sequence by sequence
+  const float* p = chunk_out + (size_t)row * n_chunks * (DH + 2);
+  float m[NC], l[NC];
+  f32x4 v[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const float* pc = p + min(c, n_chunks - 1) * (DH + 2);
+    const u32x2 *pv = reinterpret_cast<const u32x2*>(pc + f4 * 4), *pm = reinterpret_cast<const u32x2*>(pc + DH);
+    const u32x2 lo = pv[0], hi = pv[1], ml = *pm;              // rows of DH + 2 floats: 8-byte pieces
+    v[c] = f32x4{__uint_as_float(lo.x), __uint_as_float(lo.y), __uint_as_float(hi.x), __uint_as_float(hi.y)};
+    m[c] = c < n_chunks ? __uint_as_float(ml.x) : -INFINITY;
+    l[c] = __uint_as_float(ml.y);
+  }
+  if (gate_closed(g, gate) || t / per_q >= n) return;
+  float M = m[0];
+#pragma unroll
+  for (int c = 1; c < NC; ++c) M = fmaxf(M, m[c]);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   float L = 0.f;
-  for (int c = 0; c < n_chunks; ++c) {
-    const float w = __builtin_amdgcn_exp2f(p[c * (DH + 2) + DH] - M);
-    const float4 v = *reinterpret_cast<const float4*>(p + c * (DH + 2) + f4 * 4);
-    acc.x += v.x * w; acc.y += v.y * w; acc.z += v.z * w; acc.w += v.w * w;
-    L += p[c * (DH + 2) + DH + 1] * w;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const float w = __builtin_amdgcn_exp2f(m[c] - M);
+    if (c < n_chunks) {                        // (a chunk of infinities stays out as a whole)
+      acc += v[c] * w;
+      L += l[c] * w;
+    }
   }
   const float inv = 1.f / L;
   u32x2 w2;
-  w2.x = pack_bf16(acc.x * inv, acc.y * inv);
-  w2.y = pack_bf16(acc.z * inv, acc.w * inv);
+  w2.x = pack_bf16(acc[0] * inv, acc[1] * inv);
+  w2.y = pack_bf16(acc[2] * inv, acc[3] * inv);
+  const int bh = queries(row), qi = row - bh * Tq, b = heads(bh), h = bh - b * H;
   unsigned short* op = reinterpret_cast<unsigned short*>(out) + ((size_t)b * Tq + qi) * (H * DH) + h * DH + f4 * 4;
   *reinterpret_cast<u32x2*>(op) = w2;
 }
@@ -405,11 +421,18 @@ static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16*
     if ((size_t)B * H * Tq * n_chunks * (DH + 2) * 4 > chunk_ws_bytes) n_chunks = 1;
   }
   dim3 grid(q_tiles * n_chunks * H * B);
+  const AttnDivs div = {Div(q_tiles * n_chunks), Div(H), Div(n_chunks), q_tiles * n_chunks};
   hipLaunchKernelGGL(kern, grid, dim3(NQ * NSPL * 64), smem, s, q, kstore, vtstore, out, B, Tq, Tk, Tpad, H, n_chunks,
-                     chunk_ws, tk_dev, sel, g);
+                     chunk_ws, tk_dev, sel, div, g);
   if (n_chunks > 1) {
-    const int n = B * H * Tq * (DH / 4);
-    hipLaunchKernelGGL(k_attn_merge<DH>, dim3((n + 255) / 256), dim3(256), 0, s, chunk_ws, out, B, Tq, H, n_chunks, g);
+    const int n = B * H * Tq;
+    const dim3 grid((n * (DH / 4) + 255) / 256);
+    if (n_chunks <= 4)
+      hipLaunchKernelGGL((k_attn_merge<DH, 4>), grid, dim3(256), 0, s, chunk_ws, out, n, Tq, H, n_chunks, Div(Tq), Div(H), g);
+    else if (n_chunks <= 8)
+      hipLaunchKernelGGL((k_attn_merge<DH, 8>), grid, dim3(256), 0, s, chunk_ws, out, n, Tq, H, n_chunks, Div(Tq), Div(H), g);
+    else
+      hipLaunchKernelGGL((k_attn_merge<DH, 16>), grid, dim3(256), 0, s, chunk_ws, out, n, Tq, H, n_chunks, Div(Tq), Div(H), g);
   }
 }
 

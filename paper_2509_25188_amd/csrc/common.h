@@ -12,6 +12,18 @@ namespace l2pd {
 
 typedef __hip_bfloat16 bf16;
 
+// Division of a number by one that only the launch knows: two multiplications instead of some 40 instructions (with one or
+// two wavefronts on a SIMD, 0.1 us each).  m = ceil(2^31 / d), so the product is the quotient or one more: exact for
+// 0 <= x < 2^30.
+struct Div {
+  unsigned m, d;
+  Div(int d_ = 1) : m((unsigned)(((1ull << 31) + d_ - 1) / d_)), d(d_) {}
+  __device__ __forceinline__ int operator()(int x) const {
+    const unsigned q = __umulhi((unsigned)x << 1, m);
+    return (int)(q - (q * d > (unsigned)x ? 1 : 0));
+  }
+};
+
 // Device control block (int32 words).  Written by k_prepare at the start of every step.  The words
 // from CTL_SEQ_GB on hold the active block of every sequence: the batch's common one in lock step,
 // the sequence's own with per-sequence block pointers.

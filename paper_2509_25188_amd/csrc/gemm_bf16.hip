@@ -42,7 +42,8 @@ struct GemmArgs {
   const bf16* B1;
   const bf16* B2;
   int M, N, K;          // N counts tile-space columns (for pair epilogues: both sides)
-  int tiles_m, tiles_n, splits;
+  int splits, k_len;    // K range of a workgroup
+  TileMap map;
   Gate gate;
   // EPI_PARTIAL: K range z writes to parts + z * part_stride (fp32 [M, N])
   float* parts;
@@ -51,11 +52,14 @@ struct GemmArgs {
   int serial;           // EPI_PARTIAL_SER, splits == 1: the workgroup walks `serial` K ranges one after the other, each
                         // into a fresh accumulator, and writes their sum, formed in ascending order: the bits that
                         // `serial` workgroups' partials give when the RMSNorm sums them
+  int serial_stages;    // 64-deep stages of such a range
   // EPI_SWIGLU
   bf16* act;
   int F;
   // EPI_QKV
   QkvEpilogue qkv;
+  Div heads, rows_per_seq;   // by H, by Tq
+  int group_shift;      // 16-feature groups of half a head: 1 << group_shift
   // EPI_LMHEAD
   LmHeadEpilogue lm;
 };
@@ -64,10 +68,10 @@ struct GemmArgs {
 template <int BN, int EPI>
 __device__ __forceinline__ const bf16* weight_row(const GemmArgs& a, int tile_n, int r) {
   if constexpr (EPI == EPI_QKV) {
-    const int half = a.qkv.Dh / 2, gph = half / 16;        // 16-feature groups per head
+    const int half = a.qkv.Dh / 2;
     const int G = tile_n * (BN / 32) + (r >> 5), j = r & 31;
-    const int hg = G / gph, gi = G % gph;
-    const int mat = min(hg / a.qkv.H, 2), head = hg % a.qkv.H;
+    const int hg = G >> a.group_shift, gi = G & ((1 << a.group_shift) - 1);   // head of Q, K, V stacked; its group of 16 features
+    const int mat = min(a.heads(hg), 2), head = mat == 2 && hg >= 3 * a.qkv.H ? hg - a.heads(hg) * a.qkv.H : hg - mat * a.qkv.H;
     const bf16* base = mat == 0 ? a.B0 : (mat == 1 ? a.B1 : a.B2);
     return base + (size_t)(head * a.qkv.Dh + gi * 16 + (j & 15) + (j >> 4) * half) * a.K;
   } else if constexpr (EPI == EPI_SWIGLU) {
@@ -142,15 +146,14 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
   } else if constexpr (EPI == EPI_QKV) {
     static_assert(FN % 2 == 0, "fragments in pairs");
     const QkvEpilogue& e = a.qkv;
-    const int half = e.Dh / 2, gph = half / 16;
-    const bool vec4 = (e.Tq % 4 == 0) && (e.pos0 % 4 == 0) && (e.Tpad % 4 == 0) && (!e.seq_gb || e.pos_per_gb % 4 == 0);
+    const int half = e.Dh / 2, gmask = (1 << a.group_shift) - 1;
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       // sequence and position of this lane's four rows
       const int row0 = row_base + i * 16;
       int seq[4], pos[4];
       {
-        int t = row0 % e.Tq, b = row0 / e.Tq;
+        int b = a.rows_per_seq(row0), t = row0 - b * e.Tq;
         int off = (e.seq_gb && row0 < a.M) ? e.seq_gb[b] * e.pos_per_gb : 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -170,8 +173,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
       float2 cs[2][4];
       auto load_tab = [&](int p, int buf) {
         const int G = tile_n * (BN / 32) + wn * (FN / 2) + p;
-        if (G / gph >= 2 * e.H) return;                    // V (or past the last column): no rotation
-        const int dim = (G % gph) * 16 + cl;
+        if ((G >> a.group_shift) >= 2 * e.H) return;       // V (or past the last column): no rotation
+        const int dim = (G & gmask) * 16 + cl;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           cs[buf][r] = row0 + r < a.M ? e.rope[(unsigned)pos[r] * (unsigned)half + (unsigned)dim] : make_float2(0.f, 0.f);
@@ -181,13 +184,15 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
       for (int p = 0; p < FN / 2; ++p) {
         if (p + 1 < FN / 2) load_tab(p + 1, (p + 1) & 1);
         const int G = tile_n * (BN / 32) + wn * (FN / 2) + p;
-        const int hg = G / gph, gi = G % gph, mat = hg / e.H, head = hg % e.H;   // uniform over the wavefront
+        const int hg = G >> a.group_shift, gi = G & gmask, mat = a.heads(hg), head = hg - mat * e.H;   // uniform over the wavefront
         if (mat > 2) continue;
         if (mat == 2) {
-          // V is stored transposed ([B, H, Dh, Tpad]) so that attention reads keys contiguously
+          // V is stored transposed ([B, H, Dh, Tpad]) so that attention reads keys contiguously: four positions at once
+          // where the lane's rows are consecutive ones of a sequence from a multiple of four on (221 rows: 14.7 -> 13.3 us
+          // against a rule for the whole launch, which no odd window passed)
           unsigned short* vt = reinterpret_cast<unsigned short*>(e.vtstore);
           const int dim = gi * 16 + cl;
-          if (vec4 && row0 + 3 < a.M) {
+          if (seq[3] == seq[0] && pos[0] % 4 == 0 && row0 + 3 < a.M) {   // (Tpad is a multiple of 64)
             const size_t o = ((size_t)(seq[0] * e.H + head) * e.Dh + dim) * e.Tpad + pos[0];
             uint2 lo4, hi4;
             lo4.x = pack_bf16(acc[i][2 * p][0], acc[i][2 * p][1]);
@@ -331,25 +336,15 @@ __global__ void __launch_bounds__(512) k_gemm_turns(GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [RA][A tile] [RB][B tile]
   unsigned char* const smemB = smem + RA * A_BYTES;
 
-  // ---- tile assignment: consecutive ids on one XCD share a weight panel ----
-  const int total = a.tiles_m * a.tiles_n * a.splits;
-  const int per_xcd = (total + 7) / 8;
-  const int v = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (v >= total) return;
-  const int per_split = a.tiles_m * a.tiles_n;
-  const int z = v / per_split;
-  int rem = v % per_split;
-  constexpr int GM = 8;
-  const int chunk = rem / (GM * a.tiles_n);
-  rem -= chunk * GM * a.tiles_n;
-  const int gmc = min(GM, a.tiles_m - chunk * GM);
-  const int tile_n = rem / gmc;
-  const int tile_m = chunk * GM + rem % gmc;
+  // Up to the first load nothing is divided by hardware and little is waited for: at 221 rows of 1024 the 300 instructions of
+  // integer divisions here were 0.5 us of each product's 8-14.
+  int z, tile_m, tile_n;
+  if (!a.map.place(blockIdx.x, &z, &tile_m, &tile_n)) return;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int k_len = a.K / a.splits, k_begin = z * k_len, nk = k_len / BK;
+  const int k_begin = z * a.k_len, nk = a.k_len / BK;
 
   // Load i of a tile (this wavefront's pieces are i * 8 + wave, 8 rows each): lane l fills slot l of the 1 KB piece.
   const bf16* srcA[LA];
@@ -445,7 +440,7 @@ __global__ void __launch_bounds__(512) k_gemm_turns(GemmArgs a) {
 
   constexpr bool SERIAL = EPI == EPI_PARTIAL_SER;
   f32x4 tot[SERIAL ? FM : 1][SERIAL ? FN : 1];             // sum of the finished K ranges
-  const int seg = SERIAL ? nk / a.serial : 0;              // stages per K range
+  const int seg = SERIAL ? a.serial_stages : 0;            // stages per K range
   int seg_left = seg;
   if constexpr (SERIAL) {
 #pragma unroll
@@ -498,10 +493,10 @@ static void launch(GemmArgs& a, hipStream_t s) {
   constexpr int smem = ((DEPTH + 1) * BM + DEPTH * BN) * 128;
   static DynLdsAttr attr;
   attr.ensure(reinterpret_cast<const void*>(kern), smem);
-  a.tiles_m = (a.M + BM - 1) / BM;
-  a.tiles_n = (a.N + BN - 1) / BN;
-  const int total = a.tiles_m * a.tiles_n * a.splits;
-  hipLaunchKernelGGL(kern, dim3((total + 7) / 8 * 8), dim3(512), smem, s, a);
+  a.map = TileMap((a.M + BM - 1) / BM, (a.N + BN - 1) / BN, a.splits);
+  a.k_len = a.K / a.splits;
+  if (a.serial) a.serial_stages = a.k_len / 64 / a.serial;
+  hipLaunchKernelGGL(kern, dim3((a.map.total + 7) / 8 * 8), dim3(512), smem, s, a);
 }
 // Tile choice: rounds over the 256 CUs, each of a fixed part (first stages from HBM, epilogue) plus the K loop.
 // Loop times per 4096 of K with every CU busy and weights coming from HBM, as measured (4096 rows, d_ffn 12288:
@@ -528,6 +523,7 @@ void launch_gemm_qkv_bf16(const bf16* A, const bf16* wq, const bf16* wk, const b
   GemmArgs a = {};
   a.A = A; a.B0 = wq; a.B1 = wk; a.B2 = wv;
   a.M = M; a.N = 3 * e.d; a.K = K; a.splits = 1; a.gate = g; a.qkv = e;
+  a.heads = Div(e.H); a.rows_per_seq = Div(e.Tq); a.group_shift = e.Dh == 128 ? 2 : 1;   // head sizes are 64 and 128
   switch (pick_tile(M, a.N, K)) {
     case 0: launch<256, 256, 2, 4, 2, EPI_QKV>(a, s); break;
     case 1: launch<256, 192, 4, 2, 2, EPI_QKV>(a, s); break;

@@ -74,4 +74,29 @@ __device__ __forceinline__ void dma16(const void* gptr, unsigned lds_addr) {
                : "memory", "m0");
 }
 
+// Tiles of a launch: consecutive ids on one XCD share a weight panel (eight row tiles of it, then the next eight).
+struct TileMap {
+  int tiles_m, tiles_n, total, per_xcd;
+  Div per_split, chunk, last;   // by tiles_m * tiles_n, by 8 * tiles_n, by the row tiles of the last chunk
+  int per_split_n;
+  TileMap() {}
+  TileMap(int tm, int tn, int splits)
+      : tiles_m(tm), tiles_n(tn), total(tm * tn * splits), per_xcd((tm * tn * splits + 7) / 8), per_split(tm * tn),
+        chunk(8 * tn), last(tm % 8 ? tm % 8 : 8), per_split_n(tm * tn) {}
+  // false: no tile for this workgroup
+  __device__ __forceinline__ bool place(int block, int* z, int* tile_m, int* tile_n) const {
+    const int v = (block & 7) * per_xcd + (block >> 3);
+    if (v >= total) return false;
+    *z = per_split(v);
+    int rem = v - *z * per_split_n;
+    const int c = chunk(rem);
+    rem -= c * 8 * tiles_n;
+    const int n = min(8, tiles_m - c * 8);    // row tiles of the chunk
+    const int part = last(rem);
+    *tile_n = n == 8 ? rem >> 3 : part;
+    *tile_m = c * 8 + rem - *tile_n * n;
+    return true;
+  }
+};
+
 }  // namespace l2pd

@@ -21,7 +21,8 @@ struct FewArgs {
   const bf16* B1;
   const bf16* B2;
   int M, N, K;          // N counts tile-space columns (SwiGLU: gate and up columns)
-  int tiles_m, tiles_n, splits;
+  int splits, k_len;    // K range of a workgroup
+  TileMap map;
   Gate gate;
   // EPI_PARTIAL: K range z writes to parts + z * part_stride (fp32 [M, N])
   float* parts;
@@ -55,29 +56,16 @@ __global__ void __launch_bounds__(WM* WN * 64) k_gemm_few_rows(FewArgs a) {
   // [stage][A: BM rows | B: BN rows][BK bf16]
   constexpr int STAGE_BYTES = LROWS * BK * 2;
 
-  // ---- tile assignment: consecutive ids on one XCD share a weight panel ----
-  const int total = a.tiles_m * a.tiles_n * a.splits;
-  const int per_xcd = (total + 7) / 8;
-  const int v = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (v >= total) return;
-  const int per_split = a.tiles_m * a.tiles_n;
-  const int z = v / per_split;
-  int rem = v % per_split;
-  constexpr int GM = 8;
-  const int chunk = rem / (GM * a.tiles_n);
-  rem -= chunk * GM * a.tiles_n;
-  const int gmc = min(GM, a.tiles_m - chunk * GM);
-  const int tile_n = rem / gmc;
-  const int tile_m = chunk * GM + rem % gmc;
+  int z, tile_m, tile_n;
+  if (!a.map.place(blockIdx.x, &z, &tile_m, &tile_n)) return;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   const int hf = lane >> 5, lj = lane & 31;
 
-  const int k_len = a.K / a.splits;
-  const int k_begin = z * k_len;
-  const int nk = k_len / BK;
+  const int k_begin = z * a.k_len;
+  const int nk = a.k_len / BK;
 
   // ---- per-thread source pointers of the direct-to-LDS loads (fixed over the K loop) ----
   // Load q of a stage (q = wave + i*NW) fills combined tile rows RPD*q .. RPD*q+RPD-1 (A rows first, then B).
@@ -98,7 +86,7 @@ __global__ void __launch_bounds__(WM* WN * 64) k_gemm_few_rows(FewArgs a) {
         int gn = min(n0 + r, a.N - 1);
         base = a.B0;
         if (a.n_sub > 0) {
-          const int mat = gn / a.n_sub;
+          const int mat = (gn >= a.n_sub) + (gn >= 2 * a.n_sub);
           gn -= mat * a.n_sub;
           base = mat == 0 ? a.B0 : (mat == 1 ? a.B1 : a.B2);
         }
@@ -356,11 +344,9 @@ void launch(FewArgs& a, hipStream_t s) {
   constexpr int smem = NS * (BM + BN) * BK * 2;
   static DynLdsAttr attr;
   attr.ensure(reinterpret_cast<const void*>(kern), smem);
-  a.tiles_m = (a.M + BM - 1) / BM;
-  a.tiles_n = (a.N + BN - 1) / BN;
-  int total = a.tiles_m * a.tiles_n * a.splits;
-  int grid = ((total + 7) / 8) * 8;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), smem, s, a);
+  a.map = TileMap((a.M + BM - 1) / BM, (a.N + BN - 1) / BN, a.splits);
+  a.k_len = a.K / a.splits;
+  hipLaunchKernelGGL(kern, dim3((a.map.total + 7) / 8 * 8), dim3(WM * WN * 64), smem, s, a);
 }
 
 }  // namespace

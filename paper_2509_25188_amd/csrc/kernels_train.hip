@@ -95,13 +95,6 @@ __device__ __forceinline__ float log1p_unit(float e) {
   return fmaf(2.f * s * q, p, 2.f * s);
 }
 
-// Division of small numbers by a width that only the launch knows: one multiplication instead of some 40 instructions.
-// Exact while x * d < 2^32.
-struct Div {
-  unsigned m;
-  Div(int d = 1) : m(d == 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d)) {}
-  __device__ __forceinline__ int operator()(int x) const { return m ? (int)__umulhi((unsigned)x, m) : x; }
-};
 struct MfDivs {       // by the number of 16-wide tiles of the outer and the hidden width, and by one more
   Div s, h, s1, h1;
 };
