@@ -147,42 +147,46 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
     static_assert(FN % 2 == 0, "fragments in pairs");
     const QkvEpilogue& e = a.qkv;
     const int half = e.Dh / 2, gmask = (1 << a.group_shift) - 1;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      // sequence and position of this lane's four rows
+    // Rotation table, up to two row fragments ahead: the compiler cannot move a load above a store that might alias it, so
+    // read where it is needed every pair would wait out a memory round trip of its own (Q/K/V of 4096 rows 311 us with the
+    // next pair's on the way, 307 with these).
+    constexpr int AHEAD = FM < 3 ? FM : 3;
+    float2 cs[AHEAD][FN / 2][4];
+    int seq[AHEAD][4], pos[AHEAD][4];          // sequence and position of this lane's four rows
+    auto look_up = [&](int i, int buf) {
       const int row0 = row_base + i * 16;
-      int seq[4], pos[4];
-      {
-        int b = a.rows_per_seq(row0), t = row0 - b * e.Tq;
-        int off = (e.seq_gb && row0 < a.M) ? e.seq_gb[b] * e.pos_per_gb : 0;
+      int b = a.rows_per_seq(row0), t = row0 - b * e.Tq;
+      int off = (e.seq_gb && row0 < a.M) ? e.seq_gb[b] * e.pos_per_gb : 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          seq[r] = b;
-          pos[r] = e.pos0 + off + t;
-          if (++t == e.Tq) {   // next sequence of the batch
-            t = 0;
-            ++b;
-            off = (e.seq_gb && row0 + r + 1 < a.M) ? e.seq_gb[b] * e.pos_per_gb : 0;
-          }
+      for (int r = 0; r < 4; ++r) {
+        seq[buf][r] = b;
+        pos[buf][r] = e.pos0 + off + t;
+        if (++t == e.Tq) {   // next sequence of the batch
+          t = 0;
+          ++b;
+          off = (e.seq_gb && row0 + r + 1 < a.M) ? e.seq_gb[b] * e.pos_per_gb : 0;
         }
       }
-      const int seq_st = lr == 0 ? seq[0] : (lr == 1 ? seq[1] : (lr == 2 ? seq[2] : seq[3]));
-      const int pos_st = lr == 0 ? pos[0] : (lr == 1 ? pos[1] : (lr == 2 ? pos[2] : pos[3]));
-      // Rotation table, one fragment pair ahead: the compiler cannot move a load above a store that might alias
-      // it, so read in place every pair would wait out a memory round trip of its own.
-      float2 cs[2][4];
-      auto load_tab = [&](int p, int buf) {
-        const int G = tile_n * (BN / 32) + wn * (FN / 2) + p;
-        if ((G >> a.group_shift) >= 2 * e.H) return;       // V (or past the last column): no rotation
-        const int dim = (G & gmask) * 16 + cl;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          cs[buf][r] = row0 + r < a.M ? e.rope[(unsigned)pos[r] * (unsigned)half + (unsigned)dim] : make_float2(0.f, 0.f);
-      };
-      load_tab(0, 0);
 #pragma unroll
       for (int p = 0; p < FN / 2; ++p) {
-        if (p + 1 < FN / 2) load_tab(p + 1, (p + 1) & 1);
+        const int G = tile_n * (BN / 32) + wn * (FN / 2) + p;
+        if ((G >> a.group_shift) >= 2 * e.H) continue;       // V (or past the last column): no rotation
+        const int dim = (G & gmask) * 16 + cl;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)            // (rows past the last one: any place of the table)
+          cs[buf][p][r] = e.rope[(unsigned)(row0 + r < a.M ? pos[buf][r] : e.pos0) * (unsigned)half + (unsigned)dim];
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD - 1; ++i) look_up(i, i);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int row0 = row_base + i * 16, at = i % AHEAD;
+      if (i + AHEAD - 1 < FM) look_up(i + AHEAD - 1, (i + AHEAD - 1) % AHEAD);
+      const int seq_st = lr == 0 ? seq[at][0] : (lr == 1 ? seq[at][1] : (lr == 2 ? seq[at][2] : seq[at][3]));
+      const int pos_st = lr == 0 ? pos[at][0] : (lr == 1 ? pos[at][1] : (lr == 2 ? pos[at][2] : pos[at][3]));
+#pragma unroll
+      for (int p = 0; p < FN / 2; ++p) {
         const int G = tile_n * (BN / 32) + wn * (FN / 2) + p;
         const int hg = G >> a.group_shift, gi = G & gmask, mat = a.heads(hg), head = hg - mat * e.H;   // uniform over the wavefront
         if (mat > 2) continue;
@@ -192,8 +196,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
           // against a rule for the whole launch, which no odd window passed)
           unsigned short* vt = reinterpret_cast<unsigned short*>(e.vtstore);
           const int dim = gi * 16 + cl;
-          if (seq[3] == seq[0] && pos[0] % 4 == 0 && row0 + 3 < a.M) {   // (Tpad is a multiple of 64)
-            const size_t o = ((size_t)(seq[0] * e.H + head) * e.Dh + dim) * e.Tpad + pos[0];
+          if (seq[at][3] == seq[at][0] && pos[at][0] % 4 == 0 && row0 + 3 < a.M) {   // (Tpad is a multiple of 64)
+            const size_t o = ((size_t)(seq[at][0] * e.H + head) * e.Dh + dim) * e.Tpad + pos[at][0];
             uint2 lo4, hi4;
             lo4.x = pack_bf16(acc[i][2 * p][0], acc[i][2 * p][1]);
             lo4.y = pack_bf16(acc[i][2 * p][2], acc[i][2 * p][3]);
@@ -205,7 +209,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               if (row0 + r >= a.M) continue;
-              const size_t o = ((size_t)(seq[r] * e.H + head) * e.Dh + dim) * e.Tpad + pos[r];
+              const size_t o = ((size_t)(seq[at][r] * e.H + head) * e.Dh + dim) * e.Tpad + pos[at][r];
               vt[o] = f2bf(acc[i][2 * p][r]);
               vt[o + (size_t)half * e.Tpad] = f2bf(acc[i][2 * p + 1][r]);
             }
@@ -216,7 +220,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x4 (&acc)[BM / WM
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const float x1 = acc[i][2 * p][r], x2 = acc[i][2 * p + 1][r];
-            const float c = cs[p & 1][r].x, sn = cs[p & 1][r].y;
+            const float c = cs[at][p][r].x, sn = cs[at][p][r].y;
             // explicit roundings: every tile configuration must produce the same bits, whatever
             // contraction into fused multiply-adds the compiler would pick for each of them
             w[r] = pack_bf16(__fmaf_rn(x1, c, -__fmul_rn(x2, sn)), __fmaf_rn(x2, c, __fmul_rn(x1, sn)));
