@@ -502,22 +502,146 @@ static void launch(GemmArgs& a, hipStream_t s) {
   if (a.serial) a.serial_stages = a.k_len / 64 / a.serial;
   hipLaunchKernelGGL(kern, dim3((a.map.total + 7) / 8 * 8), dim3(512), smem, s, a);
 }
+// ------------------------------------------------------------------------------------------------
+// Small tiles.  A wavefront's share of a 64-deep stage is a handful of MFMAs there, and with turns every slot lasts as long as
+// a round trip to LDS: 0.33 us a stage of a 128x64 tile, whatever is loaded.  Here all wavefronts go in step, one barrier a
+// stage: behind it a wavefront reads the whole next stage's fragments into a second set of registers and multiplies the ones it
+// has, so a stage lasts as long as the LDS traffic (64x64: 48 KB) or the multiplications, whichever is longer.
+//   64x64 tiles (80 KB of LDS, two workgroups a CU) are for outputs that 128x64 tiles would give to half of the chip: what
+// a CU can load (60-100 GB/s) bounds the rest.  us, 221 rows of 1024 (FFN 2816), turns / 128x64 / 64x64: Q/K/V 10.8 / 9.9 / 8.9,
+// gate/up 9.7 / 9.2 / 9.4 (352 tiles), output 6.9 / 6.5 / 5.2, down 8.4 / 8.0 / 6.3; a product of one stage takes 4.8.
+//   128x128 tiles: Q/K/V of 192 rows of 4096 47-49 / 44, 256 rows 49 / 47, down equal; gate/up 2 % slower, which keeps turns there.
+// Every output sums in the order of the kernel above: the same bits.
+template <int BM, int BN, int WM, int WN, int NS, int EPI>
+__global__ void __launch_bounds__(WM * WN * 64) k_gemm_step(GemmArgs a) {
+  constexpr int BK = 64, NW = WM * WN;     // a stage: [A tile | B tile], NS of them in the ring
+  constexpr int FM = BM / WM / 16, FN = BN / WN / 16;
+  constexpr int A_BYTES = BM * BK * 2, STAGE = (BM + BN) * BK * 2;
+  constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW;
+  static_assert(LA * 8 * NW == BM && LB * 8 * NW == BN, "tile/wavefronts mismatch");
+  static_assert(NS >= 3 && (NS - 1) * (LA + LB) < 64 && NS * STAGE <= 163840, "ring");
+  static_assert(EPI != EPI_LMHEAD || 3 * WN * BM * 4 <= STAGE, "reduction scratch");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  int z, tile_m, tile_n;
+  if (!a.map.place(blockIdx.x, &z, &tile_m, &tile_n)) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int k_begin = z * a.k_len, nk = a.k_len / BK;
+  const bf16* srcA[LA];
+  const bf16* srcB[LB];
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    const int r = (i * NW + wave) * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    srcA[i] = a.A + (size_t)min(tile_m * BM + r, a.M - 1) * a.K + k_begin + c * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < LB; ++i) {
+    const int r = (i * NW + wave) * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    srcB[i] = weight_row<BN, EPI>(a, tile_n, r) + k_begin + c * 8;
+  }
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane(
+      (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)(smem + wave * 1024));
+  auto load = [&](int k, int slot) {
+#pragma unroll
+    for (int i = 0; i < LA; ++i) dma16(srcA[i] + k * BK, lds0 + slot * STAGE + i * NW * 1024);
+#pragma unroll
+    for (int i = 0; i < LB; ++i) dma16(srcB[i] + k * BK, lds0 + slot * STAGE + A_BYTES + i * NW * 1024);
+  };
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int fr = lane & 15;
+  int sw[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) sw[kk] = ((kk * 4 + (lane >> 4)) ^ ((fr >> 1) & 7)) << 4;
+  const int rowA = (wm * (BM / WM) + fr) * 128, rowB = A_BYTES + (wn * (BN / WN) + fr) * 128;
+  struct Frags { bf16x8_t a[FM][2], b[FN][2]; };
+  auto read = [&](Frags& f, int slot) {
+    const unsigned char* base = smem + slot * STAGE;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) f.a[i][kk] = *reinterpret_cast<const bf16x8_t*>(base + rowA + i * 2048 + sw[kk]);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) f.b[j][kk] = *reinterpret_cast<const bf16x8_t*>(base + rowB + j * 2048 + sw[kk]);
+    }
+  };
+  auto mfmas = [&](Frags& f) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[i][kk], f.b[j][kk], acc[i][j], 0, 0, 0);
+  };
+  const int2 gate = gate_words(a.gate);    // looked at when the first loads are on their way
+  const int lead = min(NS, nk);
+  for (int k = 0; k < lead; ++k) load(k, k);
+  if (gate_closed(a.gate, gate)) {
+    wait_vmcnt<0>();                       // LDS stays this workgroup's until its loads have landed
+    return;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (nk >= NS) wait_vmcnt<(NS - 1) * (LA + LB)>();
+  else wait_vmcnt<0>();
+  lds_barrier();
+  Frags f0, f1;
+  read(f0, 0);
+  int slot = 0;                     // of the stage at work
+  // One stage: its fragments are on their way or here; wait for them and for the next stage, then send off what fills
+  // this stage's place, read the next stage's fragments and multiply.
+  auto stage = [&](int k, Frags& cur, Frags& nxt) {
+    __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0): this stage's fragments are in registers
+    // the next stage has landed: at most the loads of the NS - 2 younger stages are outstanding
+    if (k + NS - 1 < nk) wait_vmcnt<(NS - 2) * (LA + LB)>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const int next = slot + 1 == NS ? 0 : slot + 1;
+    read(nxt, next);                         // (behind the last stage: what lies there, for nobody)
+    if (k + NS < nk) load(k + NS, slot);
+    mfmas(cur);
+    __builtin_amdgcn_sched_barrier(0);
+    slot = next;
+  };
+  for (int k = 0; k < nk; k += 2) {
+    stage(k, f0, f1);
+    if (k + 1 < nk) stage(k + 1, f1, f0);
+  }
+  lds_barrier();
+  epilogue<BM, BN, WM, WN, EPI>(a, acc, smem, wm, wn, tile_m, tile_n, z);
+}
+template <int BM, int BN, int WM, int WN, int NS, int EPI>
+static void launch_step(GemmArgs& a, hipStream_t s) {
+  auto kern = k_gemm_step<BM, BN, WM, WN, NS, EPI>;
+  constexpr int smem = NS * (BM + BN) * 128;
+  static DynLdsAttr attr;
+  attr.ensure(reinterpret_cast<const void*>(kern), smem);
+  a.map = TileMap((a.M + BM - 1) / BM, (a.N + BN - 1) / BN, a.splits);
+  a.k_len = a.K / a.splits;
+  hipLaunchKernelGGL(kern, dim3((a.map.total + 7) / 8 * 8), dim3(WM * WN * 64), smem, s, a);
+}
 // Tile choice: rounds over the 256 CUs, each of a fixed part (first stages from HBM, epilogue) plus the K loop.
 // Loop times per 4096 of K with every CU busy and weights coming from HBM, as measured (4096 rows, d_ffn 12288:
 // 256x256 565 us over 6 rounds, 256x192 614 over 8, 256x128 698 over 12; 512 rows: 128x192 107 over 2, 128x128 83 over
 // 2 of 12288 columns).  A larger tile moves fewer bytes per flop, so it wins whenever there are enough of them:
 // 256x256 for thousands of rows; 512 rows x 24576 gate/up columns are exactly 256 tiles of 256x192, x 12288 Q/K/V
-// columns 256 of 128x192; 128x64 is for outputs too small to occupy the chip otherwise.
+// columns 256 of 128x192; 128x64 and 64x64 are for outputs too small to occupy the chip otherwise.
 struct Tile { int bm, bn; double us; };
-constexpr Tile kTiles[6] = {{256, 256, 88.}, {256, 192, 71.}, {256, 128, 53.}, {128, 192, 48.}, {128, 128, 37.}, {128, 64, 24.}};
+constexpr Tile kTiles[7] = {{256, 256, 88.}, {256, 192, 71.}, {256, 128, 53.}, {128, 192, 48.}, {128, 128, 37.}, {128, 64, 24.}, {64, 64, 18.}};
 constexpr double kRoundUs = 6.;
 static double tile_cost(int t, int M, int N, int K, int splits) {
   const long long tiles = (long long)((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn) * splits;
   return (double)((tiles + 255) / 256) * (kRoundUs + kTiles[t].us * K / splits / 4096.);
 }
 static int pick_tile(int M, int N, int K) {
-  int best = 5;
-  for (int t = 4; t >= 0; --t)
+  int best = 6;
+  for (int t = 5; t >= 0; --t)
     if ((M > 128 || kTiles[t].bm <= 128) && tile_cost(t, M, N, K, 1) < tile_cost(best, M, N, K, 1)) best = t;
   return best;
 }
@@ -533,8 +657,9 @@ void launch_gemm_qkv_bf16(const bf16* A, const bf16* wq, const bf16* wk, const b
     case 1: launch<256, 192, 4, 2, 2, EPI_QKV>(a, s); break;
     case 2: launch<256, 128, 4, 2, 2, EPI_QKV>(a, s); break;
     case 3: launch<128, 192, 4, 2, 3, EPI_QKV>(a, s); break;
-    case 4: launch<128, 128, 4, 2, 3, EPI_QKV>(a, s); break;
-    default: launch<128, 64, 4, 2, 4, EPI_QKV>(a, s);
+    case 4: launch_step<128, 128, 4, 2, 5, EPI_QKV>(a, s); break;
+    case 5: launch_step<128, 64, 4, 2, 6, EPI_QKV>(a, s); break;
+    default: launch_step<64, 64, 2, 2, 5, EPI_QKV>(a, s);
   }
 }
 
@@ -549,7 +674,8 @@ void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16
     case 2: launch<256, 128, 4, 2, 2, EPI_SWIGLU>(a, s); break;
     case 3: launch<128, 192, 4, 2, 3, EPI_SWIGLU>(a, s); break;
     case 4: launch<128, 128, 4, 2, 3, EPI_SWIGLU>(a, s); break;
-    default: launch<128, 64, 4, 2, 4, EPI_SWIGLU>(a, s);
+    case 5: launch_step<128, 64, 4, 2, 6, EPI_SWIGLU>(a, s); break;
+    default: launch_step<64, 64, 2, 2, 5, EPI_SWIGLU>(a, s);
   }
 }
 
@@ -569,8 +695,8 @@ void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16
 constexpr double kFoldUs = 0.8;   // a partial of up to 256 rows costs the RMSNorm this much
 struct PartialPlan { int tile, splits, serial; };
 static PartialPlan plan_small_pass(int M, int N, int K) {
-  PartialPlan best = {5, 1, 0};
-  for (int t : {5, 4})
+  PartialPlan best = {6, 1, 0};
+  for (int t : {6, 5, 4})
     for (int S = 1; S <= 8 && K % (S * 64) == 0 && (S == 1 || K / S >= 512); S *= 2)
       if (tile_cost(t, M, N, K, S) + S * kFoldUs < tile_cost(best.tile, M, N, K, best.splits) + best.splits * kFoldUs)
         best = {t, S, 0};
@@ -583,12 +709,17 @@ int k_ranges(int pass_rows, int N, int K) {
 }
 static PartialPlan plan_partial(int M, int N, int K, int pass_rows) {
   const int R = k_ranges(pass_rows, N, K);
-  if (pass_rows <= 256) return {tile_cost(4, M, N, K, R) < tile_cost(5, M, N, K, R) ? 4 : 5, R, 0};
+  if (pass_rows <= 256) {
+    int best = 6;
+    for (int t : {5, 4})
+      if (tile_cost(t, M, N, K, R) < tile_cost(best, M, N, K, R)) best = t;
+    return {best, R, 0};
+  }
   M = (M + 127) / 128 * 128;   // a function of the count of 128-row tiles: the workspace is sized from it
   const double fold_us = (double)M * N * 8 / 5e6;    // a partial is written and read once, at about 5 TB/s
   PartialPlan best = {2, 1, R};
   double cost = tile_cost(2, M, N, K, 1) * 1.03 + fold_us;
-  for (int t : {0, 1, 2, 4, 5}) {
+  for (int t : {0, 1, 2, 4, 5, 6}) {
     if (M <= 128 && kTiles[t].bm > 128) continue;
     const double c = tile_cost(t, M, N, K, R) + R * fold_us;
     if (c < cost) { cost = c; best = {t, R, 0}; }
@@ -608,8 +739,9 @@ void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t
   else if (p.tile == 0) launch<256, 256, 2, 4, 2, EPI_PARTIAL>(a, s);
   else if (p.tile == 1) launch<256, 192, 4, 2, 2, EPI_PARTIAL>(a, s);
   else if (p.tile == 2) launch<256, 128, 4, 2, 2, EPI_PARTIAL>(a, s);
-  else if (p.tile == 4) launch<128, 128, 4, 2, 3, EPI_PARTIAL>(a, s);
-  else launch<128, 64, 4, 2, 4, EPI_PARTIAL>(a, s);
+  else if (p.tile == 4) launch_step<128, 128, 4, 2, 5, EPI_PARTIAL>(a, s);
+  else if (p.tile == 5) launch_step<128, 64, 4, 2, 6, EPI_PARTIAL>(a, s);
+  else launch_step<64, 64, 2, 2, 5, EPI_PARTIAL>(a, s);
 }
 
 void launch_gemm_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, const LmHeadEpilogue& e, Gate g,
