@@ -351,26 +351,36 @@ void launch(FewArgs& a, hipStream_t s) {
 
 }  // namespace
 
-int skinny_splits(int N, int K) {
-  const int tiles = (N + 127) / 128;
+// K ranges of a step's projections.  Up to 32 rows, in tiles of 64 columns: until there is a workgroup for every CU, and
+// on until the last round of them is nearly full (Q/K/V of 4096: two ranges are 1.5 workgroups a CU, four are 3: 25.4
+// against 20.6 us); more only cost the RMSNorm behind.  Up to 64 rows, in tiles of 128: a few hundred workgroups.
+int skinny_splits(int rows, int N, int K) {
+  const int cols = rows <= 32 ? 64 : 128, tiles = (N + cols - 1) / cols;
   int S = 1;
-  while (tiles * S < 256 && S < 16 && K % (S * 2 * 64) == 0 && K / (S * 2) >= 256) S *= 2;
+  while (S < 16 && K % (S * 2 * 64) == 0 && K / (S * 2) >= 256 &&
+         (tiles * S < 256 || (rows <= 32 && (tiles * S + 255) / 256 * 256 * 4 > tiles * S * 5)))
+    S *= 2;
   return S;
 }
 
 // Few rows (a block-only step of the cached decode modes: 32 or 64 rows): every GEMM is bound by
 // streaming its weights once, which needs several workgroups per CU with deep rings in flight.
-// 32- or 64-row tiles, 128 columns, K split `splits` ways into fp32 partials; up to three weight
+// K split `splits` ways into fp32 partials; up to three weight
 // matrices of n_sub rows each are stacked along N (Q/K/V, gate/up) so that one launch covers them.
 // The nonlinear epilogues (RoPE, SwiGLU) run afterwards on the summed partials.
+//   Up to 32 rows two wavefronts take 64 columns: a ring of six stages while two workgroups to a CU are all there are, of four
+// where three fit (us at 4096 / 12288 wide, these / tiles of 128 columns with four wavefronts and the ranges that those need:
+// Q/K/V 20.6 / 21.2, output 8.0 / 8.2 with half the partials, down 20.6 / 21.3 with half the partials; four ranges of the
+// last layer's down projection 20.6 / 27.8).
 void launch_gemm_skinny_bf16(const bf16* A, const bf16* w0, const bf16* w1, const bf16* w2, int n_sub, float* parts,
                              size_t part_stride, int M, int N, int K, int splits, Gate g, hipStream_t s) {
   FewArgs a = {};
   a.A = A; a.B0 = w0; a.B1 = w1; a.B2 = w2; a.n_sub = w1 ? n_sub : 0;
   a.M = M; a.N = N; a.K = K; a.splits = splits; a.gate = g;
   a.parts = parts; a.part_stride = part_stride;
-  if (M <= 32) launch<32, 128, 64, 1, 4, 4, EPI_PARTIAL>(a, s);
-  else launch<64, 128, 64, 2, 2, 4, EPI_PARTIAL>(a, s);
+  if (M > 32) launch<64, 128, 64, 2, 2, 4, EPI_PARTIAL>(a, s);
+  else if ((N + 63) / 64 * splits <= 512) launch<32, 64, 64, 1, 2, 6, EPI_PARTIAL>(a, s);
+  else launch<32, 64, 64, 1, 2, 4, EPI_PARTIAL>(a, s);
 }
 
 // Few rows and a wide FFN: 64 (32 gate + 32 up) columns per workgroup already make a few hundred

@@ -128,8 +128,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
     const int shapes[4][2] = {{3 * m.d_model, m.d_model}, {m.d_model, m.d_model}, {2 * m.d_ffn, m.d_model},
                               {m.d_model, m.d_ffn}};
     for (auto& sh : shapes) {
-      const size_t b = (size_t)skinny_splits(sh[0], sh[1]) * kSkinnyRows * sh[0] * 4;
-      if (b > skinny) skinny = b;
+      for (int r : {32, kSkinnyRows}) skinny = std::max(skinny, (size_t)skinny_splits(r, sh[0], sh[1]) * r * sh[0] * 4);
     }
     // wide path: the [d, d] and [d, F] projections split K as far as wide_splits says for the number of
     // rows at hand (it depends on the count of 128-row tiles only, so the top of every bucket is the worst case)
@@ -287,7 +286,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       QkvEpilogue e = {q, ks, vts, rope, p.Tq, p.pos0, L.Tpad, H, Dh, d, seq_gb, p.pos_per_gb};
       { Timed t(c, L2PD_K_GEMM_QKV, s);
         if (skinny) {
-          const int S = skinny_splits(3 * d, d);
+          const int S = skinny_splits(rows, 3 * d, d);
           const size_t stride = (size_t)rows * 3 * d;
           launch_gemm_skinny_bf16(xn, (const bf16*)c->wq[l], (const bf16*)c->wk[l], (const bf16*)c->wv[l], d, parts,
                                   stride, rows, 3 * d, d, S, g, s);
@@ -342,8 +341,8 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
                          p.tk_dev, QueryRows{0, 0, 0, nullptr}, g, s); }
       // Few row tiles leave CUs idle on the [d, d] and [d, F] projections: split K as far as
       // wide_splits (wide path) or skinny_splits (few-row path) says.
-      const int so = skinny ? skinny_splits(d, d) : wide_splits(rows, d, d, rows);
-      const int sd = skinny ? skinny_splits(d, F) : wide_splits(rows, d, F, rows);
+      const int so = skinny ? skinny_splits(rows, d, d) : wide_splits(rows, d, d, rows);
+      const int sd = skinny ? skinny_splits(rows, d, F) : wide_splits(rows, d, F, rows);
       // A projection whose workgroups hold whole sums adds them to h itself (what the RMSNorm would do with a single
       // partial, same bits): the sums are not written and read back
       // (1.5 % of a step of 4096 rows).
@@ -360,7 +359,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       bf16* act = c->at<bf16>(L.act);
       { Timed t(c, L2PD_K_GEMM_GATEUP, s);
         if (skinny && !swiglu_few_rows_fused(rows, F)) {
-          const int S = skinny_splits(2 * F, d);
+          const int S = skinny_splits(rows, 2 * F, d);
           const size_t stride = (size_t)rows * 2 * F;
           launch_gemm_skinny_bf16(xn, (const bf16*)c->wg[l], (const bf16*)c->wu[l], nullptr, F, parts, stride, rows,
                                   2 * F, d, S, g, s);
