@@ -688,6 +688,9 @@ void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16
 // the 8B shape four workgroups per tile occupy the chip (down projection 50 us; 83 with unsplit 128x64 tiles), at 2048
 // and more there is a tile per CU, and three more partials to write and to fold only cost (171 us and the RMSNorm
 // 28, against 141 and 60 estimated for 256x256 tiles and four partials).
+//   Four ranges from K = 8192 on, two below: two partials less to write and to fold. us, output projection of 4096 with two
+// / four ranges: 512 rows 30.1 / 26.5, the RMSNorm behind it 6.5 / 10; 768 rows 45 / 43 and 8 / 14; 1024 rows 49 / 52, 1280
+// rows 58 / 70. Steps: 3072 rows of 1024 (down K = 2816 too) 1233 -> 1192, 1280 rows of 4096 2050 -> 2022, 512 rows 2073 -> 2080.
 // Up to 256 rows (batched block-only steps of the cached modes) the split may go up to eight ways, as the estimate
 // says: 256 rows of the 8B shape split 4 ways, 128 rows 8 ways.
 // Rows that are some of a pass's (the wanted ones behind the last layer's attention) take the number of ranges of
@@ -704,7 +707,7 @@ static PartialPlan plan_small_pass(int M, int N, int K) {
 }
 int k_ranges(int pass_rows, int N, int K) {
   if (pass_rows <= 256) return plan_small_pass(pass_rows, N, K).splits;
-  if (K % 256 == 0 && K / 4 >= 512) return 4;
+  if (K % 256 == 0 && K / 4 >= 2048) return 4;
   return K % 128 == 0 && K / 2 >= 512 ? 2 : 1;
 }
 static PartialPlan plan_partial(int M, int N, int K, int pass_rows) {
