@@ -57,6 +57,11 @@ __device__ __forceinline__ int map_row(const RowMap& m, int r, const int* ctl) {
   return (r / m.rows_per_seq) * m.seq_stride + m.off_base + gb * m.off_per_gb + (r % m.rows_per_seq);
 }
 
+// whether map_row moves any of the first `rows` rows
+inline bool row_map_moves(const RowMap& m, int rows) {
+  return m.off_base || m.off_per_gb || (rows > m.rows_per_seq && m.seq_stride != m.rows_per_seq);
+}
+
 // exp(-x) for x >= 0: the product with log2(e) in two parts, the small one applied to the result to first order
 // (about 1 ulp, a third of the instructions of expf).  Beyond 200 the result is 0 (and the two parts would be
 // infinities of opposite sign); NaN stays NaN.
@@ -202,8 +207,11 @@ struct F32Product {
   int pos_per_gb;
   LmHeadEpilogue lm;
   Gate gate;
+  // filled in by launch_product_f32: rows are not simply 0, 1, ...; divisions by H * Dh / 2, Dh / 2 and Tq
+  int mapped;
+  Div per_mat, half, per_seq;
 };
-void launch_product_f32(const F32Product& a, int kind, hipStream_t s);
+void launch_product_f32(F32Product a, int kind, hipStream_t s);
 int f32_lmhead_cols(int rows, int V);   // 32 or 64
 void launch_attn_f32(const float* q, const float* kstore, const float* vstore, float* out, int B, int Tq, int Tk,
                      int Tmax, int H, int Dh, const int* tk_dev, Gate g, hipStream_t s);

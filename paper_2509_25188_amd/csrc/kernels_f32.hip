@@ -29,9 +29,9 @@ template <int EPI>
 __device__ __forceinline__ const float* weight_row(const F32Product& a, int f, int side) {
   f = min(f, a.N - 1);
   if constexpr (EPI == EPI_ROPE) {
-    const int half = a.Dh / 2, per = a.H * half, mat = f / per, i = f % per;
+    const int half = a.Dh / 2, mat = a.per_mat(f), i = f - mat * a.H * half, head = a.half(i);
     const float* W = mat == 0 ? a.W[0] : (mat == 1 ? a.W[1] : a.W[2]);
-    return W + (size_t)(i / half * a.Dh + i % half + side * half) * a.K;
+    return W + (size_t)(head * a.Dh + i - head * half + side * half) * a.K;
   } else if constexpr (EPI == EPI_SWIGLU) {
     return a.W[side] + (size_t)f * a.K;
   } else {
@@ -50,9 +50,9 @@ __device__ __forceinline__ void put_swiglu(const F32Product& a, int row, int f, 
 // rotate-half pairs (i, i + Dh/2): q rotated in place of the product, k rotated and v as it is into the stores
 __device__ __forceinline__ void put_rope(const F32Product& a, int row, int f, float x1, float x2) {
   if (row >= a.M || f >= a.N) return;
-  const int half = a.Dh / 2, per = a.H * half, mat = f / per, i = f % per, e = i % half;
-  const int b = row / a.Tq, pos = a.pos0 + seq_pos_offset(a.seq_gb, a.pos_per_gb, b) + row % a.Tq;
-  const int d = a.H * a.Dh, col = i / half * a.Dh + e;
+  const int half = a.Dh / 2, mat = a.per_mat(f), i = f - mat * a.H * half, head = a.half(i), e = i - head * half;
+  const int b = a.per_seq(row), pos = a.pos0 + seq_pos_offset(a.seq_gb, a.pos_per_gb, b) + row - b * a.Tq;
+  const int d = a.H * a.Dh, col = head * a.Dh + e;
   float* o = mat == 0 ? a.C + (size_t)row * d + col : (mat == 1 ? a.kstore : a.vstore) + ((size_t)b * a.Tmax + pos) * d + col;
   if (mat < 2) {
     const float2 rot = a.rope[(size_t)pos * half + e];
@@ -124,7 +124,7 @@ __device__ __forceinline__ void put_row(const F32Product& a, int row, int f0, in
 
 template <int FM, int FN, int KS, int EPI, bool NORM, bool VEC>
 __global__ void __launch_bounds__(256) k_product_f32(F32Product a) {
-  if (gate_skip(a.gate)) return;
+  const int2 gate = gate_words(a.gate);        // looked at when the first loads are on their way
   static_assert(KS == 1 || (KS == 4 && FM == 1), "four wavefronts share one row of fragments, or none");
   constexpr int U = KS == 4 ? 4 : 1;           // 16-deep K steps per round of loads
   constexpr int TN = (pair_epi(EPI) ? FN / 2 : FN) * 16;   // features of a tile
@@ -143,7 +143,8 @@ __global__ void __launch_bounds__(256) k_product_f32(F32Product a) {
   const float* pw[FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
-    int r = map_row(a.rows, min(m0 + i * 16 + cl, a.M - 1), a.gate.ctl);
+    int r = min(m0 + i * 16 + cl, a.M - 1);
+    if (a.mapped) r = map_row(a.rows, r, a.gate.ctl);
     if (a.tokens) r = a.tokens[r];
     pa[i] = a.A + (size_t)r * a.K + g * 4;
   }
@@ -219,16 +220,18 @@ __global__ void __launch_bounds__(256) k_product_f32(F32Product a) {
     const int c1 = min(steps, (z + 1) * per);
     Round r0, r1;
     load(r0, z * per, c1);
+    if (gate_closed(a.gate, gate)) return false;
     for (int c = z * per; c < c1; c += 2 * U) {
       load(r1, c + U, c1);
       work(r0, c, c1);
       load(r0, c + 2 * U, c1);
       work(r1, c + U, c1);
     }
+    return true;
   };
   clear();
   if constexpr (KS == 4) {
-    range(wave);
+    if (!range(wave)) return;
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
@@ -255,7 +258,7 @@ __global__ void __launch_bounds__(256) k_product_f32(F32Product a) {
     float tss[FM];
     for (int z = 0; z < 4; ++z) {
       if (z > 0) clear();
-      range(z);
+      if (!range(z)) return;
 #pragma unroll
       for (int i = 0; i < FM; ++i) {
         tss[i] = z == 0 ? ss[i] : tss[i] + ss[i];
@@ -451,7 +454,9 @@ void launch_attn(const float* q, const float* kstore, const float* vstore, float
 
 int f32_lmhead_cols(int rows, int V) { return big_product(rows, V) ? 64 : 32; }
 
-void launch_product_f32(const F32Product& a, int kind, hipStream_t s) {
+void launch_product_f32(F32Product a, int kind, hipStream_t s) {
+  a.mapped = row_map_moves(a.rows, a.M);
+  if (kind == F32_QKV) { a.per_mat = Div(a.H * (a.Dh / 2)); a.half = Div(a.Dh / 2); a.per_seq = Div(a.Tq); }
   if (kind == F32_QKV) launch_product<EPI_ROPE, true>(a, s);
   else if (kind == F32_SWIGLU) launch_product<EPI_SWIGLU, true>(a, s);
   else if (kind == F32_LMHEAD) launch_product<EPI_LMHEAD, true>(a, s);

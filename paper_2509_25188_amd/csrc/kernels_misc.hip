@@ -344,7 +344,7 @@ static bool launch_rmsnorm_row(const NormArgs& a, int n_parts, int rows, hipStre
 void launch_rmsnorm(float* h, const float* parts, int n_parts, size_t part_stride, RowMap src, const bf16* gain, bf16* y,
                     int rows, int d, float eps, bool write_back, Gate g, hipStream_t s, float* h_out) {
   if (!parts) n_parts = 0;
-  const bool mapped = src.off_base || src.off_per_gb || (rows > src.rows_per_seq && src.seq_stride != src.rows_per_seq);
+  const bool mapped = row_map_moves(src, rows);
   if (d % 4 == 0 && reinterpret_cast<uintptr_t>(gain) % 8 == 0) {
     const NormArgs a = {h, parts, part_stride, gain, y, h_out, src, d, mapped, write_back, eps, g};
     if (d <= 1024 ? launch_rmsnorm_row<4, 64>(a, n_parts, rows, s)
