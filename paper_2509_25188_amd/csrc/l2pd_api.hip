@@ -122,26 +122,7 @@ Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cac
   L.kstore = c.take(kv_one * n_kv);
   L.vstore = c.take(kv_one * n_kv);
   if (m.dtype == L2PD_BF16) {
-    // fp32 split-K partials: two [rows, d] buffers on the wide path; on the few-row path up to
-    // kSkinnyRows rows of every K range of the widest stacked projection
-    size_t skinny = 0;
-    const int shapes[4][2] = {{3 * m.d_model, m.d_model}, {m.d_model, m.d_model}, {2 * m.d_ffn, m.d_model},
-                              {m.d_model, m.d_ffn}};
-    for (auto& sh : shapes) {
-      for (int r : {32, kSkinnyRows}) skinny = std::max(skinny, (size_t)skinny_splits(r, sh[0], sh[1]) * r * sh[0] * 4);
-    }
-    // wide path: the [d, d] and [d, F] projections split K as far as wide_splits says for the number of
-    // rows at hand (it depends on the count of 128-row tiles only, so the top of every bucket is the worst case)
-    size_t wide = 0;
-    for (size_t top = 128;; top += 128) {
-      const size_t M = top < rows ? top : rows;
-      int S = 1;
-      for (int k : {m.d_model, m.d_ffn})
-        for (int pass : {(int)M, std::max((int)M, 257)}) S = std::max(S, wide_splits((int)M, m.d_model, k, pass));
-      wide = std::max(wide, (size_t)S * M * d * 4);
-      if (top >= rows) break;
-    }
-    L.parts = c.take(wide > skinny ? wide : skinny);
+    L.parts = c.take(partial_floats((long long)rows, m.d_model, m.d_ffn) * 4);
     L.attn_ws_bytes = attn_chunk_ws_bytes(m.n_heads, m.head_dim);
     L.attn_ws = c.take(L.attn_ws_bytes);
   }
