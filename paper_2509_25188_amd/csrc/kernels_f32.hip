@@ -394,14 +394,15 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, c
       }
     tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-    const float mn = fmaxf(m, tmax), alpha = exp_neg(mn - m);   // (m = -inf at first: 0)
+    // (m = -inf at first: alpha 0; scores of -inf alone so far: relative to the lowest number, sums of zero)
+    const float mn = fmaxf(m, tmax), ref = fmaxf(mn, -3.402823466e38f), alpha = exp_neg(ref - m);
     m = mn;
     l *= alpha;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        p[u][r] = exp_neg(mn - p[u][r]);
+        p[u][r] = exp_neg(ref - p[u][r]);
         l += p[u][r];
       }
 #pragma unroll
