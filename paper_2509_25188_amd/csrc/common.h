@@ -186,7 +186,7 @@ struct LmHeadEpilogue {
 //               [B, Tmax, H * Dh] stores at pos0 + t (seq_gb / pos_per_gb: per-sequence offsets as in QkvEpilogue).
 //               N = 3 * H * Dh / 2 pairs
 //   F32_SWIGLU  normalised rows times W[0], W[1]: silu(.) * . into C [rows, N]
-//   F32_LMHEAD  normalised rows times W[0]: logits and partials; a part is f32_lmhead_cols columns
+//   F32_LMHEAD  normalised rows times W[0]: logits and partials, f32_lmhead_n_part of them a row
 //   F32_PLAIN   C [rows, N] (+)= A W[0]^T
 enum { F32_PLAIN = 0, F32_QKV = 1, F32_SWIGLU = 2, F32_LMHEAD = 3 };
 struct F32Product {
@@ -212,7 +212,7 @@ struct F32Product {
   Div per_mat, half, per_seq;
 };
 void launch_product_f32(F32Product a, int kind, hipStream_t s);
-int f32_lmhead_cols(int rows, int V);   // 32 or 64
+int f32_lmhead_n_part(int V);
 void launch_attn_f32(const float* q, const float* kstore, const float* vstore, float* out, int B, int Tq, int Tk,
                      int Tmax, int H, int Dh, const int* tk_dev, Gate g, hipStream_t s);
 

@@ -22,6 +22,7 @@ namespace {
 //   NORM: rows are RMS-normalised on the way: gain is multiplied in as the row is read, the row's sum of squares is formed
 // beside the products, and the sums are scaled at the end.
 enum { EPI_PLAIN = 0, EPI_ROPE = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3 };
+constexpr int kHeadPart = 32;    // columns of a part of the vocabulary reduction
 constexpr bool pair_epi(int epi) { return epi == EPI_ROPE || epi == EPI_SWIGLU; }
 
 // Weight row behind feature f (pair epilogues: side 0 or 1 of it).
@@ -63,16 +64,18 @@ __device__ __forceinline__ void put_rope(const F32Product& a, int row, int f, fl
   o[0] = x1;
   o[half] = x2;
 }
-// The row's logits in this tile, NF fragments of 16 columns from f0 (lane cl holds column f0 + 16 j + cl): logits, and the
-// tile's (max, sum exp(x - max), lowest column that has the maximum), the mask id being no candidate.
-template <int NF>
-__device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0, int cl, float (&x)[NF]) {
+// The row's logits of one part of the vocabulary, 32 columns from f0 (lane cl holds columns f0 + cl and f0 + 16 + cl): logits,
+// and the part's (max, sum exp(x - max), lowest column that has the maximum), the mask id being no candidate.  Parts are of
+// 32 columns whatever the tile, so that a row's sums, and with them its confidence, do not depend on the batch it is in.
+__device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0, int cl, float x0, float x1) {
+  if (f0 >= a.N) return;                       // (the rest of a 64-column tile past the vocabulary)
+  float x[2] = {x0, x1};
   const LmHeadEpilogue& e = a.lm;
   const bool biased = e.bias.value != 0.f && a.gate.ctl && row < a.M &&
                       a.gate.ctl[CTL_SEQ_GB + row / e.bias.block_len] * e.bias.block_len + row % e.bias.block_len >= e.bias.gen_pos_from;
   float m = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < NF; ++j) {
+  for (int j = 0; j < 2; ++j) {
     const int col = f0 + 16 * j + cl;
     if (biased && col == e.bias.token_id) x[j] += e.bias.value;
     if (e.logits && row < a.M && col < a.N) e.logits[(size_t)row * a.N + col] = x[j];
@@ -87,9 +90,9 @@ __device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0,
   int mi = 0x7fffffff;
   float sum = 0.f;
 #pragma unroll
-  for (int j = NF - 1; j >= 0; --j) mi = x[j] == m && m > -INFINITY ? f0 + 16 * j + cl : mi;
+  for (int j = 1; j >= 0; --j) mi = x[j] == m && m > -INFINITY ? f0 + 16 * j + cl : mi;
 #pragma unroll
-  for (int j = 0; j < NF; ++j) sum += m == -INFINITY ? 0.f : exp_neg(m - x[j]);
+  for (int j = 0; j < 2; ++j) sum += m == -INFINITY ? 0.f : exp_neg(m - x[j]);
   mi = min(mi, (int)dpp<kDppRor + 8>((unsigned)mi));
   mi = min(mi, (int)dpp<kDppRor + 4>((unsigned)mi));
   mi = min(mi, (int)dpp<kDppRor + 2>((unsigned)mi));
@@ -99,7 +102,7 @@ __device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0,
   sum += dppf<kDppRor + 2>(sum);
   sum += dppf<kDppRor + 1>(sum);
   if (cl == 0 && row < a.M) {
-    const size_t o = (size_t)row * e.n_part + f0 / (16 * NF);
+    const size_t o = (size_t)row * e.n_part + f0 / kHeadPart;
     e.part_max[o] = m;
     e.part_sum[o] = sum;
     e.part_idx[o] = mi;
@@ -109,7 +112,8 @@ __device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0,
 template <int EPI, int FN>
 __device__ __forceinline__ void put_row(const F32Product& a, int row, int f0, int cl, float (&v)[FN]) {
   if constexpr (EPI == EPI_LMHEAD) {
-    put_lmhead<FN>(a, row, f0, cl, v);
+#pragma unroll
+    for (int p = 0; p < FN / 2; ++p) put_lmhead(a, row, f0 + 32 * p, cl, v[2 * p], v[2 * p + 1]);
   } else if constexpr (pair_epi(EPI)) {
 #pragma unroll
     for (int p = 0; p < FN / 2; ++p) {
@@ -453,7 +457,7 @@ void launch_attn(const float* q, const float* kstore, const float* vstore, float
 
 }  // namespace
 
-int f32_lmhead_cols(int rows, int V) { return big_product(rows, V) ? 64 : 32; }
+int f32_lmhead_n_part(int V) { return (V + kHeadPart - 1) / kHeadPart; }
 
 void launch_product_f32(F32Product a, int kind, hipStream_t s) {
   a.mapped = row_map_moves(a.rows, a.M);

@@ -91,14 +91,19 @@ int desc_supported(const l2pd_model_desc* d) {
   return L2PD_OK;
 }
 
+// Parts of the vocabulary reduction of a head row.
+int head_parts(const l2pd_model_desc& m) {
+  return m.dtype == L2PD_BF16 ? lmhead_n_part(m.vocab) : f32_lmhead_n_part(m.vocab);
+}
+
 Layout make_layout(const l2pd_model_desc& m, int max_batch, int max_seq, int cache) {
   Layout L = {};
   Carver c;
   const size_t es = m.dtype == L2PD_FP32 ? 4 : 2;
   const size_t rows = (size_t)max_batch * max_seq;
-  const size_t d = m.d_model, F = m.d_ffn, V = m.vocab;
+  const size_t d = m.d_model, F = m.d_ffn;
   L.Tpad = (int)align_up(max_seq, 64);
-  const size_t n_part = m.dtype == L2PD_FP32 ? (V + 31) / 32 : lmhead_n_part((int)V);   // the most that a head pass may have
+  const size_t n_part = head_parts(m);
   const size_t head_rows = (size_t)max_batch * 256;   // block_len <= 256
   L.rope = c.take((size_t)L.Tpad * (m.head_dim / 2) * 8);
   L.ctl = c.take((size_t)(CTL_WORDS + 2 * max_batch) * 4);   // control words, per-sequence blocks, per-sequence done flags
@@ -366,14 +371,6 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
   c->pend_stride = pend_stride;
 }
 
-// Parts of the vocabulary reduction over `rows` head rows.
-int head_parts(const l2pd_ctx* c, int rows) {
-  const int V = c->m.vocab;
-  if (c->m.dtype == L2PD_BF16) return lmhead_n_part(V);
-  const int cols = f32_lmhead_cols(rows, V);
-  return (V + cols - 1) / cols;
-}
-
 // Final RMSNorm of the selected rows + LM head.  Produces the vocabulary partials (and optionally
 // the fp32 logits) of `n_rows_per_seq` rows per sequence, taken from h through `src`.
 void run_head(l2pd_ctx* c, int B, int n_rows_per_seq, RowMap src, float* logits_out, bool want_parts,
@@ -390,7 +387,7 @@ void run_head(l2pd_ctx* c, int B, int n_rows_per_seq, RowMap src, float* logits_
     e.part_sum = c->at<float>(L.part_sum);
     e.part_idx = c->at<int32_t>(L.part_idx);
   }
-  e.n_part = head_parts(c, hr);
+  e.n_part = head_parts(m);
   e.mask_id = m.mask_id;
   e.bias = bias;
   if (m.dtype == L2PD_FP32) {
@@ -531,7 +528,7 @@ void run_step(l2pd_ctx* c, int32_t* X, int B, int P, const l2pd_decode_cfg* cfg,
   u.X = X; u.state = state; u.B = B; u.P = P; u.T = T; u.s = sl; u.n_blocks = nb;
   u.mask_id = c->m.mask_id; u.eos_id = c->m.eos_id; u.eotp = cfg->eotp;
   u.part_max = c->at<float>(L.part_max); u.part_sum = c->at<float>(L.part_sum);
-  u.part_idx = c->at<int32_t>(L.part_idx); u.n_part = head_parts(c, B * sl);
+  u.part_idx = c->at<int32_t>(L.part_idx); u.n_part = head_parts(c->m);
   if (f) {
     for (int k = 0; k < f->n_layers; ++k) { u.fw[k] = f->w_dev[k]; u.fb[k] = f->b_dev[k]; }
     u.n_layers = f->n_layers;
