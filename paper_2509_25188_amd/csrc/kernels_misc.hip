@@ -543,7 +543,8 @@ __global__ void __launch_bounds__(1024) k_update(UpdateArgs a, Gate g) {
     if (m < M) idx = 0x7fffffff;
     sum = wave_reduce(sum, [](float x, float y) { return x + y; });
     idx = wave_reduce(idx, [](int x, int y) { return min(x, y); });
-    if (lane == 0) { s_conf[j] = 1.f / sum; s_pred[j] = idx; }
+    // (no logit above -inf: the lowest token that may be committed, since what is committed indexes the embedding next)
+    if (lane == 0) { s_conf[j] = 1.f / sum; s_pred[j] = idx != 0x7fffffff ? idx : (a.mask_id == 0 ? 1 : 0); }
   }
 #pragma unroll
   for (int k = 0; k < kFilterMaxLayers; ++k) {
