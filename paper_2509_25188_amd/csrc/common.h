@@ -244,7 +244,7 @@ int k_ranges(int pass_rows, int N, int K);   // K ranges that a [pass_rows, N] p
 // multiple of the 64-wide stage.
 constexpr int kSkinnyRows = 64;
 constexpr int kSkinnyRowsAttn = 64;   // B * Tq up to which attention may chunk the keys across workgroups
-int skinny_splits(int rows, int N, int K);
+int skinny_splits(int N, int K);
 int wide_splits(int M, int N, int K, int pass_rows);   // partial buffers the wide path's [d, d] / [d, F] projections write, at most 8
 size_t partial_floats(long long rows, int d, int F);   // split-K partials of any pass of up to `rows` rows
 void launch_gemm_skinny_bf16(const bf16* A, const bf16* w0, const bf16* w1, const bf16* w2, int n_sub, float* parts,

@@ -739,8 +739,7 @@ int wide_splits(int M, int N, int K, int pass_rows) { return plan_partial(M, N, 
 size_t partial_floats(long long rows, int d, int F) {
   size_t most = 0;
   const int shapes[4][2] = {{3 * d, d}, {d, d}, {2 * F, d}, {d, F}};
-  for (auto& sh : shapes)
-    for (int r : {32, kSkinnyRows}) most = std::max(most, (size_t)skinny_splits(r, sh[0], sh[1]) * r * sh[0]);
+  for (auto& sh : shapes) most = std::max(most, (size_t)skinny_splits(sh[0], sh[1]) * kSkinnyRows * sh[0]);
   for (long long top = 128;; top += top < 256 ? 64 : 128) {
     const int M = (int)std::min(top, rows);
     for (int k : {d, F})

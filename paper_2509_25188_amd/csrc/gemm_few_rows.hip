@@ -351,14 +351,15 @@ void launch(FewArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// K ranges of a step's projections.  Up to 32 rows, in tiles of 64 columns: until there is a workgroup for every CU, and
-// on until the last round of them is nearly full (Q/K/V of 4096: two ranges are 1.5 workgroups a CU, four are 3: 25.4
-// against 20.6 us); more only cost the RMSNorm behind.  Up to 64 rows, in tiles of 128: a few hundred workgroups.
-int skinny_splits(int rows, int N, int K) {
-  const int cols = rows <= 32 ? 64 : 128, tiles = (N + cols - 1) / cols;
+// K ranges of a step's projections, the same for all of up to 64 rows: a sequence's sums do not depend on how many others
+// share its launch.  Tiles of 64 columns: ranges until there is a workgroup for every CU, and on until the last round of
+// them is nearly full (Q/K/V of 4096: two ranges are 1.5 workgroups a CU, four are 3: 25.4 against 20.6 us); more only
+// cost the RMSNorm behind.
+int skinny_splits(int N, int K) {
+  const int tiles = (N + 63) / 64;
   int S = 1;
   while (S < 16 && K % (S * 2 * 64) == 0 && K / (S * 2) >= 256 &&
-         (tiles * S < 256 || (rows <= 32 && (tiles * S + 255) / 256 * 256 * 4 > tiles * S * 5)))
+         (tiles * S < 256 || (tiles * S + 255) / 256 * 256 * 4 > tiles * S * 5))
     S *= 2;
   return S;
 }
@@ -372,14 +373,21 @@ int skinny_splits(int rows, int N, int K) {
 // where three fit (us at 4096 / 12288 wide, these / tiles of 128 columns with four wavefronts and the ranges that those need:
 // Q/K/V 20.6 / 21.2, output 8.0 / 8.2 with half the partials, down 20.6 / 21.3 with half the partials; four ranges of the
 // last layer's down projection 20.6 / 27.8).
+//   Up to 64 rows, the same ranges: four wavefronts take 64 columns, with a ring of eight stages while there is a workgroup to
+// a CU at most, of five while there are two; beyond that 128 columns.  64 rows of 4096 / 12288, these / tiles of 128 columns with
+// twice the ranges: output and down 18.1 / 17.1 on average, the RMSNorm behind them 4.8 / 5.3, a step of eight layers 1451 / 1454;
+// of 1024 / 2816: output and down 6.8 / 7.9, gate/up 8.0 / 7.9, RMSNorm 3.0 / 3.6, a step 464 / 480; 48 rows of 4096: a step 1361 / 1378.
 void launch_gemm_skinny_bf16(const bf16* A, const bf16* w0, const bf16* w1, const bf16* w2, int n_sub, float* parts,
                              size_t part_stride, int M, int N, int K, int splits, Gate g, hipStream_t s) {
   FewArgs a = {};
   a.A = A; a.B0 = w0; a.B1 = w1; a.B2 = w2; a.n_sub = w1 ? n_sub : 0;
   a.M = M; a.N = N; a.K = K; a.splits = splits; a.gate = g;
   a.parts = parts; a.part_stride = part_stride;
-  if (M > 32) launch<64, 128, 64, 2, 2, 4, EPI_PARTIAL>(a, s);
-  else if ((N + 63) / 64 * splits <= 512) launch<32, 64, 64, 1, 2, 6, EPI_PARTIAL>(a, s);
+  const int groups = (N + 63) / 64 * splits;
+  if (M > 32 && groups <= 256) launch<64, 64, 64, 2, 2, 8, EPI_PARTIAL>(a, s);
+  else if (M > 32 && groups <= 512) launch<64, 64, 64, 2, 2, 5, EPI_PARTIAL>(a, s);
+  else if (M > 32) launch<64, 128, 64, 2, 2, 4, EPI_PARTIAL>(a, s);
+  else if (groups <= 512) launch<32, 64, 64, 1, 2, 6, EPI_PARTIAL>(a, s);
   else launch<32, 64, 64, 1, 2, 4, EPI_PARTIAL>(a, s);
 }
 

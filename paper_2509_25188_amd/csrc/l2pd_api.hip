@@ -272,7 +272,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       QkvEpilogue e = {q, ks, vts, rope, p.Tq, p.pos0, L.Tpad, H, Dh, d, seq_gb, p.pos_per_gb};
       { Timed t(c, L2PD_K_GEMM_QKV, s);
         if (skinny) {
-          const int S = skinny_splits(rows, 3 * d, d);
+          const int S = skinny_splits(3 * d, d);
           const size_t stride = (size_t)rows * 3 * d;
           launch_gemm_skinny_bf16(xn, (const bf16*)c->wq[l], (const bf16*)c->wk[l], (const bf16*)c->wv[l], d, parts,
                                   stride, rows, 3 * d, d, S, g, s);
@@ -327,8 +327,8 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
                          p.tk_dev, QueryRows{0, 0, 0, nullptr}, g, s); }
       // Few row tiles leave CUs idle on the [d, d] and [d, F] projections: split K as far as
       // wide_splits (wide path) or skinny_splits (few-row path) says.
-      const int so = skinny ? skinny_splits(rows, d, d) : wide_splits(rows, d, d, rows);
-      const int sd = skinny ? skinny_splits(rows, d, F) : wide_splits(rows, d, F, rows);
+      const int so = skinny ? skinny_splits(d, d) : wide_splits(rows, d, d, rows);
+      const int sd = skinny ? skinny_splits(d, F) : wide_splits(rows, d, F, rows);
       // A projection whose workgroups hold whole sums adds them to h itself (what the RMSNorm would do with a single
       // partial, same bits): the sums are not written and read back
       // (1.5 % of a step of 4096 rows).
@@ -345,7 +345,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       bf16* act = c->at<bf16>(L.act);
       { Timed t(c, L2PD_K_GEMM_GATEUP, s);
         if (skinny && !swiglu_few_rows_fused(rows, F)) {
-          const int S = skinny_splits(rows, 2 * F, d);
+          const int S = skinny_splits(2 * F, d);
           const size_t stride = (size_t)rows * 2 * F;
           launch_gemm_skinny_bf16(xn, (const bf16*)c->wg[l], (const bf16*)c->wu[l], nullptr, F, parts, stride, rows,
                                   2 * F, d, S, g, s);

@@ -17,7 +17,7 @@ WIDTHS = (64, 576, 1024, 1088, 1152, 1216, 1344, 1536, 2048, 2752, 3072, 4096)
 
 def planners():
     lib = Bd.lib()
-    wide, few, ranges, size = (getattr(lib, n) for n in ("_ZN4l2pd11wide_splitsEiiii", "_ZN4l2pd13skinny_splitsEiii",
+    wide, few, ranges, size = (getattr(lib, n) for n in ("_ZN4l2pd11wide_splitsEiiii", "_ZN4l2pd13skinny_splitsEii",
                                                          "_ZN4l2pd8k_rangesEiii", "_ZN4l2pd14partial_floatsExii"))
     size.restype, size.argtypes = C.c_size_t, [C.c_longlong, C.c_int, C.c_int]
     return wide, few, ranges, size
@@ -30,7 +30,7 @@ def test_every_pass_fits(d):
         most = 0
         for M in range(1, ROWS + 1):
             if M <= FEW:
-                need = max(few(M, n, k) * M * n for n, k in ((3 * d, d), (d, d), (2 * F, d), (d, F)))
+                need = max(few(n, k) * M * n for n, k in ((3 * d, d), (d, d), (2 * F, d), (d, F)))
             else:
                 tail = M // 2        # the most wanted rows that the last layer's projections work on alone
                 need = max(wide(M, d, k, M) * M * d for k in (d, F))
