@@ -229,7 +229,10 @@ int32_t l2pd_filter_train(const l2pd_filter* filter, const float* conf_rows_dev,
                           int64_t n_rows, const l2pd_train_cfg* train_cfg, float* opt_state_dev,
                           float* loss_out_dev, void* stream);
 
-/* The same training with a workspace for partial gradients: the rows are dealt to workgroups, one or two launches an epoch.
+/* The same training with a workspace for partial gradients: the rows are dealt to workgroups, one or two launches an epoch
+ * (l2pd_filter_train is one launch in all).  So the call enqueues up to 2 * epochs + 1 kernels: 2.5 us of host time each until
+ * the stream's queue is full (some 16,000 launches), from then on it returns only shortly before the training ends; under
+ * stream capture each is a node (about 2 us and 1.5 KB a node to capture, a replay takes as long as the eager call).
  * l2pd_filter_train_workspace_bytes says how much a training on n_rows rows takes (0: one workgroup is the better
  * choice, or the filter is not supported).  workspace_dev: 256-byte aligned device scratch of at least that size
  * (L2PD_ENOMEM if smaller), never read before it is written, or null for l2pd_filter_train.  Results are those of
@@ -242,7 +245,7 @@ int32_t l2pd_filter_train_split(const l2pd_filter* filter, const float* conf_row
 /* l2pd_filter_train_split for callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): the same training, with the optimiser moments and the workspace
  * kept in a device array that is part of the library image instead of caller buffers.  The call allocates and frees
- * nothing, on the device or through any library.
+ * nothing, on the device or through any library, and launches what l2pd_filter_train_split does.
  *   - Limit: filters of at most 20480 parameters (10.4 MB per GPU, resident until the process
  *     ends); a larger filter returns L2PD_ENOMEM before anything is launched.  Every other argument and
  *     every result is as for l2pd_filter_train_split (same kernels, bit-identical parameters and losses).

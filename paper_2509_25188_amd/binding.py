@@ -290,7 +290,9 @@ def train_filter(flt: Dict[str, torch.Tensor], conf_rows: torch.Tensor, label_ro
                  static_scratch: bool = False):
     """Trains the filter IN PLACE (device fp32 tensors w1, b1, ..., wN, bN) on rows [n, s]; returns the
     per-epoch losses as a device tensor (`losses`, if given, receives them: [epochs] fp32 on the device).
-    `static_scratch` takes l2pd_filter_train_static: no buffer is allocated here either when `losses` is given."""
+    `static_scratch` takes l2pd_filter_train_static: no buffer is allocated here either when `losses` is given.
+    One launch or two are enqueued per epoch (one in all for few rows), so trainings of many thousand epochs keep the
+    host until shortly before their end."""
     for t in list(flt.values()) + [conf_rows, label_rows]:
         if t.dtype != torch.float32 or not t.is_contiguous() or not t.is_cuda:
             raise ValueError("train_filter needs contiguous fp32 device tensors")

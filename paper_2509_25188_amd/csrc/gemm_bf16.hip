@@ -632,6 +632,11 @@ static void launch_step(GemmArgs& a, hipStream_t s) {
 // 2 of 12288 columns).  A larger tile moves fewer bytes per flop, so it wins whenever there are enough of them:
 // 256x256 for thousands of rows; 512 rows x 24576 gate/up columns are exactly 256 tiles of 256x192, x 12288 Q/K/V
 // columns 256 of 128x192; 128x64 and 64x64 are for outputs too small to occupy the chip otherwise.
+// 128x128 and 128x64 tiles run in k_gemm_step, gate/up's 128x128 in k_gemm_turns; one figure stands for both, which differ
+// by less than the tiles do (us a round at 1024 rows and 4096 of K, in step / in turns: 128x128 Q/K/V 43.4 / 45.7, gate/up
+// 40.6 / 43.1, estimate 43; 128x64 29.4 / 30.8 and 28.6 / 29.3, estimate 30; at 256 rows equal within 1 %).  64x64: a launch
+// of one round 21-22 us, estimate 24; in several rounds two share a CU, 15.8 for 256 of them, where larger tiles are
+// faster still (Q/K/V of 1024 rows 190 us against 130 of 128x128).
 struct Tile { int bm, bn; double us; };
 constexpr Tile kTiles[7] = {{256, 256, 88.}, {256, 192, 71.}, {256, 128, 53.}, {128, 192, 48.}, {128, 128, 37.}, {128, 64, 24.}, {64, 64, 18.}};
 constexpr double kRoundUs = 6.;
@@ -690,7 +695,8 @@ void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16
 // 28, against 141 and 60 estimated for 256x256 tiles and four partials).
 //   Four ranges from K = 8192 on, two below: two partials less to write and to fold. us, output projection of 4096 with two
 // / four ranges: 512 rows 30.1 / 26.5, the RMSNorm behind it 6.5 / 10; 768 rows 45 / 43 and 8 / 14; 1024 rows 49 / 52, 1280
-// rows 58 / 70. Steps: 3072 rows of 1024 (down K = 2816 too) 1233 -> 1192, 1280 rows of 4096 2050 -> 2022, 512 rows 2073 -> 2080.
+// rows 58 / 70. Steps: 3072 rows of 1024 (down K = 2816 too) 1233 -> 1192, 1280 rows of 4096 2050 -> 2022; 512 rows, where the
+// projection loses what the norm gains, 2073 -> 2080 (within the spread of two runs).
 // Up to 256 rows (batched block-only steps of the cached modes) the split may go up to eight ways, as the estimate
 // says: 256 rows of the 8B shape split 4 ways, 128 rows 8 ways.
 // Rows that are some of a pass's (the wanted ones behind the last layer's attention) take the number of ranges of

@@ -15,9 +15,11 @@ CASES = [
     # (d, H, Dh, F, B, T)
     (64, 1, 64, 64, 1, 66), (128, 1, 128, 192, 1, 127), (320, 5, 64, 256, 1, 128), (384, 3, 128, 320, 1, 191),
     (448, 7, 64, 448, 1, 193), (512, 4, 128, 1472, 3, 83), (1024, 16, 64, 2816, 1, 221), (1024, 8, 128, 2816, 1, 97),
-    (1024, 16, 64, 2816, 2, 206),     # 412 rows: Q/K/V 128 x 64, gate/up 128 x 128, down 64 x 64 in four ranges
+    (1024, 16, 64, 2816, 2, 206),     # 412 rows: Q/K/V 128 x 64, gate/up 128 x 128, down 64 x 64 in two ranges
     (1344, 21, 64, 1344, 1, 450),     # Q/K/V 128 x 128
     (2048, 16, 128, 4096, 1, 190),
+    (1024, 8, 128, 8192, 1, 300),     # K = 8192 above 256 rows: down in four ranges
+    (512, 8, 64, 8320, 2, 150),
 ]
 
 
@@ -35,9 +37,10 @@ def test_edges_match_oracle(case):
         assert Pz.rel_err(got[b].cpu().numpy(), ora.forward(X[b].numpy())) < 2e-2, b
 
 
-def test_rows_are_the_same_bits_in_large_tiles():
+@pytest.mark.parametrize("F", [4096, 8192])     # the down projection in two ranges of K and in four
+def test_rows_are_the_same_bits_in_large_tiles(F):
     # 270 rows alone (64 x 64 and 128 x 64 tiles) and as one of twelve sequences (256-row tiles with wavefronts in turns)
-    m = synth.ModelShape(2, 1024, 8, 128, 4096, 300, 299, 298, dtype="bf16")
+    m = synth.ModelShape(2, 1024, 8, 128, F, 300, 299, 298, dtype="bf16")
     eng = Bd.Engine(m, synth.make_weights(m, 3, "cuda"), 12, 270)
     X = synth.make_prompt(5, 12, 270, 298, "cuda")
     many = eng.forward(X, 0, 200)

@@ -32,13 +32,26 @@ def train(flt, conf, label, epochs, split):
     return need, opt, loss
 
 
-# width, hidden, layers, rows
-SHAPES = [(32, 32, 2, 241), (32, 32, 2, 129), (64, 128, 2, 4096), (64, 128, 2, 17), (24, 40, 3, 333), (20, 1, 1, 1001),
-          (48, 48, 4, 2049), (1, 1, 2, 5000), (32, 32, 2, 20011), (128, 64, 2, 3001), (64, 128, 2, 16387)]
+# width, hidden, layers, rows; workgroups (1: not split) and launches an epoch that the plan takes.  The last has several chunks
+# of rows in a workgroup.
+SHAPES = [(32, 32, 2, 241, 16, 1), (32, 32, 2, 129, 9, 1), (64, 128, 2, 4096, 128, 2), (64, 128, 2, 17, 1, 0),
+          (24, 40, 3, 333, 21, 2), (20, 1, 1, 1001, 21, 1), (48, 48, 4, 2049, 65, 2), (1, 1, 2, 5000, 53, 1),
+          (32, 32, 2, 20011, 126, 2), (128, 64, 2, 3001, 94, 2), (64, 128, 2, 16387, 114, 2)]
 
 
-@pytest.mark.parametrize("s,h,L,n", SHAPES)
-def test_rows_over_workgroups_match_oracle_and_one_workgroup(s, h, L, n):
+def workspace_bytes(s, h, L, groups, launches):
+    """What such a plan asks for: two states of three images (parameters padded to 16, moments), and a partial gradient with
+    the losses of 16 wavefronts per workgroup, twice where one launch both applies and writes them."""
+    if groups == 1:
+        return 0
+    widths = [(x + 15) // 16 * 16 for x in [s] + [h] * (L - 1) + [s]]
+    image = sum(a * b for a, b in zip(widths, widths[1:])) + sum(widths[1:])
+    assert (groups * (image + 16) <= 1 << 16) == (launches == 1)      # partial gradients that every workgroup can read
+    return 4 * (6 * image + (2 if launches == 1 else 1) * groups * (image + 16))
+
+
+@pytest.mark.parametrize("s,h,L,n,groups,launches", SHAPES)
+def test_rows_over_workgroups_match_oracle_and_one_workgroup(s, h, L, n, groups, launches):
     r = np.random.default_rng(91)
     Cn = r.uniform(size=(n, s)).astype(np.float32)
     Yn = (r.uniform(size=(n, s)) < 0.2 + 0.6 * Cn).astype(np.float32)
@@ -51,7 +64,7 @@ def test_rows_over_workgroups_match_oracle_and_one_workgroup(s, h, L, n):
     need, opt, loss = train(many, Cd, Yd, epochs, True)
     again = {k: v.clone().cuda() for k, v in flt.items()}
     train(again, Cd, Yd, epochs, True)
-    assert need > 0 or n * s * h < 1 << 20
+    assert groups <= (n + 15) // 16 and need == workspace_bytes(s, h, L, groups, launches)
     ref, ref_losses = O.train_filter(Pz.np_filter(flt), Cn, Yn, epochs, lr=1e-3)
     np.testing.assert_allclose(loss.cpu().numpy(), ref_losses, rtol=1e-5, atol=1e-7)
     np.testing.assert_allclose(loss1.cpu().numpy(), ref_losses, rtol=1e-5, atol=1e-7)
