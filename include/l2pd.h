@@ -257,7 +257,8 @@ int32_t l2pd_filter_train_static(const l2pd_filter* filter, const float* conf_ro
                                  const float* label_rows_dev, int64_t n_rows, const l2pd_train_cfg* train_cfg,
                                  float* loss_out_dev, void* stream);
 
-/* Timing aid: kernel classes whose launches can be bracketed with HIP events on the launch stream. */
+/* Timing aid: kernel classes whose launches can be bracketed with HIP events on the launch stream.  (In fp32 models the
+ * RMSNorm is part of the product that reads it: L2PD_K_NORM counts no launches there.) */
 enum {
   L2PD_K_NONE = 0, L2PD_K_GEMM_QKV = 1, L2PD_K_GEMM_O = 2, L2PD_K_GEMM_GATEUP = 3,
   L2PD_K_GEMM_DOWN = 4, L2PD_K_ATTN = 5, L2PD_K_LMHEAD = 6, L2PD_K_NORM = 7, L2PD_K_UPDATE = 8

@@ -98,3 +98,31 @@ def test_workspace_is_checked_before_any_launch():
     assert call(work.data_ptr() + 4, need) == Bd.L2PD_EINVAL
     torch.cuda.synchronize()
     assert torch.equal(flt["w1"], w1)
+
+
+@pytest.mark.parametrize("s,h,n", [(32, 32, 241), (64, 128, 700)])     # one launch an epoch, and two
+def test_captured_training_equals_the_eager_one_on_every_replay(s, h, n):
+    r = np.random.default_rng(94)
+    conf = torch.tensor(r.uniform(size=(n, s)).astype(np.float32)).cuda()
+    label = (conf > 0.5).float()
+    first = {k: v.cuda() for k, v in synth.make_filter(95, s, h, "cpu").items()}
+    flt = {k: v.clone() for k, v in first.items()}
+    epochs = 40
+    want = Bd.train_filter(flt, conf, label, epochs, static_scratch=True).clone()      # (looks the array's address up)
+    trained = {k: v.clone() for k, v in flt.items()}
+    losses = torch.empty(epochs, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        Bd.train_filter(flt, conf, label, epochs, losses=losses, static_scratch=True)
+    for _ in range(4):
+        for k in flt:
+            flt[k].copy_(first[k])
+        losses.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(losses, want)
+        for k in flt:
+            assert torch.equal(flt[k], trained[k]), k
+        # eager work in between, in the same array
+        other = {k: v.clone() for k, v in first.items()}
+        Bd.train_filter(other, conf[:150], label[:150], 3, static_scratch=True)

@@ -1,7 +1,7 @@
-"""The entry point that allocates nothing: l2pd_filter_train_static keeps the optimiser moments in a
-device array of the library image.  Called through the C ABI with every buffer allocated beforehand,
-it must reproduce l2pd_filter_train (same kernel, caller-provided moments) bit for bit: on two calls
-in a row, the second on a smaller filter and fewer rows, so that whatever the first call left in the
+"""The entry point that allocates nothing: l2pd_filter_train_static keeps the optimiser moments and the workspace
+in a device array of the library image.  Called through the C ABI with every buffer allocated beforehand,
+it must reproduce l2pd_filter_train_split (same kernels, caller-provided moments and workspace; what train_filter
+calls) bit for bit: on two calls in a row, the second on a smaller filter and fewer rows, so that whatever the first call left in the
 shared array must not leak into the second."""
 import ctypes as C
 
