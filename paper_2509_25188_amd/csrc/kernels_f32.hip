@@ -318,8 +318,9 @@ void launch_product(const F32Product& a, hipStream_t s) {
 // among them in contiguous runs and join at the end (the same runs whatever the batch).  S^T = K Q^T, so that a lane holds
 // scores of one query (column cl; rows 4 g + r are keys) and its exponentials are the B operand of O^T = V^T P^T as they
 // are: MFMA r of a 16-key tile takes keys 4 g + r.  Operands from memory straight to registers, 32 keys a round, the values
-// sent off before the scores.  96 rows, 4 heads of 32: 5.0 us (7.2 with the values behind the scores, 8.9 with a wavefront per
-// query).
+// sent off before the scores, in heads of any size: asked for where they are needed, the 128 of a lane in heads of 256 are 16
+// round trips one after the other (a step of two layers, one head of 256, 32 queries over 1984 keys: 540 us, 1362 with the values
+// behind the scores, 885 with a wavefront per query).  96 rows, 4 heads of 32: 5.0 us (7.2 behind, 8.9 with a wavefront per query).
 // ND: 16-wide pieces of the head, padded with zeros.
 template <int ND, bool VEC>
 __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, const float* __restrict__ kstore,
@@ -363,19 +364,14 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, c
   for (int t = wave * per; t < t1; t += 2) {
     f32x4 s[2];
     float p[2][4];
-    // values of the round: sent off before the scores that they wait for (heads of up to 128)
-    float v[ND <= 8 ? ND : 1][2][4];
-    auto value = [&](int f, int u, int r) {
-      return f * 16 + cl < Dh ? vb[(size_t)min((t + u) * 16 + g * 4 + r, Tk - 1) * d + f * 16 + cl] : 0.f;
-    };
-    if constexpr (ND <= 8) {
+    float v[ND][2][4];      // values of the round: sent off before the scores that they wait for
 #pragma unroll
-      for (int f = 0; f < ND; ++f)
+    for (int f = 0; f < ND; ++f)
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) v[f][u][r] = value(f, u, r);
-    }
+        for (int r = 0; r < 4; ++r)
+          v[f][u][r] = f * 16 + cl < Dh ? vb[(size_t)min((t + u) * 16 + g * 4 + r, Tk - 1) * d + f * 16 + cl] : 0.f;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -416,7 +412,7 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, c
       for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          o[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(ND <= 8 ? v[ND <= 8 ? f : 0][u][r] : value(f, u, r), p[u][r], o[f], 0, 0, 0);
+          o[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[f][u][r], p[u][r], o[f], 0, 0, 0);
     }
   }
   l += __shfl_xor(l, 16, 64);
