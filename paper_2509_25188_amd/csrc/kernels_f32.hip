@@ -21,8 +21,7 @@ namespace {
 // 1,324 / 425; 8 x 512 rows, 2048 wide, FFN 4096: 19,707 / 9,417 (73 TFLOP/s).
 //   NORM: rows are RMS-normalised on the way: gain is multiplied in as the row is read, the row's sum of squares is formed
 // beside the products, and the sums are scaled at the end.
-enum { EPI_PLAIN = 0, EPI_ROPE = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3 };
-constexpr int kHeadPart = 32;    // columns of a part of the vocabulary reduction
+enum { EPI_PLAIN = 0, EPI_ROPE = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_LMHEAD_WIDE = 4 };   // LM head: parts of 32, 64 columns
 constexpr bool pair_epi(int epi) { return epi == EPI_ROPE || epi == EPI_SWIGLU; }
 
 // Weight row behind feature f (pair epilogues: side 0 or 1 of it).
@@ -64,20 +63,28 @@ __device__ __forceinline__ void put_rope(const F32Product& a, int row, int f, fl
   o[0] = x1;
   o[half] = x2;
 }
-// The row's logits of one part of the vocabulary, 32 columns from f0 (lane cl holds columns f0 + cl and f0 + 16 + cl): logits,
-// and the part's (max, sum exp(x - max), lowest column that has the maximum), the mask id being no candidate.  Parts are of
-// 32 columns whatever the tile, so that a row's sums, and with them its confidence, do not depend on the batch it is in.
-__device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0, int cl, float x0, float x1) {
-  if (f0 >= a.N) return;                       // (the rest of a 64-column tile past the vocabulary)
-  float x[2] = {x0, x1};
+// The row's logits of one part of the vocabulary, NF fragments of 16 columns from f0 (lane cl holds column f0 + 16 j + cl):
+// logits, and the part's (max, sum exp(x - max), lowest column that has the maximum), the mask id being no candidate.
+template <int NF>
+__device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0, int cl, const float* logits) {
+  if (NF == 2 && f0 >= a.N) return;            // (the rest of a 64-column tile past the vocabulary)
+  float x[NF];
+#pragma unroll
+  for (int j = 0; j < NF; ++j) x[j] = logits[j];
   const LmHeadEpilogue& e = a.lm;
-  const bool biased = e.bias.value != 0.f && a.gate.ctl && row < a.M &&
-                      a.gate.ctl[CTL_SEQ_GB + row / e.bias.block_len] * e.bias.block_len + row % e.bias.block_len >= e.bias.gen_pos_from;
+  if (e.bias.value != 0.f && (unsigned)(e.bias.token_id - f0) < 16u * NF && a.gate.ctl) {   // the biased token is in this part
+    const bool biased = row < a.M && a.gate.ctl[CTL_SEQ_GB + row / e.bias.block_len] * e.bias.block_len +
+                                             row % e.bias.block_len >= e.bias.gen_pos_from;
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+#pragma clang fp contract(off)                 // (a rounding less in one of the tiles would tell them apart)
+      if (biased && f0 + 16 * j + cl == e.bias.token_id) x[j] += e.bias.value;
+    }
+  }
   float m = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < NF; ++j) {
     const int col = f0 + 16 * j + cl;
-    if (biased && col == e.bias.token_id) x[j] += e.bias.value;
     if (e.logits && row < a.M && col < a.N) e.logits[(size_t)row * a.N + col] = x[j];
     if (col == e.mask_id || col >= a.N) x[j] = -INFINITY;
     m = fmaxf(m, x[j]);
@@ -90,9 +97,9 @@ __device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0,
   int mi = 0x7fffffff;
   float sum = 0.f;
 #pragma unroll
-  for (int j = 1; j >= 0; --j) mi = x[j] == m && m > -INFINITY ? f0 + 16 * j + cl : mi;
+  for (int j = NF - 1; j >= 0; --j) mi = x[j] == m && m > -INFINITY ? f0 + 16 * j + cl : mi;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) sum += m == -INFINITY ? 0.f : exp_neg(m - x[j]);
+  for (int j = 0; j < NF; ++j) sum += m == -INFINITY ? 0.f : exp_neg(m - x[j]);
   mi = min(mi, (int)dpp<kDppRor + 8>((unsigned)mi));
   mi = min(mi, (int)dpp<kDppRor + 4>((unsigned)mi));
   mi = min(mi, (int)dpp<kDppRor + 2>((unsigned)mi));
@@ -102,7 +109,7 @@ __device__ __forceinline__ void put_lmhead(const F32Product& a, int row, int f0,
   sum += dppf<kDppRor + 2>(sum);
   sum += dppf<kDppRor + 1>(sum);
   if (cl == 0 && row < a.M) {
-    const size_t o = (size_t)row * e.n_part + f0 / kHeadPart;
+    const size_t o = (size_t)row * e.n_part + f0 / (16 * NF);
     e.part_max[o] = m;
     e.part_sum[o] = sum;
     e.part_idx[o] = mi;
@@ -113,7 +120,9 @@ template <int EPI, int FN>
 __device__ __forceinline__ void put_row(const F32Product& a, int row, int f0, int cl, float (&v)[FN]) {
   if constexpr (EPI == EPI_LMHEAD) {
 #pragma unroll
-    for (int p = 0; p < FN / 2; ++p) put_lmhead(a, row, f0 + 32 * p, cl, v[2 * p], v[2 * p + 1]);
+    for (int p = 0; p < FN / 2; ++p) put_lmhead<2>(a, row, f0 + 32 * p, cl, v + 2 * p);
+  } else if constexpr (EPI == EPI_LMHEAD_WIDE) {
+    put_lmhead<FN>(a, row, f0, cl, v);
   } else if constexpr (pair_epi(EPI)) {
 #pragma unroll
     for (int p = 0; p < FN / 2; ++p) {
@@ -307,10 +316,11 @@ void launch_product(const F32Product& a, hipStream_t s) {
     if (vec) hipLaunchKernelGGL((k_product_f32<4, 4, 1, EPI, NORM, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_product_f32<4, 4, 1, EPI, NORM, false>), grid, dim3(256), 0, s, a);
   } else {
-    const int tn = 32 / sides;
+    constexpr int FN = EPI == EPI_LMHEAD_WIDE ? 4 : 2;
+    const int tn = 16 * FN / sides;
     const dim3 grid((a.N + tn - 1) / tn, (a.M + 15) / 16);
-    if (vec) hipLaunchKernelGGL((k_product_f32<1, 2, 4, EPI, NORM, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_product_f32<1, 2, 4, EPI, NORM, false>), grid, dim3(256), 0, s, a);
+    if (vec) hipLaunchKernelGGL((k_product_f32<1, FN, 4, EPI, NORM, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_product_f32<1, FN, 4, EPI, NORM, false>), grid, dim3(256), 0, s, a);
   }
 }
 
@@ -453,13 +463,19 @@ void launch_attn(const float* q, const float* kstore, const float* vstore, float
 
 }  // namespace
 
-int f32_lmhead_n_part(int V) { return (V + kHeadPart - 1) / kHeadPart; }
+// Parts of the vocabulary reduction: by the vocabulary alone, so that a row's sums, and with them its confidence, do not depend on
+// the batch it is in.  64 columns once the small tiles of 64 are a workgroup for every CU, 32 below.  us a step of two layers
+// of 128 (parts of 64 / 32; tiles of 32 and 64 with a part each, by the rows: the third): vocabulary 126,464, 32 head rows 169 / 191 / 170,
+// 512 rows 640 / 768 / 645; 50,000, 32 rows 83 / 88 / 88, 512 rows 348 / 404 / 349; 16,320 (- / 32 columns / by the rows), 32 rows - / 68 / 69, 512 rows - / 207 / 194.
+static int head_part_cols(int V) { return V > 255 * 64 ? 64 : 32; }
+int f32_lmhead_n_part(int V) { return (V + head_part_cols(V) - 1) / head_part_cols(V); }
 
 void launch_product_f32(F32Product a, int kind, hipStream_t s) {
   a.mapped = row_map_moves(a.rows, a.M);
   if (kind == F32_QKV) { a.per_mat = Div(a.H * (a.Dh / 2)); a.half = Div(a.Dh / 2); a.per_seq = Div(a.Tq); }
   if (kind == F32_QKV) launch_product<EPI_ROPE, true>(a, s);
   else if (kind == F32_SWIGLU) launch_product<EPI_SWIGLU, true>(a, s);
+  else if (kind == F32_LMHEAD && head_part_cols(a.N) == 64) launch_product<EPI_LMHEAD_WIDE, true>(a, s);
   else if (kind == F32_LMHEAD) launch_product<EPI_LMHEAD, true>(a, s);
   else launch_product<EPI_PLAIN, false>(a, s);
 }

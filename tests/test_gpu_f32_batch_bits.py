@@ -1,6 +1,6 @@
 """An fp32 denoising step gives a sequence the same bits whatever batch it is in: logits, confidences, tokens and filter
 outputs, with the head's products in large tiles (a batch) and in small ones (a sequence alone), and vocabularies that end in
-the first and the second half of a large tile."""
+the first and the second half of a large tile, and on either side of the size from which parts are 64 columns wide."""
 import pytest
 import torch
 
@@ -10,7 +10,7 @@ from paper_2509_25188_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("V,B,s", [(4100, 8, 128), (4139, 8, 128), (1024, 17, 256)])
+@pytest.mark.parametrize("V,B,s", [(4100, 8, 128), (4139, 8, 128), (1024, 17, 256), (16320, 6, 48), (16321, 6, 48), (40001, 5, 24)])
 def test_step_of_a_batch_gives_the_bits_of_each_sequence_alone(V, B, s):
     m = synth.ModelShape(2, 128, 4, 32, 256, V, V - 1, V - 2, dtype="fp32")
     weights = synth.make_weights(m, 820, "cuda", lm_head_scale=25.0)
