@@ -352,14 +352,15 @@ void launch(FewArgs& a, hipStream_t s) {
 }  // namespace
 
 // K ranges of a step's projections, the same for all of up to 64 rows: a sequence's sums do not depend on how many others
-// share its launch.  Tiles of 64 columns: ranges until there is a workgroup for every CU, and on until the last round of
-// them is nearly full (Q/K/V of 4096: two ranges are 1.5 workgroups a CU, four are 3: 25.4 against 20.6 us); more only
-// cost the RMSNorm behind.
+// share its launch.  Tiles of 64 columns: ranges until there is a workgroup for every CU, and on to two for every CU while the
+// last round of them is less than four fifths full (Q/K/V of 4096: two ranges are 1.5 workgroups a CU, four are 3: 25.4
+// against 20.6 us); more only cost what sums them (Q/K/V of 3072 in four ranges, 2.25 a CU, or eight: a step of eight layers
+// 793 / 811 us at 32 rows, 968 / 979 at 64).
 int skinny_splits(int N, int K) {
   const int tiles = (N + 63) / 64;
   int S = 1;
   while (S < 16 && K % (S * 2 * 64) == 0 && K / (S * 2) >= 256 &&
-         (tiles * S < 256 || (tiles * S + 255) / 256 * 256 * 4 > tiles * S * 5))
+         (tiles * S < 256 || (tiles * S < 512 && (tiles * S + 255) / 256 * 256 * 4 > tiles * S * 5)))
     S *= 2;
   return S;
 }
