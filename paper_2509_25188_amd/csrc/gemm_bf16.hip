@@ -493,14 +493,27 @@ __global__ void __launch_bounds__(512) k_gemm_turns(GemmArgs a) {
   else epilogue<BM, BN, WM, WN, EPI>(a, acc, smem, wm, wn, tile_m, tile_n, z);
 }
 
-// Up to so many rows a launch of cold weights is bound by their way from memory (dma16_once).  us, rows of 4096 with FFN 12288, loads
-// as they are / for weights used once: 256 rows, Q/K/V 45.6 / 43.7, gate/up 59.2 / 56.8, down 37.7 / 36.6, LM head 245 / 230; 512 rows
-// 56.9 / 55.9, 85.1 / 81.4, 49.7 / 48.4, 420 / 413; 768 rows and more equal within 1 %.
-constexpr int kColdRows = 512;
+// Whether a launch loads cold weights with the hint (dma16_once).  A panel's weights are read by each of its row tiles, and the hint
+// lets go of them early: it is for one row tile, or for row tiles that read a panel together.  They do on one XCD (its count of
+// tiles a multiple of them), if they are not two small ones to a CU (tiles of 128x128 on), and tiles of 128 rows if they are equally
+// long too (the last three quarters full; those of 256 rows go at the pace of their multiplications).  Otherwise the later one
+// goes to memory again.  us, loads as they are / with the hint, Q/K/V unless said:
+//   together  4096 wide, 256 rows 48.0 / 47.2, 512 rows 59.1 / 58.6, gate/up 67.0 / 66.2, 304 rows 63.1 / 62.3; 8192, 256 rows 124 / 113
+//   unequal   4096, 129 rows 41.5 / 47.8, gate/up 50.5 / 58.9, down 30.7 / 35.8; 5120, 129 rows 51.2 / 68.2, 257 rows 63.8 / 78.2
+//   an XCD's tiles no multiple of them   3584, 224 rows (168 tiles) 41.0 / 44.1, 384 rows (252) 43.2 / 45.2; 1536, 480 rows (144)
+//             22.9 / 23.9; 5120, 257 rows, gate/up (216 tiles of 256x256) 77.5 / 84.9
+//   small     3584, 192 rows (64x64) 38.8 / 42.4; 2048, 368 rows, output (128x64) 13.2 / 13.8
+// Beyond 512 rows equal within 1 %.
+bool read_once(int M, int N, int splits, int bm, int bn) {
+  const int tiles_m = (M + bm - 1) / bm, last = M - (tiles_m - 1) * bm;
+  if (M > 512 || tiles_m == 1) return M <= 512;
+  const TileMap map(tiles_m, (N + bn - 1) / bn, splits);
+  return bm >= 128 && bn >= 128 && (bm == 256 || 4 * last >= 3 * bm) && map.per_xcd % tiles_m == 0;
+}
 template <int BM, int BN, int WM, int WN, int DEPTH, int EPI, bool COLD = false>
 static void launch(GemmArgs& a, hipStream_t s) {
   if constexpr (!COLD && EPI != EPI_PARTIAL_SER)
-    if (a.gate.cold && a.M <= kColdRows) return launch<BM, BN, WM, WN, DEPTH, EPI, true>(a, s);
+    if (a.gate.cold && read_once(a.M, a.N, a.splits, BM, BN)) return launch<BM, BN, WM, WN, DEPTH, EPI, true>(a, s);
   auto kern = k_gemm_turns<BM, BN, WM, WN, DEPTH, EPI, COLD>;
   constexpr int smem = ((DEPTH + 1) * BM + DEPTH * BN) * 128;
   static DynLdsAttr attr;
@@ -630,7 +643,7 @@ __global__ void __launch_bounds__(WM * WN * 64) k_gemm_step(GemmArgs a) {
 template <int BM, int BN, int WM, int WN, int NS, int EPI, bool COLD = false>
 static void launch_step(GemmArgs& a, hipStream_t s) {
   if constexpr (!COLD)
-    if (a.gate.cold && a.M <= kColdRows) return launch_step<BM, BN, WM, WN, NS, EPI, true>(a, s);
+    if (a.gate.cold && read_once(a.M, a.N, a.splits, BM, BN)) return launch_step<BM, BN, WM, WN, NS, EPI, true>(a, s);
   auto kern = k_gemm_step<BM, BN, WM, WN, NS, EPI, COLD>;
   constexpr int smem = NS * (BM + BN) * 128;
   static DynLdsAttr attr;
