@@ -503,7 +503,8 @@ __global__ void __launch_bounds__(512) k_gemm_turns(GemmArgs a) {
 //   an XCD's tiles no multiple of them   3584, 224 rows (168 tiles) 41.0 / 44.1, 384 rows (252) 43.2 / 45.2; 1536, 480 rows (144)
 //             22.9 / 23.9; 5120, 257 rows, gate/up (216 tiles of 256x256) 77.5 / 84.9
 //   small     3584, 192 rows (64x64) 38.8 / 42.4; 2048, 368 rows, output (128x64) 13.2 / 13.8
-// Beyond 512 rows equal within 1 %.
+// Beyond 512 rows equal within 1 %.  Calls, without the hint or any later change / with it up to 512 rows / as here: one sequence of 129 rows,
+// three layers of 4096 x 12288 492 / 510 / 464, two of 5120 x 13824 482 / 512 / 457; 288 rows, six of 2048 x 5632 592 / 614 / 566.
 bool read_once(int M, int N, int splits, int bm, int bn) {
   const int tiles_m = (M + bm - 1) / bm, last = M - (tiles_m - 1) * bm;
   if (M > 512 || tiles_m == 1) return M <= 512;
