@@ -533,8 +533,8 @@ static void launch(GemmArgs& a, hipStream_t s) {
 // wavefronts of 16x32: with four of 32x32 a SIMD's one wavefront waits out every round trip to LDS.  64x32 tiles, four
 // wavefronts of 16x32, while they are a workgroup for each CU at most.  us, 64x64 in four / in eight / 64x32: 221 rows of 1024 (FFN
 // 2816), Q/K/V 8.6 / 7.3 / 7.7 (384 tiles), output 5.1 / 4.9 / 4.3, down 6.1 / 6.0 / 6.3 (512 tiles); 100 rows, Q/K/V 8.5 / 7.2 / 6.7,
-// output 4.9 / 4.8 / 4.3, down 5.9 / 5.7 / 4.9.  Projections of more than 256 tiles keep four (400 rows of 2048, output, 448
-// tiles: 9.1 / 12.1).
+// output 4.9 / 4.8 / 4.3, down 5.9 / 5.7 / 4.9; more than 256 tiles, in four / in eight: 300 rows of 3072, output (480) 14.6 / 14.7,
+// 400 of 2304, output (504) 14.3 / 14.4, down of 6144 27.1 / 26.5.
 //   128x128 tiles: Q/K/V of 192 rows of 4096 47-49 / 44, 256 rows 49 / 47, down equal; gate/up 2 % slower, which keeps turns there.
 // Every output sums in the order of the kernel above: the same bits.
 template <int BM, int BN, int WM, int WN, int NS, int EPI, bool COLD>
@@ -676,8 +676,8 @@ static double tile_cost(int t, int M, int N, int K, int splits) {
   }
   return (double)((tiles + 255) / 256) * (kRoundUs + kTiles[t].us * K / splits / 4096.);
 }
-static bool one_each(int M, int N, int cols, int splits = 1) {   // 64-row tiles of `cols` columns: one for each CU at most
-  return (long long)((M + 63) / 64) * ((N + cols - 1) / cols) * splits <= 256;
+static bool one_each(int M, int N, int splits = 1) {   // 64x32 tiles: one for each CU at most
+  return (long long)((M + 63) / 64) * ((N + 31) / 32) * splits <= 256;
 }
 static int pick_tile(int M, int N, int K) {
   int best = 6;
@@ -725,7 +725,7 @@ void launch_gemm_qkv_bf16(const bf16* A, const bf16* wq, const bf16* wk, const b
     case 4: launch_step<128, 128, 4, 2, 5, EPI_QKV>(a, s); break;
     case 5: launch_step<128, 64, 4, 2, 6, EPI_QKV>(a, s); break;
     default:
-      if (one_each(M, a.N, 32)) launch_step<64, 32, 4, 1, 6, EPI_QKV>(a, s);
+      if (one_each(M, a.N)) launch_step<64, 32, 4, 1, 6, EPI_QKV>(a, s);
       else launch_step<64, 64, 4, 2, 5, EPI_QKV>(a, s);
   }
 }
@@ -748,7 +748,7 @@ void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16
     case 4: launch<128, 128, 4, 2, 3, EPI_SWIGLU>(a, s); break;
     case 5: launch_step<128, 64, 4, 2, 6, EPI_SWIGLU>(a, s); break;
     default:
-      if (one_each(M, a.N, 32)) launch_step<64, 32, 4, 1, 6, EPI_SWIGLU>(a, s);
+      if (one_each(M, a.N)) launch_step<64, 32, 4, 1, 6, EPI_SWIGLU>(a, s);
       else launch_step<64, 64, 4, 2, 5, EPI_SWIGLU>(a, s);
   }
 }
@@ -849,9 +849,8 @@ void launch_gemm_partial_bf16(const bf16* A, const bf16* W, float* parts, size_t
   else if (p.tile == 2) launch<256, 128, 4, 2, 2, EPI_PARTIAL>(a, s);
   else if (p.tile == 4) launch_step<128, 128, 4, 2, 5, EPI_PARTIAL>(a, s);
   else if (p.tile == 5) launch_step<128, 64, 4, 2, 6, EPI_PARTIAL>(a, s);
-  else if (one_each(M, N, 32, p.splits)) launch_step<64, 32, 4, 1, 6, EPI_PARTIAL>(a, s);
-  else if (one_each(M, N, 64, p.splits)) launch_step<64, 64, 4, 2, 5, EPI_PARTIAL>(a, s);
-  else launch_step<64, 64, 2, 2, 5, EPI_PARTIAL>(a, s);
+  else if (one_each(M, N, p.splits)) launch_step<64, 32, 4, 1, 6, EPI_PARTIAL>(a, s);
+  else launch_step<64, 64, 4, 2, 5, EPI_PARTIAL>(a, s);
 }
 
 void launch_gemm_lmhead_bf16(const bf16* A, const bf16* W, int M, int V, int K, const LmHeadEpilogue& e, Gate g,

@@ -1,6 +1,6 @@
-"""Tiles of narrow models: 64x32, 64x64 one or two to a CU, at the widths and rows on both sides of the lines between them.  Against the
-oracle, and above 256 rows bit for bit against the same sequence in a batch, which takes other tiles (below 449 keys: from there on the
-attention of few workgroups deals the keys among them)."""
+"""Tiles of narrow models: 64x32, 64x64 one or two to a CU (the last shape: projections of more than 256 tiles), at the widths and
+rows on both sides of the lines between them.  Against the oracle, and above 256 rows bit for bit against the same sequence in a
+batch, which takes other tiles (below 449 keys: from there on the attention of few workgroups deals the keys among them)."""
 import pytest
 import torch
 
@@ -11,7 +11,7 @@ from tests import parity as Pz
 pytestmark = pytest.mark.gpu
 
 # (d, head size, FFN)
-SHAPES = [(256, 64, 704), (512, 128, 1408), (1024, 64, 2816), (1536, 128, 1024)]
+SHAPES = [(256, 64, 704), (512, 128, 1408), (1024, 64, 2816), (1536, 128, 1024), (2816, 128, 704)]
 
 
 def model(case):
