@@ -256,7 +256,7 @@ void launch_skinny_swiglu_finish(const float* parts, int n_parts, size_t part_st
 // act[M, F] = silu(A Wg^T) * (A Wu^T).  Few rows: launch_gemm_swiglu_bf16 (GATE_UP_TILES), launch_gemm_few_rows_swiglu_bf16
 // (GATE_UP_WIDE), or K ranges and a finishing kernel (GATE_UP_RANGES).
 enum GateUpPath { GATE_UP_TILES, GATE_UP_WIDE, GATE_UP_RANGES };
-GateUpPath few_rows_gate_up(int M, int F, int K, bool ranges);
+GateUpPath few_rows_gate_up(int F, int K, bool ranges);
 void launch_gemm_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16* act, int M, int F, int K, Gate g,
                              hipStream_t s);
 void launch_gemm_few_rows_swiglu_bf16(const bf16* A, const bf16* wg, const bf16* wu, bf16* act, int M, int F, int K, Gate g,

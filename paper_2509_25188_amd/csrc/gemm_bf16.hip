@@ -818,15 +818,16 @@ static PartialPlan plan_partial(const int rows, int N, int K, int pass_rows) {
 }
 int wide_splits(int M, int N, int K, int pass_rows) { return plan_partial(M, N, K, pass_rows).splits; }
 
-// Partials of any pass of up to `rows` rows of a [d, F] model.  Few rows: every K range of the widest stacked projection (Q/K/V, which
-// is not split today, counted too: the buffer's size stays).
+// Partials of any pass of up to `rows` rows of a [d, F] model.  Up to 64 rows: the ranges of the projections to d, and of gate/up
+// where few_rows_gate_up splits it; the same for any count of rows.
 // More rows: the projections to d, whose ranges depend on the rows through counts of tiles, of the smallest tile's 64 rows in
 // passes of up to 256 (plan_small_pass; fewer rows may have more ranges), of 128 rows above (plan_partial): the last row
 // count of every such step stands for all of it.  Rows that are some of a larger pass's take that pass's ranges.
 size_t partial_floats(long long rows, int d, int F) {
-  size_t most = 0;
-  const int shapes[4][2] = {{3 * d, d}, {d, d}, {2 * F, d}, {d, F}};
-  for (auto& sh : shapes) most = std::max(most, (size_t)skinny_splits(sh[0], sh[1]) * kSkinnyRows * sh[0]);
+  const size_t few = (size_t)std::min<long long>(rows, kSkinnyRows);
+  size_t most = few * d * std::max(skinny_splits(d, d), skinny_splits(d, F));
+  if (few_rows_gate_up(F, d, true) == GATE_UP_RANGES) most = std::max(most, few * 2 * F * skinny_splits(2 * F, d));
+  if (rows <= kSkinnyRows) return most;
   for (long long top = 128;; top += top < 256 ? 64 : 128) {
     const int M = (int)std::min(top, rows);
     for (int k : {d, F})

@@ -34,7 +34,6 @@ struct FewArgs {
 
 template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI, bool COLD>
 __global__ void __launch_bounds__(WM* WN * 64) k_gemm_few_rows(FewArgs a) {
-  constexpr int NT = WM * WN * 64;
   constexpr int NW = WM * WN;
   constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
   constexpr bool PAIR = EPI == EPI_SWIGLU;
@@ -327,7 +326,7 @@ void launch_gemm_skinny_bf16(const bf16* A, const bf16* w0, const bf16* w1, int 
 // ones the kernel above: 64 (32 gate + 32 up) columns to a wavefront, or 128 to four above 32 rows, K unsplit.  Where even
 // 32 columns leave half of the chip idle for more than 24 stages, split K and a finishing kernel (about 10 us in all, where such a
 // chain takes 0.24 us a stage), unless the rows must sum as those of a larger pass (`ranges` false).
-GateUpPath few_rows_gate_up(int M, int F, int K, bool ranges) {
+GateUpPath few_rows_gate_up(int F, int K, bool ranges) {
   if (ranges && 2 * F < 128 * 32 && K > 24 * 64) return GATE_UP_RANGES;
   return 2 * F <= 256 * 96 ? GATE_UP_TILES : GATE_UP_WIDE;   // 768 tiles of 32 columns, 256 of 96
 }

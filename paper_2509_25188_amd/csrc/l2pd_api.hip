@@ -283,7 +283,7 @@ void run_layers(l2pd_ctx* c, const Pass& p, Gate g, hipStream_t s) {
       bf16* ao = c->at<bf16>(L.attn);
       auto gate_up = [&](int n, bf16* act, bool ranges) {       // ranges: K may be split
         const bf16 *wg = (const bf16*)c->wg[l], *wu = (const bf16*)c->wu[l];
-        const GateUpPath path = n <= kSkinnyRows ? few_rows_gate_up(n, F, d, ranges) : GATE_UP_TILES;
+        const GateUpPath path = n <= kSkinnyRows ? few_rows_gate_up(F, d, ranges) : GATE_UP_TILES;
         if (path == GATE_UP_RANGES) {
           const int S = skinny_splits(2 * F, d);
           const size_t stride = (size_t)n * 2 * F;

@@ -23,6 +23,17 @@ def planners():
     return wide, few, ranges, size
 
 
+def gate_up_ranges(F, d):
+    """Whether gate/up of few rows writes partial sums: the third of its ways."""
+    return Bd.lib()._ZN4l2pd16few_rows_gate_upEiib(F, d, True) == 2
+
+
+def few_rows_need(few, d, F):
+    """Columns times ranges of the widest set of partial sums that a pass of up to 64 rows writes."""
+    sums = [(d, d), (d, F)] + ([(2 * F, d)] if gate_up_ranges(F, d) else [])
+    return max(few(n, k) * n for n, k in sums)
+
+
 @pytest.mark.parametrize("d", WIDTHS)
 def test_every_pass_fits(d):
     wide, few, ranges, size = planners()
@@ -30,7 +41,7 @@ def test_every_pass_fits(d):
         most = 0
         for M in range(1, ROWS + 1):
             if M <= FEW:
-                need = max(few(n, k) * M * n for n, k in ((3 * d, d), (d, d), (2 * F, d), (d, F)))
+                need = few_rows_need(few, d, F) * M
             else:
                 tail = M // 2        # the most wanted rows that the last layer's projections work on alone
                 need = max(wide(M, d, k, M) * M * d for k in (d, F))
@@ -39,6 +50,14 @@ def test_every_pass_fits(d):
                     need = max(need, *(wide(tail, d, k, M) * tail * d for k in (d, F)))
             most = max(most, need)
             assert size(M, d, F) >= most, (d, F, M)
+
+
+@pytest.mark.parametrize("d", WIDTHS + (1600, 2816))
+def test_small_engines_hold_no_more_than_their_sums(d):
+    wide, few, ranges, size = planners()
+    for F in FFN + (64, 1984):
+        for rows in (2, 32, FEW):
+            assert size(rows, d, F) == few_rows_need(few, d, F) * rows, (F, rows)
 
 
 @pytest.mark.gpu
