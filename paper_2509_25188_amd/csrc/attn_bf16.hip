@@ -454,7 +454,10 @@ static void launch(const bf16* q, const bf16* kstore, const bf16* vtstore, bf16*
 //     8 x 512 rows         105 / 61      (128)           2 x 300 rows   21.8 / 15.0  (25.9)
 //   16 heads of 64
 //     221 rows             6.2 / 8.4     (6.3)           8 x 221 rows   8.9 / 9.4    (12.1)
-//     (221 rows, one query wavefront a range: twice the workgroups, the tiles read by each; a step of eight layers 394.9 -> 393.8)
+//   few workgroups, two query wavefronts a range / one: twice the workgroups, the tiles read by each (with events around the launch)
+//     32 heads of 128      100 rows 11.1 / 10.8, 200 rows 11.7 / 11.4, 256 rows 11.6 / 11.4; 64 rows over 256 stored keys 12.6 / 11.2, over
+//                          384 15.7 / 14.4, four sequences of them 16.3 / 15.1 (read twice, so without the hint of ONCE)
+//     16 heads of 64       40 rows 7.7 / 7.9, 64 rows 7.9 / 7.6, 221 rows 9.1 / 8.7, 4 x 64 rows 7.8 / 7.6; 8 of 128, 4 x 64 rows 9.6 / 9.2
 //     8 x 384 rows         17.5 / 15.9   (24.2)          8 x 600 rows   32.5 / 28.2  (50.5)
 //   two ranges in all      4 x 2 side by side / 4 x 1, x 2 in turn
 //     1024 rows, 32 of 128 27.2 / 31.8   (32.0)          1280 rows      56.9 / 48.3  (68.0)

@@ -39,7 +39,8 @@ struct Gate {
   const int* ctl;     // the control block, for kernels that read more of it; nullptr: there is none
   int expect_gb;      // >= 0: skip unless the active block is this one
   const int2* words;  // never null: (active block, all done) of the control block, or zeros
-  bool cold;          // the model's weights do not fit the memory-side cache: none of them is there when a pass wants it
+  bool cold;          // no gate, but as much the same for every launch of a bf16 model: its weights do not fit the memory-side cache,
+                      // none of them is there when a pass wants it
 };
 static_assert(CTL_GB == 0 && CTL_ALL_DONE == 1, "the gate's two words");
 __device__ __forceinline__ int2 gate_words(const Gate& g) { return *g.words; }

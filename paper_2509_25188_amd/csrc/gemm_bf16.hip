@@ -696,8 +696,13 @@ static int pick_tile(int M, int N, int K) {
 //   gate/up       1024 x 2816  2048 x 8192  4096 x 11008 4096 x 12288  4096 x 14336
 //     32 rows     6.1 / 10.4   15.2 / 17.0  37.7 / 38.0  37.0 / 38.3   49.7 / 44.5     (64 columns in the second, else 32)
 //     64 rows     7.7 / 11.3   16.2 / 20.9  38.0 / 41.5  40.0 / 43.0   60.8 / 47.9     (64 in the second, then 96)
+// Both sides of the lines, us with a pair of events around the launch, weights from memory; 32 rows, then 64:
+//   256 workgroups of 32 columns: Q/K/V of 2560 (7,680 columns), 32 columns / 64 14.7 / 18.2, 18.4 / 21.8; of 2816 (8,448) 20.6 / 18.9,
+//   26.9 / 22.5; of 4096 27.8 / 25.0, 35.6 / 30.4; gate/up of 1536 x 4160 (8,320) 13.6 / 12.8, 17.3 / 14.6, of 3584 x 8192 26.0 / 23.1, 35.0 / 26.7
+//   256 of 64: gate/up of 3584 x 9472 (18,944), 32 columns up to 32 rows and 96 beyond / 64 33.7 / 36.2, 32.2 / 42.9
 // Where 32 columns make more than three workgroups for each CU (what their rings leave room for), or 96 more than one, gate/up
-// stays with gemm_few_rows.hip.
+// stays with gemm_few_rows.hip; no one tile is ahead there (that kernel / tiles of 64 columns: 4096 x 14336 50.3 / 45.5, 54.4 / 65.7,
+// 5120 x 13824 57.6 / 57.7 (52.4 with 128), 59.4 / 82.6, 3584 x 18944 65.2 / 53.1, 69.0 / 57.8, 8192 x 22016 164 / 132, 172 / 142).
 template <int EPI, int COLS, int COLS2, int WM2, int WN2>
 static void launch_few(GemmArgs& a, hipStream_t s) {
   const bool narrow = a.N <= 256 * COLS;

@@ -75,7 +75,8 @@ __device__ __forceinline__ void dma16(const void* gptr, unsigned lds_addr) {
 }
 
 // The same for weights that come from memory once and are not wanted again before the cache has forgotten them (Gate::cold).
-// Rows of 8 KB in pieces of 128 bytes, loads alone: 201 MB 34.2 us against 37.1, 1,036 MB 159 against 174.  Weights that stay in the
+// Rows of 8 KB in pieces of 128 bytes, loads alone (an order of their own, no bound for a product): 201 MB 34.2 us against 37.1,
+// 1,036 MB 159 against 174.  Weights that stay in the
 // memory-side cache (256 MB) from pass to pass lose by it: 201 MB again and again 35.3 against 30.7.
 __device__ __forceinline__ void dma16_once(const void* gptr, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"

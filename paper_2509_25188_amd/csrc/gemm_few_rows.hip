@@ -285,8 +285,10 @@ void launch(FewArgs& a, hipStream_t s) {
 
 // K ranges of a step's projections, the same for all of up to 64 rows: a sequence's sums do not depend on how many others
 // share its launch.  Tiles of 64 columns: ranges until there is a workgroup for every CU, and on to two for every CU while the
-// last round of them is less than four fifths full (12288 columns
-// of 4096: two ranges are 1.5 workgroups a CU, four are 3: 25.4 against 20.6 us); more only cost what sums them.
+// last round of them is less than four fifths full; more only cost what sums them.  The four fifths, us with events around the launch,
+// 32 rows, with / without: 5120 wide (eight ranges for four) output 16.3 / 18.5, down of 13824 30.8 / 36.3, the RMSNorm behind them
+// 7.7 / 6.8; 3072 (16 for 8) down of 8192 15.2 / 16.0; 6144 (8 for 4) output 19.8 / 20.9, down of 24576 55.5 / 68.3, but of 16384 47.0 / 46.2.
+// (64 rows: equal for the outputs and 13824 40.5 / 42.7, 8192 20.1 / 19.0, 24576 72.3 / 79.3, 16384 65.7 / 51.8.)
 int skinny_splits(int N, int K) {
   const int tiles = (N + 63) / 64;
   int S = 1;
@@ -324,8 +326,10 @@ void launch_gemm_skinny_bf16(const bf16* A, const bf16* w0, const bf16* w1, int 
 
 // Which way gate/up takes.  Tiles of gemm_bf16.hip (figures at launch_few there) while all of them are on the chip at once; wider
 // ones the kernel above: 64 (32 gate + 32 up) columns to a wavefront, or 128 to four above 32 rows, K unsplit.  Where even
-// 32 columns leave half of the chip idle for more than 24 stages, split K and a finishing kernel (about 10 us in all, where such a
-// chain takes 0.24 us a stage), unless the rows must sum as those of a larger pass (`ranges` false).
+// 32 columns leave half of the chip idle for a long chain of stages, split K and a finishing kernel, unless the rows must sum as those
+// of a larger pass (`ranges` false).  us with events around the launches, 32 and 64 rows, ranges / tiles: 4096 x 1024 14.0 / 17.3,
+// 16.0 / 22.4; 8192 x 1984 21.6 / 28.6, 24.6 / 38.9; 2816 x 1984 13.9 / 14.0, 15.9 / 17.6; 2048 x 1024 12.9 / 11.6, 14.0 / 14.4; 1600 x 1984
+// 16.1 / 10.8, 17.1 / 13.0: even at about 32 stages.  The order of the sums is part of a result, so the line stays where it was put, at 24.
 GateUpPath few_rows_gate_up(int F, int K, bool ranges) {
   if (ranges && 2 * F < 128 * 32 && K > 24 * 64) return GATE_UP_RANGES;
   return 2 * F <= 256 * 96 ? GATE_UP_TILES : GATE_UP_WIDE;   // 768 tiles of 32 columns, 256 of 96

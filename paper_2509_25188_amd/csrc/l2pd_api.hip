@@ -161,10 +161,11 @@ int ensure_device(l2pd_ctx* c, hipStream_t s) {
 }
 
 // Whether a pass finds any of its weights in the memory-side cache (256 MB).  Of weights up to twice as large it may find some,
-// depending on what the cache has dropped, and the loads stay as they are.
+// depending on what the cache has dropped, and the loads stay as they are.  (The kernels of fp32 models do not ask.)
 bool weights_cold(const l2pd_model_desc& m) {
+  if (m.dtype != L2PD_BF16) return false;
   const double d = m.d_model, per_layer = 4 * d * d + 3 * d * m.d_ffn;
-  return (m.n_layers * per_layer + d * m.vocab) * (m.dtype == L2PD_BF16 ? 2 : 4) > 512e6;
+  return (m.n_layers * per_layer + d * m.vocab) * 2 > 512e6;
 }
 
 // Launches that stop with the decode (or, expect_gb >= 0, outside that block); launches that always run.

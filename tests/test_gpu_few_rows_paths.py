@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 # (d, H, Dh, F, V): 32 columns to a workgroup, 64 or 96, wider ones, K ranges with a finishing kernel
 SHAPES = [(256, 4, 64, 4096, 300), (256, 2, 128, 4160, 129), (128, 2, 64, 8192, 127), (128, 1, 128, 8256, 128), (128, 1, 128, 12288, 300), (128, 1, 128, 12352, 257),
-          (1600, 25, 64, 64, 130), (1600, 25, 64, 1984, 130), (2688, 21, 128, 128, 200), (2816, 22, 128, 2048, 200)]
+          (1600, 25, 64, 64, 130), (1600, 25, 64, 1984, 130), (2688, 21, 128, 128, 200), (2816, 22, 128, 2048, 200),
+          (128, 1, 128, 8320, 130)]       # the last tile of 96 gate/up columns has 32
 
 
 @pytest.mark.parametrize("case", range(len(SHAPES)))
