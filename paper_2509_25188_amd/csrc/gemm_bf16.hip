@@ -507,7 +507,8 @@ __global__ void __launch_bounds__(512) k_gemm_turns(GemmArgs a) {
 // three layers of 4096 x 12288 492 / 510 / 464, two of 5120 x 13824 482 / 512 / 457; 288 rows, six of 2048 x 5632 592 / 614 / 566.
 bool read_once(int M, int N, int splits, int bm, int bn) {
   const int tiles_m = (M + bm - 1) / bm, last = M - (tiles_m - 1) * bm;
-  if (M > 512 || tiles_m == 1) return M <= 512;
+  if (M > 512) return false;
+  if (tiles_m == 1) return true;
   const TileMap map(tiles_m, (N + bn - 1) / bn, splits);
   return bm >= 128 && bn >= 128 && (bm == 256 || 4 * last >= 3 * bm) && map.per_xcd % tiles_m == 0;
 }
